@@ -421,19 +421,30 @@ hipError_t launch_sh_dense(const float* part, int64_t rows, int64_t rows_pad, in
                            const float* H, int64_t row0, const float* scale, const float* diag, int64_t panel_rows,
                            float* out, hipStream_t stream);
 // C = alpha op(A) op(B) + bias with epilogue (0 none, 1 GELU, 2 softplus); Z: pre-epilogue copy
-// or null.  split_ws (split_ws_floats floats, may be null) enables split-K for small outputs.
+// or null.  splits > 1 (a value of gemm_splits; no bias, epilogue or Z): C holds that many M x N
+// partials, one per range of K.
 hipError_t launch_gemm(int ta, int tb, int b_bf16, int epi, const float* A, const void* B, const float* bias, float* C,
-                       float* Z, int64_t M, int64_t N, int64_t K, float alpha, float* split_ws,
-                       int64_t split_ws_floats, hipStream_t stream);
-// dZ = dA * f'(Z): mode 1 GELU, mode 2 softplus
-hipError_t launch_act_backward(const float* dA, const float* Z, float* dZ, int64_t m, int mode, hipStream_t stream);
-hipError_t launch_colsum(const float* X, int64_t m, int64_t ncol, float* out, hipStream_t stream);
-// residual output A = max(C + z, 0) (A holds z on entry; C = first k columns of X) and its backward
+                       float* Z, int64_t M, int64_t N, int64_t K, float alpha, int64_t splits, hipStream_t stream);
+int64_t gemm_splits(int64_t M, int64_t N, int64_t K);
+// the most gemm_splits returns for any K
+int64_t gemm_max_splits(int64_t M, int64_t N);
+// dZ = dA * GELU'(Z), part: bias_blocks(m) x ncol FP64 column sums of dZ
+hipError_t launch_gelu_backward(const float* dA, const float* Z, float* dZ, int64_t m, int64_t ncol, double* part,
+                                hipStream_t stream);
+int64_t bias_blocks(int64_t m);
+// residual output A = max(C + z, 0) (A holds z on entry; C = first k columns of X)
 hipError_t launch_residual_relu(const float* X, int64_t ldx, float* A, int64_t rows, int64_t k, hipStream_t stream);
-hipError_t launch_residual_relu_backward(const float* dA, const float* X, int64_t ldx, const float* Z, float* dZ,
-                                         int64_t rows, int64_t k, hipStream_t stream);
-hipError_t launch_adamw(float* P, const float* G, float* M, float* V, int64_t m, int64_t n_decay, float lr, float b1,
-                        float b2, float eps, float wd, int64_t t, hipStream_t stream);
+// Partials of the parameters' gradient: weights (W1, W2, W3) as split-K partials, biases (b1, b2,
+// b3) as FP64 row-block sums.
+struct GradParts {
+    const float* wpart[3];
+    int64_t wsize[3], splits[3];
+    const double* bpart[3];
+    int64_t bsize[3], bblocks[3];
+};
+// G = summed partials, then AdamW step t (1, 2, ...), unless coef[3] != 0
+hipError_t launch_grad_adamw(const GradParts& gp, const double* coef, float* P, float* G, float* M, float* V, float lr,
+                             float b1, float b2, float eps, float wd, int64_t t, hipStream_t stream);
 hipError_t launch_to_bf16(const float* x, uint16_t* y, int64_t m, hipStream_t stream);
 // successive projection on R (m x k FP64, destroyed); pick: k device int64; bval/bidx: nb entries
 hipError_t launch_spa(double* R, int64_t m, int64_t k, double* bval, int64_t* bidx, int nb, int64_t* pick,
@@ -447,8 +458,14 @@ hipError_t launch_project_rows(const float* Y, int64_t m, int64_t w, const doubl
                                int out_f64, void* out, hipStream_t stream);
 hipError_t launch_anchor_solve(const float* Y, int64_t w, const double* M, int64_t k, const int64_t* anchors,
                                double* W, int32_t* status, hipStream_t stream);
-hipError_t launch_gram_loss_grad(const float* A, const float* B, const double* AtA, const double* AtB, int64_t k,
-                                 int64_t m, float ca, float cb, float* dA, hipStream_t stream);
+hipError_t launch_gram3(const float* A, const float* B, int64_t k, int64_t m, double* work, double* out,
+                        hipStream_t stream);
+hipError_t launch_loss_coef(const double* gram3, int64_t k, int kind, double* coef, hipStream_t stream);
+// part: loss_backward_blocks(m) x k FP64 column sums of dZ
+hipError_t launch_loss_backward(const float* A, const float* B, const double* gram3, const double* coef, const float* X,
+                                int64_t ldx, const float* Z, int residual, int64_t k, int64_t m, float* dZ, double* part,
+                                hipStream_t stream);
+int64_t loss_backward_blocks(int64_t m);
 hipError_t launch_clip_cols(const float* X, int64_t m, int64_t w, int64_t k, float* out, hipStream_t stream);
 hipError_t launch_scale(float* x, int64_t m, float a, hipStream_t stream);
 hipError_t launch_span_overlap(const double* MA, const double* AtB, const double* MB, int64_t k, double* out,

@@ -67,7 +67,8 @@ hipError_t launch_sh_dense(const float* part, int64_t rows, int64_t rows_pad, in
 // quarter as 2 x 2 blocks of v_mfma_f32_16x16x4_f32 (FP32 products and
 // accumulation: the bf16 weights are widened exactly).  blockIdx.z splits K
 // into ranges of kchunk: with more than one range every range writes its own
-// partial C + z M N (no bias, no epilogue) for a fixed-order reduction.
+// partial C + z M N (no bias, no epilogue), summed in order by the kernel that
+// applies the gradient.
 // EPI: 0 none, 1 GELU x Phi(x) (Phi from erfc), 2 softplus.  Z (optional)
 // receives the value before the epilogue.
 // ---------------------------------------------------------------------------
@@ -150,35 +151,29 @@ __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, 
         }
 }
 
-// out[e] = sum_z part[z][e] in fixed order
-__global__ void sum_split_kernel(const float* __restrict__ part, int splits, int64_t m, float* __restrict__ out) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
-        float s = 0.0f;
-        for (int z = 0; z < splits; ++z) s += part[z * m + e];
-        out[e] = s;
-    }
+// K ranges of a weight gradient (m x n, contraction over K rows): enough to
+// fill the card where the output has few tiles, none shorter than 256 rows
+int64_t gemm_splits(int64_t M, int64_t N, int64_t K) {
+    const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64);
+    if (tiles >= 256 || K < 512) return 1;
+    const int64_t splits = std::max<int64_t>(1, std::min<int64_t>(256 / tiles, K / 256));
+    const int64_t kchunk = ((K + splits - 1) / splits + 15) / 16 * 16;
+    return (K + kchunk - 1) / kchunk;
+}
+int64_t gemm_max_splits(int64_t M, int64_t N) {
+    const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64);
+    return tiles >= 256 ? 1 : 256 / tiles;
 }
 
 hipError_t launch_gemm(int ta, int tb, int b_bf16, int epi, const float* A, const void* B, const float* bias, float* C,
-                       float* Z, int64_t M, int64_t N, int64_t K, float alpha, float* split_ws, int64_t split_ws_floats,
-                       hipStream_t stream) {
-    if (M < 1 || N < 1 || K < 1) return hipErrorInvalidValue;
-    // split K for tall contractions (weight gradients) whose output grid is small
-    int64_t splits = 1;
-    const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64);
-    if (tiles < 256 && K >= 512 && split_ws) {
-        splits = std::min<int64_t>(256 / tiles, K / 256);
-        splits = std::min<int64_t>(splits, split_ws_floats / (M * N));
-        if (splits < 2 || epi != 0 || bias) splits = 1;
-    }
-    int64_t kchunk = (K + splits - 1) / splits;
-    kchunk = (kchunk + 15) / 16 * 16;
-    splits = (K + kchunk - 1) / kchunk;
-    float* dst = splits > 1 ? split_ws : C;
+                       float* Z, int64_t M, int64_t N, int64_t K, float alpha, int64_t splits, hipStream_t stream) {
+    if (M < 1 || N < 1 || K < 1 || splits < 1 || (splits > 1 && (epi != 0 || bias || Z))) return hipErrorInvalidValue;
+    const int64_t kchunk = ((K + splits - 1) / splits + 15) / 16 * 16;
+    if ((K + kchunk - 1) / kchunk != splits) return hipErrorInvalidValue;
     dim3 grid((N + 63) / 64, (M + 63) / 64, splits), block(256);
-#define G(TA, TB, BT, E)                                                                                       \
-    hipLaunchKernelGGL((gemm_kernel<TA, TB, BT, E>), grid, block, 0, stream, A, (const BT*)B, bias, dst, Z, M, N, \
-                       K, kchunk, alpha)
+#define G(TA, TB, BT, E)                                                                                     \
+    hipLaunchKernelGGL((gemm_kernel<TA, TB, BT, E>), grid, block, 0, stream, A, (const BT*)B, bias, C, Z, M, N, K, \
+                       kchunk, alpha)
     if (b_bf16) {
         if (ta == 0 && tb == 0 && epi == 0) G(0, 0, uint16_t, 0);
         else if (ta == 0 && tb == 0 && epi == 1) G(0, 0, uint16_t, 1);
@@ -193,31 +188,50 @@ hipError_t launch_gemm(int ta, int tb, int b_bf16, int epi, const float* A, cons
         else return hipErrorInvalidValue;
     }
 #undef G
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || splits == 1) return e;
-    const int64_t m = M * N;
-    int64_t blocks = (m + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(sum_split_kernel, dim3(blocks), dim3(256), 0, stream, (const float*)split_ws, (int)splits, m, C);
     return hipGetLastError();
 }
 
-// dZ = dA * f'(Z): mode 1 GELU' (Phi(z) + z phi(z)), mode 2 softplus' (sigmoid)
-__global__ void act_backward_kernel(const float* __restrict__ dA, const float* __restrict__ Zpre, float* __restrict__ dZ,
-                                    int64_t m, int mode) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
-        const float z = Zpre[i];
-        float d;
-        if (mode == 1) d = normal_cdf_f(z) + z * expf(-0.5f * z * z) * 0.3989422804014327f;
-        else d = 0.5f * (1.0f + tanhf(0.5f * z));
-        dZ[i] = dA[i] * d;
+// Backward of an activation and the bias gradient's partial sums in one pass:
+// dZ = dA * GELU'(Z) (Phi(z) + z phi(z)), in place where dZ = dA, and the FP64
+// column sums of dZ over every block of BIAS_ROWS rows.  A work-group takes 64
+// columns of one row block, so m = 20000 rows of 256 columns are 628
+// work-groups: with one work-group per 64 columns summing all rows one after
+// another the three bias sums of a training step took 3.6 of its 4.6 ms
+// (dependent FP64 adds behind load latency, 9 work-groups on 256 CUs); fused
+// here they cost no pass of their own (15.6 us a GELU layer before, without
+// the sums, 17.0 us now, m = 20000, 256 columns).
+constexpr int BIAS_ROWS = 128;
+
+int64_t bias_blocks(int64_t m) { return (m + BIAS_ROWS - 1) / BIAS_ROWS; }
+
+__global__ __launch_bounds__(256) void gelu_backward_kernel(const float* dA, const float* __restrict__ Zpre, float* dZ,
+                                                            int64_t m, int64_t ncol, double* __restrict__ part) {
+    __shared__ double red[4][64];
+    const int lc = threadIdx.x & 63, ph = threadIdx.x >> 6;
+    const int64_t col = blockIdx.x * 64 + lc;
+    const int64_t r0 = (int64_t)blockIdx.y * BIAS_ROWS;
+    const int64_t r1 = r0 + BIAS_ROWS < m ? r0 + BIAS_ROWS : m;
+    double s = 0.0;
+    if (col < ncol) {
+#pragma unroll 4
+        for (int64_t i = r0 + ph; i < r1; i += 4) {
+            const float z = Zpre[i * ncol + col];
+            const float d = normal_cdf_f(z) + z * expf(-0.5f * z * z) * 0.3989422804014327f;
+            const float v = dA[i * ncol + col] * d;
+            dZ[i * ncol + col] = v;
+            s += (double)v;
+        }
     }
+    red[ph][lc] = s;
+    __syncthreads();
+    if (ph == 0 && col < ncol) part[blockIdx.y * ncol + col] = red[0][lc] + red[1][lc] + red[2][lc] + red[3][lc];
 }
 
-hipError_t launch_act_backward(const float* dA, const float* Z, float* dZ, int64_t m, int mode, hipStream_t stream) {
-    int64_t blocks = (m + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(act_backward_kernel, dim3(blocks), dim3(256), 0, stream, dA, Z, dZ, m, mode);
+hipError_t launch_gelu_backward(const float* dA, const float* Z, float* dZ, int64_t m, int64_t ncol, double* part,
+                                hipStream_t stream) {
+    if (bias_blocks(m) > 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(gelu_backward_kernel, dim3((ncol + 63) / 64, bias_blocks(m)), dim3(256), 0, stream, dA, Z, dZ, m,
+                       ncol, part);
     return hipGetLastError();
 }
 
@@ -233,17 +247,6 @@ __global__ void residual_relu_kernel(const float* __restrict__ X, int64_t ldx, f
     }
 }
 
-// dZ = dA [C + z > 0]
-__global__ void residual_relu_backward_kernel(const float* __restrict__ dA, const float* __restrict__ X, int64_t ldx,
-                                              const float* __restrict__ Z, float* __restrict__ dZ, int64_t rows,
-                                              int k) {
-    const int64_t m = rows * k;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = i / k;
-        dZ[i] = X[r * ldx + (i - r * k)] + Z[i] > 0.0f ? dA[i] : 0.0f;
-    }
-}
-
 hipError_t launch_residual_relu(const float* X, int64_t ldx, float* A, int64_t rows, int64_t k, hipStream_t stream) {
     int64_t blocks = (rows * k + 255) / 256;
     if (blocks > 65536) blocks = 65536;
@@ -251,57 +254,60 @@ hipError_t launch_residual_relu(const float* X, int64_t ldx, float* A, int64_t r
     return hipGetLastError();
 }
 
-hipError_t launch_residual_relu_backward(const float* dA, const float* X, int64_t ldx, const float* Z, float* dZ,
-                                         int64_t rows, int64_t k, hipStream_t stream) {
-    int64_t blocks = (rows * k + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(residual_relu_backward_kernel, dim3(blocks), dim3(256), 0, stream, dA, X, ldx, Z, dZ, rows,
-                       (int)k);
-    return hipGetLastError();
-}
-
-// column sums of an (m x ncol) FP32 matrix (bias gradients), FP64 accumulation
-__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ X, int64_t m, int ncol, float* __restrict__ out) {
-    __shared__ double red[4][64];
-    const int lc = threadIdx.x & 63, ph = threadIdx.x >> 6;
-    const int64_t col = blockIdx.x * 64 + lc;
-    double s = 0.0;
-    if (col < ncol)
-        for (int64_t i = ph; i < m; i += 4) s += (double)X[i * ncol + col];
-    red[ph][lc] = s;
-    __syncthreads();
-    if (ph == 0 && col < ncol) out[col] = (float)(red[0][lc] + red[1][lc] + red[2][lc] + red[3][lc]);
-}
-
-hipError_t launch_colsum(const float* X, int64_t m, int64_t ncol, float* out, hipStream_t stream) {
-    hipLaunchKernelGGL(colsum_kernel, dim3((ncol + 63) / 64), dim3(256), 0, stream, X, m, (int)ncol, out);
-    return hipGetLastError();
-}
-
-// AdamW on a flat parameter vector; the first n_decay entries get decoupled
-// weight decay.  t = step number (1, 2, ...).
-__global__ void adamw_kernel(float* __restrict__ P, const float* __restrict__ G, float* __restrict__ Mm,
-                             float* __restrict__ V, int64_t m, int64_t n_decay, float lr, float b1, float b2,
-                             float eps, float wd, float c1, float c2) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
-        const float g = G[i];
-        const float mi = b1 * Mm[i] + (1.0f - b1) * g;
-        const float vi = b2 * V[i] + (1.0f - b2) * g * g;
-        Mm[i] = mi;
-        V[i] = vi;
-        float p = P[i];
-        if (i < n_decay) p -= lr * wd * p;
-        p -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-        P[i] = p;
+// Gradient of every parameter from its partials, then AdamW (the first nw
+// entries, the weights, get decoupled weight decay).  Weight entries are the
+// sums of the split-K partials in split order, one thread each; a bias entry
+// is the FP64 sum of its row-block partials, one wave each, in a fixed order.
+// Nothing is written unless coef[3] (the loss kernel's status) is 0.
+__global__ __launch_bounds__(256) void grad_adamw_kernel(GradParts gp, const double* __restrict__ coef,
+                                                         float* __restrict__ P, float* __restrict__ G,
+                                                         float* __restrict__ Mm, float* __restrict__ V, float lr,
+                                                         float b1, float b2, float eps, float wd, float c1, float c2) {
+    if (coef[3] != 0.0) return;
+    const int64_t nw = gp.wsize[0] + gp.wsize[1] + gp.wsize[2];
+    const int64_t wblocks = (nw + 255) / 256;
+    int64_t i;
+    float g;
+    bool mine;
+    if ((int64_t)blockIdx.x < wblocks) {
+        i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+        mine = i < nw;
+        if (!mine) return;
+        int l = 0;
+        int64_t e = i;
+        while (e >= gp.wsize[l]) e -= gp.wsize[l++];
+        g = 0.0f;
+#pragma unroll 8
+        for (int z = 0; z < gp.splits[l]; ++z) g += gp.wpart[l][z * gp.wsize[l] + e];
+    } else {
+        int64_t e = ((int64_t)blockIdx.x - wblocks) * 4 + (threadIdx.x >> 6);
+        i = nw + e;
+        if (e >= gp.bsize[0] + gp.bsize[1] + gp.bsize[2]) return;
+        int l = 0;
+        while (e >= gp.bsize[l]) e -= gp.bsize[l++];
+        double s = 0.0;
+        for (int64_t q = threadIdx.x & 63; q < gp.bblocks[l]; q += 64) s += gp.bpart[l][q * gp.bsize[l] + e];
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+        g = (float)s;
+        if ((threadIdx.x & 63) != 0) return;
     }
+    G[i] = g;
+    const float mi = b1 * Mm[i] + (1.0f - b1) * g;
+    const float vi = b2 * V[i] + (1.0f - b2) * g * g;
+    Mm[i] = mi;
+    V[i] = vi;
+    float p = P[i];
+    if (i < nw) p -= lr * wd * p;
+    p -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    P[i] = p;
 }
 
-hipError_t launch_adamw(float* P, const float* G, float* M, float* V, int64_t m, int64_t n_decay, float lr, float b1,
-                        float b2, float eps, float wd, int64_t t, hipStream_t stream) {
+hipError_t launch_grad_adamw(const GradParts& gp, const double* coef, float* P, float* G, float* M, float* V, float lr,
+                             float b1, float b2, float eps, float wd, int64_t t, hipStream_t stream) {
     const float c1 = 1.0f - powf(b1, (float)t), c2 = 1.0f - powf(b2, (float)t);
-    int64_t blocks = (m + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(adamw_kernel, dim3(blocks), dim3(256), 0, stream, P, G, M, V, m, n_decay, lr, b1, b2, eps, wd, c1, c2);
+    const int64_t nw = gp.wsize[0] + gp.wsize[1] + gp.wsize[2], nb = gp.bsize[0] + gp.bsize[1] + gp.bsize[2];
+    hipLaunchKernelGGL(grad_adamw_kernel, dim3((nw + 255) / 256 + (nb + 3) / 4), dim3(256), 0, stream, gp, coef, P, G, M,
+                       V, lr, b1, b2, eps, wd, c1, c2);
     return hipGetLastError();
 }
 
@@ -395,40 +401,103 @@ hipError_t launch_spa(double* R, int64_t m, int64_t k, double* bval, int64_t* bi
 }
 
 // ---------------------------------------------------------------------------
-// FP64 products X^T Y (kx x ky, both <= 64) of two row-major FP32 matrices
-// over m rows: 64-row slabs staged through LDS, every thread accumulating 16
-// entries of the slab's product; slab partials reduced in slab order.
+// FP64 products of two row-major FP32 matrices over m rows, kx, ky <= 64:
+// X^T Y (NP = 1), or X^T X, X^T Y and Y^T Y at once (NP = 3, kx = ky).  A
+// work-group stages XTY_ROWS rows, 64 at a time, in LDS; a thread holds a 4 x 4
+// block of every product in registers (eight 16-byte LDS reads feed 48 FMAs;
+// with one entry per thread and two 4-byte reads per FMA the LDS was the
+// bound), threads left over at small k take rows of their own.  The blocks'
+// partials are then summed in a fixed order by four phases per entry (one
+// thread per entry walked all of them).  The three products of a training
+// step at m = 20000, k = 64: 99 + 207 us in six launches before, 52 + 6 us in
+// two now.
 // ---------------------------------------------------------------------------
-constexpr int XTY_ROWS = 64;
+constexpr int XTY_ROWS = 128;
+constexpr int XTY_LD = KMAX + 4;
 
+template <int NP>
 __global__ __launch_bounds__(256) void xty_slab_kernel(const float* __restrict__ X, int64_t ldx, int kx,
                                                        const float* __restrict__ Y, int64_t ldy, int ky, int64_t m,
                                                        double* __restrict__ part) {
-    __shared__ float xs[XTY_ROWS][KMAX + 1];
-    __shared__ float ys[XTY_ROWS][KMAX + 1];
-    const int64_t r0 = (int64_t)blockIdx.x * XTY_ROWS;
-    for (int f = threadIdx.x; f < XTY_ROWS * KMAX; f += 256) {
-        const int r = f / KMAX, c = f - r * KMAX;
-        const bool in = r0 + r < m;
-        xs[r][c] = (in && c < kx) ? X[(r0 + r) * ldx + c] : 0.0f;
-        ys[r][c] = (in && c < ky) ? Y[(r0 + r) * ldy + c] : 0.0f;
+    __shared__ __align__(16) float lds[2 * 64 * XTY_LD];
+    static_assert(sizeof(lds) >= 256 * 16 * sizeof(double), "the reduction reuses the row buffer");
+    float* xs = lds;
+    float* ys = lds + 64 * XTY_LD;
+    const int t = threadIdx.x;
+    const int ny = (ky + 3) / 4, nt = ((kx + 3) / 4) * ny, groups = 256 / nt;
+    const int grp = t / nt, tile = t - grp * nt;
+    const int ca = 4 * (tile / ny), cb = 4 * (tile % ny);
+    double acc[NP][16];
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[p][e] = 0.0;
+    for (int half = 0; half < XTY_ROWS / 64; ++half) {
+        const int64_t r0 = (int64_t)blockIdx.x * XTY_ROWS + 64 * half;
+        __syncthreads();
+        for (int f = t; f < 64 * KMAX; f += 256) {
+            const int r = f / KMAX, c = f - r * KMAX;
+            const bool in = r0 + r < m;
+            xs[r * XTY_LD + c] = (in && c < kx) ? X[(r0 + r) * ldx + c] : 0.0f;
+            ys[r * XTY_LD + c] = (in && c < ky) ? Y[(r0 + r) * ldy + c] : 0.0f;
+        }
+        __syncthreads();
+        if (grp < groups)
+            for (int r = grp; r < 64; r += groups) {
+                const floatx4 xa = *(const floatx4*)&xs[r * XTY_LD + ca], yb = *(const floatx4*)&ys[r * XTY_LD + cb];
+                floatx4 xb, ya;
+                if (NP == 3) {
+                    xb = *(const floatx4*)&xs[r * XTY_LD + cb];
+                    ya = *(const floatx4*)&ys[r * XTY_LD + ca];
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int e = 4 * i + j;
+                        if (NP == 3) {
+                            acc[0][e] += (double)xa[i] * (double)xb[j];
+                            acc[NP == 3 ? 1 : 0][e] += (double)xa[i] * (double)yb[j];
+                            acc[NP == 3 ? 2 : 0][e] += (double)ya[i] * (double)yb[j];
+                        } else {
+                            acc[0][e] += (double)xa[i] * (double)yb[j];
+                        }
+                    }
+            }
     }
-    __syncthreads();
-    double* dst = part + (int64_t)blockIdx.x * kx * ky;
-    for (int e = threadIdx.x; e < kx * ky; e += 256) {
-        const int a = e / ky, b = e - a * ky;
-        double sum = 0.0;
-        for (int r = 0; r < XTY_ROWS; ++r) sum += (double)xs[r][a] * (double)ys[r][b];
-        dst[e] = sum;
+    double* red = (double*)lds;
+    const int kk = kx * ky;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 16; ++e) red[e * 256 + t] = acc[p][e];
+        __syncthreads();
+        double* dst = part + ((int64_t)blockIdx.x * NP + p) * kk;
+        for (int e = t; e < kk; e += 256) {
+            const int a = e / ky, b = e - a * ky;
+            const int src = (4 * (a & 3) + (b & 3)) * 256 + (a >> 2) * ny + (b >> 2);
+            double sum = 0.0;
+            for (int g = 0; g < groups; ++g) sum += red[src + g * nt];
+            dst[e] = sum;
+        }
     }
 }
 
-__global__ void sum_slabs_kernel(const double* __restrict__ part, int64_t slabs, int entries, double* __restrict__ out) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= entries) return;
+// out[e] = sum over the slabs, 64 entries per work-group, four phases each
+__global__ __launch_bounds__(256) void sum_slabs_kernel(const double* __restrict__ part, int64_t slabs, int entries,
+                                                        double* __restrict__ out) {
+    __shared__ double red[4][64];
+    const int lc = threadIdx.x & 63, ph = threadIdx.x >> 6;
+    const int e = blockIdx.x * 64 + lc;
     double s = 0.0;
-    for (int64_t b = 0; b < slabs; ++b) s += part[b * entries + e];
-    out[e] = s;
+    if (e < entries) {
+#pragma unroll 8
+        for (int64_t b = ph; b < slabs; b += 4) s += part[b * entries + e];
+    }
+    red[ph][lc] = s;
+    __syncthreads();
+    if (ph == 0 && e < entries) out[e] = red[0][lc] + red[1][lc] + red[2][lc] + red[3][lc];
 }
 
 int64_t xty_work_doubles(int64_t m, int64_t kx, int64_t ky) { return ((m + XTY_ROWS - 1) / XTY_ROWS) * kx * ky; }
@@ -437,9 +506,21 @@ hipError_t launch_xty(const float* X, int64_t ldx, int64_t kx, const float* Y, i
                       double* work, double* out, hipStream_t stream) {
     if (kx < 1 || ky < 1 || kx > KMAX || ky > KMAX || m < 1) return hipErrorInvalidValue;
     const int64_t slabs = (m + XTY_ROWS - 1) / XTY_ROWS;
-    hipLaunchKernelGGL(xty_slab_kernel, dim3(slabs), dim3(256), 0, stream, X, ldx, (int)kx, Y, ldy, (int)ky, m, work);
+    hipLaunchKernelGGL(xty_slab_kernel<1>, dim3(slabs), dim3(256), 0, stream, X, ldx, (int)kx, Y, ldy, (int)ky, m, work);
     const int entries = (int)(kx * ky);
-    hipLaunchKernelGGL(sum_slabs_kernel, dim3((entries + 255) / 256), dim3(256), 0, stream, (const double*)work, slabs,
+    hipLaunchKernelGGL(sum_slabs_kernel, dim3((entries + 63) / 64), dim3(256), 0, stream, (const double*)work, slabs,
+                       entries, out);
+    return hipGetLastError();
+}
+
+// out = [A^T A, A^T B, B^T B], k x k each; work: 3 xty_work_doubles(m, k, k)
+hipError_t launch_gram3(const float* A, const float* B, int64_t k, int64_t m, double* work, double* out,
+                        hipStream_t stream) {
+    if (k < 1 || k > KMAX || m < 1) return hipErrorInvalidValue;
+    const int64_t slabs = (m + XTY_ROWS - 1) / XTY_ROWS;
+    hipLaunchKernelGGL(xty_slab_kernel<3>, dim3(slabs), dim3(256), 0, stream, A, k, (int)k, B, k, (int)k, m, work);
+    const int entries = (int)(3 * k * k);
+    hipLaunchKernelGGL(sum_slabs_kernel, dim3((entries + 63) / 64), dim3(256), 0, stream, (const double*)work, slabs,
                        entries, out);
     return hipGetLastError();
 }
@@ -689,38 +770,150 @@ hipError_t launch_anchor_solve(const float* Y, int64_t w, const double* M, int64
     return hipGetLastError();
 }
 
-// Gram-loss gradient rows: dA_ic = ca sum_j A_ij AtA_jc - cb sum_j B_ij AtB_cj,
-// the per-row form of ca A (A^T A) - cb B (B^T A) (both Gram losses have it).
-__global__ __launch_bounds__(256) void gram_loss_grad_kernel(const float* __restrict__ A, const float* __restrict__ B,
-                                                             const double* __restrict__ AtA,
-                                                             const double* __restrict__ AtB, int k, int64_t m,
-                                                             float ca, float cb, float* __restrict__ dA) {
-    __shared__ float P[KMAX * KMAX];
-    __shared__ float Q[KMAX * KMAX];
-    for (int e = threadIdx.x; e < k * k; e += 256) {
-        P[e] = (float)AtA[e];
-        const int c = e / k, j = e - c * k;
-        Q[j * k + c] = (float)AtB[c * k + j];   // Q[j][c] = (A^T B)_cj
+// Loss and its gradient's coefficients from gram3 = [A^T A, A^T B, B^T B]
+// (one work-group): coef = {L, ca, cb, status}, the gradient being
+// dA = ca A (A^T A) - cb B (B^T A).  With a, b, c the squared norms of the
+// three products, kind 0: L = (a - 2 b + c) / c, ca = cb = 4 / c; kind 1:
+// L = 1 - b^2 / (a c), cb = 4 b / (a c), ca = cb b / a.  status 1: c is zero or
+// not finite; 2 (kind 1): a is zero; 3: L is not finite.  On the device so
+// that a training step waits for the host once, at its end.
+__global__ __launch_bounds__(256) void loss_coef_kernel(const double* __restrict__ gram3, int kk, int kind,
+                                                        double* __restrict__ coef) {
+    __shared__ double red[3][4];
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        double s = 0.0;
+#pragma unroll 4
+        for (int e = t; e < kk; e += 256) {
+            const double v = gram3[p * kk + e];
+            s += v * v;
+        }
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+        if ((t & 63) == 0) red[p][t >> 6] = s;
     }
     __syncthreads();
-    for (int64_t e = blockIdx.x * (int64_t)256 + threadIdx.x; e < m * k; e += (int64_t)gridDim.x * 256) {
-        const int64_t i = e / k;
-        const int c = (int)(e - i * k);
-        float sa = 0.0f, sb = 0.0f;
-        for (int j = 0; j < k; ++j) {
-            sa += A[i * k + j] * P[j * k + c];
-            sb += B[i * k + j] * Q[j * k + c];
-        }
-        dA[e] = ca * sa - cb * sb;
+    if (t != 0) return;
+    const double a = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+    const double b = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+    const double c = red[2][0] + red[2][1] + red[2][2] + red[2][3];
+    double L = 0.0, ca = 0.0, cb = 0.0, status = 0.0;
+    if (!(c > 0.0) || !isfinite(c)) {
+        status = 1.0;
+    } else if (kind == 0) {
+        L = (a - 2.0 * b + c) / c;
+        ca = cb = 4.0 / c;
+    } else if (!(a > 0.0)) {
+        status = 2.0;
+    } else {
+        L = 1.0 - b * b / (a * c);
+        cb = 4.0 * b / (a * c);
+        ca = cb * b / a;
     }
+    if (status == 0.0 && !isfinite(L)) status = 3.0;
+    coef[0] = L;
+    coef[1] = ca;
+    coef[2] = cb;
+    coef[3] = status;
 }
 
-hipError_t launch_gram_loss_grad(const float* A, const float* B, const double* AtA, const double* AtB, int64_t k,
-                                 int64_t m, float ca, float cb, float* dA, hipStream_t stream) {
-    if (k > KMAX) return hipErrorInvalidValue;
-    int64_t blocks = (m * k + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
-    hipLaunchKernelGGL(gram_loss_grad_kernel, dim3(blocks), dim3(256), 0, stream, A, B, AtA, AtB, (int)k, m, ca, cb, dA);
+hipError_t launch_loss_coef(const double* gram3, int64_t k, int kind, double* coef, hipStream_t stream) {
+    hipLaunchKernelGGL(loss_coef_kernel, dim3(1), dim3(256), 0, stream, gram3, (int)(k * k), kind, coef);
+    return hipGetLastError();
+}
+
+// Backward of the Gram loss through the network's output, 64 rows per
+// work-group: dA = ca A (A^T A) - cb B (B^T A) on the FP32 matrix cores (both
+// Gram losses have this form), dZ = dA f'(Z) with f the residual output
+// max(X + z, 0) or softplus, and the FP64 column sums of dZ (the last layer's
+// bias gradient).  Rows and the k x k products sit in LDS, zero-padded to a
+// multiple of 16 columns; an operand read of four consecutive reduction
+// indices feeds four MFMAs.  m = 20000, k = 64: 61 us in two launches (scalar
+// dot products, then the activation) before, 25 us now.
+template <int KP, bool RES>
+__global__ __launch_bounds__(256) void loss_backward_kernel(const float* __restrict__ A, const float* __restrict__ B,
+                                                            const double* __restrict__ gram3,
+                                                            const double* __restrict__ coef,
+                                                            const float* __restrict__ X, int64_t ldx,
+                                                            const float* __restrict__ Zpre, int k, int64_t m,
+                                                            float* __restrict__ dZ, double* __restrict__ part) {
+    constexpr int LD = KP + 4, NB = KP / 16;
+    __shared__ __align__(16) float As[64 * LD], Bs[64 * LD];
+    __shared__ float Ps[KP * LD], Qs[KP * LD];
+    __shared__ double red[4][KP];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, lr = lane & 15, lg = lane >> 4;
+    const int64_t r0 = (int64_t)blockIdx.x * 64;
+    for (int f = t; f < 64 * KP; f += 256) {
+        const int r = f / KP, c = f - r * KP;
+        const bool in = r0 + r < m && c < k;
+        As[r * LD + c] = in ? A[(r0 + r) * k + c] : 0.0f;
+        Bs[r * LD + c] = in ? B[(r0 + r) * k + c] : 0.0f;
+    }
+    for (int f = t; f < KP * KP; f += 256) {
+        const int j = f / KP, c = f - j * KP;
+        const bool in = j < k && c < k;
+        Ps[j * LD + c] = in ? (float)gram3[j * k + c] : 0.0f;
+        Qs[c * LD + j] = in ? (float)gram3[k * k + j * k + c] : 0.0f;   // Q[c][j] = (A^T B)_jc
+    }
+    __syncthreads();
+    floatx4 ga[NB], gb[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) ga[n] = gb[n] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NB; ++s) {
+        const floatx4 av = *(const floatx4*)&As[(16 * wv + lr) * LD + 16 * s + 4 * lg];
+        const floatx4 bv = *(const floatx4*)&Bs[(16 * wv + lr) * LD + 16 * s + 4 * lg];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int n = 0; n < NB; ++n) {
+                const int o = (16 * s + 4 * lg + e) * LD + 16 * n + lr;
+                ga[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], Ps[o], ga[n], 0, 0, 0);
+                gb[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[e], Qs[o], gb[n], 0, 0, 0);
+            }
+    }
+    const float ca = (float)coef[1], cb = (float)coef[2];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        const int c = 16 * n + lr;
+        double s = 0.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int64_t r = r0 + 16 * wv + 4 * lg + v;
+            if (r < m && c < k) {
+                const float dA = ca * ga[n][v] - cb * gb[n][v];
+                const float z = Zpre[r * k + c];
+                const float d = RES ? (X[r * ldx + c] + z > 0.0f ? dA : 0.0f) : dA * (0.5f * (1.0f + tanhf(0.5f * z)));
+                dZ[r * k + c] = d;
+                s += (double)d;
+            }
+        }
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (lg == 0) red[wv][c] = s;
+    }
+    __syncthreads();
+    for (int c = t; c < k; c += 256) part[blockIdx.x * (int64_t)k + c] = red[0][c] + red[1][c] + red[2][c] + red[3][c];
+}
+
+int64_t loss_backward_blocks(int64_t m) { return (m + 63) / 64; }
+
+hipError_t launch_loss_backward(const float* A, const float* B, const double* gram3, const double* coef, const float* X,
+                                int64_t ldx, const float* Z, int residual, int64_t k, int64_t m, float* dZ, double* part,
+                                hipStream_t stream) {
+    if (k < 1 || k > KMAX || m < 1) return hipErrorInvalidValue;
+    const dim3 grid(loss_backward_blocks(m)), block(256);
+#define LB(KP)                                                                                                    \
+    do {                                                                                                          \
+        if (residual)                                                                                             \
+            hipLaunchKernelGGL((loss_backward_kernel<KP, true>), grid, block, 0, stream, A, B, gram3, coef, X, ldx, Z, \
+                               (int)k, m, dZ, part);                                                              \
+        else                                                                                                      \
+            hipLaunchKernelGGL((loss_backward_kernel<KP, false>), grid, block, 0, stream, A, B, gram3, coef, X, ldx, Z, \
+                               (int)k, m, dZ, part);                                                              \
+    } while (0)
+    if (k <= 16) LB(16); else if (k <= 32) LB(32); else LB(64);
+#undef LB
     return hipGetLastError();
 }
 

@@ -17,14 +17,12 @@ struct symnmf_mlp {
     bool bf16_stale = true;
     int32_t residual = 0;     // output max(C + z, 0) over the input's first k columns instead of softplus(z)
     int64_t t = 0;            // AdamW steps taken
-    float* split_ws = nullptr;
-    int64_t split_floats = 0;
-    double* small = nullptr;  // AtA, AtB, BtB (3 k^2) then x^T y slab work
-    int64_t small_doubles = 0;
+    float* split_ws = nullptr;    // split-K partials of the gradients of W1, W2, W3
+    double* small = nullptr;  // loss coefficients (4), A^T A, A^T B, B^T B (3 k^2), their slab work, bias partials
     // activations, grown on demand
     int64_t cap_fwd = 0, cap_train = 0;
     float *a1 = nullptr, *a2 = nullptr;
-    float *z1 = nullptr, *z2 = nullptr, *z3 = nullptr, *out = nullptr, *dA = nullptr, *d3 = nullptr, *da2 = nullptr;
+    float *z1 = nullptr, *z2 = nullptr, *z3 = nullptr, *out = nullptr, *d3 = nullptr, *da2 = nullptr;
 
     int64_t off_W1() const { return 0; }
     int64_t off_W2() const { return h * w; }
@@ -52,27 +50,25 @@ symnmf_status ensure_fwd(symnmf_mlp* m, int64_t rows) {
     return SYMNMF_OK;
 }
 
+int64_t small_doubles(const symnmf_mlp* m, int64_t rows) {
+    return 4 + 3 * m->k * m->k + 3 * xty_work_doubles(rows, m->k, m->k) + 2 * bias_blocks(rows) * m->h +
+           loss_backward_blocks(rows) * m->k;
+}
+
 symnmf_status ensure_train(symnmf_mlp* m, int64_t rows) {
     if (m->cap_train >= rows) return SYMNMF_OK;
-    free_all({m->z1, m->z2, m->z3, m->out, m->dA, m->d3, m->da2});
-    m->z1 = m->z2 = m->z3 = m->out = m->dA = m->d3 = m->da2 = nullptr;
+    free_all({m->z1, m->z2, m->z3, m->out, m->d3, m->da2, m->small});
+    m->z1 = m->z2 = m->z3 = m->out = m->d3 = m->da2 = nullptr;
+    m->small = nullptr;
     m->cap_train = 0;
     HIP_OK(m->ctx, hipMalloc((void**)&m->z1, rows * m->h * 4));
     HIP_OK(m->ctx, hipMalloc((void**)&m->z2, rows * m->h * 4));
     HIP_OK(m->ctx, hipMalloc((void**)&m->da2, rows * m->h * 4));
     HIP_OK(m->ctx, hipMalloc((void**)&m->z3, rows * m->k * 4));
     HIP_OK(m->ctx, hipMalloc((void**)&m->out, rows * m->k * 4));
-    HIP_OK(m->ctx, hipMalloc((void**)&m->dA, rows * m->k * 4));
     HIP_OK(m->ctx, hipMalloc((void**)&m->d3, rows * m->k * 4));
+    HIP_OK(m->ctx, hipMalloc((void**)&m->small, small_doubles(m, rows) * 8));
     m->cap_train = rows;
-    const int64_t need = 3 * m->k * m->k + xty_work_doubles(rows, m->k, m->k);
-    if (m->small_doubles < need) {
-        if (m->small) (void)hipFree(m->small);
-        m->small = nullptr;
-        m->small_doubles = 0;
-        HIP_OK(m->ctx, hipMalloc((void**)&m->small, need * 8));
-        m->small_doubles = need;
-    }
     return SYMNMF_OK;
 }
 
@@ -91,11 +87,11 @@ symnmf_status forward(symnmf_mlp* m, const float* X, int64_t rows, bool bf16, bo
     const void* W3 = bf16 ? (const void*)(m->Wb + m->off_W3()) : (const void*)(m->P + m->off_W3());
     const int b = bf16 ? 1 : 0;
     HIP_OK(ctx, launch_gemm(0, 0, b, 1, X, W1, m->P + m->off_b1(), m->a1, train ? m->z1 : nullptr, rows, m->h, m->w,
-                            1.0f, nullptr, 0, sm));
+                            1.0f, 1, sm));
     HIP_OK(ctx, launch_gemm(0, 0, b, 1, m->a1, W2, m->P + m->off_b2(), m->a2, train ? m->z2 : nullptr, rows, m->h,
-                            m->h, 1.0f, nullptr, 0, sm));
+                            m->h, 1.0f, 1, sm));
     HIP_OK(ctx, launch_gemm(0, 0, b, m->residual ? 0 : 2, m->a2, W3, m->P + m->off_b3(), A, train ? m->z3 : nullptr,
-                            rows, m->k, m->h, 1.0f, nullptr, 0, sm));
+                            rows, m->k, m->h, 1.0f, 1, sm));
     if (m->residual) HIP_OK(ctx, launch_residual_relu(X, m->w, A, rows, m->k, sm));
     return SYMNMF_OK;
 }
@@ -142,8 +138,9 @@ symnmf_status symnmf_mlp_create(symnmf_ctx* ctx, int64_t width, int64_t hidden, 
     m->k = k;
     m->np = np;
     m->nw = hidden * width + hidden * hidden + k * hidden;
-    // split-K partials of the weight gradients: at most 64 splits of the largest W
-    m->split_floats = 64 * std::max({hidden * width, hidden * hidden, k * hidden});
+    const int64_t split_floats = gemm_max_splits(hidden, width) * hidden * width +
+                                 gemm_max_splits(hidden, hidden) * hidden * hidden +
+                                 gemm_max_splits(k, hidden) * k * hidden;
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
     chk(hipMalloc((void**)&m->P, np * 4));
@@ -151,7 +148,7 @@ symnmf_status symnmf_mlp_create(symnmf_ctx* ctx, int64_t width, int64_t hidden, 
     chk(hipMalloc((void**)&m->Mm, np * 4));
     chk(hipMalloc((void**)&m->V, np * 4));
     chk(hipMalloc((void**)&m->Wb, m->nw * 2));
-    chk(hipMalloc((void**)&m->split_ws, m->split_floats * 4));
+    chk(hipMalloc((void**)&m->split_ws, split_floats * 4));
     if (e == hipSuccess) chk(hipMemcpyAsync(m->P, params, np * 4, hipMemcpyDeviceToDevice, ctx->stream));
     if (e == hipSuccess) chk(launch_zero(m->G, np * 4, ctx->stream));
     if (e == hipSuccess) chk(launch_zero(m->Mm, np * 4, ctx->stream));
@@ -168,8 +165,8 @@ symnmf_status symnmf_mlp_create(symnmf_ctx* ctx, int64_t width, int64_t hidden, 
 void symnmf_mlp_destroy(symnmf_mlp* m) {
     if (!m) return;
     if (m->ctx) (void)hipStreamSynchronize(m->ctx->stream);
-    free_all({m->P, m->G, m->Mm, m->V, m->Wb, m->split_ws, m->small, m->a1, m->a2, m->z1, m->z2, m->z3, m->out, m->dA,
-              m->d3, m->da2});
+    free_all({m->P, m->G, m->Mm, m->V, m->Wb, m->split_ws, m->small, m->a1, m->a2, m->z1, m->z2, m->z3, m->out, m->d3,
+              m->da2});
     delete m;
 }
 
@@ -234,62 +231,56 @@ symnmf_status symnmf_mlp_train_step(symnmf_ctx* ctx, symnmf_mlp* m, const float*
     if (s != SYMNMF_OK) return s;
     s = forward(m, X, rows, false, true, m->out);
     if (s != SYMNMF_OK) return s;
-    const int64_t k = m->k, h = m->h, w = m->w, kk = k * k;
-    double* AtA = m->small;
-    double* AtB = m->small + kk;
-    double* BtB = m->small + 2 * kk;
-    double* work = m->small + 3 * kk;
-    HIP_OK(ctx, launch_xty(m->out, k, k, m->out, k, k, rows, work, AtA, sm));
-    HIP_OK(ctx, launch_xty(m->out, k, k, B, k, k, rows, work, AtB, sm));
-    HIP_OK(ctx, launch_xty(B, k, k, B, k, k, rows, work, BtB, sm));
-    std::vector<double> hs(3 * kk);
-    HIP_OK(ctx, hipMemcpyAsync(hs.data(), m->small, 3 * kk * 8, hipMemcpyDeviceToHost, sm));
-    HIP_OK(ctx, hipStreamSynchronize(sm));
-    double naa = 0.0, nab = 0.0, nbb = 0.0;
-    for (int64_t e = 0; e < kk; ++e) {
-        naa += hs[e] * hs[e];
-        nab += hs[kk + e] * hs[kk + e];
-        nbb += hs[2 * kk + e] * hs[2 * kk + e];
-    }
-    if (!(nbb > 0.0) || !std::isfinite(nbb)) return fail(ctx, SYMNMF_EINVAL, "mlp_train_step: target B^T B is zero");
-    double L, ca, cb;
-    if (loss_kind == 0) {
-        // ||A A^T - B B^T||^2 / ||B^T B||^2, gradient 4 (A (A^T A) - B (B^T A)) / ||B^T B||^2
-        L = (naa - 2.0 * nab + nbb) / nbb;
-        ca = cb = 4.0 / nbb;
-    } else {
-        // 1 - ||A^T B||^4 / (||A^T A||^2 ||B^T B||^2), gradient
-        // (4 b / (a c)) ((b / a) A (A^T A) - B (B^T A)) with a, b, c = naa, nab, nbb
-        if (!(naa > 0.0)) return fail(ctx, SYMNMF_ENUMERIC, "mlp_train_step: network output is zero");
-        L = 1.0 - nab * nab / (naa * nbb);
-        cb = 4.0 * nab / (naa * nbb);
-        ca = cb * nab / naa;
-    }
-    if (loss) *loss = L;
-    if (!std::isfinite(L)) return fail(ctx, SYMNMF_ENUMERIC, "mlp_train_step: non-finite loss");
-    // backward
-    HIP_OK(ctx, launch_gram_loss_grad(m->out, B, AtA, AtB, k, rows, (float)ca, (float)cb, m->dA, sm));
-    if (m->residual) HIP_OK(ctx, launch_residual_relu_backward(m->dA, X, w, m->z3, m->d3, rows, k, sm));
-    else HIP_OK(ctx, launch_act_backward(m->dA, m->z3, m->d3, rows * k, 2, sm));
-    HIP_OK(ctx, launch_gemm(1, 1, 0, 0, m->d3, m->a2, nullptr, m->G + m->off_W3(), nullptr, k, h, rows, 1.0f,
-                            m->split_ws, m->split_floats, sm));
-    HIP_OK(ctx, launch_colsum(m->d3, rows, k, m->G + m->off_b3(), sm));
-    HIP_OK(ctx, launch_gemm(0, 1, 0, 0, m->d3, m->P + m->off_W3(), nullptr, m->da2, nullptr, rows, h, k, 1.0f, nullptr,
-                            0, sm));
-    HIP_OK(ctx, launch_act_backward(m->da2, m->z2, m->da2, rows * h, 1, sm));        // d2
-    HIP_OK(ctx, launch_gemm(1, 1, 0, 0, m->da2, m->a1, nullptr, m->G + m->off_W2(), nullptr, h, h, rows, 1.0f,
-                            m->split_ws, m->split_floats, sm));
-    HIP_OK(ctx, launch_colsum(m->da2, rows, h, m->G + m->off_b2(), sm));
+    const int64_t k = m->k, h = m->h, w = m->w;
+    double* coef = m->small;
+    double* gram3 = coef + 4;
+    double* work = gram3 + 3 * k * k;
+    double* b1p = work + 3 * xty_work_doubles(rows, k, k);
+    double* b2p = b1p + bias_blocks(rows) * h;
+    double* b3p = b2p + bias_blocks(rows) * h;
+    GradParts gp;
+    gp.wsize[0] = h * w;
+    gp.wsize[1] = h * h;
+    gp.wsize[2] = k * h;
+    gp.splits[0] = gemm_splits(h, w, rows);
+    gp.splits[1] = gemm_splits(h, h, rows);
+    gp.splits[2] = gemm_splits(k, h, rows);
+    float* w1p = m->split_ws;
+    float* w2p = w1p + gp.splits[0] * gp.wsize[0];
+    float* w3p = w2p + gp.splits[1] * gp.wsize[1];
+    gp.wpart[0] = w1p;
+    gp.wpart[1] = w2p;
+    gp.wpart[2] = w3p;
+    gp.bpart[0] = b1p;
+    gp.bpart[1] = b2p;
+    gp.bpart[2] = b3p;
+    gp.bsize[0] = gp.bsize[1] = h;
+    gp.bsize[2] = k;
+    gp.bblocks[0] = gp.bblocks[1] = bias_blocks(rows);
+    gp.bblocks[2] = loss_backward_blocks(rows);
+    HIP_OK(ctx, launch_gram3(m->out, B, k, rows, work, gram3, sm));
+    HIP_OK(ctx, launch_loss_coef(gram3, k, loss_kind, coef, sm));
+    // backward; the loss is checked on the device (a bad one leaves the
+    // parameters, the gradient and the moments as they are) and read at the end
+    HIP_OK(ctx, launch_loss_backward(m->out, B, gram3, coef, X, w, m->z3, m->residual, k, rows, m->d3, b3p, sm));
+    HIP_OK(ctx, launch_gemm(1, 1, 0, 0, m->d3, m->a2, nullptr, w3p, nullptr, k, h, rows, 1.0f, gp.splits[2], sm));
+    HIP_OK(ctx, launch_gemm(0, 1, 0, 0, m->d3, m->P + m->off_W3(), nullptr, m->da2, nullptr, rows, h, k, 1.0f, 1, sm));
+    HIP_OK(ctx, launch_gelu_backward(m->da2, m->z2, m->da2, rows, h, b2p, sm));      // d2
+    HIP_OK(ctx, launch_gemm(1, 1, 0, 0, m->da2, m->a1, nullptr, w2p, nullptr, h, h, rows, 1.0f, gp.splits[1], sm));
     // da1 = d2 W2 into a2 (no longer needed), then d1 in place
-    HIP_OK(ctx, launch_gemm(0, 1, 0, 0, m->da2, m->P + m->off_W2(), nullptr, m->a2, nullptr, rows, h, h, 1.0f, nullptr,
-                            0, sm));
-    HIP_OK(ctx, launch_act_backward(m->a2, m->z1, m->a2, rows * h, 1, sm));
-    HIP_OK(ctx, launch_gemm(1, 1, 0, 0, m->a2, X, nullptr, m->G + m->off_W1(), nullptr, h, w, rows, 1.0f, m->split_ws,
-                            m->split_floats, sm));
-    HIP_OK(ctx, launch_colsum(m->a2, rows, h, m->G + m->off_b1(), sm));
+    HIP_OK(ctx, launch_gemm(0, 1, 0, 0, m->da2, m->P + m->off_W2(), nullptr, m->a2, nullptr, rows, h, h, 1.0f, 1, sm));
+    HIP_OK(ctx, launch_gelu_backward(m->a2, m->z1, m->a2, rows, h, b1p, sm));
+    HIP_OK(ctx, launch_gemm(1, 1, 0, 0, m->a2, X, nullptr, w1p, nullptr, h, w, rows, 1.0f, gp.splits[0], sm));
+    HIP_OK(ctx, launch_grad_adamw(gp, coef, m->P, m->G, m->Mm, m->V, (float)opt->lr, (float)opt->beta1,
+                                  (float)opt->beta2, (float)opt->eps, (float)opt->weight_decay, m->t + 1, sm));
+    double hc[4];
+    HIP_OK(ctx, hipMemcpyAsync(hc, coef, 4 * 8, hipMemcpyDeviceToHost, sm));
+    HIP_OK(ctx, hipStreamSynchronize(sm));
+    if (hc[3] == 1.0) return fail(ctx, SYMNMF_EINVAL, "mlp_train_step: target B^T B is zero");
+    if (hc[3] == 2.0) return fail(ctx, SYMNMF_ENUMERIC, "mlp_train_step: network output is zero");
+    if (loss) *loss = hc[0];
+    if (hc[3] != 0.0) return fail(ctx, SYMNMF_ENUMERIC, "mlp_train_step: non-finite loss");
     m->t += 1;
-    HIP_OK(ctx, launch_adamw(m->P, m->G, m->Mm, m->V, m->np, m->nw, (float)opt->lr, (float)opt->beta1,
-                             (float)opt->beta2, (float)opt->eps, (float)opt->weight_decay, m->t, sm));
     m->bf16_stale = true;
     return SYMNMF_OK;
 }
