@@ -69,12 +69,6 @@ __global__ __launch_bounds__(256) void check_input_kernel(const float* __restric
     if (negative) atomicOr(flag, BAD_NEGATIVE);
 }
 
-hipError_t launch_check_input(const float* X, int64_t count, float sign, int32_t* flag, hipStream_t stream) {
-    const int64_t blocks = std::min<int64_t>((count + 255) / 256, 4096);
-    if (blocks > 0) hipLaunchKernelGGL(check_input_kernel, dim3(blocks), dim3(256), 0, stream, X, count, sign, flag);
-    return hipGetLastError();
-}
-
 hipError_t launch_standardise(const float* X, int64_t T, int64_t n, void* Z, int z_f64, int64_t ldz, int32_t* bad,
                               hipStream_t stream) {
     if (z_f64)
@@ -87,17 +81,24 @@ hipError_t launch_standardise(const float* X, int64_t T, int64_t n, void* Z, int
 // ---------------------------------------------------------------------------
 // TPDM pieces
 // ---------------------------------------------------------------------------
-// dst (cols x rows) = sign * src (rows x cols)^T, 64 x 64 tiles through LDS.
-template <typename T>
-__global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ src, int64_t rows, int64_t cols,
-                                                        T* __restrict__ dst, T sign) {
-    __shared__ T tile[64][65];
+// dst (cols x rows) = sign * src (rows x cols)^T, 64 x 64 tiles through LDS;
+// raises BAD_NONFINITE in *flag on the way (the input check as a pass of its
+// own cost 129 us of reading X at T = 20000, n = 4096).
+__global__ __launch_bounds__(256) void transpose_kernel(const float* __restrict__ src, int64_t rows, int64_t cols,
+                                                        float* __restrict__ dst, float sign, int32_t* __restrict__ flag) {
+    __shared__ float tile[64][65];
     const int64_t r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+    bool nonfinite = false;
     for (int i = ty; i < 64; i += 4) {
         const int64_t r = r0 + i, c = c0 + tx;
-        if (r < rows && c < cols) tile[i][tx] = src[r * cols + c] * sign;
+        if (r < rows && c < cols) {
+            const float v = src[r * cols + c];
+            nonfinite |= !isfinite(v);
+            tile[i][tx] = v * sign;
+        }
     }
+    if (nonfinite) atomicOr(flag, BAD_NONFINITE);
     __syncthreads();
     for (int i = ty; i < 64; i += 4) {
         const int64_t c = c0 + i, r = r0 + tx;
@@ -113,101 +114,350 @@ __device__ inline uint32_t sortable_key(float v) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// One work-group per column: bitonic sort of the column's keys in LDS, then
-// rank r_t = 1 + #{keys < key_t} + #{t' < t : key_t' = key_t}.
+// Ranks of one column per work-group: a stable radix sort of the keys (four
+// 8-bit digits, lowest first) with the sample numbers carried along, so that
+// equal keys keep their order and a sample's final position + 1 is its rank
+// r_t = 1 + #{keys < key_t} + #{t' < t : key_t' = key_t}.
+// Keys and sample numbers stay in registers (IPT per thread; a wave owns 64 IPT
+// consecutive positions, item j of lane l at 64 j + l) and go through LDS once
+// per digit.  A lane finds the lanes of its wave with its digit from eight
+// ballots, its place among them is a popcount, and one lane per digit advances
+// the wave's counter, so there are no atomics and no dependence on the values'
+// distribution.  Bound by the vector ALU (ballots and masks: 32 bits an item)
+// and the LDS.  The bitonic sort of LDS keys that stood here (120 passes over
+// 32768 keys for T = 20000, then a binary search per sample) took 37.0 ms at
+// n = 4096, T = 20000; this takes 1.03 ms.
 constexpr int RANK_MAX_T = 32768;
-__global__ __launch_bounds__(1024) void rank_kernel(const float* __restrict__ Xt, int64_t T, int32_t* __restrict__ R) {
-    extern __shared__ uint32_t keys[];
+
+template <int THREADS, int IPT>
+__global__ __launch_bounds__(THREADS) void rank_kernel(const float* __restrict__ Xt, int T, uint16_t* __restrict__ R) {
+    constexpr int WAVES = THREADS / 64, CAP = THREADS * IPT;
+    // where both fit (CAP <= 20480) the sample numbers have their own buffer;
+    // otherwise they follow the keys through the same one
+    constexpr bool BOTH = CAP * 6 + WAVES * 1024 <= 150 * 1024;
+    __shared__ uint32_t keys[CAP + (BOTH ? CAP / 2 : 0)];
+    __shared__ uint32_t cnt[WAVES * 256];
+    __shared__ uint32_t wsum[4];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int64_t col = blockIdx.x;
     const float* x = Xt + col * T;
-    int P2 = 1;
-    while (P2 < T) P2 <<= 1;
-    for (int i = threadIdx.x; i < P2; i += blockDim.x) keys[i] = i < T ? sortable_key(x[i]) : 0xffffffffu;
-    __syncthreads();
-    for (int size = 2; size <= P2; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = threadIdx.x; i < (P2 >> 1); i += blockDim.x) {
-                const int lo = 2 * stride * (i / stride) + (i % stride);
-                const int hi = lo + stride;
-                const bool asc = (lo & size) == 0;
-                const uint32_t a = keys[lo], b = keys[hi];
-                if ((a > b) == asc) { keys[lo] = b; keys[hi] = a; }
+    const int base0 = wv * (IPT * 64) + lane;           // position of item 0; item j lies 64 j further
+    constexpr int IDS = BOTH ? 2 * CAP : 0;             // sample numbers, in 16-bit words of the key buffer
+    // per item its key, and its sample number (low half) with its position
+    uint32_t k[IPT], ir[IPT];
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+        const int pos = base0 + 64 * j;
+        ir[j] = (uint32_t)pos;
+        k[j] = pos < T ? sortable_key(x[pos]) : 0xffffffffu;   // padding sorts last
+    }
+    for (int shift = 0; shift < 32; shift += 8) {
+        for (int i = t; i < WAVES * 256; i += THREADS) cnt[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) {
+            const uint32_t d = (k[j] >> shift) & 255u;
+            // lanes of the wave with the same digit: those that vote alike on every bit
+            uint32_t lo = ~0u, hi = ~0u;
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const uint32_t bit = (uint32_t)((int32_t)(d << (31 - b)) >> 31);   // 0 or ~0
+                const uint64_t votes = __ballot(bit != 0);
+                lo &= ~((uint32_t)votes ^ bit);
+                hi &= ~((uint32_t)(votes >> 32) ^ bit);
             }
+            const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+            const uint32_t prev = cnt[wv * 256 + d];
+            ir[j] = (ir[j] & 0xffffu) | ((prev + below) << 16);
+            // packed here and the digit formed anew below: left to itself the
+            // compiler keeps three registers an item alive, and spills
+            asm volatile("" : "+v"(ir[j]), "+v"(k[j]));
+            // the LDS operations of a wave run in order: every lane reads the
+            // counter before the first lane of each digit advances it (the
+            // fences keep the compiler to that order)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (below == 0) cnt[wv * 256 + d] = prev + (uint32_t)(__popc(lo) + __popc(hi));
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        __syncthreads();
+        // exclusive prefix of the counters over (digit, wave)
+        uint32_t tot = 0, incl = 0;
+        if (t < 256) {
+            for (int q = 0; q < WAVES; ++q) {
+                const uint32_t c = cnt[q * 256 + t];
+                cnt[q * 256 + t] = tot;
+                tot += c;
+            }
+            incl = tot;
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t up = __shfl_up(incl, off, 64);
+                if (lane >= off) incl += up;
+            }
+            if (lane == 63) wsum[wv] = incl;
+        }
+        __syncthreads();
+        if (t < 256) {
+            uint32_t base = incl - tot;
+            for (int q = 0; q < wv; ++q) base += wsum[q];
+            for (int q = 0; q < WAVES; ++q) cnt[q * 256 + t] += base;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) ir[j] += cnt[wv * 256 + ((k[j] >> shift) & 255u)] << 16;
+        if (shift == 24) break;
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) {
+            keys[ir[j] >> 16] = k[j];
+            if (BOTH) ((uint16_t*)keys)[IDS + (ir[j] >> 16)] = (uint16_t)ir[j];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) k[j] = keys[base0 + 64 * j];
+        if (!BOTH) {
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < IPT; ++j) ((uint16_t*)keys)[IDS + (ir[j] >> 16)] = (uint16_t)ir[j];
             __syncthreads();
         }
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) ir[j] = ((const uint16_t*)keys)[IDS + base0 + 64 * j];
+        if (!BOTH) __syncthreads();
     }
-    for (int64_t t = threadIdx.x; t < T; t += blockDim.x) {
-        const uint32_t k = sortable_key(x[t]);
-        int lo = 0, hi = (int)T;                 // first index with keys[idx] >= k
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (keys[mid] < k) lo = mid + 1; else hi = mid;
-        }
-        int32_t rank = lo + 1;
-        const bool tie = (lo + 1 < T && keys[lo + 1] == k);
-        if (tie)
-            for (int64_t s = 0; s < t; ++s) rank += (sortable_key(x[s]) == k) ? 1 : 0;
-        R[col * T + t] = rank;
-    }
+    // ranks in sample order (the key buffer is free: its last reads lie before
+    // the barriers of the last digit)
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) ((uint16_t*)keys)[ir[j] & 0xffffu] = (uint16_t)((ir[j] >> 16) + 1);
+    __syncthreads();
+    for (int i = t; i < T; i += THREADS) R[col * T + i] = ((const uint16_t*)keys)[i];
 }
 
-// Radial norm of sample t from its ranks (row t of Rt, n values), FP64.
-__global__ __launch_bounds__(256) void norms_kernel(const int32_t* __restrict__ Rt, int64_t T, int64_t n,
-                                                    double* __restrict__ norms) {
-    __shared__ double red[4];
-    const int64_t t = blockIdx.x;
+static void launch_rank(const float* Xt, int64_t T, int64_t n, uint16_t* R, hipStream_t stream) {
+    // the fewest registers and threads that hold a column: T <= 2048, 8192, 20480, 32768
+    if (T <= 2048)
+        hipLaunchKernelGGL((rank_kernel<256, 8>), dim3(n), dim3(256), 0, stream, Xt, (int)T, R);
+    else if (T <= 8192)
+        hipLaunchKernelGGL((rank_kernel<512, 16>), dim3(n), dim3(512), 0, stream, Xt, (int)T, R);
+    else if (T <= 20480)
+        hipLaunchKernelGGL((rank_kernel<1024, 20>), dim3(n), dim3(1024), 0, stream, Xt, (int)T, R);
+    else
+        hipLaunchKernelGGL((rank_kernel<1024, 32>), dim3(n), dim3(1024), 0, stream, Xt, (int)T, R);
+}
+
+// Squared Pareto(2) margin of rank r: x^2 = 1 / (1 - r / (T + 1)).
+__device__ inline double pareto_sq(uint16_t r, double Tp1) { return Tp1 / (Tp1 - (double)r); }
+
+// Squared radial norms of the samples from the ranks (n x T), FP64: a
+// work-group sums 256 samples over one of NORM_PARTS column ranges, then the
+// ranges are added in order.  One division per entry where x was formed by a
+// power and squared: 522 us before (and 167 us to transpose the ranks), 60 us
+// now at n = 4096, T = 20000.
+constexpr int NORM_PARTS = 64;
+
+__global__ __launch_bounds__(256) void norm_parts_kernel(const uint16_t* __restrict__ R, int64_t T, int64_t n,
+                                                         double* __restrict__ part) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= T) return;
+    const int64_t j0 = blockIdx.y * n / NORM_PARTS, j1 = (blockIdx.y + 1) * n / NORM_PARTS;
     const double Tp1 = (double)T + 1.0;
     double s = 0.0;
-    for (int64_t j = threadIdx.x; j < n; j += 256) {
-        const double x = pow(1.0 - (double)Rt[t * n + j] / Tp1, -0.5);
-        s += x * x;
-    }
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) norms[t] = sqrt(red[0] + red[1] + red[2] + red[3]);
+#pragma unroll 4
+    for (int64_t j = j0; j < j1; ++j) s += pareto_sq(R[j * T + t], Tp1);
+    part[blockIdx.y * T + t] = s;
 }
 
-// Indices of the n_exc largest norms in increasing t (ties to the lower t),
-// given v* = the n_exc-th largest norm.
-__global__ void compact_kernel(const double* __restrict__ norms, int64_t T, int64_t n_exc,
-                               const double* __restrict__ vstar, int32_t* __restrict__ idx) {
-    if (threadIdx.x != 0) return;
-    const double v = vstar[0];
-    int64_t greater = 0;
-    for (int64_t t = 0; t < T; ++t) greater += norms[t] > v ? 1 : 0;
-    int64_t equal_left = n_exc - greater, a = 0;
-    for (int64_t t = 0; t < T && a < n_exc; ++t) {
-        if (norms[t] > v) idx[a++] = (int32_t)t;
-        else if (norms[t] == v && equal_left > 0) { idx[a++] = (int32_t)t; --equal_left; }
-    }
+__global__ __launch_bounds__(256) void norm_sum_kernel(const double* __restrict__ part, int64_t T,
+                                                       double* __restrict__ norms) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= T) return;
+    double s = 0.0;
+#pragma unroll 8
+    for (int p = 0; p < NORM_PARTS; ++p) s += part[p * T + t];
+    norms[t] = sqrt(s);
 }
 
-// Omega_aj = x(R[t_a][j]) / ||x_{t_a}||, then column j scaled to unit norm.
-template <typename ZT>
-__global__ __launch_bounds__(256) void omega_kernel(const int32_t* __restrict__ Rt, int64_t T, int64_t n,
-                                                    const double* __restrict__ norms,
-                                                    const int32_t* __restrict__ idx, int64_t n_exc,
-                                                    ZT* __restrict__ Om, int64_t ldz) {
-    __shared__ double red[4][64];
-    const int lc = threadIdx.x & 63, ph = threadIdx.x >> 6;
-    const int64_t col = blockIdx.x * 64 + lc;
-    const double Tp1 = (double)T + 1.0;
-    double ss = 0.0;
-    if (col < n)
-        for (int64_t a = ph; a < n_exc; a += 4) {
-            const int64_t t = idx[a];
-            const double w = pow(1.0 - (double)Rt[t * n + col] / Tp1, -0.5) / norms[t];
-            ss += w * w;
+// Indices of the n_exc largest norms in increasing t, ties to the lower t, in
+// one work-group: the n_exc-th largest value v* by an MSB-first radix selection
+// on the bit patterns (monotone for non-negative values), then every thread
+// places the samples of its own range of t from a scan of the counts above and
+// at v*.  The placement by one thread walking all samples took 3.38 ms at
+// T = 20000 and the selection 100 us in 17 launches; together 58 us now.
+__global__ __launch_bounds__(1024) void exceed_kernel(const double* __restrict__ norms, int64_t T, int64_t n_exc,
+                                                      int32_t* __restrict__ idx) {
+    __shared__ uint32_t hist[256];
+    __shared__ uint64_t sh_prefix, sh_rank;
+    __shared__ int64_t wg[16], we[16];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    uint64_t prefix = 0, mask = 0, rank = (uint64_t)(T - n_exc);
+    for (int shift = 56; shift >= 0; shift -= 8) {
+        if (t < 256) hist[t] = 0;
+        __syncthreads();
+        for (int64_t i = t; i < T; i += 1024) {
+            const uint64_t key = __builtin_bit_cast(uint64_t, norms[i]);
+            if ((key & mask) == prefix) {
+                // norms agree in their upper digits: one add for a wave whose
+                // lanes all hold the same digit
+                const uint32_t d = (uint32_t)(key >> shift) & 255u;
+                const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+                const uint64_t act = __ballot(true), eq = __ballot(d == d0);
+                if (eq == act) {
+                    if (lane == __ffsll((unsigned long long)act) - 1) atomicAdd(&hist[d0], (uint32_t)__popcll(act));
+                } else {
+                    atomicAdd(&hist[d], 1u);
+                }
+            }
         }
-    red[ph][lc] = ss;
+        __syncthreads();
+        if (wv == 0) {
+            // the digit that holds the rank, from a scan of four bins per lane
+            uint32_t c[4], tot = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                c[q] = hist[4 * lane + q];
+                tot += c[q];
+            }
+            uint32_t incl = tot;
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t up = __shfl_up(incl, off, 64);
+                if (lane >= off) incl += up;
+            }
+            uint64_t below = incl - tot;
+            if (rank >= below && rank < incl) {
+                int q = 0;
+                while (rank >= below + c[q]) below += c[q++];
+                sh_prefix = prefix | ((uint64_t)(4 * lane + q) << shift);
+                sh_rank = rank - below;
+            }
+        }
+        __syncthreads();
+        prefix = sh_prefix;
+        rank = sh_rank;
+        mask |= (uint64_t)255u << shift;
+    }
+    // on the keys, so that every place is filled whatever the norms hold (X
+    // with a NaN is refused by the caller after these kernels have run)
+    auto key_of = [&](int64_t i) { return __builtin_bit_cast(uint64_t, norms[i]); };
+    const int64_t per = (T + 1023) / 1024, t0 = min(t * per, T), t1 = min(t0 + per, T);
+    int64_t greater = 0, equal = 0;
+    for (int64_t i = t0; i < t1; ++i) {
+        greater += key_of(i) > prefix ? 1 : 0;
+        equal += key_of(i) == prefix ? 1 : 0;
+    }
+    int64_t ig = greater, ie = equal;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int64_t ug = __shfl_up(ig, off, 64), ue = __shfl_up(ie, off, 64);
+        if (lane >= off) {
+            ig += ug;
+            ie += ue;
+        }
+    }
+    if (lane == 63) {
+        wg[wv] = ig;
+        we[wv] = ie;
+    }
     __syncthreads();
-    const double c = sqrt(red[0][lc] + red[1][lc] + red[2][lc] + red[3][lc]);
-    if (col >= n) return;
-    for (int64_t a = ph; a < n_exc; a += 4) {
-        const int64_t t = idx[a];
-        const double w = pow(1.0 - (double)Rt[t * n + col] / Tp1, -0.5) / norms[t];
-        Om[a * ldz + col] = (ZT)(w / c);
+    int64_t bg = ig - greater, be = ie - equal, all = 0;
+    for (int q = 0; q < 16; ++q) {
+        if (q < wv) {
+            bg += wg[q];
+            be += we[q];
+        }
+        all += wg[q];
+    }
+    const int64_t take = n_exc - all;                  // samples at v* that are kept: the first ones
+    int64_t out = bg + min(be, take);
+    for (int64_t i = t0; i < t1; ++i) {
+        if (key_of(i) > prefix) idx[out++] = (int32_t)i;
+        else if (key_of(i) == prefix && be++ < take) idx[out++] = (int32_t)i;
+    }
+}
+
+// Angular rows Omega_aj = x_j(t_a) / ||x_{t_a}||, columns scaled to unit norm,
+// in two launches over 64-column x 64-row tiles: FP64 column sums of squares
+// per tile, then the scaled rows (each tile adds its columns' sums in order).
+// x comes from the ranks (n x T, read along the samples and turned through LDS
+// for the row-major store) or, RAW, from X itself with the tail's sign.  One
+// work-group per 64 columns walking all rows took 393 us at n = 4096, 1000
+// rows; the two launches take 53 us.
+template <bool RAW>
+__device__ inline double omega_entry(const float* __restrict__ X, const uint16_t* __restrict__ R, int64_t T, int64_t n,
+                                     float sign, int64_t t, int64_t col, double norm) {
+    if (RAW) return (double)sign * (double)X[t * n + col] / norm;
+    return sqrt(pareto_sq(R[col * T + t], (double)T + 1.0)) / norm;
+}
+
+template <bool RAW>
+__global__ __launch_bounds__(256) void omega_sq_kernel(const float* __restrict__ X, const uint16_t* __restrict__ R,
+                                                       int64_t T, int64_t n, float sign, const double* __restrict__ norms,
+                                                       const int32_t* __restrict__ idx, int64_t n_exc,
+                                                       double* __restrict__ part) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t c0 = (int64_t)blockIdx.x * 64, a0 = (int64_t)blockIdx.y * 64;
+    if (RAW) {
+        __shared__ double red[4][64];
+        const int64_t col = c0 + lane;
+        double ss = 0.0;
+        if (col < n)
+            for (int64_t a = a0 + wv; a < min(a0 + 64, n_exc); a += 4) {
+                const int64_t t = idx[a];
+                const double w = omega_entry<RAW>(X, R, T, n, sign, t, col, norms[t]);
+                ss += w * w;
+            }
+        red[wv][lane] = ss;
+        __syncthreads();
+        if (wv == 0 && col < n) part[blockIdx.y * n + col] = red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane];
+    } else {
+        const int64_t a = a0 + lane, t = a < n_exc ? idx[a] : 0;
+        const double nt = a < n_exc ? norms[t] : 1.0;
+#pragma unroll 4
+        for (int q = 0; q < 16; ++q) {
+            const int64_t col = c0 + 16 * wv + q;
+            if (col >= n) break;
+            const double w = a < n_exc ? omega_entry<RAW>(X, R, T, n, sign, t, col, nt) : 0.0;
+            double ss = w * w;
+            for (int off = 32; off > 0; off >>= 1) ss += __shfl_down(ss, off, 64);
+            if (lane == 0) part[blockIdx.y * n + col] = ss;
+        }
+    }
+}
+
+template <bool RAW, typename ZT>
+__global__ __launch_bounds__(256) void omega_kernel(const float* __restrict__ X, const uint16_t* __restrict__ R,
+                                                    int64_t T, int64_t n, float sign, const double* __restrict__ norms,
+                                                    const int32_t* __restrict__ idx, int64_t n_exc,
+                                                    const double* __restrict__ part, ZT* __restrict__ Om, int64_t ldz) {
+    __shared__ double red[4][64];
+    __shared__ ZT tile[RAW ? 1 : 64][65];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t c0 = (int64_t)blockIdx.x * 64, a0 = (int64_t)blockIdx.y * 64;
+    double ss = 0.0;
+    if (c0 + lane < n)
+        for (int64_t p = wv; p < gridDim.y; p += 4) ss += part[p * n + c0 + lane];
+    red[wv][lane] = ss;
+    __syncthreads();
+    if (wv == 0) red[0][lane] = sqrt(red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane]);
+    __syncthreads();
+    if (!RAW) {
+        const int64_t a = a0 + lane, t = a < n_exc ? idx[a] : 0;
+        const double nt = a < n_exc ? norms[t] : 1.0;
+#pragma unroll 4
+        for (int q = 0; q < 16; ++q) {
+            const int64_t col = c0 + 16 * wv + q;
+            if (col >= n) break;
+            if (a < n_exc)
+                tile[RAW ? 0 : lane][16 * wv + q] =
+                    (ZT)(omega_entry<RAW>(X, R, T, n, sign, t, col, nt) / red[0][16 * wv + q]);
+        }
+        __syncthreads();
+    }
+    if (c0 + lane >= n) return;
+    for (int64_t a = a0 + wv; a < min(a0 + 64, n_exc); a += 4) {
+        if (RAW) {
+            const int64_t t = idx[a];
+            Om[a * ldz + c0 + lane] =
+                (ZT)(omega_entry<RAW>(X, R, T, n, sign, t, c0 + lane, norms[t]) / red[0][lane]);
+        } else {
+            Om[a * ldz + c0 + lane] = tile[RAW ? 0 : a - a0][lane];
+        }
     }
 }
 
@@ -227,96 +477,74 @@ __global__ __launch_bounds__(256) void norms_raw_kernel(const float* __restrict_
     if (threadIdx.x == 0) norms[t] = sqrt(red[0] + red[1] + red[2] + red[3]);
 }
 
-// Raw marginals: Omega_aj = sign * X[t_a][j] / ||x_{t_a}||, column j scaled to unit norm.
-template <typename ZT>
-__global__ __launch_bounds__(256) void omega_raw_kernel(const float* __restrict__ X, int64_t n, float sign,
-                                                        const double* __restrict__ norms,
-                                                        const int32_t* __restrict__ idx, int64_t n_exc,
-                                                        ZT* __restrict__ Om, int64_t ldz) {
-    __shared__ double red[4][64];
-    const int lc = threadIdx.x & 63, ph = threadIdx.x >> 6;
-    const int64_t col = blockIdx.x * 64 + lc;
-    double ss = 0.0;
-    if (col < n)
-        for (int64_t a = ph; a < n_exc; a += 4) {
-            const int64_t t = idx[a];
-            const double w = (double)X[t * n + col] / norms[t];
-            ss += w * w;
-        }
-    red[ph][lc] = ss;
-    __syncthreads();
-    const double c = sqrt(red[0][lc] + red[1][lc] + red[2][lc] + red[3][lc]);
-    if (col >= n) return;
-    for (int64_t a = ph; a < n_exc; a += 4) {
-        const int64_t t = idx[a];
-        const double w = (double)sign * (double)X[t * n + col] / norms[t];
-        Om[a * ldz + col] = (ZT)(w / c);
-    }
+// Work of launch_tpdm_omega: the transposed samples (n x T floats), the ranks
+// (n x T, 16 bits) and the norm partials, none of them for raw marginals; the
+// norms, the kept indices, the column sums of squares per 64 kept rows.
+struct TpdmWork {
+    int64_t xt, ranks, parts, norms, idx, sq, total;
+};
+static TpdmWork tpdm_work(int64_t T, int64_t n, int64_t n_exc, int raw) {
+    TpdmWork w;
+    int64_t off = 0;
+    auto take = [&](int64_t bytes) {
+        const int64_t at = off;
+        off += round_up(bytes, 256);
+        return at;
+    };
+    w.xt = take(raw ? 0 : T * n * 4);
+    w.ranks = take(raw ? 0 : T * n * 2);
+    w.parts = take(raw ? 0 : NORM_PARTS * T * 8);
+    w.norms = take(T * 8);
+    w.idx = take(T * 4);
+    w.sq = take((n_exc + 63) / 64 * n * 8);
+    w.total = off;
+    return w;
 }
 
-int64_t tpdm_work_bytes(int64_t T, int64_t n, int raw) {
-    const int64_t planes = raw ? 0 : round_up(T * n * 4, 256) * 2;
-    return planes + round_up(T * 8, 256) + round_up(T * 4, 256) + round_up(select_tmp_bytes(), 256) + 256;
+int64_t tpdm_work_bytes(int64_t T, int64_t n, int64_t n_exc, int raw) { return tpdm_work(T, n, n_exc, raw).total; }
+
+template <bool RAW>
+static void launch_omega_rows(const float* X, const uint16_t* R, int64_t T, int64_t n, float sign, const double* norms,
+                              const int32_t* idx, int64_t n_exc, double* sq, void* Omega, int z_f64, int64_t ldz,
+                              hipStream_t stream) {
+    const dim3 grid((n + 63) / 64, (n_exc + 63) / 64), tb(256);
+    hipLaunchKernelGGL(omega_sq_kernel<RAW>, grid, tb, 0, stream, X, R, T, n, sign, norms, idx, n_exc, sq);
+    if (z_f64)
+        hipLaunchKernelGGL((omega_kernel<RAW, double>), grid, tb, 0, stream, X, R, T, n, sign, norms, idx, n_exc,
+                           (const double*)sq, (double*)Omega, ldz);
+    else
+        hipLaunchKernelGGL((omega_kernel<RAW, float>), grid, tb, 0, stream, X, R, T, n, sign, norms, idx, n_exc,
+                           (const double*)sq, (float*)Omega, ldz);
 }
 
 hipError_t launch_tpdm_omega(const float* X, int64_t T, int64_t n, int lower, int raw, void* Omega, int z_f64,
-                             int64_t ldz, int64_t n_exc, void* work, hipStream_t stream) {
+                             int64_t ldz, int64_t n_exc, void* work, int32_t* flag, hipStream_t stream) {
     if (!raw && T > RANK_MAX_T) return hipErrorInvalidValue;
+    const float sign = lower ? -1.0f : 1.0f;
     char* w = (char*)work;
-    float* Xt = (float*)w;                       // n x T, later reused for Rt (T x n)
-    int32_t* R = nullptr;                        // n x T
-    if (!raw) {
-        w += round_up(T * n * 4, 256);
-        R = (int32_t*)w;
-        w += round_up(T * n * 4, 256);
-    }
-    double* norms = (double*)w;
-    w += round_up(T * 8, 256);
-    int32_t* idx = (int32_t*)w;
-    w += round_up(T * 4, 256);
-    void* sel = w;
-    w += round_up(select_tmp_bytes(), 256);
-    double* vstar = (double*)w;
-    dim3 tb(256);
+    const TpdmWork o = tpdm_work(T, n, n_exc, raw);
+    double* norms = (double*)(w + o.norms);
+    int32_t* idx = (int32_t*)(w + o.idx);
+    double* sq = (double*)(w + o.sq);
+    const dim3 tb(256);
     if (raw) {
-        const float sign = lower ? -1.0f : 1.0f;
+        const int64_t blocks = std::min<int64_t>((T * n + 255) / 256, 4096);
+        hipLaunchKernelGGL(check_input_kernel, dim3(blocks), tb, 0, stream, X, T * n, sign, flag);
         hipLaunchKernelGGL(norms_raw_kernel, dim3(T), tb, 0, stream, X, n, norms);
-        hipError_t e = launch_select(norms, 1, 0, T, T - n_exc, sel, vstar, stream);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(compact_kernel, dim3(1), dim3(64), 0, stream, (const double*)norms, T, n_exc,
-                           (const double*)vstar, idx);
-        if (z_f64)
-            hipLaunchKernelGGL(omega_raw_kernel<double>, dim3((n + 63) / 64), tb, 0, stream, X, n, sign,
-                               (const double*)norms, (const int32_t*)idx, n_exc, (double*)Omega, ldz);
-        else
-            hipLaunchKernelGGL(omega_raw_kernel<float>, dim3((n + 63) / 64), tb, 0, stream, X, n, sign,
-                               (const double*)norms, (const int32_t*)idx, n_exc, (float*)Omega, ldz);
+        hipLaunchKernelGGL(exceed_kernel, dim3(1), dim3(1024), 0, stream, (const double*)norms, T, n_exc, idx);
+        launch_omega_rows<true>(X, nullptr, T, n, sign, norms, idx, n_exc, sq, Omega, z_f64, ldz, stream);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(transpose_kernel<float>, dim3((n + 63) / 64, (T + 63) / 64), tb, 0, stream, X, T, n, Xt,
-                       lower ? -1.0f : 1.0f);
-    int P2 = 1;
-    while (P2 < T) P2 <<= 1;
-    if (P2 * 4 > 65536) {
-        hipError_t ea = hipFuncSetAttribute((const void*)rank_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            P2 * 4);
-        if (ea != hipSuccess) return ea;
-    }
-    hipLaunchKernelGGL(rank_kernel, dim3(n), dim3(1024), (size_t)P2 * 4, stream, (const float*)Xt, T, R);
-    int32_t* Rt = (int32_t*)Xt;
-    hipLaunchKernelGGL(transpose_kernel<int32_t>, dim3((T + 63) / 64, (n + 63) / 64), tb, 0, stream,
-                       (const int32_t*)R, n, T, Rt, (int32_t)1);
-    hipLaunchKernelGGL(norms_kernel, dim3(T), tb, 0, stream, (const int32_t*)Rt, T, n, norms);
-    hipError_t e = launch_select(norms, 1, 0, T, T - n_exc, sel, vstar, stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(compact_kernel, dim3(1), dim3(64), 0, stream, (const double*)norms, T, n_exc,
-                       (const double*)vstar, idx);
-    if (z_f64)
-        hipLaunchKernelGGL(omega_kernel<double>, dim3((n + 63) / 64), tb, 0, stream, (const int32_t*)Rt, T, n,
-                           (const double*)norms, (const int32_t*)idx, n_exc, (double*)Omega, ldz);
-    else
-        hipLaunchKernelGGL(omega_kernel<float>, dim3((n + 63) / 64), tb, 0, stream, (const int32_t*)Rt, T, n,
-                           (const double*)norms, (const int32_t*)idx, n_exc, (float*)Omega, ldz);
+    float* Xt = (float*)(w + o.xt);
+    uint16_t* R = (uint16_t*)(w + o.ranks);
+    double* parts = (double*)(w + o.parts);
+    hipLaunchKernelGGL(transpose_kernel, dim3((n + 63) / 64, (T + 63) / 64), tb, 0, stream, X, T, n, Xt, sign, flag);
+    launch_rank(Xt, T, n, R, stream);
+    const unsigned tblocks = (unsigned)((T + 255) / 256);
+    hipLaunchKernelGGL(norm_parts_kernel, dim3(tblocks, NORM_PARTS), tb, 0, stream, (const uint16_t*)R, T, n, parts);
+    hipLaunchKernelGGL(norm_sum_kernel, dim3(tblocks), tb, 0, stream, (const double*)parts, T, norms);
+    hipLaunchKernelGGL(exceed_kernel, dim3(1), dim3(1024), 0, stream, (const double*)norms, T, n_exc, idx);
+    launch_omega_rows<false>(nullptr, R, T, n, sign, norms, idx, n_exc, sq, Omega, z_f64, ldz, stream);
     return hipGetLastError();
 }
 

@@ -389,13 +389,13 @@ struct BuildOut {
 // zero-variance columns.
 constexpr int32_t BAD_NONFINITE = 1 << 30;
 constexpr int32_t BAD_NEGATIVE = 1 << 29;
-hipError_t launch_check_input(const float* X, int64_t count, float sign, int32_t* flag, hipStream_t stream);
 hipError_t launch_standardise(const float* X, int64_t T, int64_t n, void* Z, int z_f64, int64_t ldz, int32_t* bad,
                               hipStream_t stream);
-// TPDM: Omega (n_exc x ldz, FP32 or FP64) = column-normalised angular rows.
+// TPDM: Omega (n_exc x ldz, FP32 or FP64) = column-normalised angular rows; raises the input
+// check's bits in *flag.
 hipError_t launch_tpdm_omega(const float* X, int64_t T, int64_t n, int lower, int raw, void* Omega, int z_f64,
-                             int64_t ldz, int64_t n_exc, void* work, hipStream_t stream);
-int64_t tpdm_work_bytes(int64_t T, int64_t n, int raw);
+                             int64_t ldz, int64_t n_exc, void* work, int32_t* flag, hipStream_t stream);
+int64_t tpdm_work_bytes(int64_t T, int64_t n, int64_t n_exc, int raw);
 // sums: device FP64 array of syrk_sum_words(o) words; [0..2] = sum S, sum S^2,
 // sum S_stored^2 on return.  panel_max: FP8 only, zeroed, one word per panel.
 int64_t syrk_sum_words(const BuildOut& o);

@@ -332,7 +332,7 @@ static bool build_ws(const symnmf_sbuild_params* p, BuildWs& w) {
     w.sums = syrk_sum_words(o) * 8;
     w.pmax = (p->dtype == SYMNMF_S_FP8 ? (p->rows + p->fp8_panel_rows - 1) / p->fp8_panel_rows : 1) * 4;
     w.bad = 4;
-    w.work = p->kind == SYMNMF_TPDM ? tpdm_work_bytes(p->T, p->n, p->raw_marginals) : 0;
+    w.work = p->kind == SYMNMF_TPDM ? tpdm_work_bytes(p->T, p->n, w.K, p->raw_marginals) : 0;
     w.planes = (p->dtype == SYMNMF_S_BF16 || p->dtype == SYMNMF_S_FP8) ? syrk_split_ws_bytes(w.K, w.ldz) : 0;
     return true;
 }
@@ -384,18 +384,14 @@ symnmf_status symnmf_build_S(symnmf_ctx* ctx, const float* X, const symnmf_sbuil
     void* sums = sc.get(w.sums);
     void* pmax = sc.get(w.pmax);
     void* bad = sc.get(w.bad);
-    void* work = w.work ? sc.get(w.work) : nullptr;
+    void* work = w.work ? sc.get(w.work, false) : nullptr;
     void* planes = w.planes ? sc.get(w.planes) : nullptr;
     if (sc.err != hipSuccess) return scratch_fail(ctx, sc, "build_S");
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
     chk(launch_zero(buf, L.total, st));
     if (p->kind == SYMNMF_ABS_CORR) chk(launch_standardise(X, T, n, Z, z_f64, ldz, (int32_t*)bad, st));
-    else {
-        const float sign = p->raw_marginals ? (p->lower_tail ? -1.0f : 1.0f) : 0.0f;
-        chk(launch_check_input(X, T * n, sign, (int32_t*)bad, st));
-        chk(launch_tpdm_omega(X, T, n, p->lower_tail, p->raw_marginals, Z, z_f64, ldz, K, work, st));
-    }
+    else chk(launch_tpdm_omega(X, T, n, p->lower_tail, p->raw_marginals, Z, z_f64, ldz, K, work, (int32_t*)bad, st));
     int32_t hbad = 0;
     chk(hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, st));
     chk(hipStreamSynchronize(st));
