@@ -446,14 +446,14 @@ struct GradParts {
 hipError_t launch_grad_adamw(const GradParts& gp, const double* coef, float* P, float* G, float* M, float* V, float lr,
                              float b1, float b2, float eps, float wd, int64_t t, hipStream_t stream);
 hipError_t launch_to_bf16(const float* x, uint16_t* y, int64_t m, hipStream_t stream);
-// successive projection on R (m x k FP64, destroyed); pick: k device int64; bval/bidx: nb entries
+// successive projection on R (k columns of m FP64, destroyed); pick: k device int64; bval/bidx: 2 nb entries
 hipError_t launch_spa(double* R, int64_t m, int64_t k, double* bval, int64_t* bidx, int nb, int64_t* pick,
                       hipStream_t stream);
 int64_t xty_work_doubles(int64_t m, int64_t kx, int64_t ky);
 hipError_t launch_xty(const float* X, int64_t ldx, int64_t kx, const float* Y, int64_t ldy, int64_t ky, int64_t m,
                       double* work, double* out, hipStream_t stream);
-hipError_t launch_jacobi_topk(const double* G, int64_t w, int64_t k, double* V, double* M, double* lam,
-                              int32_t* status, hipStream_t stream);
+hipError_t launch_jacobi_topk(const double* G, int64_t w, int64_t k, double* M, double* lam, int32_t* status,
+                              hipStream_t stream);
 hipError_t launch_project_rows(const float* Y, int64_t m, int64_t w, const double* W, int64_t k, int64_t ldo,
                                int out_f64, void* out, hipStream_t stream);
 hipError_t launch_anchor_solve(const float* Y, int64_t w, const double* M, int64_t k, const int64_t* anchors,

@@ -324,78 +324,108 @@ hipError_t launch_to_bf16(const float* x, uint16_t* y, int64_t m, hipStream_t st
 }
 
 // ---------------------------------------------------------------------------
-// Successive projection (Gillis & Vavasis 2014) on the rows of R (m x k, FP64
-// working copy): argmax of the residual row norms (lowest index on ties) in
-// two passes, then every row is projected off the chosen row's direction.
+// Successive projection (Gillis & Vavasis 2014) on the rows of R (m x k, FP64,
+// stored by columns): argmax of the residual row norms (lowest index on ties),
+// then every row is projected off the chosen row's direction.  One launch per
+// pick: every work-group finds pick s - 1 from the block maxima of the launch
+// before, projects its rows and leaves their block maximum for the next launch
+// (two buffers in turn).  The picked row itself is read by all work-groups of
+// its launch, so its owner clears it one launch later and counts its norm as 0
+// meanwhile.  Four launches per pick over row-major rows (a serial scan of the
+// block maxima among them) took 32.3 us a pick at m = 20000, k = 32; this takes
+// 11.6 us.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void spa_argmax_blocks(const double* __restrict__ R, int64_t m, int k,
-                                                         double* __restrict__ bval, int64_t* __restrict__ bidx) {
-    __shared__ double sv[256];
-    __shared__ int64_t si[256];
-    double best = -1.0;
-    int64_t bi = 0;
-    for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < m; i += (int64_t)gridDim.x * 256) {
-        double s = 0.0;
-        for (int c = 0; c < k; ++c) s += R[i * k + c] * R[i * k + c];
-        if (s > best) { best = s; bi = i; }
+__device__ inline void spa_better(double& v, int64_t& i, double ov, int64_t oi) {
+    if (ov > v || (ov == v && oi < i)) {
+        v = ov;
+        i = oi;
     }
-    sv[threadIdx.x] = best;
-    si[threadIdx.x] = bi;
+}
+
+// argmax over the work-group, valid in every thread
+__device__ inline void spa_block_argmax(double& v, int64_t& i, double* sv, int64_t* si) {
+    for (int off = 32; off > 0; off >>= 1) spa_better(v, i, __shfl_xor(v, off, 64), __shfl_xor(i, off, 64));
     __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) {
-            const double a = sv[threadIdx.x], b = sv[threadIdx.x + off];
-            const int64_t ia = si[threadIdx.x], ib = si[threadIdx.x + off];
-            if (b > a || (b == a && ib < ia)) { sv[threadIdx.x] = b; si[threadIdx.x] = ib; }
+    if ((threadIdx.x & 63) == 0) {
+        sv[threadIdx.x >> 6] = v;
+        si[threadIdx.x >> 6] = i;
+    }
+    __syncthreads();
+    v = sv[0];
+    i = si[0];
+    for (int q = 1; q < 4; ++q) spa_better(v, i, sv[q], si[q]);
+}
+
+__global__ __launch_bounds__(256) void spa_step_kernel(double* __restrict__ R, int64_t m, int k, int step,
+                                                       const double* __restrict__ bval_in,
+                                                       const int64_t* __restrict__ bidx_in, int nb,
+                                                       double* __restrict__ bval_out, int64_t* __restrict__ bidx_out,
+                                                       int64_t* __restrict__ pick) {
+    __shared__ double u[KMAX];
+    __shared__ double sv[4];
+    __shared__ int64_t si[4];
+    const int t = threadIdx.x;
+    int64_t p = -1, prev = -1;
+    if (step > 0) {
+        double v = -1.0;
+        int64_t i = INT64_MAX;
+        for (int b = t; b < nb; b += 256) spa_better(v, i, bval_in[b], bidx_in[b]);
+        spa_block_argmax(v, i, sv, si);
+        p = i;
+        if (step > 1) prev = pick[step - 2];
+        if (blockIdx.x == 0 && t == 0) pick[step - 1] = p;
+        if (step == k) return;                              // the last launch only picks
+        if (t < 64) {
+            const double x = t < k ? R[t * m + p] : 0.0;
+            double s = 0.0;
+            for (int c = 0; c < k; ++c) {
+                const double y = __shfl(x, c, 64);
+                s += y * y;
+            }
+            const double nrm = sqrt(s);
+            if (t < k) u[t] = nrm > 0.0 ? x / nrm : 0.0;
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) { bval[blockIdx.x] = sv[0]; bidx[blockIdx.x] = si[0]; }
-}
-
-__global__ void spa_argmax_final(const double* __restrict__ bval, const int64_t* __restrict__ bidx, int nb,
-                                 int64_t* __restrict__ pick, int step) {
-    if (threadIdx.x != 0) return;
     double best = -1.0;
     int64_t bi = 0;
-    for (int b = 0; b < nb; ++b)
-        if (bval[b] > best || (bval[b] == best && bidx[b] < bi)) { best = bval[b]; bi = bidx[b]; }
-    pick[step] = bi;
-}
-
-__global__ __launch_bounds__(256) void spa_project(double* __restrict__ R, int64_t m, int k, const int64_t* __restrict__ pick,
-                                                   int step) {
-    __shared__ double u[KMAX];
-    __shared__ double nrm;
-    const int64_t p = pick[step];
-    if (threadIdx.x == 0) {
+    for (int64_t i = blockIdx.x * (int64_t)256 + t; i < m; i += (int64_t)gridDim.x * 256) {
         double s = 0.0;
-        for (int c = 0; c < k; ++c) s += R[p * k + c] * R[p * k + c];
-        nrm = sqrt(s);
+        if (i == p) {
+            // read by every work-group of this launch: left alone
+        } else if (i == prev) {
+            for (int c = 0; c < k; ++c) R[c * m + i] = 0.0;
+        } else if (step > 0) {
+            double d = 0.0;
+#pragma unroll 8
+            for (int c = 0; c < k; ++c) d += R[c * m + i] * u[c];
+#pragma unroll 8
+            for (int c = 0; c < k; ++c) {
+                const double r = R[c * m + i] - d * u[c];
+                R[c * m + i] = r;
+                s += r * r;
+            }
+        } else {
+#pragma unroll 8
+            for (int c = 0; c < k; ++c) s += R[c * m + i] * R[c * m + i];
+        }
+        if (s > best) { best = s; bi = i; }
     }
-    __syncthreads();
-    if ((int)threadIdx.x < k) u[threadIdx.x] = nrm > 0.0 ? R[p * k + threadIdx.x] / nrm : 0.0;
-    __syncthreads();
-    for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < m; i += (int64_t)gridDim.x * 256) {
-        if (i == p) continue;
-        double d = 0.0;
-        for (int c = 0; c < k; ++c) d += R[i * k + c] * u[c];
-        for (int c = 0; c < k; ++c) R[i * k + c] -= d * u[c];
+    spa_block_argmax(best, bi, sv, si);
+    if (t == 0) {
+        bval_out[blockIdx.x] = best;
+        bidx_out[blockIdx.x] = bi;
     }
 }
 
-__global__ void spa_zero_row(double* __restrict__ R, int k, const int64_t* __restrict__ pick, int step) {
-    const int64_t p = pick[step];
-    if ((int)threadIdx.x < k) R[p * k + threadIdx.x] = 0.0;
-}
-
+// bval / bidx: two buffers of nb entries each
 hipError_t launch_spa(double* R, int64_t m, int64_t k, double* bval, int64_t* bidx, int nb, int64_t* pick,
                       hipStream_t stream) {
-    for (int s = 0; s < k; ++s) {
-        hipLaunchKernelGGL(spa_argmax_blocks, dim3(nb), dim3(256), 0, stream, (const double*)R, m, (int)k, bval, bidx);
-        hipLaunchKernelGGL(spa_argmax_final, dim3(1), dim3(64), 0, stream, (const double*)bval, (const int64_t*)bidx, nb, pick, s);
-        hipLaunchKernelGGL(spa_project, dim3(nb), dim3(256), 0, stream, R, m, (int)k, (const int64_t*)pick, s);
-        hipLaunchKernelGGL(spa_zero_row, dim3(1), dim3(64), 0, stream, R, (int)k, (const int64_t*)pick, s);
+    for (int s = 0; s <= k; ++s) {
+        const int in = (s + 1) & 1, out = s & 1;
+        hipLaunchKernelGGL(spa_step_kernel, dim3(s == k ? 1 : nb), dim3(256), 0, stream, R, m, (int)k, s,
+                           (const double*)bval + in * nb, (const int64_t*)bidx + in * nb, nb, bval + out * nb,
+                           bidx + out * nb, pick);
     }
     return hipGetLastError();
 }
@@ -533,40 +563,51 @@ hipError_t launch_gram3(const float* A, const float* B, int64_t k, int64_t m, do
 // largest eigenvalues (descending, lower index first on ties) and
 // M = V_k diag(lambda)^-1/2 (w x k).  status[0] = 1 when a selected
 // eigenvalue is not positive and finite, 2 when the sweeps do not converge.
-// V: w x w FP64 device scratch.
+// A serial chain of about 600 rounds: bound by the latency of a round.  With 32
+// pairs a thread owns the 2 x 2 block of two pairs, so J^T A J is one read and
+// one write per entry and a round has two barriers (rotations; update of A and
+// V), A and V both in LDS.  Updating rows and columns in turn with V in global
+// memory and four barriers a round, the norm and the selection on one thread,
+// took 5.13 ms at w = 64; this takes 1.07 ms.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void jacobi_topk_kernel(const double* __restrict__ G, int w, int k,
-                                                          double* __restrict__ V, double* __restrict__ Mout,
-                                                          double* __restrict__ lam_out, int32_t* __restrict__ status) {
+constexpr int JT = 1024;
+
+__global__ __launch_bounds__(JT) void jacobi_topk_kernel(const double* __restrict__ G, int w, int k,
+                                                         double* __restrict__ Mout, double* __restrict__ lam_out,
+                                                         int32_t* __restrict__ status) {
     __shared__ double A[KMAX][KMAX + 1];
+    __shared__ double V[KMAX][KMAX + 1];
     __shared__ int order[KMAX];
-    __shared__ int done;
-    __shared__ double floor_abs;
+    __shared__ int rotated, bad;
+    __shared__ double red[JT / 64];
     __shared__ double cs_s[KMAX / 2], sn_s[KMAX / 2];
     __shared__ int p_s[KMAX / 2], q_s[KMAX / 2];
     const int t = threadIdx.x;
-    for (int e = t; e < w * w; e += 256) {
-        const int i = e / w, j = e - i * w;
-        A[i][j] = 0.5 * (G[i * w + j] + G[j * w + i]);
-        V[e] = i == j ? 1.0 : 0.0;
-    }
-    const int wp = w + (w & 1);    // even player count; index w (odd w) is a bye
+    const int wp = w + (w & 1);    // even player count; index w (odd w) is a bye: a zero row and column
     const int half = wp / 2;
+    double fro = 0.0;
+    for (int e = t; e < wp * wp; e += JT) {
+        const int i = e / wp, j = e - i * wp;
+        const double a = i < w && j < w ? 0.5 * (G[i * w + j] + G[j * w + i]) : 0.0;
+        A[i][j] = a;
+        V[i][j] = i == j ? 1.0 : 0.0;
+        fro += a * a;
+    }
     // a pair is rotated when |a_pq| > max(1e-14 sqrt(|a_pp a_qq|), 1e-15 ||G||_F)
     // (the relative criterion of Demmel & Veselic 1992, with an absolute floor
     // so that rounding noise inside a null space of a semidefinite G does not
     // keep the sweeps going); converged after a sweep with no rotation
+    for (int off = 32; off > 0; off >>= 1) fro += __shfl_xor(fro, off, 64);
+    if ((t & 63) == 0) red[t >> 6] = fro;
+    if (t < KMAX) order[t] = 0;
+    if (t == 0) bad = 0;
     __syncthreads();
-    if (t == 0) {
-        double s = 0.0;
-        for (int i = 0; i < w; ++i)
-            for (int j = 0; j < w; ++j) s += A[i][j] * A[i][j];
-        floor_abs = 1e-15 * sqrt(s);
-    }
+    fro = 0.0;
+    for (int q = 0; q < JT / 64; ++q) fro += red[q];
+    const double floor_abs = 1e-15 * sqrt(fro);
     int sweep = 0;
     for (; sweep < 60; ++sweep) {
-        __syncthreads();
-        if (t == 0) done = 1;
+        if (t == 0) rotated = 0;
         __syncthreads();
         for (int r = 0; r < wp - 1; ++r) {
             // pair i of round r: (wp-1, r) for i = 0, else ((r+i) mod (wp-1), (r-i) mod (wp-1));
@@ -577,110 +618,125 @@ __global__ __launch_bounds__(256) void jacobi_topk_kernel(const double* __restri
                 else { p = (r + t) % (wp - 1); q = (r - t + (wp - 1)) % (wp - 1); }
                 if (p > q) { const int tmp = p; p = q; q = tmp; }
                 double c = 1.0, sn = 0.0;
-                if (q < w) {
-                    const double apq = A[p][q];
-                    if (fabs(apq) > fmax(1e-14 * sqrt(fabs(A[p][p] * A[q][q])), floor_abs)) {
-                        done = 0;
-                        const double tau = (A[q][q] - A[p][p]) / (2.0 * apq);
-                        const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-                        c = 1.0 / sqrt(1.0 + tt * tt);
-                        sn = tt * c;
-                    }
+                const double apq = A[p][q], app = A[p][p], aqq = A[q][q];
+                if (fabs(apq) > fmax(1e-14 * sqrt(fabs(app * aqq)), floor_abs)) {
+                    rotated = 1;
+                    const double tau = (aqq - app) / (2.0 * apq);
+                    const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
+                    c = 1.0 / sqrt(1.0 + tt * tt);
+                    sn = tt * c;
                 }
                 cs_s[t] = c; sn_s[t] = sn; p_s[t] = p; q_s[t] = q;
             }
             __syncthreads();
-            // rows: A <- J^T A
-            for (int f = t; f < half * w; f += 256) {
-                const int pi = f / w, col = f - pi * w;
-                const int p = p_s[pi], q = q_s[pi];
-                if (q >= w || sn_s[pi] == 0.0) continue;
-                const double c = cs_s[pi], sn = sn_s[pi];
-                const double ap = A[p][col], aq = A[q][col];
-                A[p][col] = c * ap - sn * aq;
-                A[q][col] = sn * ap + c * aq;
+            // A <- J^T A J by 2 x 2 blocks, V <- V J
+            for (int f = t; f < half * half; f += JT) {
+                const int bi = f / half, bj = f - bi * half;
+                const double ci = cs_s[bi], si = sn_s[bi], cj = cs_s[bj], sj = sn_s[bj];
+                if (si == 0.0 && sj == 0.0) continue;
+                const int pi = p_s[bi], qi = q_s[bi], pj = p_s[bj], qj = q_s[bj];
+                const double a = A[pi][pj], b = A[pi][qj], c = A[qi][pj], d = A[qi][qj];
+                const double ra = ci * a - si * c, rb = ci * b - si * d;
+                const double rc = si * a + ci * c, rd = si * b + ci * d;
+                A[pi][pj] = cj * ra - sj * rb;
+                A[pi][qj] = sj * ra + cj * rb;
+                A[qi][pj] = cj * rc - sj * rd;
+                A[qi][qj] = sj * rc + cj * rd;
             }
-            __syncthreads();
-            // columns: A <- A J, V <- V J
-            for (int f = t; f < half * w; f += 256) {
-                const int pi = f / w, row = f - pi * w;
-                const int p = p_s[pi], q = q_s[pi];
-                if (q >= w || sn_s[pi] == 0.0) continue;
-                const double c = cs_s[pi], sn = sn_s[pi];
-                const double ap = A[row][p], aq = A[row][q];
-                A[row][p] = c * ap - sn * aq;
-                A[row][q] = sn * ap + c * aq;
-                const double vp = V[row * w + p], vq = V[row * w + q];
-                V[row * w + p] = c * vp - sn * vq;
-                V[row * w + q] = sn * vp + c * vq;
+            for (int f = t; f < half * w; f += JT) {
+                const int bj = f / w, row = f - bj * w;
+                const double c = cs_s[bj], sn = sn_s[bj];
+                if (sn == 0.0) continue;
+                const int p = p_s[bj], q = q_s[bj];
+                const double vp = V[row][p], vq = V[row][q];
+                V[row][p] = c * vp - sn * vq;
+                V[row][q] = sn * vp + c * vq;
             }
             __syncthreads();
         }
-        if (done) break;
+        const int any = rotated;
+        __syncthreads();
+        if (!any) break;
+    }
+    // place of every eigenvalue in descending order, lower index first on ties
+    if (t < w) {
+        const double l = A[t][t];
+        int rank = 0;
+        for (int j = 0; j < w; ++j) rank += A[j][j] > l || (A[j][j] == l && j < t) ? 1 : 0;
+        if (rank < k) order[rank] = t;
+        if (!(l == l) || (rank < k && (!(l > 0.0) || !isfinite(l)))) bad = 1;
     }
     __syncthreads();
-    if (t == 0) {
-        int32_t st = sweep >= 60 ? 2 : 0;
-        bool used[KMAX];
-        for (int i = 0; i < w; ++i) used[i] = false;
-        for (int c = 0; c < k; ++c) {
-            int best = -1;
-            for (int i = 0; i < w; ++i)
-                if (!used[i] && (best < 0 || A[i][i] > A[best][best])) best = i;
-            used[best] = true;
-            order[c] = best;
-            const double l = A[best][best];
-            lam_out[c] = l;
-            if (!(l > 0.0) || !isfinite(l)) st = 1;
-        }
-        status[0] = st;
-    }
-    __syncthreads();
-    for (int e = t; e < w * k; e += 256) {
+    if (t < k) lam_out[t] = A[order[t]][order[t]];
+    if (t == 0) status[0] = bad ? 1 : (sweep >= 60 ? 2 : 0);
+    for (int e = t; e < w * k; e += JT) {
         const int i = e / k, c = e - i * k;
         const double l = A[order[c]][order[c]];
-        Mout[e] = l > 0.0 ? V[i * w + order[c]] / sqrt(l) : 0.0;
+        Mout[e] = l > 0.0 ? V[i][order[c]] / sqrt(l) : 0.0;
     }
 }
 
-hipError_t launch_jacobi_topk(const double* G, int64_t w, int64_t k, double* V, double* M, double* lam,
-                              int32_t* status, hipStream_t stream) {
+hipError_t launch_jacobi_topk(const double* G, int64_t w, int64_t k, double* M, double* lam, int32_t* status,
+                              hipStream_t stream) {
     if (w < 1 || w > KMAX || k < 1 || k > w) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(jacobi_topk_kernel, dim3(1), dim3(256), 0, stream, G, (int)w, (int)k, V, M, lam, status);
+    hipLaunchKernelGGL(jacobi_topk_kernel, dim3(1), dim3(JT), 0, stream, G, (int)w, (int)k, M, lam, status);
     return hipGetLastError();
 }
 
-// out (m x ldo) = Y (m x w, FP32) W (w x k, FP64): FP64 sums; OUT = double
-// writes k columns (ldo = k), OUT = float writes ldo columns, zero past k.
+// Y (m x w, FP32) W (w x k, FP64) with FP64 sums: to FP64 by columns (k columns
+// of m, the order the anchor search reads), or to FP32 rows of ldo columns, zero
+// past k.  A work-group takes 64 rows, a wave 16 columns of them at a time: the
+// rows sit in LDS with an odd stride, a lane owns a row and W's entries are the
+// same for the whole wave.
 template <typename OUT>
 __global__ __launch_bounds__(256) void project_rows_kernel(const float* __restrict__ Y, int64_t m, int w,
                                                            const double* __restrict__ W, int k, int ldo,
                                                            OUT* __restrict__ out) {
     __shared__ double Ws[KMAX * KMAX];
-    for (int e = threadIdx.x; e < w * k; e += 256) Ws[e] = W[e];
+    __shared__ float Ys[64][KMAX + 1];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int64_t r0 = (int64_t)blockIdx.x * 64;
+    for (int e = t; e < w * k; e += 256) Ws[e] = W[e];
+    for (int f = t; f < 64 * w; f += 256) {
+        const int r = f / w, c = f - r * w;
+        Ys[r][c] = r0 + r < m ? Y[(r0 + r) * w + c] : 0.0f;
+    }
     __syncthreads();
-    const int64_t total = m * ldo;
-    for (int64_t e = blockIdx.x * (int64_t)256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-        const int64_t i = e / ldo;
-        const int c = (int)(e - i * ldo);
+    float res[KMAX / 4];                                    // FP32 form: this lane's row, columns 16 wv ..
+#pragma unroll
+    for (int q = 0; q < KMAX / 4; ++q) {
+        const int c = (KMAX / 4) * wv + q;
         double s = 0.0;
         if (c < k)
-            for (int l = 0; l < w; ++l) s += (double)Y[i * w + l] * Ws[l * k + c];
-        out[e] = (OUT)s;
+            for (int l = 0; l < w; ++l) s += (double)Ys[lane][l] * Ws[l * k + c];
+        if (sizeof(OUT) == 8) {
+            if (c < k && r0 + lane < m) out[c * m + r0 + lane] = (OUT)s;
+        } else {
+            res[q] = (float)s;
+        }
+    }
+    if (sizeof(OUT) == 8) return;
+    // turn the rows through LDS for a coalesced store
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < KMAX / 4; ++q) Ys[lane][(KMAX / 4) * wv + q] = res[q];
+    __syncthreads();
+    for (int f = t; f < 64 * ldo; f += 256) {
+        const int r = f / ldo, c = f - r * ldo;
+        if (r0 + r < m) out[(r0 + r) * ldo + c] = (OUT)Ys[r][c];
     }
 }
 
 hipError_t launch_project_rows(const float* Y, int64_t m, int64_t w, const double* W, int64_t k, int64_t ldo,
                                int out_f64, void* out, hipStream_t stream) {
-    if (w > KMAX || k > KMAX || ldo < k) return hipErrorInvalidValue;
-    int64_t blocks = (m * ldo + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
+    if (w > KMAX || k > KMAX || ldo < k || ldo > KMAX) return hipErrorInvalidValue;
+    const dim3 grid((m + 63) / 64), block(256);
     if (out_f64)
-        hipLaunchKernelGGL(project_rows_kernel<double>, dim3(blocks), dim3(256), 0, stream, Y, m, (int)w, W, (int)k,
-                           (int)ldo, (double*)out);
+        hipLaunchKernelGGL(project_rows_kernel<double>, grid, block, 0, stream, Y, m, (int)w, W, (int)k, (int)ldo,
+                           (double*)out);
     else
-        hipLaunchKernelGGL(project_rows_kernel<float>, dim3(blocks), dim3(256), 0, stream, Y, m, (int)w, W, (int)k,
-                           (int)ldo, (float*)out);
+        hipLaunchKernelGGL(project_rows_kernel<float>, grid, block, 0, stream, Y, m, (int)w, W, (int)k, (int)ldo,
+                           (float*)out);
     return hipGetLastError();
 }
 
@@ -690,39 +746,54 @@ hipError_t launch_project_rows(const float* Y, int64_t m, int64_t w, const doubl
 // row l of M.  C = Y W then equals Z A^-1 with Z = Y M.  status[0] = 0, or 3
 // when a pivot is below 1e-13 times the largest entry of A.
 // ---------------------------------------------------------------------------
+// A serial chain of 3 k short stages: the pivot is found by one wave, the solves
+// update all rows of M at once, column by column (the subtractions of a row keep
+// their order).  Pivots and row solves on single threads, the latter with their
+// vector in scratch memory, took 163 us at w = 64, k = 32; this takes 94 us.
 __global__ __launch_bounds__(256) void anchor_solve_kernel(const float* __restrict__ Y, int w,
                                                            const double* __restrict__ M, int k,
                                                            const int64_t* __restrict__ anchors, double* __restrict__ W,
                                                            int32_t* __restrict__ status) {
     __shared__ double LU[KMAX][KMAX + 1];
+    __shared__ double X[KMAX][KMAX + 1];
     __shared__ int perm[KMAX];
-    __shared__ double amax;
+    __shared__ double wmax[4];
     __shared__ int piv, singular;
     const int t = threadIdx.x;
     if (t == 0) singular = 0;
+    double mx = 0.0;
     for (int e = t; e < k * k; e += 256) {
         const int j = e / k, c = e - j * k;
         const int64_t row = anchors[j];
         double s = 0.0;
+#pragma unroll 8
         for (int l = 0; l < w; ++l) s += (double)Y[row * w + l] * M[l * k + c];
         LU[j][c] = s;
+        mx = fmax(mx, fabs(s));
     }
+    for (int e = t; e < w * k; e += 256) X[e / k][e % k] = M[e];
     if (t < k) perm[t] = t;
+    for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+    if ((t & 63) == 0) wmax[t >> 6] = mx;
     __syncthreads();
-    if (t == 0) {
-        double m = 0.0;
-        for (int j = 0; j < k; ++j)
-            for (int c = 0; c < k; ++c) m = fmax(m, fabs(LU[j][c]));
-        amax = m;
-    }
-    __syncthreads();
+    const double amax = fmax(fmax(wmax[0], wmax[1]), fmax(wmax[2], wmax[3]));
     for (int j = 0; j < k; ++j) {
-        if (t == 0) {
-            int p = j;
-            for (int i = j + 1; i < k; ++i)
-                if (fabs(LU[i][j]) > fabs(LU[p][j])) p = i;
-            piv = p;
-            if (!(fabs(LU[p][j]) > 1e-13 * amax)) singular = 1;
+        if (t < 64) {
+            // largest |entry| of the column at or below the diagonal, the first on ties
+            double v = t >= j && t < k ? fabs(LU[t][j]) : -1.0;
+            int i = t >= j && t < k ? t : KMAX;
+            for (int off = 32; off > 0; off >>= 1) {
+                const double ov = __shfl_xor(v, off, 64);
+                const int oi = __shfl_xor(i, off, 64);
+                if (ov > v || (ov == v && oi < i)) {
+                    v = ov;
+                    i = oi;
+                }
+            }
+            if (t == 0) {
+                piv = i < k ? i : j;                       // a column of NaNs: no exchange, singular
+                if (!(v > 1e-13 * amax)) singular = 1;
+            }
         }
         __syncthreads();
         const int p = piv;
@@ -746,20 +817,24 @@ __global__ __launch_bounds__(256) void anchor_solve_kernel(const float* __restri
     }
     // P A = L U  =>  A^T = U^T L^T P.  For row l of M: U^T y = m (forward),
     // L^T x = y (backward, unit diagonal), w = P^T x, i.e. w[perm[i]] = x[i].
-    for (int l = t; l < w; l += 256) {
-        double x[KMAX];
-        for (int i = 0; i < k; ++i) {
-            double s = M[l * k + i];
-            for (int j = 0; j < i; ++j) s -= LU[j][i] * x[j];
-            x[i] = LU[i][i] != 0.0 ? s / LU[i][i] : 0.0;
+    for (int j = 0; j < k; ++j) {
+        const double d = LU[j][j];
+        for (int l = t; l < w; l += 256) X[l][j] = d != 0.0 ? X[l][j] / d : 0.0;
+        __syncthreads();
+        for (int e = t; e < w * (k - j - 1); e += 256) {
+            const int l = e % w, i = j + 1 + e / w;
+            X[l][i] -= LU[j][i] * X[l][j];
         }
-        for (int i = k - 1; i >= 0; --i) {
-            double s = x[i];
-            for (int j = i + 1; j < k; ++j) s -= LU[j][i] * x[j];
-            x[i] = s;
-        }
-        for (int i = 0; i < k; ++i) W[l * k + perm[i]] = x[i];
+        __syncthreads();
     }
+    for (int j = k - 1; j > 0; --j) {
+        for (int e = t; e < w * j; e += 256) {
+            const int l = e % w, i = e / w;
+            X[l][i] -= LU[j][i] * X[l][j];
+        }
+        __syncthreads();
+    }
+    for (int e = t; e < w * k; e += 256) W[(e / k) * k + perm[e % k]] = X[e / k][e % k];
     if (t == 0) status[0] = singular ? 3 : 0;
 }
 

@@ -304,8 +304,8 @@ static SketchWs sketch_ws(const symnmf_ctx* ctx, const symnmf_S* S, int64_t widt
 // Scratch of symnmf_canonical.
 static int64_t canonical_ws(int64_t n, int64_t width, int64_t k) {
     const int nb = (int)std::min<int64_t>(1024, (n + 255) / 256);
-    return ws_sum({xty_work_doubles(n, width, width) * 8, width * width * 8, width * width * 8, width * k * 8, k * 8, 8,
-                   n * k * 8, nb * 8, nb * 8, k * 8, width * k * 8});
+    return ws_sum({xty_work_doubles(n, width, width) * 8, width * width * 8, width * k * 8, k * 8, 8, n * k * 8, 2 * nb * 8,
+                   2 * nb * 8, k * 8, width * k * 8});
 }
 
 int64_t symnmf_sketch_workspace(const symnmf_ctx* ctx, const symnmf_S* S, int64_t width) {
@@ -330,7 +330,7 @@ int64_t symnmf_warm_start_workspace(const symnmf_ctx* ctx, const symnmf_S* S, in
 
 int64_t symnmf_subspace_error_workspace(int64_t n, int64_t k) {
     if (n < 1 || k < 1 || k > KMAX) return -1;
-    return ws_round((6 * k * k + k + 1 + xty_work_doubles(n, k, k)) * 8 + 16);
+    return ws_round((5 * k * k + k + 1 + xty_work_doubles(n, k, k)) * 8 + 16);
 }
 
 symnmf_status symnmf_sketch(symnmf_ctx* ctx, const symnmf_S* S, uint64_t omega_seed, int64_t width, float* Y) {
@@ -376,13 +376,12 @@ symnmf_status symnmf_canonical(symnmf_ctx* ctx, const float* Y, int64_t n, int64
     CallScratch sc(ctx);
     void* work = sc.get(xty_work_doubles(n, width, width) * 8, false);
     void* G = sc.get(width * width * 8, false);
-    void* V = sc.get(width * width * 8, false);
     void* M = sc.get(width * k * 8, false);
     void* lam = sc.get(k * 8, false);
     void* status = sc.get(8);
     void* R = sc.get(n * k * 8, false);
-    void* bval = sc.get(nb * 8, false);
-    void* bidx = sc.get(nb * 8, false);
+    void* bval = sc.get(2 * nb * 8, false);
+    void* bidx = sc.get(2 * nb * 8, false);
     void* pick = sc.get(k * 8, false);
     void* W = sc.get(width * k * 8, false);
     if (sc.err != hipSuccess) return scratch_fail(ctx, sc, "canonical");
@@ -391,7 +390,7 @@ symnmf_status symnmf_canonical(symnmf_ctx* ctx, const float* Y, int64_t n, int64
     int32_t st[2] = {0, 0};
     {
         chk(launch_xty(Y, width, width, Y, width, width, n, (double*)work, (double*)G, sm));
-        chk(launch_jacobi_topk((const double*)G, width, k, (double*)V, (double*)M, (double*)lam, (int32_t*)status, sm));
+        chk(launch_jacobi_topk((const double*)G, width, k, (double*)M, (double*)lam, (int32_t*)status, sm));
         chk(launch_project_rows(Y, n, width, (const double*)M, k, k, 1, R, sm));
         chk(launch_spa((double*)R, n, k, (double*)bval, (int64_t*)bidx, nb, (int64_t*)pick, sm));
         chk(launch_anchor_solve(Y, width, (const double*)M, k, (const int64_t*)pick, (double*)W,
@@ -449,13 +448,13 @@ symnmf_status symnmf_subspace_error(symnmf_ctx* ctx, const float* A, const float
     HIP_OK(ctx, hipSetDevice(ctx->device));
     hipStream_t sm = ctx->stream;
     const int64_t kk = k * k;
-    // AtA, BtB, AtB, V, MA, MB, lam(k), overlap(1), work
+    // AtA, BtB, AtB, MA, MB, lam(k), overlap(1), work
     const int64_t work = xty_work_doubles(n, k, k);
     CallScratch sc(ctx);
-    double* d = (double*)sc.get((6 * kk + k + 1 + work) * 8 + 16);
+    double* d = (double*)sc.get((5 * kk + k + 1 + work) * 8 + 16);
     if (sc.err != hipSuccess) return scratch_fail(ctx, sc, "subspace_error");
-    double *AtA = d, *BtB = d + kk, *AtB = d + 2 * kk, *V = d + 3 * kk, *MA = d + 4 * kk, *MB = d + 5 * kk;
-    double *lam = d + 6 * kk, *ov = lam + k, *wk = ov + 1;
+    double *AtA = d, *BtB = d + kk, *AtB = d + 2 * kk, *MA = d + 3 * kk, *MB = d + 4 * kk;
+    double *lam = d + 5 * kk, *ov = lam + k, *wk = ov + 1;
     int32_t* status = (int32_t*)(wk + work);
     int32_t st[2] = {0, 0};
     double overlap = 0.0;
@@ -464,8 +463,8 @@ symnmf_status symnmf_subspace_error(symnmf_ctx* ctx, const float* A, const float
     chk(launch_xty(A, k, k, A, k, k, n, wk, AtA, sm));
     chk(launch_xty(B, k, k, B, k, k, n, wk, BtB, sm));
     chk(launch_xty(A, k, k, B, k, k, n, wk, AtB, sm));
-    chk(launch_jacobi_topk(AtA, k, k, V, MA, lam, status, sm));
-    chk(launch_jacobi_topk(BtB, k, k, V, MB, lam, status + 1, sm));
+    chk(launch_jacobi_topk(AtA, k, k, MA, lam, status, sm));
+    chk(launch_jacobi_topk(BtB, k, k, MB, lam, status + 1, sm));
     chk(launch_span_overlap(MA, AtB, MB, k, ov, sm));
     chk(hipMemcpyAsync(&overlap, ov, 8, hipMemcpyDeviceToHost, sm));
     chk(hipMemcpyAsync(st, status, 8, hipMemcpyDeviceToHost, sm));
