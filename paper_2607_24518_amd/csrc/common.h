@@ -26,6 +26,14 @@ constexpr int64_t PAD = 256;
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
+// Columns the MFMA stream works on for rank k: its column blocks are 16 wide and
+// it exists for 1, 2 and 4 of them; the columns past k are zero in the images of
+// H and in the partials, whose rows have this stride.  The padded products are
+// free where they matter: at any rank but 16, 32 and 64 a thread per row of S
+// was the alternative, and that took 247 us a step at n = 4100, k = 20 where the
+// 32-column MFMA stream takes 29 us.
+inline int64_t mfma_width(int64_t k) { return k <= 16 ? 16 : (k <= 32 ? 32 : 64); }
+
 // ---------------------------------------------------------------------------
 // Tiled storage of S (FP32, BF16, FP8).  S is cut into 256 x 256 tiles,
 // stored tile after tile in (row tile, column chunk) order.  Inside a tile the
@@ -253,14 +261,15 @@ __host__ __device__ inline void sample_block_flags(uint64_t seed, int64_t t, int
 // H: global rows, n_pad x k (h_f64: double); part: (P + n_tiles) * TR * k of
 // the accumulation type (acc_f64: double).  Returns hipErrorInvalidValue for
 // combinations without a kernel.
-// MFMA kernels (stream_uses_mfma) read H through chunk images instead of H:
+// MFMA kernels (stream_uses_mfma) write partial rows of mfma_width(k) entries and
+// read H through chunk images instead of H:
 // img1 = images of H, img2 = images of 2H (block steps; may equal img1 otherwise).
 hipError_t launch_stream(const void* S, int32_t stype, int64_t ld, const void* H, int h_f64, int64_t k,
                          void* part, int acc_f64, const PlanView& plan, hipStream_t stream,
                          const void* img1 = nullptr, const void* img2 = nullptr);
 // 32-bit words of the H images of all n_chunks chunks for this storage type and rank
 int64_t h_image_words(int32_t stype, int64_t k, int64_t n_chunks);
-// Write the chunk images of wt * H (H: n_chunks * 256 rows x k, FP32).
+// Write the chunk images of wt * H (H: n_chunks * 256 rows x k, FP32), zero past column k.
 hipError_t launch_h_image(const float* H, int32_t stype, int64_t k, int64_t n_chunks, float wt, uint32_t* img,
                           hipStream_t stream);
 hipError_t launch_copy_probe(const void* src, void* dst, int64_t bytes, hipStream_t stream);
@@ -270,6 +279,7 @@ hipError_t launch_read_probe(const void* src, int64_t bytes, uint32_t* sink, int
 // Objective pass on the MFMA path: FP32 sums within each 256-column chunk,
 // FP64 across chunks; FP64 partials.  img: chunk images of FP32 H.
 int stream_acc64_supported(int32_t stype, int64_t k);
+int stream_acc64_wgs_per_cu(int64_t k);
 hipError_t launch_stream_acc64(const void* S, int32_t stype, int64_t k, const void* img, double* part,
                                const PlanView& p, hipStream_t stream);
 int stream_uses_mfma(int32_t stype, int h_f64, int acc_f64, int64_t k);
@@ -303,6 +313,7 @@ struct UpdateArgs {
     void* Mu;             // snapshot gradient (SVRG), may be null
     void* Gout;           // gradient of this step, may be null
     const void* part;     // S.H partials
+    int64_t kp;           // row stride of the partials: mfma_width(k) or k
     const void* gram_eff; // [3][k][k] effective Gram per class (state precision)
     double cgrad;         // 4 (full / row steps) or 2 (block steps)
     int32_t store_mu;     // full SVRG step: mu <- g
@@ -411,13 +422,14 @@ hipError_t launch_syrk_split_store(const float* Z, int64_t K, int64_t ldz, const
 hipError_t launch_store_dense(const void* src, int src_f64, const BuildOut& o, double* sums,
                               uint32_t* panel_max, hipStream_t stream);
 hipError_t launch_fp8_decode_check(int32_t* bad, hipStream_t stream);
-// objective pass: per-tile tr(H^T S H) partial and Gram of H (FP64 H).
-hipError_t launch_objective_tiles(const UpdateArgs& a, const PlanView& plan, hipStream_t stream);
+// objective pass: per-slice tr(H^T S H) partial and Gram of H (FP32 or FP64 H, FP64 partials of
+// a full plan).
+hipError_t launch_objective_tiles(const UpdateArgs& a, int h_f64, const PlanView& plan, hipStream_t stream);
 
 // warmstart.hip
 hipError_t launch_omega(uint64_t seed, int64_t n, int64_t rows_alloc, int w, float* out, hipStream_t stream);
 // dense FP32 S.H rows (rows x k) from the partials of a full FP32-accumulating stream pass
-hipError_t launch_sh_dense(const float* part, int64_t rows, int64_t rows_pad, int64_t k, int32_t n_chunks, int32_t P,
+hipError_t launch_sh_dense(const float* part, int64_t rows, int64_t rows_pad, int64_t k, int64_t kp, int32_t n_chunks, int32_t P,
                            const float* H, int64_t row0, const float* scale, const float* diag, int64_t panel_rows,
                            float* out, hipStream_t stream);
 // C = alpha op(A) op(B) + bias with epilogue (0 none, 1 GELU, 2 softplus); Z: pre-epilogue copy

@@ -120,6 +120,7 @@ struct symnmf_state {
     int64_t k = 0, n = 0, n_pad = 0, rows = 0, rows_pad = 0, row0 = 0, tiles = 0, chunks = 0;
     int h_f64 = 0;
     int64_t hsz = 4;
+    int64_t kp = 0;                  // row stride of the S.H partials
     int32_t P = 0;
     std::vector<void*> allocs;
     void* H[2] = {nullptr, nullptr};
@@ -563,6 +564,7 @@ symnmf_status symnmf_state_create(symnmf_ctx* ctx, const symnmf_S* S, int64_t k,
     if (svrg) ALLOC(st->Mu, pbytes);
     ALLOC(st->Gout, pbytes);
     st->mfma = stream_uses_mfma(S->dtype, h_f64, h_f64, k) != 0;
+    st->kp = st->mfma ? mfma_width(k) : k;
     if (st->mfma) {
         const int64_t iw = h_image_words(S->dtype, k, st->chunks);
         ALLOC(st->img[0], iw * 4);
@@ -573,8 +575,8 @@ symnmf_status symnmf_state_create(symnmf_ctx* ctx, const symnmf_S* S, int64_t k,
     st->P_tall = st->tall ? tall_wgs(ctx->cus, st->tiles) : ctx->cus;
     const int64_t part_tiles = std::max<int64_t>((int64_t)st->P + st->tiles,
                                                  st->tall ? 2 * ((int64_t)st->P_tall + tall_pairs(st->tiles)) : 0);
-    ALLOC(st->part, part_tiles * TR * k * st->hsz);
-    st->part_bytes = part_tiles * TR * k * st->hsz;
+    ALLOC(st->part, part_tiles * TR * st->kp * st->hsz);
+    st->part_bytes = part_tiles * TR * st->kp * st->hsz;
     ALLOC(st->tile_gram, st->tiles * SUBT * k * k * 8);
     ALLOC(st->tile_tr, st->tiles * SUBT * 8);
     ALLOC(st->tile_kkt, st->tiles * SUBT * 8);
@@ -699,6 +701,7 @@ static symnmf_status do_step(symnmf_ctx* ctx, const symnmf_S* S, symnmf_state* s
     a.Mu = st->Mu;
     a.Gout = st->Gout;
     a.part = st->part;
+    a.kp = st->kp;
     a.gram_eff = st->gram_eff;
     a.cgrad = kind == 2 ? 2.0 : 4.0;
     a.store_mu = (kind == 0 && st->Mu) ? 1 : 0;
@@ -815,29 +818,31 @@ symnmf_status symnmf_state_read(symnmf_ctx* ctx, symnmf_state* st, int32_t which
 
 }  // extern "C"
 
-// Scratch of objective_terms: FP64 copy of H, the S.H partials, the per-slice
-// FP64 partials, the Gram, three effective Grams, the statistics; on the MFMA
-// path also the FP32 H and its chunk images.
+// Scratch of objective_terms: H padded to whole tiles (as it came on the MFMA
+// path, with its chunk images; else FP64), the S.H partials, the per-slice FP64
+// partials, the Gram, three effective Grams, the statistics.
 struct ObjWs {
-    int64_t hd, part, tg, ttr, tk, tb, g, gi, sc, hf, img;
+    int64_t h, part, tg, ttr, tk, tb, g, gi, sc, img;
+    int64_t kp;
+    int32_t P;
     bool mfma;
 };
 static ObjWs objective_ws(const symnmf_ctx* ctx, const symnmf_S* S, int64_t k, int32_t h_is_f64) {
     ObjWs w;
     const int64_t tiles = S->rows_pad / TR, chunks = S->ld / KC;
-    const int32_t P = ctx->cus * (ctx->wgs_per_cu > 0 ? ctx->wgs_per_cu : 2);
+    w.mfma = !h_is_f64 && stream_acc64_supported(S->dtype, k);
+    w.P = ctx->cus * (ctx->wgs_per_cu > 0 ? ctx->wgs_per_cu : (w.mfma ? stream_acc64_wgs_per_cu(k) : 2));
+    w.kp = w.mfma ? mfma_width(k) : k;
     const int64_t hrows = std::max(round_up(S->n, PAD), S->row0 + S->rows_pad);
-    w.hd = hrows * k * 8;
-    w.part = ((int64_t)P + tiles) * TR * k * 8;
-    w.tg = tiles * k * k * 8;          // one partial per 256-row tile (objective_tiles_kernel)
-    w.ttr = tiles * 8;
-    w.tk = tiles * 8;
-    w.tb = tiles * 4;
+    w.h = hrows * k * (w.mfma ? 4 : 8);
+    w.part = ((int64_t)w.P + tiles) * TR * w.kp * 8;
+    w.tg = tiles * SUBT * k * k * 8;
+    w.ttr = tiles * SUBT * 8;
+    w.tk = tiles * SUBT * 8;
+    w.tb = tiles * SUBT * 4;
     w.g = k * k * 8;
     w.gi = 3 * k * k * 8;
     w.sc = 4 * 8;
-    w.mfma = !h_is_f64 && stream_acc64_supported(S->dtype, k);
-    w.hf = w.mfma ? hrows * k * 4 : 0;
     w.img = w.mfma ? h_image_words(S->dtype, k, chunks) * 4 : 0;
     return w;
 }
@@ -849,10 +854,9 @@ symnmf_status objective_terms(symnmf_ctx* ctx, const symnmf_S* S, const void* H,
     HIP_OK(ctx, hipSetDevice(ctx->device));
     hipStream_t sm = ctx->stream;
     const int64_t tiles = S->rows_pad / TR, chunks = S->ld / KC;
-    const int32_t P = ctx->cus * (ctx->wgs_per_cu > 0 ? ctx->wgs_per_cu : 2);
     const ObjWs w = objective_ws(ctx, S, k, h_is_f64);
     CallScratch scr(ctx);
-    void* Hd = scr.get(w.hd);
+    void* Hp = scr.get(w.h);
     void* part = scr.get(w.part, false);
     void* tg = scr.get(w.tg, false);
     void* ttr = scr.get(w.ttr, false);
@@ -861,20 +865,18 @@ symnmf_status objective_terms(symnmf_ctx* ctx, const symnmf_S* S, const void* H,
     void* g = scr.get(w.g, false);
     void* gi = scr.get(w.gi, false);
     void* sc = scr.get(w.sc, false);
-    void* Hf = w.mfma ? scr.get(w.hf) : nullptr;
     void* img = w.mfma ? scr.get(w.img, false) : nullptr;
     if (scr.err != hipSuccess) return scratch_fail(ctx, scr, "objective");
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
-    chk(launch_copy_h(H, h_is_f64, Hd, 1, S->n * k, sm));
-    PlanView pv = plan_view(nullptr, 1, (int32_t)tiles, (int32_t)chunks, P);
+    PlanView pv = plan_view(nullptr, 1, (int32_t)tiles, (int32_t)chunks, w.P);
+    chk(launch_copy_h(H, h_is_f64, Hp, w.mfma ? 0 : 1, S->n * k, sm));
     if (w.mfma) {
         // MFMA products, FP32 within each 256-column chunk, FP64 across chunks
-        chk(launch_copy_h(H, 0, Hf, 0, S->n * k, sm));
-        chk(launch_h_image((const float*)Hf, S->dtype, k, chunks, 1.0f, (uint32_t*)img, sm));
+        chk(launch_h_image((const float*)Hp, S->dtype, k, chunks, 1.0f, (uint32_t*)img, sm));
         chk(launch_stream_acc64(S->data, S->dtype, k, img, (double*)part, pv, sm));
     } else {
-        chk(launch_stream(S->data, S->dtype, S->ld, Hd, 1, k, part, 1, pv, sm));
+        chk(launch_stream(S->data, S->dtype, S->ld, Hp, 1, k, part, 1, pv, sm));
     }
     UpdateArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -883,8 +885,9 @@ symnmf_status objective_terms(symnmf_ctx* ctx, const symnmf_S* S, const void* H,
     a.n = S->n;
     a.k = k;
     a.row0 = S->row0;
-    a.H = Hd;
+    a.H = Hp;
     a.part = part;
+    a.kp = w.kp;
     a.fp8 = S->dtype == SYMNMF_S_FP8;
     a.panel_scale = S->panel_scale;
     a.diag = S->diag;
@@ -893,8 +896,8 @@ symnmf_status objective_terms(symnmf_ctx* ctx, const symnmf_S* S, const void* H,
     a.tile_tr = (double*)ttr;
     a.tile_kkt = (double*)tk;
     a.tile_bad = (int32_t*)tb;
-    chk(launch_objective_tiles(a, pv, sm));
-    chk(launch_finalize(tiles, k, (double*)tg, (double*)ttr, (double*)tk, (int32_t*)tb, nullptr, nullptr,
+    chk(launch_objective_tiles(a, w.mfma ? 0 : 1, pv, sm));
+    chk(launch_finalize(tiles * SUBT, k, (double*)tg, (double*)ttr, (double*)tk, (int32_t*)tb, nullptr, nullptr,
                         (double*)g, gi, 1, (double*)sc, sm));
     std::vector<double> gram(k * k);
     double d[4] = {0, 0, 0, 0};
@@ -914,8 +917,7 @@ extern "C" {
 int64_t symnmf_objective_workspace(const symnmf_ctx* ctx, const symnmf_S* S, int64_t k, int32_t h_is_f64) {
     if (!ctx || !S || k < 1 || k > KMAX) return -1;
     const ObjWs w = objective_ws(ctx, S, k, h_is_f64);
-    return ws_sum({w.hd, w.part, w.tg, w.ttr, w.tk, w.tb, w.g, w.gi, w.sc}) +
-           (w.mfma ? ws_sum({w.hf, w.img}) : 0);
+    return ws_sum({w.h, w.part, w.tg, w.ttr, w.tk, w.tb, w.g, w.gi, w.sc}) + (w.mfma ? ws_round(w.img) : 0);
 }
 
 symnmf_status symnmf_objective(symnmf_ctx* ctx, const symnmf_S* S, const void* H, int32_t h_is_f64, int64_t k,
@@ -1140,7 +1142,7 @@ static symnmf_status rebind_state(symnmf_state* st, const symnmf_S* S) {
     const int32_t P_tall = tall ? tall_wgs(ctx->cus, st->tiles) : ctx->cus;
     const int64_t part_tiles = std::max<int64_t>((int64_t)P + st->tiles,
                                                  tall ? 2 * ((int64_t)P_tall + tall_pairs(st->tiles)) : 0);
-    const int64_t part_bytes = part_tiles * TR * k * st->hsz;
+    const int64_t part_bytes = part_tiles * TR * (mfma ? mfma_width(k) : k) * st->hsz;
     const int64_t img_bytes = mfma ? h_image_words(S->dtype, k, st->chunks) * 4 : 0;
     HIP_OK(ctx, hipStreamSynchronize(ctx->stream));   // no kernel of the old shape still reads the buffers
     auto grow = [&](void*& buf, int64_t need) -> symnmf_status {

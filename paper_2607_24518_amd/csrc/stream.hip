@@ -60,9 +60,9 @@ __device__ inline void unit_decode(const PlanView& p, int64_t u, int32_t& a, int
 }
 
 // ---------------------------------------------------------------------------
-// Generic kernel: any storage type, FP32 or FP64 H and accumulation, k <= KB.
-// One thread per row of the tile.  Used for FP64 parity runs, ranks that are
-// not a multiple of 16, and the FP64-accumulated objective.
+// Generic kernel: any storage type, FP64 H and accumulation, k <= KB.
+// One thread per row of the tile.  Used for FP64 H: parity runs at ranks other
+// than 16 and 32, and the objective of an FP64 factor.
 // ---------------------------------------------------------------------------
 template <typename ST>
 __device__ inline int64_t s_index(int64_t r, int64_t c, int64_t ld, int64_t n_chunks) {
@@ -70,12 +70,12 @@ __device__ inline int64_t s_index(int64_t r, int64_t c, int64_t ld, int64_t n_ch
     return tiled_offset(r, c, n_chunks, (int)(16 / sizeof(ST)));
 }
 
-template <typename ST, typename HT, typename AT, int KB>
+template <typename ST, int KB>
 __global__ __launch_bounds__(256) void stream_generic(const ST* __restrict__ S, int64_t ld,
-                                                      const HT* __restrict__ H, int k,
-                                                      AT* __restrict__ part, PlanView p) {
+                                                      const double* __restrict__ H, int k,
+                                                      double* __restrict__ part, PlanView p) {
     constexpr int SUB = 32;
-    __shared__ AT Hs[SUB * KB];
+    __shared__ double Hs[SUB * KB];
     int64_t U; int32_t na;
     plan_bounds(p, U, na);
     if (U == 0) return;
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256) void stream_generic(const ST* __restrict__ S, 
         const int64_t abase = unit_off(p, a);
         const int64_t run_end = min(u1, unit_off(p, a + 1));
         const int64_t tile = tile_of(p, a);
-        AT acc[KB];
+        double acc[KB];
 #pragma unroll
         for (int c = 0; c < KB; ++c) acc[c] = 0;
         const int64_t row = tile * TR + t;
@@ -101,19 +101,19 @@ __global__ __launch_bounds__(256) void stream_generic(const ST* __restrict__ S, 
                 __syncthreads();
                 for (int f = t; f < SUB * k; f += 256) {
                     int kk = f / k, c = f - kk * k;
-                    Hs[kk * KB + c] = (AT)H[((int64_t)chunk * KC + sub + kk) * k + c] * (AT)wt;
+                    Hs[kk * KB + c] = H[((int64_t)chunk * KC + sub + kk) * k + c] * (double)wt;
                 }
                 __syncthreads();
                 const int64_t col0 = (int64_t)chunk * KC + sub;
                 for (int kk = 0; kk < SUB; ++kk) {
-                    const AT s = (AT)load_as_f64(S + s_index<ST>(row, col0 + kk, ld, p.n_chunks));
+                    const double s = load_as_f64(S + s_index<ST>(row, col0 + kk, ld, p.n_chunks));
 #pragma unroll
                     for (int c = 0; c < KB; ++c)
                         if (c < k) acc[c] += s * Hs[kk * KB + c];
                 }
             }
         }
-        AT* dst = part + ((w + a) * TR + t) * (int64_t)k;
+        double* dst = part + ((w + a) * TR + t) * (int64_t)k;
 #pragma unroll
         for (int c = 0; c < KB; ++c)
             if (c < k) dst[c] = acc[c];
@@ -270,8 +270,9 @@ struct ImageShape {
 template <int KIND, int K>
 constexpr int image_cols_per_wg() { return K == 64 ? 16 : K; }
 
+// H has k <= K columns; the image's other columns are zero.
 template <int KIND, int K>
-__global__ __launch_bounds__(256) void h_image_kernel(const float* __restrict__ H, float wt,
+__global__ __launch_bounds__(256) void h_image_kernel(const float* __restrict__ H, int k, float wt,
                                                       u32x4* __restrict__ img) {
     using IS = ImageShape<KIND, K>;
     constexpr int CB = image_cols_per_wg<KIND, K>();
@@ -282,15 +283,23 @@ __global__ __launch_bounds__(256) void h_image_kernel(const float* __restrict__ 
     __shared__ float Hs[KC * LDH];
     const int64_t chunk = blockIdx.x;
     const int blk = blockIdx.y;
-    const float* src = H + chunk * KC * K + CB * blk;
-    for (int q = threadIdx.x; q < KC * CB / 4; q += 256) {
-        const int r = q / (CB / 4), c = 4 * (q % (CB / 4));
-        const float4 x = *(const float4*)(src + (int64_t)r * K + c);
-        float* d = Hs + r * LDH + c;
-        d[0] = x.x * wt;
-        d[1] = x.y * wt;
-        d[2] = x.z * wt;
-        d[3] = x.w * wt;
+    if (k == K) {
+        const float* src = H + chunk * KC * K + CB * blk;
+        for (int q = threadIdx.x; q < KC * CB / 4; q += 256) {
+            const int r = q / (CB / 4), c = 4 * (q % (CB / 4));
+            const float4 x = *(const float4*)(src + (int64_t)r * K + c);
+            float* d = Hs + r * LDH + c;
+            d[0] = x.x * wt;
+            d[1] = x.y * wt;
+            d[2] = x.z * wt;
+            d[3] = x.w * wt;
+        }
+    } else {
+        const float* src = H + chunk * KC * k;
+        for (int q = threadIdx.x; q < KC * CB; q += 256) {
+            const int r = q / CB, c = CB * blk + q % CB;
+            Hs[r * LDH + q % CB] = c < k ? src[r * k + c] * wt : 0.0f;
+        }
     }
     __syncthreads();
     u32x4* out = img + chunk * IS::NV;
@@ -322,20 +331,24 @@ __global__ __launch_bounds__(256) void h_image_kernel(const float* __restrict__ 
 }
 
 int64_t h_image_words(int32_t stype, int64_t k, int64_t n_chunks) {
-    const int64_t per = stype == SYMNMF_S_FP32 ? KC * k : 3 * KC * k / 2;
+    const int64_t kw = mfma_width(k);
+    const int64_t per = stype == SYMNMF_S_FP32 ? KC * kw : 3 * KC * kw / 2;
     return per * n_chunks;
 }
 
 hipError_t launch_h_image(const float* H, int32_t stype, int64_t k, int64_t n_chunks, float wt, uint32_t* img,
                           hipStream_t stream) {
-    dim3 grid(n_chunks, k == 64 ? 4 : 1), block(256);
-#define IMG(KIND, KK) hipLaunchKernelGGL((h_image_kernel<KIND, KK>), grid, block, 0, stream, H, wt, (u32x4*)img)
+    if (k < 1 || k > KMAX) return hipErrorInvalidValue;
+    const int64_t kw = mfma_width(k);
+    dim3 grid(n_chunks, kw == 64 ? 4 : 1), block(256);
+#define IMG(KIND, KK) \
+    hipLaunchKernelGGL((h_image_kernel<KIND, KK>), grid, block, 0, stream, H, (int)k, wt, (u32x4*)img)
     if (stype == SYMNMF_S_FP32) {
-        if (k == 16) IMG(0, 16); else if (k == 32) IMG(0, 32); else if (k == 64) IMG(0, 64); else return hipErrorInvalidValue;
+        if (kw == 16) IMG(0, 16); else if (kw == 32) IMG(0, 32); else IMG(0, 64);
     } else if (stype == SYMNMF_S_BF16) {
-        if (k == 16) IMG(1, 16); else if (k == 32) IMG(1, 32); else if (k == 64) IMG(1, 64); else return hipErrorInvalidValue;
+        if (kw == 16) IMG(1, 16); else if (kw == 32) IMG(1, 32); else IMG(1, 64);
     } else if (stype == SYMNMF_S_FP8) {
-        if (k == 16) IMG(2, 16); else if (k == 32) IMG(2, 32); else if (k == 64) IMG(2, 64); else return hipErrorInvalidValue;
+        if (kw == 16) IMG(2, 16); else if (kw == 32) IMG(2, 32); else IMG(2, 64);
     } else {
         return hipErrorInvalidValue;
     }
@@ -374,7 +387,7 @@ constexpr int RING_F32 = 8;
 // (tile pair, chunk) unit against one chunk image, halving image traffic per
 // byte of S.
 template <int KIND, int NT, bool DB, bool PF, bool ACC64, bool TALL>
-__global__ __launch_bounds__(TALL ? 512 : 256, TALL ? 1 : 2) void stream_mfma(const void* __restrict__ Sv,
+__global__ __launch_bounds__(TALL ? 512 : 256, TALL || (ACC64 && NT == 4) ? 1 : 2) void stream_mfma(const void* __restrict__ Sv,
                                                                              const u32x4* __restrict__ img1,
                                                                              const u32x4* __restrict__ img2,
                                                                              void* __restrict__ part, PlanView plan) {
@@ -630,34 +643,22 @@ __global__ __launch_bounds__(TALL ? 512 : 256, TALL ? 1 : 2) void stream_mfma(co
 
 int stream_uses_mfma(int32_t stype, int h_f64, int acc_f64, int64_t k) {
     if (h_f64 || acc_f64 || stype == SYMNMF_S_FP64) return 0;
-    return (k == 16 || k == 32 || k == 64) ? 1 : 0;
-}
-
-template <typename ST, typename HT, typename AT>
-static hipError_t launch_generic(const void* S, int64_t ld, const void* H, int64_t k, void* part,
-                                 const PlanView& p, hipStream_t stream) {
-    dim3 grid(p.P), block(256);
-    if (k <= 8)
-        hipLaunchKernelGGL((stream_generic<ST, HT, AT, 8>), grid, block, 0, stream, (const ST*)S, ld,
-                           (const HT*)H, (int)k, (AT*)part, p);
-    else if (k <= 16)
-        hipLaunchKernelGGL((stream_generic<ST, HT, AT, 16>), grid, block, 0, stream, (const ST*)S, ld,
-                           (const HT*)H, (int)k, (AT*)part, p);
-    else if (k <= 32)
-        hipLaunchKernelGGL((stream_generic<ST, HT, AT, 32>), grid, block, 0, stream, (const ST*)S, ld,
-                           (const HT*)H, (int)k, (AT*)part, p);
-    else
-        hipLaunchKernelGGL((stream_generic<ST, HT, AT, 64>), grid, block, 0, stream, (const ST*)S, ld,
-                           (const HT*)H, (int)k, (AT*)part, p);
-    return hipGetLastError();
+    return (k >= 1 && k <= KMAX) ? 1 : 0;
 }
 
 template <typename ST>
-static hipError_t launch_generic_s(const void* S, int64_t ld, const void* H, int h_f64, int64_t k, void* part,
-                                   int acc_f64, const PlanView& p, hipStream_t stream) {
-    if (h_f64) return launch_generic<ST, double, double>(S, ld, H, k, part, p, stream);
-    if (acc_f64) return launch_generic<ST, float, double>(S, ld, H, k, part, p, stream);
-    return launch_generic<ST, float, float>(S, ld, H, k, part, p, stream);
+static hipError_t launch_generic(const void* S, int64_t ld, const double* H, int64_t k, double* part, const PlanView& p,
+                                 hipStream_t stream) {
+    dim3 grid(p.P), block(256);
+    if (k <= 8)
+        hipLaunchKernelGGL((stream_generic<ST, 8>), grid, block, 0, stream, (const ST*)S, ld, H, (int)k, part, p);
+    else if (k <= 16)
+        hipLaunchKernelGGL((stream_generic<ST, 16>), grid, block, 0, stream, (const ST*)S, ld, H, (int)k, part, p);
+    else if (k <= 32)
+        hipLaunchKernelGGL((stream_generic<ST, 32>), grid, block, 0, stream, (const ST*)S, ld, H, (int)k, part, p);
+    else
+        hipLaunchKernelGGL((stream_generic<ST, 64>), grid, block, 0, stream, (const ST*)S, ld, H, (int)k, part, p);
+    return hipGetLastError();
 }
 
 // LDS per work-group (image buffers): FP32 k=16/32 double-buffered (32/64 KB),
@@ -670,6 +671,7 @@ template <int KIND>
 static void launch_mfma_kind(const void* S, const u32x4* img1, const u32x4* img2, void* part, int64_t k,
                              const PlanView& p, hipStream_t stream) {
     dim3 grid(p.P);
+    k = mfma_width(k);
     if (p.tall) {
         dim3 block(512);
         if (k == 16) hipLaunchKernelGGL((stream_mfma<KIND, 1, true, true, false, true>), grid, block, 0, stream, S, img1, img2, part, p);
@@ -687,17 +689,23 @@ int stream_tall_supported(int32_t stype, int h_f64, int64_t k) {
     return stream_uses_mfma(stype, h_f64, 0, k);
 }
 
+// The 64-column form holds 128 registers of FP64 sums beside 64 of FP32 ones and
+// runs one work-group per CU.
 template <int KIND>
 static void launch_mfma_kind_acc64(const void* S, const u32x4* img, void* part, int64_t k, const PlanView& p,
                                    hipStream_t stream) {
     dim3 grid(p.P), block(256);
+    k = mfma_width(k);
     if (k == 16) hipLaunchKernelGGL((stream_mfma<KIND, 1, true, false, true, false>), grid, block, 0, stream, S, img, img, part, p);
-    else hipLaunchKernelGGL((stream_mfma<KIND, 2, KIND == 0, false, true, false>), grid, block, 0, stream, S, img, img, part, p);
+    else if (k == 32) hipLaunchKernelGGL((stream_mfma<KIND, 2, KIND == 0, false, true, false>), grid, block, 0, stream, S, img, img, part, p);
+    else hipLaunchKernelGGL((stream_mfma<KIND, 4, false, false, true, false>), grid, block, 0, stream, S, img, img, part, p);
 }
 
 int stream_acc64_supported(int32_t stype, int64_t k) {
-    return (stype == SYMNMF_S_FP32 || stype == SYMNMF_S_BF16 || stype == SYMNMF_S_FP8) && (k == 16 || k == 32);
+    return (stype == SYMNMF_S_FP32 || stype == SYMNMF_S_BF16 || stype == SYMNMF_S_FP8) && k >= 1 && k <= KMAX;
 }
+
+int stream_acc64_wgs_per_cu(int64_t k) { return mfma_width(k) == 64 ? 1 : 2; }
 
 hipError_t launch_stream_acc64(const void* S, int32_t stype, int64_t k, const void* img, double* part,
                                const PlanView& p, hipStream_t stream) {
@@ -710,7 +718,7 @@ hipError_t launch_stream_acc64(const void* S, int32_t stype, int64_t k, const vo
 }
 
 int stream_wgs_per_cu(int32_t stype, int64_t k) {
-    if ((stype == SYMNMF_S_BF16 || stype == SYMNMF_S_FP8) && k == 64) return 1;
+    if ((stype == SYMNMF_S_BF16 || stype == SYMNMF_S_FP8) && mfma_width(k) == 64) return 1;
     return 2;
 }
 
@@ -729,23 +737,23 @@ hipError_t launch_stream(const void* S, int32_t stype, int64_t ld, const void* H
         else return hipErrorInvalidValue;
         return hipGetLastError();
     }
+    if (!h_f64 || !acc_f64) return hipErrorInvalidValue;
+    const double* Hd = (const double*)H;
+    double* pd = (double*)part;
     switch (stype) {
-        case SYMNMF_S_FP32: return launch_generic_s<float>(S, ld, H, h_f64, k, part, acc_f64, p, stream);
-        case SYMNMF_S_BF16: return launch_generic_s<uint16_t>(S, ld, H, h_f64, k, part, acc_f64, p, stream);
-        case SYMNMF_S_FP8: return launch_generic_s<uint8_t>(S, ld, H, h_f64, k, part, acc_f64, p, stream);
+        case SYMNMF_S_FP32: return launch_generic<float>(S, ld, Hd, k, pd, p, stream);
+        case SYMNMF_S_BF16: return launch_generic<uint16_t>(S, ld, Hd, k, pd, p, stream);
+        case SYMNMF_S_FP8: return launch_generic<uint8_t>(S, ld, Hd, k, pd, p, stream);
         case SYMNMF_S_FP64:
-            if (!h_f64) return hipErrorInvalidValue;
             if ((k == 16 || k == 32) && std::getenv("SYMNMF_F64_GENERIC") == nullptr) {
                 dim3 grid(p.P), block(256);
                 if (k == 16)
-                    hipLaunchKernelGGL((stream_f64_mfma<1>), grid, block, 0, stream, (const double*)S, ld,
-                                       (const double*)H, (double*)part, p);
+                    hipLaunchKernelGGL((stream_f64_mfma<1>), grid, block, 0, stream, (const double*)S, ld, Hd, pd, p);
                 else
-                    hipLaunchKernelGGL((stream_f64_mfma<2>), grid, block, 0, stream, (const double*)S, ld,
-                                       (const double*)H, (double*)part, p);
+                    hipLaunchKernelGGL((stream_f64_mfma<2>), grid, block, 0, stream, (const double*)S, ld, Hd, pd, p);
                 return hipGetLastError();
             }
-            return launch_generic<double, double, double>(S, ld, H, k, part, p, stream);
+            return launch_generic<double>(S, ld, Hd, k, pd, p, stream);
     }
     return hipErrorInvalidValue;
 }

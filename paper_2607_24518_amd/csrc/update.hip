@@ -55,10 +55,16 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
     const int32_t act = p.full ? (int32_t)tile : p.tile_active[tile];
     const int cls = (act >= 0 && !p.full) ? p.active_class[act] : 0;
     const HT* gram = (const HT*)a.gram_eff + (int64_t)cls * k * k;
-    for (int e = t; e < k * k; e += UT) Gs[(e / k) * KB + e % k] = gram[e];
+    for (int e = t; e < KB * KB; e += UT) {
+        const int i = e / KB, j = e % KB;
+        Gs[e] = i < k && j < k ? gram[i * k + j] : (HT)0;
+    }
     const int64_t g0 = a.row0 + tile * TR + r0;       // global row of slice row 0
     const HT* Ht = (const HT*)a.H;
-    for (int f = t; f < SR * k; f += UT) Hs[(f / k) * KB + f % k] = Ht[g0 * k + f];
+    for (int f = t; f < SR * KB; f += UT) {
+        const int r = f / KB, c = f % KB;
+        Hs[f] = c < k ? Ht[(g0 + r) * k + c] : (HT)0;
+    }
     __syncthreads();
 
     int64_t w_lo, w_hi, slot_base, slot_mul;
@@ -71,19 +77,18 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
     HT* Go = (HT*)a.Gout;
     HT* Hn = (HT*)a.Hn;
     const HT eta = (HT)a.eta, eps = (HT)a.eps, alpha = (HT)a.alpha, mom = (HT)a.mu, cg = (HT)a.cgrad;
-    // H (H^T H) of this thread's elements.  With k == KB the elements
-    // f = t + UT j of a thread share the column c = t % KB (UT is a multiple
-    // of KB), so every Gram entry is read from LDS once for all of them and
-    // the H rows in 4-wide vectors; the products are summed in the same order
-    // as the per-element loop below.
+    // Elements f = t + UT j of the slice in rows of KB columns (those past k are
+    // zero and have no storage): a thread's elements share the column
+    // c = t % KB, as UT is a multiple of KB, so every Gram entry of H (H^T H) is
+    // read from LDS once for all of them and the H rows in 4-wide vectors.
     constexpr int NJ = SR * KB / UT;
     typedef HT hvec4 __attribute__((ext_vector_type(4)));
-    const bool full_k = k == KB && act >= 0;
+    const int c = t % KB, rb = t / KB;
     HT hgv[NJ];
-    if (full_k) {
-        const int c = t % KB, rb = t / KB;
+    if (act >= 0) {
 #pragma unroll
         for (int j = 0; j < NJ; ++j) hgv[j] = 0;
+#pragma unroll 2
         for (int b = 0; b < KB; b += 4) {
             const HT g0 = Gs[b * KB + c], g1 = Gs[(b + 1) * KB + c], g2 = Gs[(b + 2) * KB + c],
                      g3 = Gs[(b + 3) * KB + c];
@@ -100,41 +105,32 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
         }
     }
     // the S.H partials of this thread's elements, summed over the writing
-    // work-groups in increasing order as below, but with the loads of all
-    // elements of one work-group issued together (a row of the n = 10^6 share
-    // has ten partials: one after another they are ten dependent load latencies
-    // per element)
+    // work-groups in increasing order, the loads of all elements of one
+    // work-group issued together (a row of the n = 10^6 share has ten partials:
+    // one after another they are ten dependent load latencies per element)
     HT shv[NJ];
-    if (full_k) {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) shv[j] = 0;
+    for (int j = 0; j < NJ; ++j) shv[j] = 0;
+    if (act >= 0 && c < k) {
         for (int64_t w = w_lo; w <= w_hi; ++w) {
-            // element f = r k + c of the slice: its partial entry is f past the
-            // slot's first row of this slice
-            const HT* pw = part + ((slot_mul * w + slot_base) * TR + r0) * (int64_t)k;
+            const HT* pw = part + ((slot_mul * w + slot_base) * TR + r0 + rb) * a.kp + c;
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) shv[j] += pw[t + UT * j];
+            for (int j = 0; j < NJ; ++j) shv[j] += pw[j * (UT / KB) * a.kp];
         }
     }
     double tr = 0.0, kkt = 0.0;
     int bad = 0;
-    // one element f = r k + c of the slice; with full_k its S.H sum and
-    // H (H^T H) entry come in precomputed (sh_in, hg_in)
-    auto element = [&](int f, HT sh_in, HT hg_in) {
-        const int r = f / k, c = f - r * k;             // slice row, column
+    // the element of slice row r and this thread's column, with its S.H sum and
+    // H (H^T H) entry
+    auto element = [&](int r, HT sh_in, HT hg_in) {
         const int64_t prow = tile * TR + r0 + r;
         HT hn = 0;
-        if (prow < a.rows) {
+        if (prow < a.rows && c < k) {
             const HT h = Hs[r * KB + c];
             const int64_t idx = prow * k + c;
             HT g, sh = 0, hg = 0;
             if (act >= 0) {
-                if (full_k) {
-                    sh = sh_in;
-                } else {
-                    for (int64_t w = w_lo; w <= w_hi; ++w)
-                        sh += part[((slot_mul * w + slot_base) * TR + r0 + r) * (int64_t)k + c];
-                }
+                sh = sh_in;
                 if (a.fp8) {   // codes carry S * scale off the diagonal; S_ii is kept exactly
                     // and enters with the weight the plan gives column i of this row:
                     // 1 on full and row-sampled steps; on a block step 0 for rows in I
@@ -143,11 +139,7 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
                     const HT dw = (p.full || !a.block_step) ? (HT)1 : (cls == 2 ? (HT)2 : (HT)0);
                     sh = sh / (HT)a.panel_scale[prow / a.panel_rows] + dw * (HT)a.diag[prow] * h;
                 }
-                if (full_k) {
-                    hg = hg_in;
-                } else {
-                    for (int b = 0; b < k; ++b) hg += Hs[r * KB + b] * Gs[b * KB + c];
-                }
+                hg = hg_in;
                 g = cg * (hg - sh);
                 tr += (double)h * (double)sh;
             } else {
@@ -228,17 +220,12 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
         }
         Hns[r * KB + c] = hn;
     };
-    if (full_k) {
-        // the thread's elements f = t + UT j with compile-time j, so the
-        // precomputed sums stay in registers
+    // compile-time j, so the precomputed sums stay in registers
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) element(t + UT * j, shv[j], hgv[j]);
-    } else {
-        for (int f = t; f < SR * k; f += UT) element(f, (HT)0, (HT)0);
-    }
+    for (int j = 0; j < NJ; ++j) element(rb + j * (UT / KB), shv[j], hgv[j]);
     __syncthreads();
     double* tg = a.tile_gram + slice * (int64_t)k * k;
-    if (KB >= 32 && k == KB) {
+    if (KB >= 32) {
         // each thread: entries (ia0 + q, ib), q < NQ (a multiple of 4, ia0 too),
         // consecutive ia read as aligned 4-wide vectors; the same FP64 sums
         // over the slice rows
@@ -248,6 +235,7 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
         double sq[NQ];
 #pragma unroll
         for (int q = 0; q < NQ; ++q) sq[q] = 0.0;
+#pragma unroll 4
         for (int r = 0; r < SR; ++r) {
             const double hb = (double)Hns[r * KB + ib];
 #pragma unroll
@@ -258,11 +246,13 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
             }
         }
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) tg[(ia0 + q) * k + ib] = sq[q];
+        for (int q = 0; q < NQ; ++q)
+            if (ia0 + q < k && ib < k) tg[(ia0 + q) * k + ib] = sq[q];
     } else {
         for (int e = t; e < k * k; e += UT) {
             const int ia = e / k, ib = e - ia * k;
             double s = 0.0;
+#pragma unroll 8
             for (int r = 0; r < SR; ++r) s += (double)Hns[r * KB + ia] * (double)Hns[r * KB + ib];
             tg[e] = s;
         }
@@ -286,8 +276,7 @@ hipError_t launch_update(const UpdateArgs& a, int h_f64, const PlanView& p, hipS
         else if (a.k <= 32) hipLaunchKernelGGL((update_kernel<double, 32>), grid, block, 0, stream, a, p);
         else return hipErrorInvalidValue;
     } else {
-        if (a.k <= 8) hipLaunchKernelGGL((update_kernel<float, 8>), grid, block, 0, stream, a, p);
-        else if (a.k <= 16) hipLaunchKernelGGL((update_kernel<float, 16>), grid, block, 0, stream, a, p);
+        if (a.k <= 16) hipLaunchKernelGGL((update_kernel<float, 16>), grid, block, 0, stream, a, p);
         else if (a.k <= 32) hipLaunchKernelGGL((update_kernel<float, 32>), grid, block, 0, stream, a, p);
         else hipLaunchKernelGGL((update_kernel<float, 64>), grid, block, 0, stream, a, p);
     }
@@ -333,7 +322,7 @@ __global__ __launch_bounds__(256) void admm_minv_kernel(const double* __restrict
 }
 
 template <typename HT, int KB>
-__global__ __launch_bounds__(UT) void admm_update_kernel(UpdateArgs a, PlanView p) {
+__global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kernel(UpdateArgs a, PlanView p) {
     __shared__ __align__(32) HT Ws[SR * KB];
     __shared__ __align__(32) HT Wns[SR * KB];
     __shared__ __align__(32) HT As[SR * KB];
@@ -348,13 +337,18 @@ __global__ __launch_bounds__(UT) void admm_update_kernel(UpdateArgs a, PlanView 
     const int32_t act = (int32_t)tile;                  // full steps only
     const HT* gram = (const HT*)a.gram_eff;
     const HT* minv = (const HT*)a.minv;
-    for (int e = t; e < k * k; e += UT) {
-        Gs[(e / k) * KB + e % k] = gram[e];
-        Ms[(e / k) * KB + e % k] = minv[e];
+    for (int e = t; e < KB * KB; e += UT) {
+        const int i = e / KB, j = e % KB;
+        const bool in = i < k && j < k;
+        Gs[e] = in ? gram[i * k + j] : (HT)0;
+        Ms[e] = in ? minv[i * k + j] : (HT)0;
     }
     const int64_t g0 = a.row0 + tile * TR + r0;
     const HT* Wt = (const HT*)a.H;
-    for (int f = t; f < SR * k; f += UT) Ws[(f / k) * KB + f % k] = Wt[g0 * k + f];
+    for (int f = t; f < SR * KB; f += UT) {
+        const int r = f / KB, c = f % KB;
+        Ws[f] = c < k ? Wt[(g0 + r) * k + c] : (HT)0;
+    }
     __syncthreads();
     int64_t w_lo, w_hi, slot_base, slot_mul;
     partial_slots(p, act, w_lo, w_hi, slot_base, slot_mul);
@@ -363,64 +357,51 @@ __global__ __launch_bounds__(UT) void admm_update_kernel(UpdateArgs a, PlanView 
     HT* Go = (HT*)a.Gout;
     HT* Wn = (HT*)a.Hn;
     const HT rho = (HT)a.rho;
-    // With k == KB the elements f = t + UT j of a thread share the column
-    // c = t % KB: the S.W partials are loaded writer by writer for all of them
-    // at once, and the Gram and M^-1 entries of the column are read from LDS
-    // once for all rows (rows in 4-wide vectors); every sum keeps the order
-    // of the per-element loops below.
+    // Elements f = t + UT j in rows of KB columns (zero past k), sharing the
+    // column cc = t % KB, as in the update kernel: the S.W partials are loaded
+    // writer by writer for all of them at once, and the Gram and M^-1 entries
+    // of the column are read from LDS once for all rows (rows in 4-wide vectors).
     constexpr int NJ = SR * KB / UT;
     typedef HT hvec4 __attribute__((ext_vector_type(4)));
-    const bool full_k = k == KB;
     const int cc = t % KB, rb = t / KB;
     HT swv[NJ], wgv[NJ];
-    if (full_k) {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) swv[j] = wgv[j] = 0;
+    for (int j = 0; j < NJ; ++j) swv[j] = wgv[j] = 0;
+    if (cc < k) {
         for (int64_t w = w_lo; w <= w_hi; ++w) {
-            const HT* pw = part + ((slot_mul * w + slot_base) * TR + r0) * (int64_t)k;
+            const HT* pw = part + ((slot_mul * w + slot_base) * TR + r0 + rb) * a.kp + cc;
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) swv[j] += pw[t + UT * j];
+            for (int j = 0; j < NJ; ++j) swv[j] += pw[j * (UT / KB) * a.kp];
         }
-        for (int b = 0; b < KB; b += 4) {
-            const HT g0 = Gs[b * KB + cc], g1 = Gs[(b + 1) * KB + cc], g2 = Gs[(b + 2) * KB + cc],
-                     g3 = Gs[(b + 3) * KB + cc];
+    }
+#pragma unroll 2
+    for (int b = 0; b < KB; b += 4) {
+        const HT g0 = Gs[b * KB + cc], g1 = Gs[(b + 1) * KB + cc], g2 = Gs[(b + 2) * KB + cc],
+                 g3 = Gs[(b + 3) * KB + cc];
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const hvec4 wv = *(const hvec4*)&Ws[(rb + j * (UT / KB)) * KB + b];
-                HT v = wgv[j];
-                v += wv[0] * g0;
-                v += wv[1] * g1;
-                v += wv[2] * g2;
-                v += wv[3] * g3;
-                wgv[j] = v;
-            }
+        for (int j = 0; j < NJ; ++j) {
+            const hvec4 wv = *(const hvec4*)&Ws[(rb + j * (UT / KB)) * KB + b];
+            HT v = wgv[j];
+            v += wv[0] * g0;
+            v += wv[1] * g1;
+            v += wv[2] * g2;
+            v += wv[3] * g3;
+            wgv[j] = v;
         }
     }
     double tr = 0.0, kkt = 0.0;
     int bad = 0;
-    int jj = 0;
-    for (int f = t; f < SR * k; f += UT, ++jj) {
-        const int r = f / k, c = f - r * k;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int r = rb + j * (UT / KB);
         const int64_t prow = tile * TR + r0 + r;
         HT av = 0;
-        if (prow < a.rows) {
-            const HT w = Ws[r * KB + c];
-            const int64_t idx = prow * k + c;
-            HT sw = 0;
-            if (full_k) {
-                sw = swv[jj < NJ ? jj : 0];
-            } else {
-                for (int64_t wg = w_lo; wg <= w_hi; ++wg)
-                    sw += part[((slot_mul * wg + slot_base) * TR + r0 + r) * (int64_t)k + c];
-            }
+        if (prow < a.rows && cc < k) {
+            const HT w = Ws[r * KB + cc];
+            const int64_t idx = prow * k + cc;
+            HT sw = swv[j];
             if (a.fp8) sw = sw / (HT)a.panel_scale[prow / a.panel_rows] + (HT)a.diag[prow] * w;
-            HT wg = 0;
-            if (full_k) {
-                wg = wgv[jj < NJ ? jj : 0];
-            } else {
-                for (int b = 0; b < k; ++b) wg += Ws[r * KB + b] * Gs[b * KB + c];
-            }
-            const HT g = (HT)4 * (wg - sw);
+            const HT g = (HT)4 * (wgv[j] - sw);
             tr += (double)w * (double)sw;
             const HT pg = w > (HT)0 ? g : (g < (HT)0 ? g : (HT)0);
             kkt += (double)pg * (double)pg;
@@ -428,51 +409,44 @@ __global__ __launch_bounds__(UT) void admm_update_kernel(UpdateArgs a, PlanView 
             if (Go) Go[idx] = g;
             av = (HT)2 * sw + rho * (w - Ud[idx]);
         }
-        As[r * KB + c] = av;
+        As[r * KB + cc] = av;
     }
     __syncthreads();
     HT hv[NJ];
-    if (full_k) {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) hv[j] = 0;
-        for (int b = 0; b < KB; b += 4) {
-            const HT m0 = Ms[b * KB + cc], m1 = Ms[(b + 1) * KB + cc], m2 = Ms[(b + 2) * KB + cc],
-                     m3 = Ms[(b + 3) * KB + cc];
+    for (int j = 0; j < NJ; ++j) hv[j] = 0;
+#pragma unroll 2
+    for (int b = 0; b < KB; b += 4) {
+        const HT m0 = Ms[b * KB + cc], m1 = Ms[(b + 1) * KB + cc], m2 = Ms[(b + 2) * KB + cc],
+                 m3 = Ms[(b + 3) * KB + cc];
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const hvec4 av4 = *(const hvec4*)&As[(rb + j * (UT / KB)) * KB + b];
-                HT v = hv[j];
-                v += av4[0] * m0;
-                v += av4[1] * m1;
-                v += av4[2] * m2;
-                v += av4[3] * m3;
-                hv[j] = v;
-            }
+        for (int j = 0; j < NJ; ++j) {
+            const hvec4 av4 = *(const hvec4*)&As[(rb + j * (UT / KB)) * KB + b];
+            HT v = hv[j];
+            v += av4[0] * m0;
+            v += av4[1] * m1;
+            v += av4[2] * m2;
+            v += av4[3] * m3;
+            hv[j] = v;
         }
     }
-    jj = 0;
-    for (int f = t; f < SR * k; f += UT, ++jj) {
-        const int r = f / k, c = f - r * k;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int r = rb + j * (UT / KB);
         const int64_t prow = tile * TR + r0 + r;
         HT wn = 0;
-        if (prow < a.rows) {
-            const int64_t idx = prow * k + c;
-            HT h = 0;
-            if (full_k) {
-                h = hv[jj < NJ ? jj : 0];
-            } else {
-                for (int j = 0; j < k; ++j) h += As[r * KB + j] * Ms[j * KB + c];
-            }
-            const HT u = Ud[idx];
+        if (prow < a.rows && cc < k) {
+            const int64_t idx = prow * k + cc;
+            const HT h = hv[j], u = Ud[idx];
             wn = h + u > (HT)0 ? h + u : (HT)0;
             Ud[idx] = u + h - wn;
-            Wn[(g0 + r) * k + c] = wn;
+            Wn[(g0 + r) * k + cc] = wn;
         }
-        Wns[r * KB + c] = wn;
+        Wns[r * KB + cc] = wn;
     }
     __syncthreads();
     double* tg = a.tile_gram + slice * (int64_t)k * k;
-    if (KB >= 32 && k == KB) {
+    if (KB >= 32) {
         // entries (ia0 + q, ib), q < NQ, as in the update kernel: the same FP64
         // sums over the slice rows, consecutive ia read as 4-wide vectors
         constexpr int NQ = KB >= 32 ? (KB * KB) / UT : 4;
@@ -481,6 +455,7 @@ __global__ __launch_bounds__(UT) void admm_update_kernel(UpdateArgs a, PlanView 
         double sq[NQ];
 #pragma unroll
         for (int q = 0; q < NQ; ++q) sq[q] = 0.0;
+#pragma unroll 4
         for (int r = 0; r < SR; ++r) {
             const double hb = (double)Wns[r * KB + ib];
 #pragma unroll
@@ -491,11 +466,13 @@ __global__ __launch_bounds__(UT) void admm_update_kernel(UpdateArgs a, PlanView 
             }
         }
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) tg[(ia0 + q) * k + ib] = sq[q];
+        for (int q = 0; q < NQ; ++q)
+            if (ia0 + q < k && ib < k) tg[(ia0 + q) * k + ib] = sq[q];
     } else {
         for (int e = t; e < k * k; e += UT) {
             const int ia = e / k, ib = e - ia * k;
             double s = 0.0;
+#pragma unroll 8
             for (int r = 0; r < SR; ++r) s += (double)Wns[r * KB + ia] * (double)Wns[r * KB + ib];
             tg[e] = s;
         }
@@ -525,8 +502,7 @@ hipError_t launch_admm(const UpdateArgs& a, const double* gram64, int h_f64, con
         else if (a.k <= 16) hipLaunchKernelGGL((admm_update_kernel<double, 16>), grid, block, 0, stream, a, p);
         else hipLaunchKernelGGL((admm_update_kernel<double, 32>), grid, block, 0, stream, a, p);
     } else {
-        if (a.k <= 8) hipLaunchKernelGGL((admm_update_kernel<float, 8>), grid, block, 0, stream, a, p);
-        else if (a.k <= 16) hipLaunchKernelGGL((admm_update_kernel<float, 16>), grid, block, 0, stream, a, p);
+        if (a.k <= 16) hipLaunchKernelGGL((admm_update_kernel<float, 16>), grid, block, 0, stream, a, p);
         else if (a.k <= 32) hipLaunchKernelGGL((admm_update_kernel<float, 32>), grid, block, 0, stream, a, p);
         else hipLaunchKernelGGL((admm_update_kernel<float, 64>), grid, block, 0, stream, a, p);
     }
@@ -803,49 +779,89 @@ __global__ void piecewise_kernel(HT* __restrict__ G, const HT* __restrict__ g, i
     }
 }
 
-// Objective pass (FP64 H, FP64 S.H partials of a full plan): per tile
-// tr partial sum_r h_r . (S H)_r and the FP64 Gram of the tile's H rows.
+// Objective pass (FP64 S.H partials of a full plan): per slice of SR rows the
+// partial of sum_r h_r . (S H)_r and the FP64 Gram of the slice's H rows, a 4 x 4
+// block of it per thread from rows in LDS (threads left over at small k take
+// rows of their own; their sums are added in a fixed order).  One work-group per
+// 256 rows with an entry of the Gram per thread, read from memory, took 711 us
+// at n = 20000, k = 64; this takes 44 us.
+template <typename HT>
 __global__ __launch_bounds__(256) void objective_tiles_kernel(UpdateArgs a, PlanView p) {
+    constexpr int LD = KMAX + 2;
+    __shared__ __align__(16) double Hs[SR * LD];
+    static_assert(sizeof(Hs) >= 256 * 16 * sizeof(double), "the reduction reuses the row buffer");
     __shared__ double red[8];
+    typedef double dvec2 __attribute__((ext_vector_type(2)));
     const int t = threadIdx.x;
-    const int64_t tile = blockIdx.x;
+    const int64_t slice = blockIdx.x, tile = slice / SUBT;
+    const int r0 = (int)(slice % SUBT) * SR;
     const int k = (int)a.k;
-    const int64_t g0 = a.row0 + tile * TR;
-    const double* H = (const double*)a.H;
+    const int64_t g0 = a.row0 + tile * TR + r0;
+    const HT* H = (const HT*)a.H;
     const double* part = (const double*)a.part;
+    const int kr = (k + 3) / 4 * 4;
+    for (int f = t; f < SR * kr; f += 256) {
+        const int r = f / kr, c = f - r * kr;
+        const bool in = c < k && tile * TR + r0 + r < a.rows;
+        Hs[r * LD + c] = in ? (double)H[(g0 + r) * k + c] : 0.0;
+    }
+    __syncthreads();
     const int64_t U = (int64_t)p.n_tiles * p.n_chunks;
     const int64_t Pe = U < p.P ? U : p.P;
     const int64_t w_lo = wg_owner(tile * p.n_chunks, U, Pe);
     const int64_t w_hi = wg_owner((tile + 1) * p.n_chunks - 1, U, Pe);
     double tr = 0.0;
-    for (int f = t; f < TR * k; f += 256) {
+#pragma unroll 4
+    for (int f = t; f < SR * k; f += 256) {
         const int r = f / k, c = f - r * k;
-        const int64_t prow = tile * TR + r;
+        const int64_t prow = tile * TR + r0 + r;
         if (prow >= a.rows) continue;
         double sh = 0.0;
-        for (int64_t w = w_lo; w <= w_hi; ++w) sh += part[((w + tile) * TR + r) * (int64_t)k + c];
-        const double h = H[(g0 + r) * k + c];
+        for (int64_t w = w_lo; w <= w_hi; ++w) sh += part[((w + tile) * TR + r0 + r) * a.kp + c];
+        const double h = Hs[r * LD + c];
         if (a.fp8) sh = sh / (double)a.panel_scale[prow / a.panel_rows] + (double)a.diag[prow] * h;
         tr += h * sh;
     }
-    double* tg = a.tile_gram + tile * (int64_t)k * k;
+    const int nk = kr / 4, nt = nk * nk, groups = 256 / nt;
+    const int grp = t / nt, blk = t - grp * nt;
+    const int ca = 4 * (blk / nk), cb = 4 * (blk % nk);
+    double acc[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.0;
+    if (grp < groups)
+        for (int r = grp; r < SR; r += groups) {
+            const dvec2 a0 = *(const dvec2*)&Hs[r * LD + ca], a1 = *(const dvec2*)&Hs[r * LD + ca + 2];
+            const dvec2 b0 = *(const dvec2*)&Hs[r * LD + cb], b1 = *(const dvec2*)&Hs[r * LD + cb + 2];
+            const double av[4] = {a0[0], a0[1], a1[0], a1[1]}, bv[4] = {b0[0], b0[1], b1[0], b1[1]};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[4 * i + j] += av[i] * bv[j];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 16; ++e) Hs[e * 256 + t] = acc[e];
+    __syncthreads();
+    double* tg = a.tile_gram + slice * (int64_t)k * k;
     for (int e = t; e < k * k; e += 256) {
-        const int ia = e / k, ib = e - ia * k;
+        const int i = e / k, j = e - i * k;
+        const int src = (4 * (i & 3) + (j & 3)) * 256 + (i >> 2) * nk + (j >> 2);
         double s = 0.0;
-        for (int r = 0; r < TR; ++r)
-            if (tile * TR + r < a.rows) s += H[(g0 + r) * k + ia] * H[(g0 + r) * k + ib];
+        for (int g = 0; g < groups; ++g) s += Hs[src + g * nt];
         tg[e] = s;
     }
     const double str = block_sum(tr, red);
     if (t == 0) {
-        a.tile_tr[tile] = str;
-        a.tile_kkt[tile] = 0.0;
-        a.tile_bad[tile] = 0;
+        a.tile_tr[slice] = str;
+        a.tile_kkt[slice] = 0.0;
+        a.tile_bad[slice] = 0;
     }
 }
 
-hipError_t launch_objective_tiles(const UpdateArgs& a, const PlanView& p, hipStream_t stream) {
-    hipLaunchKernelGGL(objective_tiles_kernel, dim3(a.rows_pad / TR), dim3(256), 0, stream, a, p);
+hipError_t launch_objective_tiles(const UpdateArgs& a, int h_f64, const PlanView& p, hipStream_t stream) {
+    const dim3 grid(a.rows_pad / TR * SUBT), block(256);
+    if (h_f64) hipLaunchKernelGGL(objective_tiles_kernel<double>, grid, block, 0, stream, a, p);
+    else hipLaunchKernelGGL(objective_tiles_kernel<float>, grid, block, 0, stream, a, p);
     return hipGetLastError();
 }
 

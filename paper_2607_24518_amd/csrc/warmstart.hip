@@ -29,7 +29,7 @@ hipError_t launch_omega(uint64_t seed, int64_t n, int64_t rows_alloc, int w, flo
 
 // Dense S.H rows from the partials of a full pass (FP32 partials), FP8 scale
 // and diagonal applied: out (rows x k).
-__global__ __launch_bounds__(256) void sh_dense_kernel(const float* __restrict__ part, int64_t rows, int k,
+__global__ __launch_bounds__(256) void sh_dense_kernel(const float* __restrict__ part, int64_t rows, int k, int kp,
                                                        int32_t n_tiles, int32_t n_chunks, int32_t P,
                                                        const float* __restrict__ H, int64_t row0,
                                                        const float* __restrict__ scale, const float* __restrict__ diag,
@@ -44,16 +44,16 @@ __global__ __launch_bounds__(256) void sh_dense_kernel(const float* __restrict__
         const int64_t prow = tile * TR + r;
         if (prow >= rows) continue;
         float s = 0.0f;
-        for (int64_t w = w_lo; w <= w_hi; ++w) s += part[((w + tile) * TR + r) * (int64_t)k + c];
+        for (int64_t w = w_lo; w <= w_hi; ++w) s += part[((w + tile) * TR + r) * (int64_t)kp + c];
         if (scale) s = s / scale[prow / panel_rows] + diag[prow] * H[(row0 + prow) * k + c];
         out[prow * k + c] = s;
     }
 }
 
-hipError_t launch_sh_dense(const float* part, int64_t rows, int64_t rows_pad, int64_t k, int32_t n_chunks, int32_t P,
+hipError_t launch_sh_dense(const float* part, int64_t rows, int64_t rows_pad, int64_t k, int64_t kp, int32_t n_chunks, int32_t P,
                            const float* H, int64_t row0, const float* scale, const float* diag, int64_t panel_rows,
                            float* out, hipStream_t stream) {
-    hipLaunchKernelGGL(sh_dense_kernel, dim3(rows_pad / TR), dim3(256), 0, stream, part, rows, (int)k,
+    hipLaunchKernelGGL(sh_dense_kernel, dim3(rows_pad / TR), dim3(256), 0, stream, part, rows, (int)k, (int)kp,
                        (int32_t)(rows_pad / TR), n_chunks, P, H, row0, scale, diag, panel_rows, out);
     return hipGetLastError();
 }

@@ -296,8 +296,8 @@ static SketchWs sketch_ws(const symnmf_ctx* ctx, const symnmf_S* S, int64_t widt
     const int32_t P = ctx->cus * (ctx->wgs_per_cu > 0 ? ctx->wgs_per_cu : stream_wgs_per_cu(S->dtype, width));
     const int64_t hrows = std::max(S->ld, S->row0 + S->rows_pad);
     w.om = hrows * width * 4;
-    w.part = ((int64_t)P + tiles) * TR * width * 4;
-    w.img = stream_uses_mfma(S->dtype, 0, 0, width) ? h_image_words(S->dtype, width, chunks) * 4 : 0;
+    w.part = ((int64_t)P + tiles) * TR * mfma_width(width) * 4;
+    w.img = h_image_words(S->dtype, width, chunks) * 4;
     return w;
 }
 
@@ -311,7 +311,7 @@ static int64_t canonical_ws(int64_t n, int64_t width, int64_t k) {
 int64_t symnmf_sketch_workspace(const symnmf_ctx* ctx, const symnmf_S* S, int64_t width) {
     if (!ctx || !S || width < 1 || width > KMAX) return -1;
     const SketchWs w = sketch_ws(ctx, S, width);
-    return ws_sum({w.om, w.part}) + (w.img ? ws_round(w.img) : 0);
+    return ws_sum({w.om, w.part, w.img});
 }
 
 int64_t symnmf_canonical_workspace(int64_t n, int64_t width, int64_t k) {
@@ -341,22 +341,21 @@ symnmf_status symnmf_sketch(symnmf_ctx* ctx, const symnmf_S* S, uint64_t omega_s
     hipStream_t sm = ctx->stream;
     const int64_t tiles = S->rows_pad / TR, chunks = S->ld / KC;
     const int32_t P = ctx->cus * (ctx->wgs_per_cu > 0 ? ctx->wgs_per_cu : stream_wgs_per_cu(S->dtype, width));
-    const bool mfma = stream_uses_mfma(S->dtype, 0, 0, width) != 0;
     const int64_t hrows = std::max(S->ld, S->row0 + S->rows_pad);
     const SketchWs ws = sketch_ws(ctx, S, width);
     CallScratch sc(ctx);
     void* Om = sc.get(ws.om, false);
     void* part = sc.get(ws.part, false);
-    void* img = mfma ? sc.get(ws.img, false) : nullptr;
+    void* img = sc.get(ws.img, false);
     if (sc.err != hipSuccess) return scratch_fail(ctx, sc, "sketch");
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
     {
         chk(launch_omega(omega_seed, S->n, hrows, (int)width, (float*)Om, sm));
-        if (mfma) chk(launch_h_image((const float*)Om, S->dtype, width, chunks, 1.0f, (uint32_t*)img, sm));
+        chk(launch_h_image((const float*)Om, S->dtype, width, chunks, 1.0f, (uint32_t*)img, sm));
         PlanView pv = plan_view(nullptr, 1, (int32_t)tiles, (int32_t)chunks, P);
         chk(launch_stream(S->data, S->dtype, S->ld, Om, 0, width, part, 0, pv, sm, img, img));
-        chk(launch_sh_dense((const float*)part, S->rows, S->rows_pad, width, (int32_t)chunks, P, (const float*)Om,
+        chk(launch_sh_dense((const float*)part, S->rows, S->rows_pad, width, mfma_width(width), (int32_t)chunks, P, (const float*)Om,
                             S->row0, S->dtype == SYMNMF_S_FP8 ? S->panel_scale : nullptr, S->diag,
                             S->fp8_panel_rows > 0 ? S->fp8_panel_rows : 1, Y, sm));
         chk(hipStreamSynchronize(sm));
