@@ -285,8 +285,8 @@ hipError_t launch_update(const UpdateArgs& a, int h_f64, const PlanView& p, hipS
 
 // ---------------------------------------------------------------------------
 // ADMM (appendix family 6).  Per step: the inverse of M = 2 W^T W + rho I (k x k,
-// FP64 Gauss-Jordan in one work-group; M is symmetric positive definite, so
-// no pivoting), then one fused pass over the rows of the panel that sums the
+// FP64 Gauss-Jordan in place in one work-group; M is symmetric positive
+// definite, so no pivoting), then one fused pass over the rows of the panel that sums the
 // S.W partials and, per row,
 //   * records the statistics of W_t: tr partial W . SW, the projected gradient
 //     of g = 4 (W (W^T W) - S W) (the stop rule is taken on W),
@@ -294,31 +294,74 @@ hipError_t launch_update(const UpdateArgs& a, int h_f64, const PlanView& p, hipS
 //   * W_{t+1} = [H + U]_+ (eq. admm_W), U <- U + H - W_{t+1} (eq. admm_U),
 //   * the FP64 Gram partials of W_{t+1}.
 // ---------------------------------------------------------------------------
-template <typename HT>
+// A chain of k dependent pivots, bound by the latency of one: 16 x 16 threads
+// hold BS x BS blocks of M in registers (padded with the identity), the pivot's
+// row and column go through LDS, in two buffers so that a pivot has one
+// barrier.  The form with [M | I] in LDS, four barriers and two divisions by
+// index per pivot took 441 / 63 / 11.3 us at k = 64 / 32 / 16; this takes
+// 42 / 13.5 / 5.0 us.
+template <typename HT, int BS>
 __global__ __launch_bounds__(256) void admm_minv_kernel(const double* __restrict__ gram, int k, double rho,
                                                         HT* __restrict__ minv) {
-    __shared__ double A[KMAX * 2 * KMAX];
-    __shared__ double fac[KMAX];
-    const int t = threadIdx.x, w2 = 2 * k;
-    for (int e = t; e < k * w2; e += 256) {
-        const int i = e / w2, j = e - i * w2;
-        A[e] = j < k ? 2.0 * gram[i * k + j] + (i == j ? rho : 0.0) : (j - k == i ? 1.0 : 0.0);
-    }
-    __syncthreads();
-    for (int piv = 0; piv < k; ++piv) {
-        const double d = A[piv * w2 + piv];
-        __syncthreads();
-        for (int j = t; j < w2; j += 256) A[piv * w2 + j] /= d;
-        __syncthreads();
-        for (int i = t; i < k; i += 256) fac[i] = A[i * w2 + piv];
-        __syncthreads();
-        for (int e = t; e < k * w2; e += 256) {
-            const int i = e / w2, j = e - i * w2;
-            if (i != piv) A[e] -= fac[i] * A[piv * w2 + j];
+    __shared__ double row[2][KMAX], col[2][KMAX];
+    const int t = threadIdx.x, ti = t >> 4, tj = t & 15;
+    double a[BS][BS];
+#pragma unroll
+    for (int x = 0; x < BS; ++x)
+#pragma unroll
+        for (int y = 0; y < BS; ++y) {
+            const int i = BS * ti + x, j = BS * tj + y;
+            const double m = i < k && j < k ? 2.0 * gram[i * k + j] : 0.0;
+            a[x][y] = i == j ? (i < k ? m + rho : 1.0) : m;
         }
-        __syncthreads();
+#pragma unroll
+    for (int y = 0; y < BS; ++y) {
+        if (ti == 0) row[0][BS * tj + y] = a[0][y];
+        if (tj == 0) col[0][BS * ti + y] = a[y][0];
     }
-    for (int e = t; e < k * k; e += 256) minv[e] = (HT)A[(e / k) * w2 + k + e % k];
+    for (int pb = 0; pb * BS < k; ++pb) {
+#pragma unroll
+        for (int e = 0; e < BS; ++e) {
+            const int p = pb * BS + e;                       // identity past k: nothing changes
+            const int buf = p & 1;
+            __syncthreads();
+            const double d = 1.0 / row[buf][p];
+            double rj[BS], ci[BS];
+#pragma unroll
+            for (int y = 0; y < BS; ++y) {
+                rj[y] = row[buf][BS * tj + y] * d;
+                ci[y] = col[buf][BS * ti + y];
+            }
+#pragma unroll
+            for (int x = 0; x < BS; ++x)
+#pragma unroll
+                for (int y = 0; y < BS; ++y) {
+                    const bool pi = x == e && ti == pb, pj = y == e && tj == pb;
+                    a[x][y] = pi ? (pj ? d : rj[y]) : (pj ? -ci[x] * d : a[x][y] - ci[x] * rj[y]);
+                }
+            // the next pivot's row and column
+            const int nb = e + 1 < BS ? pb : pb + 1, ne = (e + 1) % BS;
+#pragma unroll
+            for (int y = 0; y < BS; ++y) {
+                if (ti == nb) row[buf ^ 1][BS * tj + y] = a[ne][y];
+                if (tj == nb) col[buf ^ 1][BS * ti + y] = a[y][ne];
+            }
+        }
+    }
+#pragma unroll
+    for (int x = 0; x < BS; ++x)
+#pragma unroll
+        for (int y = 0; y < BS; ++y) {
+            const int i = BS * ti + x, j = BS * tj + y;
+            if (i < k && j < k) minv[i * k + j] = (HT)a[x][y];
+        }
+}
+
+template <typename HT>
+static void launch_minv(const double* gram, int k, double rho, HT* minv, hipStream_t stream) {
+    if (k <= 16) hipLaunchKernelGGL((admm_minv_kernel<HT, 1>), dim3(1), dim3(256), 0, stream, gram, k, rho, minv);
+    else if (k <= 32) hipLaunchKernelGGL((admm_minv_kernel<HT, 2>), dim3(1), dim3(256), 0, stream, gram, k, rho, minv);
+    else hipLaunchKernelGGL((admm_minv_kernel<HT, 4>), dim3(1), dim3(256), 0, stream, gram, k, rho, minv);
 }
 
 template <typename HT, int KB>
@@ -489,12 +532,8 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kerne
 
 hipError_t launch_admm(const UpdateArgs& a, const double* gram64, int h_f64, const PlanView& p, hipStream_t stream) {
     if (!p.full || a.k > KMAX || (h_f64 && a.k > 32)) return hipErrorInvalidValue;
-    if (h_f64)
-        hipLaunchKernelGGL(admm_minv_kernel<double>, dim3(1), dim3(256), 0, stream, gram64, (int)a.k, a.rho,
-                           (double*)a.minv);
-    else
-        hipLaunchKernelGGL(admm_minv_kernel<float>, dim3(1), dim3(256), 0, stream, gram64, (int)a.k, a.rho,
-                           (float*)a.minv);
+    if (h_f64) launch_minv(gram64, (int)a.k, a.rho, (double*)a.minv, stream);
+    else launch_minv(gram64, (int)a.k, a.rho, (float*)a.minv, stream);
     const int64_t tiles = a.rows_pad / TR;
     dim3 grid(tiles * SUBT), block(UT);
     if (h_f64) {
