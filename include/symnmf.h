@@ -427,7 +427,8 @@ symnmf_status symnmf_probe_read(symnmf_ctx* ctx, const void* src, void* sink, in
 /* HIP-event timing of the kernels a step launches, on the context's stream.
  * Reading (ms_out / launches_out non-NULL, 5 entries each: 0 = S.H stream,
  * 1 = fused update, 2 = finalize, 3 = plan of a sub-sampled step, 4 = H
- * chunk images for the MFMA stream)
+ * chunk images for the MFMA stream, where the update does not write them: a
+ * state's first step, and panels whose row0 is no multiple of 64)
  * synchronises and returns the summed milliseconds and launch counts since the
  * last call; every call then clears the record and sets profiling on or off
  * (enable).  Off by default; timing adds two events per kernel. */

@@ -269,9 +269,10 @@ hipError_t launch_stream(const void* S, int32_t stype, int64_t ld, const void* H
                          const void* img1 = nullptr, const void* img2 = nullptr);
 // 32-bit words of the H images of all n_chunks chunks for this storage type and rank
 int64_t h_image_words(int32_t stype, int64_t k, int64_t n_chunks);
-// Write the chunk images of wt * H (H: n_chunks * 256 rows x k, FP32), zero past column k.
-hipError_t launch_h_image(const float* H, int32_t stype, int64_t k, int64_t n_chunks, float wt, uint32_t* img,
-                          hipStream_t stream);
+// Write the images of chunks [chunk0, chunk0 + n_chunks) of wt * H (FP32, 256 rows x k per chunk;
+// img: those of all chunks), zero past column k.
+hipError_t launch_h_image(const float* H, int32_t stype, int64_t k, int64_t chunk0, int64_t n_chunks, float wt,
+                          uint32_t* img, hipStream_t stream);
 hipError_t launch_copy_probe(const void* src, void* dst, int64_t bytes, hipStream_t stream);
 // plain read of bytes (multiple of 16); sink: sink_words words (>= 4), one per wave
 hipError_t launch_read_probe(const void* src, int64_t bytes, uint32_t* sink, int64_t sink_words,
@@ -327,6 +328,10 @@ struct UpdateArgs {
     double* tile_tr;      // [tiles] sum H_t * SH_t
     double* tile_kkt;     // [tiles] sum proj(g)^2
     int32_t* tile_bad;    // [tiles] non-finite gradient count
+    void* img1;           // chunk images of H_{t+1} to bring up to date (null: none), of 2 H_{t+1}
+    void* img2;           // in img2 (may be null); row0 is then a multiple of 64
+    int32_t img_kind;     // 0 FP32 S, 1 BF16, 2 FP8
+    int64_t n_chunks;     // column chunks of S
     double rho;           // ADMM consensus penalty
     void* minv;           // ADMM: (2 W^T W + rho I)^-1, k x k (state precision)
     double beta1, beta2, beta3;   // Adam / NAdam / Adan decays

@@ -581,7 +581,7 @@ hipError_t s_times(const KCall& kc, const void* X, void* Y) {
         const char* Xs = (const char*)X + s * kc.rows_pad * kc.w * kc.esz;
         char* Ys = (char*)Y + s * kc.rows_pad * kc.w * kc.esz;
         hipError_t e = hipSuccess;
-        if (kc.mfma) e = launch_h_image((const float*)Xs, S->dtype, kc.w, kc.chunks, 1.0f, (uint32_t*)kc.img, kc.sm);
+        if (kc.mfma) e = launch_h_image((const float*)Xs, S->dtype, kc.w, 0, kc.chunks, 1.0f, (uint32_t*)kc.img, kc.sm);
         if (e == hipSuccess)
             e = launch_stream(S->data, S->dtype, S->ld, Xs, kc.f64, kc.w, kc.part, kc.f64, kc.pv, kc.sm, kc.img, kc.img);
         if (e != hipSuccess) return e;

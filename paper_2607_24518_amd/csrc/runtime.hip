@@ -136,7 +136,9 @@ struct symnmf_state {
     double* ring = nullptr;
     int32_t *plan = nullptr, *tiles_I = nullptr, *tiles_J = nullptr, *counts = nullptr;
     void* sel = nullptr;
-    void* img[2] = {nullptr, nullptr};   // chunk images of H and 2H (MFMA stream)
+    void* img[2] = {nullptr, nullptr};   // chunk images of the current iterate and twice it (MFMA stream)
+    bool img_ready = false;              // every chunk's image is that of the current iterate, or of the one
+                                         // before in the panel's chunks where the update does not write them
     int64_t img_bytes = 0, part_bytes = 0;   // capacities of img[*] and part
     bool mfma = false;
     bool tall = false;               // full steps run the 8-wave stream kernel
@@ -655,11 +657,19 @@ static symnmf_status do_step(symnmf_ctx* ctx, const symnmf_S* S, symnmf_state* s
     }
     const void* Hc = st->H[st->cur];
     void* Hn = st->H[1 - st->cur];
-    if (st->mfma) {
+    // The update kernels write the images of the rows they form, 64 rows at a
+    // time; a panel that starts off a multiple of 64 has its chunks' images
+    // written here instead.  The images of the rows outside a panel stay.
+    const bool img_fused = st->mfma && st->row0 % SR == 0;
+    if (st->mfma && !(st->img_ready && img_fused)) {
         ProfScope pi(ctx, PK_IMAGE);
-        HIP_OK(ctx, launch_h_image((const float*)Hc, S->dtype, st->k, st->chunks, 1.0f, (uint32_t*)st->img[0], sm));
-        if (kind == 2)
-            HIP_OK(ctx, launch_h_image((const float*)Hc, S->dtype, st->k, st->chunks, 2.0f, (uint32_t*)st->img[1], sm));
+        const int64_t c0 = st->img_ready ? st->row0 / KC : 0;
+        const int64_t c1 = st->img_ready ? (st->row0 + st->rows + KC - 1) / KC : st->chunks;
+        for (int i = 0; i < 2; ++i)
+            if (st->img[i])
+                HIP_OK(ctx, launch_h_image((const float*)Hc, S->dtype, st->k, c0, c1 - c0, i ? 2.0f : 1.0f,
+                                           (uint32_t*)st->img[i], sm));
+        st->img_ready = true;
     }
     {
         ProfScope ps(ctx, PK_STREAM);
@@ -714,6 +724,12 @@ static symnmf_status do_step(symnmf_ctx* ctx, const symnmf_S* S, symnmf_state* s
     a.tile_tr = st->tile_tr;
     a.tile_kkt = st->tile_kkt;
     a.tile_bad = st->tile_bad;
+    if (img_fused) {
+        a.img1 = st->img[0];
+        a.img2 = st->img[1];
+        a.img_kind = S->dtype == SYMNMF_S_FP32 ? 0 : (S->dtype == SYMNMF_S_BF16 ? 1 : 2);
+        a.n_chunks = st->chunks;
+    }
     {
         ProfScope ps(ctx, PK_UPDATE);
         if (p.method == SYMNMF_ADMM) {
@@ -873,7 +889,7 @@ symnmf_status objective_terms(symnmf_ctx* ctx, const symnmf_S* S, const void* H,
     chk(launch_copy_h(H, h_is_f64, Hp, w.mfma ? 0 : 1, S->n * k, sm));
     if (w.mfma) {
         // MFMA products, FP32 within each 256-column chunk, FP64 across chunks
-        chk(launch_h_image((const float*)Hp, S->dtype, k, chunks, 1.0f, (uint32_t*)img, sm));
+        chk(launch_h_image((const float*)Hp, S->dtype, k, 0, chunks, 1.0f, (uint32_t*)img, sm));
         chk(launch_stream_acc64(S->data, S->dtype, k, img, (double*)part, pv, sm));
     } else {
         chk(launch_stream(S->data, S->dtype, S->ld, Hp, 1, k, part, 1, pv, sm));
@@ -1168,6 +1184,7 @@ static symnmf_status rebind_state(symnmf_state* st, const symnmf_S* S) {
         st->img_bytes = img_bytes;
     }
     st->S = *S;
+    st->img_ready = false;
     st->mfma = mfma;
     st->P = P;
     st->tall = tall;

@@ -20,7 +20,7 @@
 // The reduction index of one MFMA may be any permutation of the columns as
 // long as A and B agree; each kernel uses the one in which a lane's 16 bytes
 // of S are consecutive columns.
-#include "common.h"
+#include "image.h"
 
 namespace symnmf {
 
@@ -220,59 +220,22 @@ __global__ __launch_bounds__(256, 2) void stream_f64_mfma(const double* __restri
     }
 }
 
-// ---------------------------------------------------------------------------
-// H images.  KIND 0 (FP32 S): floats in the order Hs[nt][s][g][c][m];
-// KIND 1 (BF16 S): three bf16 planes, each Hb[nt][s][g][c][i];
-// KIND 2 (FP8 S): three bf16 planes, each Hb[nt][s][h][g][c][i].
-// (nt = H column / 16, c = H column % 16; the other indices split the chunk
-// column kk as the matching kernel's sub-step reads it.)
-// ---------------------------------------------------------------------------
-__device__ inline void split3_bf16(float x, uint16_t& hi, uint16_t& mid, uint16_t& lo) {
-    hi = f32_to_bf16_bits(x);
-    const float r1 = x - bf16_bits_to_f32(hi);
-    mid = f32_to_bf16_bits(r1);
-    const float r2 = r1 - bf16_bits_to_f32(mid);
-    lo = f32_to_bf16_bits(r2);
-}
-
-// First chunk row kk0 and H column of image vector v (16 bytes: 4 floats for
-// KIND 0, 8 bf16 of one plane otherwise); the vector holds rows kk0, kk0 + 1, ...
-// of that column, in the order given above.
-template <int KIND>
-__device__ inline void image_vector_origin(int v, int& kk0, int& col) {
-    const int c = v & 15, g = (v >> 4) & 3;
-    if (KIND == 0) {
-        kk0 = 16 * ((v >> 6) & 15) + 4 * g;
-        col = 16 * (v >> 10) + c;
-    } else if (KIND == 1) {
-        kk0 = 32 * ((v >> 6) & 7) + 8 * g;
-        col = 16 * (v >> 9) + c;
-    } else {
-        kk0 = 64 * ((v >> 7) & 3) + 16 * g + 8 * ((v >> 6) & 1);
-        col = 16 * (v >> 9) + c;
-    }
-}
-
-template <int KIND, int K>
-struct ImageShape {
-    static constexpr int BUFW = KIND == 0 ? KC * K : 3 * KC * K / 2;   // 32-bit words per chunk image
-    static constexpr int NV = BUFW / 4;                                 // 16-byte vectors per image
-    static constexpr int PLANE = KC * K;                                // bf16 elements per plane
-};
-
 // One work-group per (chunk, block of CB columns of H): the block's 256 x CB
 // values (scaled by wt) are staged in LDS with 16-byte loads, then every
 // thread assembles whole 16-byte image vectors (all three bf16 planes at once
 // for KIND 1, 2) and writes them in order.  Each 16-column block is a
 // contiguous run of every plane of the image.  At k = 64 a work-group takes
 // 16 columns (17 KB of LDS, eight work-groups per CU instead of two); below,
-// the whole chunk.
+// the whole chunk.  The update kernels keep the images of a state's iterate
+// current themselves (write_image_slice); this kernel writes those of a new
+// state, of a factor handed in, and the chunks of a row panel whose first row
+// is no multiple of 64.
 template <int KIND, int K>
 constexpr int image_cols_per_wg() { return K == 64 ? 16 : K; }
 
 // H has k <= K columns; the image's other columns are zero.
 template <int KIND, int K>
-__global__ __launch_bounds__(256) void h_image_kernel(const float* __restrict__ H, int k, float wt,
+__global__ __launch_bounds__(256) void h_image_kernel(const float* __restrict__ H, int k, int64_t chunk0, float wt,
                                                       u32x4* __restrict__ img) {
     using IS = ImageShape<KIND, K>;
     constexpr int CB = image_cols_per_wg<KIND, K>();
@@ -281,7 +244,7 @@ __global__ __launch_bounds__(256) void h_image_kernel(const float* __restrict__ 
     constexpr int VP = KC * K / EPV;                      // vectors per plane
     constexpr int VB = VP / (K / CB);                     // ... per plane and column block
     __shared__ float Hs[KC * LDH];
-    const int64_t chunk = blockIdx.x;
+    const int64_t chunk = chunk0 + blockIdx.x;
     const int blk = blockIdx.y;
     if (k == K) {
         const float* src = H + chunk * KC * K + CB * blk;
@@ -336,13 +299,13 @@ int64_t h_image_words(int32_t stype, int64_t k, int64_t n_chunks) {
     return per * n_chunks;
 }
 
-hipError_t launch_h_image(const float* H, int32_t stype, int64_t k, int64_t n_chunks, float wt, uint32_t* img,
-                          hipStream_t stream) {
-    if (k < 1 || k > KMAX) return hipErrorInvalidValue;
+hipError_t launch_h_image(const float* H, int32_t stype, int64_t k, int64_t chunk0, int64_t n_chunks, float wt,
+                          uint32_t* img, hipStream_t stream) {
+    if (k < 1 || k > KMAX || n_chunks < 1) return hipErrorInvalidValue;
     const int64_t kw = mfma_width(k);
     dim3 grid(n_chunks, kw == 64 ? 4 : 1), block(256);
 #define IMG(KIND, KK) \
-    hipLaunchKernelGGL((h_image_kernel<KIND, KK>), grid, block, 0, stream, H, (int)k, wt, (u32x4*)img)
+    hipLaunchKernelGGL((h_image_kernel<KIND, KK>), grid, block, 0, stream, H, (int)k, chunk0, wt, (u32x4*)img)
     if (stype == SYMNMF_S_FP32) {
         if (kw == 16) IMG(0, 16); else if (kw == 32) IMG(0, 32); else IMG(0, 64);
     } else if (stype == SYMNMF_S_BF16) {

@@ -12,7 +12,7 @@
 //   * writes H_{t+1} and accumulates in FP64 the per-tile partials of
 //     tr(H_t^T S H_t), ||grad_proj||^2 (eq. proj_grad) and Gram(H_{t+1}).
 // The finalize kernel reduces the tile partials in a fixed order.
-#include "common.h"
+#include "image.h"
 
 namespace symnmf {
 
@@ -224,6 +224,9 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
 #pragma unroll
     for (int j = 0; j < NJ; ++j) element(rb + j * (UT / KB), shv[j], hgv[j]);
     __syncthreads();
+    if constexpr (sizeof(HT) == 4)
+        if (a.img1 && g0 < a.n_chunks * KC)
+            write_image_slice<KB>(a.img_kind, Hns, Hs, (int)min(a.rows - tile * TR - r0, (int64_t)SR), g0, a.img1, a.img2);
     double* tg = a.tile_gram + slice * (int64_t)k * k;
     if (KB >= 32) {
         // each thread: entries (ia0 + q, ib), q < NQ (a multiple of 4, ia0 too),
@@ -488,6 +491,9 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kerne
         Wns[r * KB + cc] = wn;
     }
     __syncthreads();
+    if constexpr (sizeof(HT) == 4)
+        if (a.img1 && g0 < a.n_chunks * KC)
+            write_image_slice<KB>(a.img_kind, Wns, Ws, (int)min(a.rows - tile * TR - r0, (int64_t)SR), g0, a.img1, a.img2);
     double* tg = a.tile_gram + slice * (int64_t)k * k;
     if (KB >= 32) {
         // entries (ia0 + q, ib), q < NQ, as in the update kernel: the same FP64

@@ -352,7 +352,7 @@ symnmf_status symnmf_sketch(symnmf_ctx* ctx, const symnmf_S* S, uint64_t omega_s
     auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
     {
         chk(launch_omega(omega_seed, S->n, hrows, (int)width, (float*)Om, sm));
-        chk(launch_h_image((const float*)Om, S->dtype, width, chunks, 1.0f, (uint32_t*)img, sm));
+        chk(launch_h_image((const float*)Om, S->dtype, width, 0, chunks, 1.0f, (uint32_t*)img, sm));
         PlanView pv = plan_view(nullptr, 1, (int32_t)tiles, (int32_t)chunks, P);
         chk(launch_stream(S->data, S->dtype, S->ld, Om, 0, width, part, 0, pv, sm, img, img));
         chk(launch_sh_dense((const float*)part, S->rows, S->rows_pad, width, mfma_width(width), (int32_t)chunks, P, (const float*)Om,
