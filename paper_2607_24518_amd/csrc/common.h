@@ -298,8 +298,7 @@ struct PlanRequest {
     uint64_t seed;
     int64_t t;
 };
-hipError_t launch_plan(const PlanRequest& r, int32_t* plan_base, int32_t* tiles_I, int32_t* tiles_J,
-                       int32_t* counts, hipStream_t stream);
+hipError_t launch_plan(const PlanRequest& r, int32_t* plan_base, hipStream_t stream);
 
 struct UpdateArgs {
     int64_t rows, rows_pad, n, k;           // panel rows, padded rows, instruments, rank
@@ -362,9 +361,9 @@ hipError_t launch_finalize(int64_t tiles, int64_t k, const double* tile_gram, co
                            double* stats, hipStream_t stream);
 
 // Effective Gram matrices of a block step: out[0] = Gram_J, out[1] = Gram_I,
-// out[2] = Gram_I + Gram_J from per-tile Gram partials of H_t.
-hipError_t launch_gram_select(int64_t k, const double* tile_gram, const int32_t* tiles_I,
-                              const int32_t* tiles_J, const int32_t* counts, void* gram_eff, int h_f64,
+// out[2] = Gram_I + Gram_J from the per-slice Gram partials of H_t and the
+// classes of the plan's tiles.
+hipError_t launch_gram_select(int64_t k, const double* tile_gram, const PlanView& plan, void* gram_eff, int h_f64,
                               hipStream_t stream);
 
 hipError_t launch_init_H(float* H, int64_t n, int64_t k, uint64_t seed, float scale, hipStream_t stream);

@@ -134,7 +134,7 @@ struct symnmf_state {
     void* gram_eff = nullptr;
     double* gram_fixed = nullptr;
     double* ring = nullptr;
-    int32_t *plan = nullptr, *tiles_I = nullptr, *tiles_J = nullptr, *counts = nullptr;
+    int32_t* plan = nullptr;
     void* sel = nullptr;
     void* img[2] = {nullptr, nullptr};   // chunk images of the current iterate and twice it (MFMA stream)
     bool img_ready = false;              // every chunk's image is that of the current iterate, or of the one
@@ -589,12 +589,7 @@ symnmf_status symnmf_state_create(symnmf_ctx* ctx, const symnmf_S* S, int64_t k,
     ALLOC(st->ring, HCAP * 4 * 8);
     ALLOC(st->scal, 16 * 8);
     ALLOC(st->sel, select_tmp_bytes());
-    if (svrg) {
-        ALLOC(st->plan, plan_words(st->tiles, st->chunks) * 4);
-        ALLOC(st->tiles_I, st->tiles * 4);
-        ALLOC(st->tiles_J, st->tiles * 4);
-        ALLOC(st->counts, 16);
-    }
+    if (svrg) ALLOC(st->plan, plan_words(st->tiles, st->chunks) * 4);
     const bool panel = st->rows < st->n;
     if (panel) ALLOC(st->gram_fixed, k * k * 8);
 #undef ALLOC
@@ -650,10 +645,9 @@ static symnmf_status do_step(symnmf_ctx* ctx, const symnmf_S* S, symnmf_state* s
         r.seed = p.seed;
         r.t = t;
         ProfScope ps(ctx, PK_PLAN);
-        HIP_OK(ctx, launch_plan(r, st->plan, st->tiles_I, st->tiles_J, st->counts, sm));
+        HIP_OK(ctx, launch_plan(r, st->plan, sm));
         if (kind == 2)
-            HIP_OK(ctx, launch_gram_select(st->k, st->tile_gram, st->tiles_I, st->tiles_J, st->counts, st->gram_eff,
-                                           st->h_f64, sm));
+            HIP_OK(ctx, launch_gram_select(st->k, st->tile_gram, pv, st->gram_eff, st->h_f64, sm));
     }
     const void* Hc = st->H[st->cur];
     void* Hn = st->H[1 - st->cur];
