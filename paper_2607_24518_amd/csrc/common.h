@@ -322,7 +322,7 @@ struct UpdateArgs {
                           // weight of column i's chunk for the row's class (0, 0, 2)
     const float* panel_scale;
     const float* diag;    // FP8: S_ii of every panel row
-    int64_t panel_rows;
+    int64_t panel_rows;   // below 2^31 (clamped)
     double* tile_gram;    // [tiles][k][k] Gram of H_{t+1} rows
     double* tile_tr;      // [tiles] sum H_t * SH_t
     double* tile_kkt;     // [tiles] sum proj(g)^2

@@ -713,7 +713,7 @@ static symnmf_status do_step(symnmf_ctx* ctx, const symnmf_S* S, symnmf_state* s
     a.block_step = kind == 2 ? 1 : 0;
     a.panel_scale = S->panel_scale;
     a.diag = S->diag;
-    a.panel_rows = S->fp8_panel_rows > 0 ? S->fp8_panel_rows : 1;
+    a.panel_rows = std::clamp<int64_t>(S->fp8_panel_rows, 1, INT32_MAX);   // no panel is taller than S
     a.tile_gram = st->tile_gram;
     a.tile_tr = st->tile_tr;
     a.tile_kkt = st->tile_kkt;
@@ -901,7 +901,7 @@ symnmf_status objective_terms(symnmf_ctx* ctx, const symnmf_S* S, const void* H,
     a.fp8 = S->dtype == SYMNMF_S_FP8;
     a.panel_scale = S->panel_scale;
     a.diag = S->diag;
-    a.panel_rows = S->fp8_panel_rows > 0 ? S->fp8_panel_rows : 1;
+    a.panel_rows = std::clamp<int64_t>(S->fp8_panel_rows, 1, INT32_MAX);   // no panel is taller than S
     a.tile_gram = (double*)tg;
     a.tile_tr = (double*)ttr;
     a.tile_kkt = (double*)tk;

@@ -26,6 +26,29 @@ __device__ inline double softplus_f(double x) { return fmax(x, 0.0) + log1p(exp(
 __device__ inline float sigmoid_f(float x) { return 0.5f * (1.0f + tanhf(0.5f * x)); }
 __device__ inline double sigmoid_f(double x) { return 0.5 * (1.0 + tanh(0.5 * x)); }
 
+// tr, kkt and the non-finite count of a work-group of UT threads at once
+__device__ inline void block_sum3(double& tr, double& kkt, double& bad, double (*sh)[3]) {
+    const int t = threadIdx.x;
+    for (int off = 32; off > 0; off >>= 1) {
+        tr += __shfl_down(tr, off, 64);
+        kkt += __shfl_down(kkt, off, 64);
+        bad += __shfl_down(bad, off, 64);
+    }
+    if ((t & 63) == 0) {
+        sh[t >> 6][0] = tr;
+        sh[t >> 6][1] = kkt;
+        sh[t >> 6][2] = bad;
+    }
+    __syncthreads();
+    tr = kkt = bad = 0.0;
+    if (t == 0)
+        for (int i = 0; i < (int)(blockDim.x >> 6); ++i) {
+            tr += sh[i][0];
+            kkt += sh[i][1];
+            bad += sh[i][2];
+        }
+}
+
 __device__ inline double block_sum(double v, double* sh) {
     const int t = threadIdx.x;
     for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
@@ -41,12 +64,16 @@ __device__ inline double block_sum(double v, double* sh) {
 
 constexpr int UT = 256;   // threads of the update work-group (one row slice of SR rows)
 
-template <typename HT, int KB>
-__global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(UpdateArgs a, PlanView p) {
+// RULE: the update rule (SYMNMF_ADAM stands for NADAM too), SP: its softplus form.
+// Both are fixed at compile time: with every rule in one kernel a slice of
+// 64 x 32 took 18.5 us at n = 4100 (68 work-groups, so the time of one; 16.1 us
+// now), most of it code and registers of the other rules.
+template <typename HT, int KB, int RULE, bool SP>
+__global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 5 : 1) void update_kernel(UpdateArgs a, PlanView p) {
     __shared__ __align__(32) HT Hs[SR * KB];
     __shared__ __align__(32) HT Hns[SR * KB];
     __shared__ HT Gs[KB * KB];
-    __shared__ double red[UT / 64];
+    __shared__ double red[UT / 64][3];
     const int t = threadIdx.x;
     const int64_t slice = blockIdx.x;
     const int64_t tile = slice / SUBT;
@@ -55,18 +82,8 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
     const int32_t act = p.full ? (int32_t)tile : p.tile_active[tile];
     const int cls = (act >= 0 && !p.full) ? p.active_class[act] : 0;
     const HT* gram = (const HT*)a.gram_eff + (int64_t)cls * k * k;
-    for (int e = t; e < KB * KB; e += UT) {
-        const int i = e / KB, j = e % KB;
-        Gs[e] = i < k && j < k ? gram[i * k + j] : (HT)0;
-    }
-    const int64_t g0 = a.row0 + tile * TR + r0;       // global row of slice row 0
-    const HT* Ht = (const HT*)a.H;
-    for (int f = t; f < SR * KB; f += UT) {
-        const int r = f / KB, c = f % KB;
-        Hs[f] = c < k ? Ht[(g0 + r) * k + c] : (HT)0;
-    }
-    __syncthreads();
-
+    constexpr int NJ = SR * KB / UT;
+    const int c = t % KB, rb = t / KB;
     int64_t w_lo, w_hi, slot_base, slot_mul;
     partial_slots(p, act, w_lo, w_hi, slot_base, slot_mul);
     const HT* part = (const HT*)a.part;
@@ -77,13 +94,48 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
     HT* Go = (HT*)a.Gout;
     HT* Hn = (HT*)a.Hn;
     const HT eta = (HT)a.eta, eps = (HT)a.eps, alpha = (HT)a.alpha, mom = (HT)a.mu, cg = (HT)a.cgrad;
+    const int64_t g0 = a.row0 + tile * TR + r0;       // global row of slice row 0
+    const HT* Ht = (const HT*)a.H;
+    // What a thread needs from memory is asked for before the first barrier, so
+    // that a slice waits for memory once: the Gram and H into LDS, the S.H
+    // partials and the accumulator of its own elements into registers.
+    // The partials are summed over the writing work-groups in increasing order,
+    // the loads of all elements of one work-group issued together (a row of the
+    // n = 10^6 share has ten partials: one after another they are ten dependent
+    // load latencies per element).
+    constexpr int NG = (KB * KB + UT - 1) / UT;
+    HT shv[NJ], gv[NJ], hl[NJ], gl[NG];
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+        const int e = t + UT * q, i = e / KB, j = e % KB;
+        gl[q] = i < k && j < k ? gram[i * k + j] : (HT)0;
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int r = rb + j * (UT / KB);
+        const int64_t prow = tile * TR + r0 + r;
+        hl[j] = c < k ? Ht[(g0 + r) * k + c] : (HT)0;
+        gv[j] = prow < a.rows && c < k && RULE != SYMNMF_MU ? G[prow * k + c] : (HT)0;
+        shv[j] = 0;
+    }
+    if (act >= 0 && c < k) {
+        for (int64_t w = w_lo; w <= w_hi; ++w) {
+            const HT* pw = part + ((slot_mul * w + slot_base) * TR + r0 + rb) * a.kp + c;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) shv[j] += pw[j * (UT / KB) * a.kp];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < NG; ++q)
+        if (t + UT * q < KB * KB) Gs[t + UT * q] = gl[q];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) Hs[t + UT * j] = hl[j];
+    __syncthreads();
     // Elements f = t + UT j of the slice in rows of KB columns (those past k are
     // zero and have no storage): a thread's elements share the column
     // c = t % KB, as UT is a multiple of KB, so every Gram entry of H (H^T H) is
     // read from LDS once for all of them and the H rows in 4-wide vectors.
-    constexpr int NJ = SR * KB / UT;
     typedef HT hvec4 __attribute__((ext_vector_type(4)));
-    const int c = t % KB, rb = t / KB;
     HT hgv[NJ];
     if (act >= 0) {
 #pragma unroll
@@ -104,25 +156,11 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
             }
         }
     }
-    // the S.H partials of this thread's elements, summed over the writing
-    // work-groups in increasing order, the loads of all elements of one
-    // work-group issued together (a row of the n = 10^6 share has ten partials:
-    // one after another they are ten dependent load latencies per element)
-    HT shv[NJ];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) shv[j] = 0;
-    if (act >= 0 && c < k) {
-        for (int64_t w = w_lo; w <= w_hi; ++w) {
-            const HT* pw = part + ((slot_mul * w + slot_base) * TR + r0 + rb) * a.kp + c;
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) shv[j] += pw[j * (UT / KB) * a.kp];
-        }
-    }
     double tr = 0.0, kkt = 0.0;
     int bad = 0;
-    // the element of slice row r and this thread's column, with its S.H sum and
-    // H (H^T H) entry
-    auto element = [&](int r, HT sh_in, HT hg_in) {
+    // the element of slice row r and this thread's column, with its S.H sum,
+    // H (H^T H) entry and accumulator
+    auto element = [&](int r, HT sh_in, HT hg_in, HT acc_in) {
         const int64_t prow = tile * TR + r0 + r;
         HT hn = 0;
         if (prow < a.rows && c < k) {
@@ -137,7 +175,7 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
                     // only or J only (their own block is not among the streamed
                     // chunks) and 2 for rows in both sets
                     const HT dw = (p.full || !a.block_step) ? (HT)1 : (cls == 2 ? (HT)2 : (HT)0);
-                    sh = sh / (HT)a.panel_scale[prow / a.panel_rows] + dw * (HT)a.diag[prow] * h;
+                    sh = sh / (HT)a.panel_scale[(uint32_t)prow / (uint32_t)a.panel_rows] + dw * (HT)a.diag[prow] * h;
                 }
                 hg = hg_in;
                 g = cg * (hg - sh);
@@ -145,73 +183,73 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
             } else {
                 g = Mu[idx];
             }
-            const HT pg = a.softplus ? g : (h > (HT)0 ? g : (g < (HT)0 ? g : (HT)0));
+            const HT pg = SP ? g : (h > (HT)0 ? g : (g < (HT)0 ? g : (HT)0));
             kkt += (double)pg * (double)pg;
             if (!(g == g) || g - g != (HT)0) ++bad;
             if (a.store_mu) Mu[idx] = g;
             if (Go) Go[idx] = g;
-            if (a.method == SYMNMF_ADAM || a.method == SYMNMF_NADAM || a.method == SYMNMF_ADAN) {
+            if (RULE == SYMNMF_ADAM || RULE == SYMNMF_ADAN) {
                 // family 3, Adam-type rules on x = Theta (softplus) or H (projected)
-                const HT x = a.softplus ? Th[idx] : h;
-                const HT gx = a.softplus ? g * sigmoid_f(x) : g;
+                const HT x = SP ? Th[idx] : h;
+                const HT gx = SP ? g * sigmoid_f(x) : g;
                 const HT b1 = (HT)a.beta1, b2 = (HT)a.beta2;
                 const HT m = b1 * M[idx] + ((HT)1 - b1) * gx;
                 M[idx] = m;
                 HT step;
-                if (a.method == SYMNMF_ADAN) {
+                if (RULE == SYMNMF_ADAN) {
                     const HT b3 = (HT)a.beta3;
                     HT* D = (HT*)a.D;
                     HT* Gp = (HT*)a.Gp;
                     const HT diff = a.first ? (HT)0 : gx - Gp[idx];
                     const HT d = b2 * D[idx] + ((HT)1 - b2) * diff;
                     const HT u = gx + b2 * diff;
-                    const HT nv = b3 * G[idx] + ((HT)1 - b3) * u * u;
+                    const HT nv = b3 * acc_in + ((HT)1 - b3) * u * u;
                     D[idx] = d;
                     G[idx] = nv;
                     Gp[idx] = gx;
                     step = (m / (HT)a.bc1 + b2 * d / (HT)a.bc2) / (dev_sqrt(nv / (HT)a.bc3) + eps);
                 } else {
-                    const HT v = b2 * G[idx] + ((HT)1 - b2) * gx * gx;
+                    const HT v = b2 * acc_in + ((HT)1 - b2) * gx * gx;
                     G[idx] = v;
                     HT mh = m / (HT)a.bc1;
                     if (a.method == SYMNMF_NADAM) mh = b1 * mh + ((HT)1 - b1) * gx / (HT)a.bc1;
                     step = mh / (dev_sqrt(v / (HT)a.bc2) + eps);
                 }
                 const HT xn = x - eta * step;
-                if (a.softplus) {
+                if (SP) {
                     Th[idx] = xn;
                     hn = softplus_f(xn);
                 } else {
                     hn = xn > (HT)0 ? xn : (HT)0;
                 }
-            } else if (a.method == SYMNMF_MU) {
+            } else if (RULE == SYMNMF_MU) {
                 // family 1: dampened multiplicative update, H stays >= 0
                 hn = (HT)0.5 * h * ((HT)1 + sh / (hg + eps));
-            } else if (a.softplus) {
+            } else if (SP) {
                 HT th = Th[idx];
                 const HT gt = g * sigmoid_f(th);
-                if (a.method == SYMNMF_RMSPROP) {
-                    const HT v = alpha * G[idx] + ((HT)1 - alpha) * gt * gt;
+                if (RULE == SYMNMF_RMSPROP) {
+                    const HT v = alpha * acc_in + ((HT)1 - alpha) * gt * gt;
                     const HT m = mom * M[idx] + eta * gt / (dev_sqrt(v) + eps);
                     G[idx] = v;
                     M[idx] = m;
                     th -= m;
                 } else {
-                    const HT acc = G[idx] + gt * gt;
+                    const HT acc = acc_in + gt * gt;
                     G[idx] = acc;
                     th -= eta * gt / (dev_sqrt(acc) + eps);
                 }
                 Th[idx] = th;
                 hn = softplus_f(th);
-            } else if (a.method == SYMNMF_RMSPROP) {
-                const HT v = alpha * G[idx] + ((HT)1 - alpha) * g * g;
+            } else if (RULE == SYMNMF_RMSPROP) {
+                const HT v = alpha * acc_in + ((HT)1 - alpha) * g * g;
                 const HT m = mom * M[idx] + eta * g / (dev_sqrt(v) + eps);
                 G[idx] = v;
                 M[idx] = m;
                 hn = h - m;
                 hn = hn > (HT)0 ? hn : (HT)0;
             } else {
-                const HT acc = G[idx] + g * g;
+                const HT acc = acc_in + g * g;
                 G[idx] = acc;
                 hn = h - eta * g / (dev_sqrt(acc) + eps);
                 hn = hn > (HT)0 ? hn : (HT)0;
@@ -222,7 +260,7 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
     };
     // compile-time j, so the precomputed sums stay in registers
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) element(rb + j * (UT / KB), shv[j], hgv[j]);
+    for (int j = 0; j < NJ; ++j) element(rb + j * (UT / KB), shv[j], hgv[j], gv[j]);
     __syncthreads();
     if constexpr (sizeof(HT) == 4)
         if (a.img1 && g0 < a.n_chunks * KC)
@@ -260,30 +298,45 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 7 : 1) void update_kernel(Upd
             tg[e] = s;
         }
     }
-    const double str = block_sum(tr, red);
-    const double skk = block_sum(kkt, red);
-    const double sbad = block_sum((double)bad, red);
+    double nbad = (double)bad;
+    block_sum3(tr, kkt, nbad, red);
     if (t == 0) {
-        a.tile_tr[slice] = str;
-        a.tile_kkt[slice] = skk;
-        a.tile_bad[slice] = (int32_t)sbad;
+        a.tile_tr[slice] = tr;
+        a.tile_kkt[slice] = kkt;
+        a.tile_bad[slice] = (int32_t)nbad;
     }
 }
 
-hipError_t launch_update(const UpdateArgs& a, int h_f64, const PlanView& p, hipStream_t stream) {
-    const int64_t tiles = a.rows_pad / TR;
-    dim3 grid(tiles * SUBT), block(UT);
-    if (h_f64) {
-        if (a.k <= 8) hipLaunchKernelGGL((update_kernel<double, 8>), grid, block, 0, stream, a, p);
-        else if (a.k <= 16) hipLaunchKernelGGL((update_kernel<double, 16>), grid, block, 0, stream, a, p);
-        else if (a.k <= 32) hipLaunchKernelGGL((update_kernel<double, 32>), grid, block, 0, stream, a, p);
-        else return hipErrorInvalidValue;
-    } else {
-        if (a.k <= 16) hipLaunchKernelGGL((update_kernel<float, 16>), grid, block, 0, stream, a, p);
-        else if (a.k <= 32) hipLaunchKernelGGL((update_kernel<float, 32>), grid, block, 0, stream, a, p);
-        else hipLaunchKernelGGL((update_kernel<float, 64>), grid, block, 0, stream, a, p);
-    }
+template <typename HT, int RULE, bool SP>
+static hipError_t launch_rule(const UpdateArgs& a, const PlanView& p, hipStream_t stream) {
+    const dim3 grid(a.rows_pad / TR * SUBT), block(UT);
+    constexpr bool F64 = sizeof(HT) == 8;
+    if (F64 && a.k <= 8) hipLaunchKernelGGL((update_kernel<HT, F64 ? 8 : 16, RULE, SP>), grid, block, 0, stream, a, p);
+    else if (a.k <= 16) hipLaunchKernelGGL((update_kernel<HT, 16, RULE, SP>), grid, block, 0, stream, a, p);
+    else if (a.k <= 32) hipLaunchKernelGGL((update_kernel<HT, 32, RULE, SP>), grid, block, 0, stream, a, p);
+    else if (!F64) hipLaunchKernelGGL((update_kernel<HT, F64 ? 32 : 64, RULE, SP>), grid, block, 0, stream, a, p);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
+}
+
+template <typename HT>
+static hipError_t launch_update_t(const UpdateArgs& a, const PlanView& p, hipStream_t stream) {
+#define RULE(R) return a.softplus ? launch_rule<HT, R, true>(a, p, stream) : launch_rule<HT, R, false>(a, p, stream)
+    switch (a.method) {
+        case SYMNMF_ADAGRAD: RULE(SYMNMF_ADAGRAD);
+        case SYMNMF_RMSPROP: RULE(SYMNMF_RMSPROP);
+        case SYMNMF_ADAM:
+        case SYMNMF_NADAM: RULE(SYMNMF_ADAM);
+        case SYMNMF_ADAN: RULE(SYMNMF_ADAN);
+        case SYMNMF_MU:
+            if (!a.softplus) return launch_rule<HT, SYMNMF_MU, false>(a, p, stream);
+    }
+#undef RULE
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_update(const UpdateArgs& a, int h_f64, const PlanView& p, hipStream_t stream) {
+    return h_f64 ? launch_update_t<double>(a, p, stream) : launch_update_t<float>(a, p, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -374,7 +427,7 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kerne
     __shared__ __align__(32) HT As[SR * KB];
     __shared__ HT Gs[KB * KB];
     __shared__ HT Ms[KB * KB];
-    __shared__ double red[UT / 64];
+    __shared__ double red[UT / 64][3];
     const int t = threadIdx.x;
     const int64_t slice = blockIdx.x;
     const int64_t tile = slice / SUBT;
@@ -383,19 +436,16 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kerne
     const int32_t act = (int32_t)tile;                  // full steps only
     const HT* gram = (const HT*)a.gram_eff;
     const HT* minv = (const HT*)a.minv;
-    for (int e = t; e < KB * KB; e += UT) {
-        const int i = e / KB, j = e % KB;
-        const bool in = i < k && j < k;
-        Gs[e] = in ? gram[i * k + j] : (HT)0;
-        Ms[e] = in ? minv[i * k + j] : (HT)0;
-    }
+    // Elements f = t + UT j in rows of KB columns (zero past k), sharing the
+    // column cc = t % KB, as in the update kernel: the Gram and M^-1 entries of
+    // the column are read from LDS once for all rows (rows in 4-wide vectors),
+    // and everything from memory, the S.W partials and the dual among it, is
+    // asked for before the first barrier.
+    constexpr int NJ = SR * KB / UT;
+    typedef HT hvec4 __attribute__((ext_vector_type(4)));
+    const int cc = t % KB, rb = t / KB;
     const int64_t g0 = a.row0 + tile * TR + r0;
     const HT* Wt = (const HT*)a.H;
-    for (int f = t; f < SR * KB; f += UT) {
-        const int r = f / KB, c = f % KB;
-        Ws[f] = c < k ? Wt[(g0 + r) * k + c] : (HT)0;
-    }
-    __syncthreads();
     int64_t w_lo, w_hi, slot_base, slot_mul;
     partial_slots(p, act, w_lo, w_hi, slot_base, slot_mul);
     const HT* part = (const HT*)a.part;
@@ -403,16 +453,23 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kerne
     HT* Go = (HT*)a.Gout;
     HT* Wn = (HT*)a.Hn;
     const HT rho = (HT)a.rho;
-    // Elements f = t + UT j in rows of KB columns (zero past k), sharing the
-    // column cc = t % KB, as in the update kernel: the S.W partials are loaded
-    // writer by writer for all of them at once, and the Gram and M^-1 entries
-    // of the column are read from LDS once for all rows (rows in 4-wide vectors).
-    constexpr int NJ = SR * KB / UT;
-    typedef HT hvec4 __attribute__((ext_vector_type(4)));
-    const int cc = t % KB, rb = t / KB;
-    HT swv[NJ], wgv[NJ];
+    constexpr int NG = (KB * KB + UT - 1) / UT;
+    HT swv[NJ], wgv[NJ], uv[NJ], wl[NJ], gl[NG], ml[NG];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) swv[j] = wgv[j] = 0;
+    for (int q = 0; q < NG; ++q) {
+        const int e = t + UT * q, i = e / KB, j = e % KB;
+        const bool in = i < k && j < k;
+        gl[q] = in ? gram[i * k + j] : (HT)0;
+        ml[q] = in ? minv[i * k + j] : (HT)0;
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int r = rb + j * (UT / KB);
+        const int64_t prow = tile * TR + r0 + r;
+        wl[j] = cc < k ? Wt[(g0 + r) * k + cc] : (HT)0;
+        uv[j] = prow < a.rows && cc < k ? Ud[prow * k + cc] : (HT)0;
+        swv[j] = wgv[j] = 0;
+    }
     if (cc < k) {
         for (int64_t w = w_lo; w <= w_hi; ++w) {
             const HT* pw = part + ((slot_mul * w + slot_base) * TR + r0 + rb) * a.kp + cc;
@@ -420,6 +477,15 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kerne
             for (int j = 0; j < NJ; ++j) swv[j] += pw[j * (UT / KB) * a.kp];
         }
     }
+#pragma unroll
+    for (int q = 0; q < NG; ++q)
+        if (t + UT * q < KB * KB) {
+            Gs[t + UT * q] = gl[q];
+            Ms[t + UT * q] = ml[q];
+        }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) Ws[t + UT * j] = wl[j];
+    __syncthreads();
 #pragma unroll 2
     for (int b = 0; b < KB; b += 4) {
         const HT g0 = Gs[b * KB + cc], g1 = Gs[(b + 1) * KB + cc], g2 = Gs[(b + 2) * KB + cc],
@@ -446,14 +512,14 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kerne
             const HT w = Ws[r * KB + cc];
             const int64_t idx = prow * k + cc;
             HT sw = swv[j];
-            if (a.fp8) sw = sw / (HT)a.panel_scale[prow / a.panel_rows] + (HT)a.diag[prow] * w;
+            if (a.fp8) sw = sw / (HT)a.panel_scale[(uint32_t)prow / (uint32_t)a.panel_rows] + (HT)a.diag[prow] * w;
             const HT g = (HT)4 * (wgv[j] - sw);
             tr += (double)w * (double)sw;
             const HT pg = w > (HT)0 ? g : (g < (HT)0 ? g : (HT)0);
             kkt += (double)pg * (double)pg;
             if (!(g == g) || g - g != (HT)0) ++bad;
             if (Go) Go[idx] = g;
-            av = (HT)2 * sw + rho * (w - Ud[idx]);
+            av = (HT)2 * sw + rho * (w - uv[j]);
         }
         As[r * KB + cc] = av;
     }
@@ -483,7 +549,7 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kerne
         HT wn = 0;
         if (prow < a.rows && cc < k) {
             const int64_t idx = prow * k + cc;
-            const HT h = hv[j], u = Ud[idx];
+            const HT h = hv[j], u = uv[j];
             wn = h + u > (HT)0 ? h + u : (HT)0;
             Ud[idx] = u + h - wn;
             Wn[(g0 + r) * k + cc] = wn;
@@ -526,13 +592,12 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kerne
             tg[e] = s;
         }
     }
-    const double str = block_sum(tr, red);
-    const double skk = block_sum(kkt, red);
-    const double sbad = block_sum((double)bad, red);
+    double nbad = (double)bad;
+    block_sum3(tr, kkt, nbad, red);
     if (t == 0) {
-        a.tile_tr[slice] = str;
-        a.tile_kkt[slice] = skk;
-        a.tile_bad[slice] = (int32_t)sbad;
+        a.tile_tr[slice] = tr;
+        a.tile_kkt[slice] = kkt;
+        a.tile_bad[slice] = (int32_t)nbad;
     }
 }
 
@@ -884,7 +949,7 @@ __global__ __launch_bounds__(256) void objective_tiles_kernel(UpdateArgs a, Plan
         double sh = 0.0;
         for (int64_t w = w_lo; w <= w_hi; ++w) sh += part[((w + tile) * TR + r0 + r) * a.kp + c];
         const double h = Hs[r * LD + c];
-        if (a.fp8) sh = sh / (double)a.panel_scale[prow / a.panel_rows] + (double)a.diag[prow] * h;
+        if (a.fp8) sh = sh / (double)a.panel_scale[(uint32_t)prow / (uint32_t)a.panel_rows] + (double)a.diag[prow] * h;
         tr += h * sh;
     }
     const int nk = kr / 4, nt = nk * nk, groups = 256 / nt;
