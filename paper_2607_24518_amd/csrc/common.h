@@ -135,6 +135,7 @@ template <> __device__ inline double load_as_f64<uint8_t>(const uint8_t* p) { re
 struct PlanView {
     int32_t full;
     int32_t tall;             // full plans only: units are (pair of row tiles, chunk), see below
+    int32_t quarter;          // full plans only: four work-groups per w, one per 64 rows of its tiles
     int32_t n_tiles;          // row tiles of the stored panel
     int32_t n_chunks;         // column chunks (ld / KC)
     int32_t P;                // launched persistent work-groups
@@ -154,7 +155,7 @@ inline int64_t plan_words(int64_t n_tiles, int64_t n_chunks) {
 }
 inline PlanView plan_view(int32_t* base, int32_t full, int32_t n_tiles, int32_t n_chunks, int32_t P) {
     PlanView v;
-    v.full = full; v.tall = 0; v.n_tiles = n_tiles; v.n_chunks = n_chunks; v.P = P;
+    v.full = full; v.tall = 0; v.quarter = 0; v.n_tiles = n_tiles; v.n_chunks = n_chunks; v.P = P;
     v.hdr = base;
     v.active_tile = base + 8;
     v.active_class = v.active_tile + n_tiles;
@@ -288,6 +289,9 @@ int stream_uses_mfma(int32_t stype, int h_f64, int acc_f64, int64_t k);
 int stream_wgs_per_cu(int32_t stype, int64_t k);
 // whether full steps of this storage and rank run the tall (8-wave) kernel
 int stream_tall_supported(int32_t stype, int h_f64, int64_t k);
+// work-groups w of a full step that runs the quarter-tile kernel (a plan with quarter = 1), or 0
+// where the step has too many units for it
+int32_t stream_quarter_wgs(int cus, int32_t stype, int64_t n_tiles, int64_t n_chunks, int64_t k);
 
 // plan.hip: build the device plan of a sub-sampled step.
 struct PlanRequest {

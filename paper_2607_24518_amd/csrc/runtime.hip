@@ -143,6 +143,7 @@ struct symnmf_state {
     bool mfma = false;
     bool tall = false;               // full steps run the 8-wave stream kernel
     int32_t P_tall = 0;
+    int32_t P_quarter = 0;           // full steps run the quarter-tile kernel with this many work-groups w
     double* scal = nullptr;          // device scalars (median, sums)
     int64_t t = 0;
     int ring_full[HCAP] = {};
@@ -480,6 +481,14 @@ static symnmf_status state_alloc(symnmf_state* st, void** out, int64_t bytes) {
     return SYMNMF_OK;
 }
 
+// Work-groups of the quarter-tile stream kernel for the full steps of a state,
+// or 0.  The sampled methods keep the kernels above for them: only one step
+// in snapshot_s is a full one.
+static int32_t quarter_wgs(const symnmf_state* st) {
+    if (!st->mfma || st->p.method == SYMNMF_ROW_SVRG || st->p.method == SYMNMF_BLOCK_SVRG) return 0;
+    return std::min(st->P, stream_quarter_wgs(st->ctx->cus, st->S.dtype, st->tiles, st->chunks, st->k));
+}
+
 static double tau_g_of(const symnmf_state* st) {
     const double n = (double)st->n;
     return st->p.tau_g_inf * std::max(1.0, st->p.n_ref / n);
@@ -575,6 +584,7 @@ symnmf_status symnmf_state_create(symnmf_ctx* ctx, const symnmf_S* S, int64_t k,
     }
     st->tall = stream_tall_supported(S->dtype, h_f64, k) != 0 && std::getenv("SYMNMF_NO_TALL") == nullptr;
     st->P_tall = st->tall ? tall_wgs(ctx->cus, st->tiles) : ctx->cus;
+    st->P_quarter = quarter_wgs(st);
     const int64_t part_tiles = std::max<int64_t>((int64_t)st->P + st->tiles,
                                                  st->tall ? 2 * ((int64_t)st->P_tall + tall_pairs(st->tiles)) : 0);
     ALLOC(st->part, part_tiles * TR * st->kp * st->hsz);
@@ -627,7 +637,10 @@ static symnmf_status do_step(symnmf_ctx* ctx, const symnmf_S* S, symnmf_state* s
     if (p.method == SYMNMF_ROW_SVRG) kind = (t % p.snapshot_s == 0) ? 0 : 1;
     if (p.method == SYMNMF_BLOCK_SVRG) kind = (st->phi >= 1.0 || t % p.snapshot_s == 0) ? 0 : 2;
     PlanView pv = plan_view(st->plan, kind == 0, (int32_t)st->tiles, (int32_t)st->chunks, st->P);
-    if (kind == 0 && st->tall) {
+    if (kind == 0 && st->P_quarter > 0) {
+        pv.quarter = 1;
+        pv.P = st->P_quarter;
+    } else if (kind == 0 && st->tall) {
         pv.tall = 1;
         pv.P = st->P_tall;
     }
@@ -1183,6 +1196,7 @@ static symnmf_status rebind_state(symnmf_state* st, const symnmf_S* S) {
     st->P = P;
     st->tall = tall;
     st->P_tall = P_tall;
+    st->P_quarter = quarter_wgs(st);
     st->have_prev = false;
     st->stag_run = 0;
     return SYMNMF_OK;

@@ -20,6 +20,8 @@
 // The reduction index of one MFMA may be any permutation of the columns as
 // long as A and B agree; each kernel uses the one in which a lane's 16 bytes
 // of S are consecutive columns.
+#include <algorithm>
+
 #include "image.h"
 
 namespace symnmf {
@@ -604,6 +606,165 @@ __global__ __launch_bounds__(TALL ? 512 : 256, TALL || (ACC64 && NT == 4) ? 1 : 
     }
 }
 
+// ---------------------------------------------------------------------------
+// Full steps of a few units.  A unit of the kernel above keeps a CU's matrix
+// cores busy for 7 (BF16) to 14 us (FP32, k = 32), so a step with fewer units
+// than a few per CU takes as long as its longest run of units, most CUs idle.
+// Here a work-group takes 64 rows of a tile and its four waves a quarter of
+// the chunk's columns each (whole sub-steps), so a unit is spread over four
+// CUs and sixteen waves; each wave reads its S and its part of the image (from
+// L2) straight into registers, one unit ahead, and the four waves' sums meet in
+// LDS once per tile.  The partial of work-group w for tile a goes to slot
+// w + a as usual, written by the four work-groups 4 w .. 4 w + 3.
+// ---------------------------------------------------------------------------
+template <int KIND, int NT>
+__global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_quarter(const void* __restrict__ Sv,
+                                                                      const u32x4* __restrict__ img,
+                                                                      float* __restrict__ part, PlanView p) {
+    constexpr int K = 16 * NT;
+    using IS = ImageShape<KIND, K>;
+    constexpr int EB = KIND == 0 ? 4 : (KIND == 1 ? 2 : 1);
+    constexpr int NS = KIND == 0 ? 16 : (KIND == 1 ? 8 : 4);
+    constexpr int QS = NS / 4;                             // sub-steps of a wave
+    constexpr int NH = KIND == 2 ? 2 : 1, NP = KIND == 0 ? 1 : 3;
+    constexpr int NB = QS * NH * NP * NT;                  // image vectors of a lane
+    __shared__ __align__(16) float red[4][64 * K];
+    const int64_t U = (int64_t)p.n_tiles * p.n_chunks;
+    const int64_t Pe = U < p.P ? U : p.P;
+    const int64_t w = blockIdx.x >> 2;
+    const int sub = blockIdx.x & 3;
+    if (w >= Pe) return;
+    const int64_t u0 = wg_start(w, U, Pe), u1 = wg_start(w + 1, U, Pe);
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, lr = lane & 15, lg = lane >> 4;
+
+    auto load = [&](int64_t tile, int64_t ch, u32x4 (&s)[QS][4], u32x4 (&b)[NB]) {
+        const u32x4* sp = (const u32x4*)((const uint8_t*)Sv + (tile * p.n_chunks + ch) * TILE_ELEMS * EB +
+                                         (int64_t)sub * (TILE_ELEMS * EB / 4)) + lane;
+        const u32x4* hb = img + ch * IS::NV;
+#pragma unroll
+        for (int q = 0; q < QS; ++q)
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) s[q][rg] = __builtin_nontemporal_load(sp + ((wv * QS + q) * 4 + rg) * 64);
+#pragma unroll
+        for (int q = 0; q < QS; ++q)
+#pragma unroll
+            for (int h = 0; h < NH; ++h)
+#pragma unroll
+                for (int pl = 0; pl < NP; ++pl)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        b[((q * NH + h) * NP + pl) * NT + nt] =
+                            hb[pl * (IS::PLANE / 8) + (((nt * NS + wv * QS + q) * NH + h) * 4 + lg) * 16 + lr];
+    };
+
+    floatx4 acc[4][NT];
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[rg][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    u32x4 s[QS][4], b[NB], sn[QS][4], bn[NB];
+    int64_t tile = u0 / p.n_chunks, ch = u0 - tile * p.n_chunks;
+    load(tile, ch, s, b);
+    for (int64_t u = u0; u < u1; ++u) {
+        // the last unit loads itself again: in bounds, unused
+        int64_t tile_n = tile, ch_n = ch;
+        if (u + 1 < u1 && ++ch_n == p.n_chunks) {
+            ch_n = 0;
+            ++tile_n;
+        }
+        load(tile_n, ch_n, sn, bn);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < QS; ++q) {
+            if (KIND == 0) {
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+#pragma unroll
+                    for (int rg = 0; rg < 4; ++rg)
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt)
+                            acc[rg][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                __builtin_bit_cast(floatx4, s[q][rg])[m], __builtin_bit_cast(floatx4, b[q * NT + nt])[m],
+                                acc[rg][nt], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int h = 0; h < NH; ++h) {
+                    bf16x8 av[4];
+#pragma unroll
+                    for (int rg = 0; rg < 4; ++rg) {
+                        const u32x4 r = s[q][rg];
+                        if (KIND == 2) {
+                            const uint32_t w0 = h ? r[2] : r[0], w1 = h ? r[3] : r[1];
+                            bf16x2 q0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, false);
+                            bf16x2 q1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, true);
+                            bf16x2 q2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, false);
+                            bf16x2 q3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, true);
+                            av[rg] = bf16x8{q0[0], q0[1], q1[0], q1[1], q2[0], q2[1], q3[0], q3[1]};
+                        } else {
+                            av[rg] = __builtin_bit_cast(bf16x8, r);
+                        }
+                    }
+#pragma unroll
+                    for (int pl = 0; pl < NP; ++pl)
+#pragma unroll
+                        for (int rg = 0; rg < 4; ++rg)
+#pragma unroll
+                            for (int nt = 0; nt < NT; ++nt)
+                                acc[rg][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    av[rg], __builtin_bit_cast(bf16x8, b[((q * NH + h) * NP + pl) * NT + nt]),
+                                    acc[rg][nt], 0, 0, 0);
+                }
+            }
+        }
+        if (u + 1 == u1 || tile_n != tile) {
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) red[wv][(16 * rg + 4 * lg + v) * K + 16 * nt + lr] = acc[rg][nt][v];
+                    acc[rg][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+                }
+            __syncthreads();
+            float* dst = part + ((w + tile) * TR + 64 * sub) * (int64_t)K;
+#pragma unroll
+            for (int f = 4 * t; f < 64 * K; f += 1024) {
+                const floatx4 r0 = *(const floatx4*)&red[0][f], r1 = *(const floatx4*)&red[1][f];
+                const floatx4 r2 = *(const floatx4*)&red[2][f], r3 = *(const floatx4*)&red[3][f];
+                floatx4 o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = (r0[e] + r1[e]) + (r2[e] + r3[e]);
+                *(floatx4*)&dst[f] = o;
+            }
+            __syncthreads();
+        }
+        tile = tile_n;
+        ch = ch_n;
+#pragma unroll
+        for (int q = 0; q < QS; ++q)
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) s[q][rg] = sn[q][rg];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) b[i] = bn[i];
+    }
+}
+
+// One work-group per CU (64 w of four): with two or four per CU a tile has more
+// partials to write and to sum (n = 4100, k = 32, FP32: 40.6, 48.4 and 58.1 us a
+// step).  The line lies where the measured steps cross: FP32 S up to 32 columns
+// gains to 12000 instruments (U = 2209: 118 us against 138 of the tall kernel)
+// and about breaks even at 16000; BF16 / FP8 S gains to 8192 (U = 1024: 50.3 /
+// 45.2 against 63.8 / 52.8 us) and loses at 12000 or 16000; 64 columns gain to
+// 6000 (U = 576: 104 / 77 / 77 against 128 / 87 / 85 us, FP32 / BF16 / FP8) and
+// lose or tie at 8192.  At 512 instruments: k = 16 19.0 against 28.9 us, k = 32
+// 24.8 against 41.0 us, k = 64 50.5 against 78.5 us (FP32).
+int32_t stream_quarter_wgs(int cus, int32_t stype, int64_t n_tiles, int64_t n_chunks, int64_t k) {
+    const int64_t U = n_tiles * n_chunks, P = std::max(cus / 4, 1);
+    const int64_t most = mfma_width(k) == 64 ? 768 : (stype == SYMNMF_S_FP32 ? 2304 : 1024);
+    if (U > most) return 0;
+    return (int32_t)std::min(U, P);
+}
+
 int stream_uses_mfma(int32_t stype, int h_f64, int acc_f64, int64_t k) {
     if (h_f64 || acc_f64 || stype == SYMNMF_S_FP64) return 0;
     return (k >= 1 && k <= KMAX) ? 1 : 0;
@@ -635,6 +796,13 @@ static void launch_mfma_kind(const void* S, const u32x4* img1, const u32x4* img2
                              const PlanView& p, hipStream_t stream) {
     dim3 grid(p.P);
     k = mfma_width(k);
+    if (p.quarter) {
+        const dim3 qg(4 * p.P), qb(256);
+        if (k == 16) hipLaunchKernelGGL((stream_quarter<KIND, 1>), qg, qb, 0, stream, S, img1, (float*)part, p);
+        else if (k == 32) hipLaunchKernelGGL((stream_quarter<KIND, 2>), qg, qb, 0, stream, S, img1, (float*)part, p);
+        else hipLaunchKernelGGL((stream_quarter<KIND, 4>), qg, qb, 0, stream, S, img1, (float*)part, p);
+        return;
+    }
     if (p.tall) {
         dim3 block(512);
         if (k == 16) hipLaunchKernelGGL((stream_mfma<KIND, 1, true, true, false, true>), grid, block, 0, stream, S, img1, img2, part, p);
