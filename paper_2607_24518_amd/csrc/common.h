@@ -270,10 +270,16 @@ hipError_t launch_stream(const void* S, int32_t stype, int64_t ld, const void* H
                          const void* img1 = nullptr, const void* img2 = nullptr);
 // 32-bit words of the H images of all n_chunks chunks for this storage type and rank
 int64_t h_image_words(int32_t stype, int64_t k, int64_t n_chunks);
-// Write the images of chunks [chunk0, chunk0 + n_chunks) of wt * H (FP32, 256 rows x k per chunk;
-// img: those of all chunks), zero past column k.
+// Write the images of chunks [chunk0, chunk0 + n_chunks) of wt * H (FP32, 256 rows x k per chunk,
+// rows ldh apart, 0 = k; img: those of all chunks), zero past column k.
 hipError_t launch_h_image(const float* H, int32_t stype, int64_t k, int64_t chunk0, int64_t n_chunks, float wt,
-                          uint32_t* img, hipStream_t stream);
+                          uint32_t* img, hipStream_t stream, int64_t ldh = 0);
+// out (rows x k, row stride ldo) = the dense product from the partials of a full pass (float or
+// double, rows of kp); FP8: / scale + diag X, X the streamed factor's rows of this panel (stride ldo)
+template <typename T>
+hipError_t launch_dense_rows(const T* part, int64_t rows, int64_t k, int64_t kp, const PlanView& plan, const T* X,
+                             int64_t ldo, const float* scale, const float* diag, int64_t panel_rows, T* out,
+                             hipStream_t stream);
 hipError_t launch_copy_probe(const void* src, void* dst, int64_t bytes, hipStream_t stream);
 // plain read of bytes (multiple of 16); sink: sink_words words (>= 4), one per wave
 hipError_t launch_read_probe(const void* src, int64_t bytes, uint32_t* sink, int64_t sink_words,
@@ -436,10 +442,6 @@ hipError_t launch_objective_tiles(const UpdateArgs& a, int h_f64, const PlanView
 
 // warmstart.hip
 hipError_t launch_omega(uint64_t seed, int64_t n, int64_t rows_alloc, int w, float* out, hipStream_t stream);
-// dense FP32 S.H rows (rows x k) from the partials of a full FP32-accumulating stream pass
-hipError_t launch_sh_dense(const float* part, int64_t rows, int64_t rows_pad, int64_t k, int64_t kp, int32_t n_chunks, int32_t P,
-                           const float* H, int64_t row0, const float* scale, const float* diag, int64_t panel_rows,
-                           float* out, hipStream_t stream);
 // C = alpha op(A) op(B) + bias with epilogue (0 none, 1 GELU, 2 softplus); Z: pre-epilogue copy
 // or null.  splits > 1 (a value of gemm_splits; no bias, epilogue or Z): C holds that many M x N
 // partials, one per range of K.

@@ -113,25 +113,165 @@ __global__ __launch_bounds__(KT) void rownorm_finish_kernel(const double* __rest
 }
 
 // --------------------------------------------------------------------------
-// Dense S.X of one slice from the stream's partial tiles (fixed order over
-// the work-groups that streamed each tile).  FP8: partial / scale + S_ii X_i.
+// Cluster sums of FP32 storage.  A row of the label matrix W has one non-zero,
+// so M = S W is n^2 multiply-adds and not n^2 K, if the columns of S are
+// brought into the order of their clusters.  Every 256-column chunk gets a list
+// of its columns, grouped by 16-cluster block (one MFMA accumulator tile) and
+// in the order in which the stream's MFMAs reduce them; strips of 16 rows x 256
+// columns are staged in LDS and the listed columns taken from there, four to
+// an MFMA whose other operand holds 1 / ||s_j|| at the column's cluster and
+// zero elsewhere.  Adding a zero product changes no sum, so every sum has the same
+// terms in the same order, and the same value, as the dense product, whose
+// runs of units (one FP32 partial each, added in increasing order) are kept.
+// n = 20000, 141 clusters: 0.346 ms (4.7 TB/s of S; 0.26 ms, 6.3 TB/s, without
+// the MFMAs), where the dense product took three passes, 1.34 ms.
 // --------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(KT) void slice_dense_kernel(const T* __restrict__ part, int64_t rows, int w, PlanView p,
-                                                         const float* __restrict__ scale,
-                                                         const float* __restrict__ diag, int64_t panel_rows,
-                                                         const T* __restrict__ X, T* __restrict__ Y) {
-    const int32_t tile = blockIdx.x;
-    int64_t w_lo, w_hi, sb, sm;
-    partial_slots(p, tile, w_lo, w_hi, sb, sm);
-    for (int f = threadIdx.x; f < TR * w; f += KT) {
-        const int r = f / w, c = f - r * w;
-        const int64_t row = (int64_t)tile * TR + r;
-        if (row >= rows) continue;
-        T s = 0;
-        for (int64_t q = w_lo; q <= w_hi; ++q) s += part[((sm * q + sb) * TR + r) * (int64_t)w + c];
-        if (scale) s = s / (T)scale[row / panel_rows] + (T)diag[row] * X[row * w + c];
-        Y[row * w + c] = s;
+constexpr int CL_PAD = 8;                         // entries of one loop step (two MFMAs)
+constexpr int CL_NB = 12;                         // 16-cluster blocks of a pass over S
+constexpr int CL_PARTS = 4;                       // waves that share a strip, each a quarter of the blocks
+constexpr int CL_ENT = KC + CL_NB * (CL_PAD - 1) + 2 * CL_PAD;   // entries of a list and what is read past its end
+constexpr int CL_WORDS = 2 * CL_ENT + 16;         // entries (position | cluster << 16, weight), block starts / CL_PAD
+static_assert(CL_ENT % 4 == 0, "lists are moved in 16-byte vectors");
+
+// One work-group per (chunk, pass): the list of the chunk's columns with
+// clusters [16 CL_NB pass, 16 CL_NB (pass + 1)).  Thread t takes the column
+// that the dense product reduces as number t of the chunk.  Blocks are listed
+// in the order part 0 (blocks 0, 4, 8), part 1, ..., so that a wave's entries
+// are contiguous.
+__global__ __launch_bounds__(KT) void cluster_lists_kernel(const int32_t* __restrict__ labels,
+                                                           const double* __restrict__ norms, int64_t n,
+                                                           uint32_t* __restrict__ lists) {
+    __shared__ uint32_t out[CL_WORDS];
+    __shared__ int cnt[KT / 64][CL_NB];
+    __shared__ int start[CL_NB + 1];
+    const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
+    const int s = t >> 4, m = (t >> 2) & 3, g = t & 3;
+    const int64_t j = (int64_t)blockIdx.x * KC + 16 * s + 4 * g + m;
+    const int64_t lab = j < n ? (int64_t)labels[j] - (int64_t)blockIdx.y * 16 * CL_NB : -1;
+    const int b = lab >= 0 && lab < 16 * CL_NB ? (int)lab >> 4 : -1;
+    for (int i = t; i < CL_WORDS; i += KT) out[i] = 0;
+    const int place = b < 0 ? -1 : b % CL_PARTS * (CL_NB / CL_PARTS) + b / CL_PARTS;
+    int rank = 0;
+#pragma unroll
+    for (int q = 0; q < CL_NB; ++q) {
+        const uint64_t in = __ballot(place == q);
+        if (place == q) rank = __popcll(in & ((1ull << lane) - 1));
+        if (lane == 0) cnt[wv][q] = __popcll(in);
+    }
+    __syncthreads();
+    if (t == 0) {
+        int at = 0;
+        for (int q = 0; q < CL_NB; ++q) {
+            start[q] = at;
+            int c = 0;
+            for (int v = 0; v < KT / 64; ++v) {
+                const int x = cnt[v][q];
+                cnt[v][q] = at + c;
+                c += x;
+            }
+            at += (c + CL_PAD - 1) / CL_PAD * CL_PAD;
+        }
+        start[CL_NB] = at;
+    }
+    __syncthreads();
+    if (b >= 0) {
+        const int e = cnt[wv][place] + rank;
+        // byte position of the column in a 16-row strip of the tile, row 0
+        out[2 * e] = (uint32_t)(s * 1024 + g * 256 + m * 4) | (uint32_t)(lab & 15) << 16;
+        out[2 * e + 1] = __builtin_bit_cast(uint32_t, (float)(1.0 / norms[j]));
+    }
+    if (t <= CL_NB) out[2 * CL_ENT + t] = (uint32_t)(start[t] / CL_PAD);
+    __syncthreads();
+    uint32_t* dst = lists + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * CL_WORDS;
+    for (int i = t; i < CL_WORDS; i += KT) dst[i] = out[i];
+}
+
+// One work-group per 32 rows, over all chunks: sums of the clusters of one
+// pass.  A strip's four waves load a quarter of it each, the next chunk's in
+// flight while the current one is reduced, and take a quarter of the blocks
+// each.  (A wave to a strip, all blocks its own, needs fewer barriers but left
+// 1264 waves with a chain of 44 dependent steps a chunk: 479 us.)
+template <int NB>
+__global__ __launch_bounds__(512, 6) void cluster_sums_kernel(const u32x4* __restrict__ S, PlanView p,
+                                                              const uint32_t* __restrict__ lists, int64_t n,
+                                                              int64_t rows_pad, int w, int col0,
+                                                              float* __restrict__ M) {
+    constexpr int NP = NB / CL_PARTS;             // blocks of a wave
+    constexpr int LV = CL_WORDS / 4;              // 16-byte vectors of a list
+    static_assert(NB % CL_PARTS == 0 && LV <= 512, "blocks split evenly, one vector of a list per thread");
+    __shared__ u32x4 strips[2][KC * 16 / 4];
+    __shared__ __align__(16) uint32_t lst[CL_WORDS];
+    const int t = threadIdx.x, lane = t & 63, lr = lane & 15, lg = lane >> 4;
+    const int part = (t >> 6) & 3, strip = t >> 8;
+    const int32_t tile = blockIdx.x >> 3, sixteen = (int)(blockIdx.x & 7) * 2 + strip;   // strip of the tile
+    const int64_t C = p.n_chunks;
+    // runs of units of this tile's pair, as the dense product splits them
+    const int64_t U = tall_pairs(p.n_tiles) * C, Pe = U < p.P ? U : p.P, u0 = (int64_t)(tile >> 1) * C;
+    int64_t run = wg_owner(u0, U, Pe), end_u = wg_start(run + 1, U, Pe);
+    const u32x4* src = S + (int64_t)tile * C * (TILE_ELEMS / 4) +
+                       (((sixteen >> 2) * 16 + 4 * part) * 4 + (sixteen & 3)) * 64 + lane;
+    const u32x4* lsrc = (const u32x4*)lists + min(t, LV - 1);
+    u32x4 pre[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) pre[s] = __builtin_nontemporal_load(src + s * 256);
+    u32x4 lpre = lsrc[0];
+    floatx4 acc[NP], tot[NP];
+#pragma unroll
+    for (int b = 0; b < NP; ++b) acc[b] = tot[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const char* base = (const char*)strips[strip] + lr * 16;
+    const uint2* ent = (const uint2*)lst + lg;
+    auto strip_at = [&](uint2 e) { return *(const float*)(base + (e.x & 0xffffu)); };
+    auto weight = [&](uint2 e) { return (int)(e.x >> 16) == lr ? __builtin_bit_cast(float, e.y) : 0.0f; };
+    for (int64_t c = 0; c < C; ++c) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) strips[strip][(4 * part + s) * 64 + lane] = pre[s];
+        if (t < LV) ((u32x4*)lst)[t] = lpre;
+        // the last chunk loads itself again, unread: no branch around the loads
+        const int64_t cn = c + 1 < C ? c + 1 : c;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) pre[s] = __builtin_nontemporal_load(src + cn * (TILE_ELEMS / 4) + s * 256);
+        lpre = lsrc[cn * LV];
+        __syncthreads();
+        const uint32_t* starts = lst + 2 * CL_ENT + part * (CL_NB / CL_PARTS);
+        int q = __builtin_amdgcn_readfirstlane((int)starts[0]);
+        uint2 e0 = ent[CL_PAD * q], e1 = ent[CL_PAD * q + 4], f0 = ent[CL_PAD * q + 8], f1 = ent[CL_PAD * q + 12];
+        float a0 = strip_at(e0), a1 = strip_at(e1);
+#pragma unroll
+        for (int b = 0; b < NP; ++b) {
+            const int end = __builtin_amdgcn_readfirstlane((int)starts[b + 1]);
+            for (; q < end; ++q) {
+                const float x0 = a0, x1 = a1, w0 = weight(e0), w1 = weight(e1);
+                e0 = f0;
+                e1 = f1;
+                a0 = strip_at(e0);
+                a1 = strip_at(e1);
+                f0 = ent[CL_PAD * (q + 2)];
+                f1 = ent[CL_PAD * (q + 2) + 4];
+                acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(x0, w0, acc[b], 0, 0, 0);
+                acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(x1, w1, acc[b], 0, 0, 0);
+            }
+        }
+        if (c + 1 == C || u0 + c + 1 == end_u) {
+            end_u = wg_start(++run + 1, U, Pe);
+#pragma unroll
+            for (int b = 0; b < NP; ++b)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    tot[b][v] += acc[b][v];
+                    acc[b][v] = 0.0f;
+                }
+        }
+        __syncthreads();
+    }
+    const int64_t r0 = (int64_t)tile * TR + 16 * sixteen + 4 * lg;
+#pragma unroll
+    for (int b = 0; b < NP; ++b) {
+        const int col = col0 + 16 * (CL_PARTS * b + part);
+        const int64_t slice = col / w;
+        float* out = M + slice * rows_pad * w + (col - (int)slice * w) + lr;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (r0 + v < n) out[(r0 + v) * w] = tot[b][v];
     }
 }
 
@@ -185,6 +325,7 @@ __global__ __launch_bounds__(KT) void colsq_kernel(const T* __restrict__ M, int6
     const int t = threadIdx.x, groups = KT / w, c = t % w, g = t / w;
     const T* base = M + ((int64_t)s * rows_pad + b * TR) * w;
     double a = 0.0;
+#pragma unroll 16
     for (int r = g; r < TR; r += groups) {
         const double v = (double)base[(int64_t)r * w + c];
         a += v * v;
@@ -206,6 +347,7 @@ __global__ __launch_bounds__(KT) void colnorm_finish_kernel(const double* __rest
     const int64_t col = (int64_t)blockIdx.x * KT + threadIdx.x;
     if (col >= ncol) return;
     double s = 0.0;
+#pragma unroll 16
     for (int64_t b = 0; b < blocks; ++b) s += part[b * ncol + col];
     inv[col] = (col < K && counts[col] > 0 && s > 0.0 && s < INFINITY) ? 1.0 / sqrt(s) : 0.0;
 }
@@ -268,27 +410,63 @@ __device__ inline void block_sum2(double a, int64_t b, double* out_a, int64_t* o
     }
 }
 
+// Four neighbouring lanes take the columns k = 4 q + (0..3) of a row, so that a
+// wave reads whole 16-byte pieces of 16 rows at once; a thread per row read
+// rows 256 bytes apart, one column at a time (n = 20000, K = 141: 47 us, 31 us now).
+// The row with the larger product wins and, among equal ones, the lower index;
+// a NaN never beats another value, but wins from column 0, as in a scan by
+// increasing index.
 template <typename T>
 __global__ __launch_bounds__(KT) void assign_kernel(const T* __restrict__ P, const double* __restrict__ norms,
                                                     int64_t n, int64_t rows_pad, int w, int64_t K,
                                                     int32_t* __restrict__ labels, T* __restrict__ best,
                                                     int32_t* __restrict__ counts, double* __restrict__ jpart,
                                                     int64_t* __restrict__ chpart, int track) {
-    const int64_t i = (int64_t)blockIdx.x * KT + threadIdx.x;
+    __shared__ T bvs[KT];
+    __shared__ int32_t bks[KT];
+    const int t = threadIdx.x, g = t & 3;
+    for (int h = 0; h < 4; ++h) {
+        const int64_t i = (int64_t)blockIdx.x * KT + 64 * h + (t >> 2);
+        T bv = -INFINITY;
+        int32_t bk = -1;
+        if (i < n) {
+            for (int64_t s = 0; s * w < K; ++s) {
+                const int left = (int)min((int64_t)w, K - s * w);
+                const T* row = P + (s * rows_pad + i) * w;
+#pragma unroll 8
+                for (int c = g; c < left; c += 4) {
+                    const T v = row[c];
+                    if (v > bv || (s == 0 && c == 0)) {   // strict: ties keep the lower index
+                        bv = v;
+                        bk = (int32_t)(s * w + c);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int o = 1; o < 4; o <<= 1) {
+            const T ov = __shfl_xor(bv, o, 64);
+            const int32_t ok = __shfl_xor(bk, o, 64);
+            // lane 0's best (column 0 among its columns) is kept if it is NaN
+            const bool nan0 = !(bv == bv), onan = !(ov == ov);
+            const bool take = ok >= 0 && (bk < 0 || onan || (!nan0 && (ov > bv || (ov == bv && ok < bk))));
+            if (take) {
+                bv = ov;
+                bk = ok;
+            }
+        }
+        if (g == 0) {
+            bvs[64 * h + (t >> 2)] = bv;
+            bks[64 * h + (t >> 2)] = bk;
+        }
+    }
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * KT + t;
     double jl = 0.0;
     int64_t ch = 0;
     if (i < n) {
-        T bv = P[i * w];
-        int32_t bk = 0;
-        for (int64_t kk = 1; kk < K; ++kk) {
-            const int64_t s = kk / w;
-            const T v = P[(s * rows_pad + i) * w + (kk - s * w)];
-            if (v > bv) {   // strict: ties keep the lower index
-                bv = v;
-                bk = (int32_t)kk;
-            }
-        }
-        const double cv = (double)bv / norms[i];
+        const int32_t bk = bks[t];
+        const double cv = (double)bvs[t] / norms[i];
         jl = 1.0 - cv;
         ch = (track && labels[i] != bk) ? 1 : 0;   // labels hold the previous assignment only when tracked
         labels[i] = bk;
@@ -469,6 +647,7 @@ struct KCall {
     int64_t n, rows_pad, tiles, chunks, K, w, nsl, ncol;
     bool f64, mfma;
     int64_t esz;
+    bool by_label;           // cluster sums by cluster_sums_kernel
     PlanView pv;
     void* part = nullptr;    // stream partials
     void* img = nullptr;     // chunk images of one slice
@@ -483,6 +662,9 @@ struct KCall {
 
     int64_t factor_elems() const { return nsl * rows_pad * w; }
     int64_t factor_bytes() const { return factor_elems() * esz; }
+    int64_t passes() const { return (K + 16 * CL_NB - 1) / (16 * CL_NB); }
+    // of the label factor W, or of the lists that take its place
+    int64_t weights_bytes() const { return by_label ? passes() * chunks * CL_WORDS * 4 : factor_bytes(); }
     int64_t row_blocks() const { return (n + KT - 1) / KT; }
 };
 
@@ -521,6 +703,11 @@ symnmf_status kcall_setup(symnmf_ctx* ctx, const symnmf_S* S, int64_t K, Scratch
                                                   : (kc.f64 ? 2 : stream_wgs_per_cu(S->dtype, kc.w)));
         part_tiles = (int64_t)kc.pv.P + kc.tiles;
     }
+    // FP32 storage and K > 32: 0.35 ms for up to 192 clusters at n = 20000
+    // against 0.42 .. 0.47 per 64 dense columns; 32 dense columns take 0.29.
+    // BF16 and FP8 products reduce 32 columns in one MFMA, in an order that the
+    // lists could not keep.
+    kc.by_label = S->dtype == SYMNMF_S_FP32 && kc.pv.tall && kc.w == 64;
     kc.part = sc.get(part_tiles * TR * kc.w * kc.esz);
     if (kc.mfma) kc.img = sc.get(h_image_words(S->dtype, kc.w, kc.chunks) * 4);
     kc.norms = (double*)sc.get(kc.rows_pad * 8);
@@ -573,39 +760,61 @@ symnmf_status compute_norms(symnmf_ctx* ctx, KCall& kc, Scratch& sc) {
     return SYMNMF_OK;
 }
 
-// Y = S X for slice-major factors (every slice one stream pass)
+// Y = S X for slice-major factors (every slice one stream pass, the last one of
+// as few columns as the MFMA kernels have for what is left of K)
 hipError_t s_times(const KCall& kc, const void* X, void* Y) {
     const symnmf_S* S = kc.S;
     const bool fp8 = S->dtype == SYMNMF_S_FP8;
+    const float* scale = fp8 ? S->panel_scale : nullptr;
+    const float* diag = fp8 ? S->diag : nullptr;
+    const int64_t pr = S->fp8_panel_rows > 0 ? S->fp8_panel_rows : 1;
     for (int64_t s = 0; s < kc.nsl; ++s) {
         const char* Xs = (const char*)X + s * kc.rows_pad * kc.w * kc.esz;
         char* Ys = (char*)Y + s * kc.rows_pad * kc.w * kc.esz;
+        const int64_t cols = kc.mfma ? mfma_width(std::min(kc.w, kc.K - s * kc.w)) : kc.w;
         hipError_t e = hipSuccess;
-        if (kc.mfma) e = launch_h_image((const float*)Xs, S->dtype, kc.w, 0, kc.chunks, 1.0f, (uint32_t*)kc.img, kc.sm);
+        if (kc.mfma)
+            e = launch_h_image((const float*)Xs, S->dtype, cols, 0, kc.chunks, 1.0f, (uint32_t*)kc.img, kc.sm, kc.w);
         if (e == hipSuccess)
-            e = launch_stream(S->data, S->dtype, S->ld, Xs, kc.f64, kc.w, kc.part, kc.f64, kc.pv, kc.sm, kc.img, kc.img);
+            e = launch_stream(S->data, S->dtype, S->ld, Xs, kc.f64, cols, kc.part, kc.f64, kc.pv, kc.sm, kc.img, kc.img);
         if (e != hipSuccess) return e;
-        const float* scale = fp8 ? S->panel_scale : nullptr;
-        const float* diag = fp8 ? S->diag : nullptr;
-        const int64_t pr = S->fp8_panel_rows > 0 ? S->fp8_panel_rows : 1;
         if (kc.f64)
-            hipLaunchKernelGGL(slice_dense_kernel<double>, dim3((unsigned)kc.tiles), dim3(KT), 0, kc.sm,
-                               (const double*)kc.part, kc.n, (int)kc.w, kc.pv, scale, diag, pr, (const double*)Xs,
-                               (double*)Ys);
+            e = launch_dense_rows((const double*)kc.part, kc.n, cols, cols, kc.pv, (const double*)Xs, kc.w, scale, diag,
+                                  pr, (double*)Ys, kc.sm);
         else
-            hipLaunchKernelGGL(slice_dense_kernel<float>, dim3((unsigned)kc.tiles), dim3(KT), 0, kc.sm,
-                               (const float*)kc.part, kc.n, (int)kc.w, kc.pv, scale, diag, pr, (const float*)Xs,
-                               (float*)Ys);
-        e = hipGetLastError();
+            e = launch_dense_rows((const float*)kc.part, kc.n, cols, cols, kc.pv, (const float*)Xs, kc.w, scale, diag,
+                                  pr, (float*)Ys, kc.sm);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
+// M = S W(labels), W the label factor (or the lists) to be built in W
 template <typename T>
-hipError_t launch_weights_t(const KCall& kc, const int32_t* labels, void* W) {
-    hipLaunchKernelGGL(weights_kernel<T>, dim3(blocks_for(kc.factor_elems())), dim3(KT), 0, kc.sm, labels, kc.norms,
-                       kc.n, kc.rows_pad, (int)kc.w, kc.factor_elems(), (T*)W);
+hipError_t s_times_labels(const KCall& kc, const int32_t* labels, void* W, void* M) {
+    if (!kc.by_label) {
+        hipLaunchKernelGGL(weights_kernel<T>, dim3(blocks_for(kc.factor_elems())), dim3(KT), 0, kc.sm, labels, kc.norms,
+                           kc.n, kc.rows_pad, (int)kc.w, kc.factor_elems(), (T*)W);
+        hipError_t e = hipGetLastError();
+        return e == hipSuccess ? s_times(kc, W, M) : e;
+    }
+    uint32_t* lists = (uint32_t*)W;
+    const dim3 grid((unsigned)(8 * kc.tiles)), block(512);
+    hipLaunchKernelGGL(cluster_lists_kernel, dim3((unsigned)kc.chunks, (unsigned)kc.passes()), dim3(KT), 0, kc.sm,
+                       labels, kc.norms, kc.n, lists);
+    for (int64_t q = 0; q < kc.passes(); ++q) {
+        const int col0 = (int)(16 * CL_NB * q), left = (int)kc.ncol - col0;
+        const uint32_t* ls = lists + q * kc.chunks * CL_WORDS;
+        if (left <= 64)
+            hipLaunchKernelGGL(cluster_sums_kernel<4>, grid, block, 0, kc.sm, (const u32x4*)kc.S->data, kc.pv, ls, kc.n,
+                               kc.rows_pad, (int)kc.w, col0, (float*)M);
+        else if (left <= 128)
+            hipLaunchKernelGGL(cluster_sums_kernel<8>, grid, block, 0, kc.sm, (const u32x4*)kc.S->data, kc.pv, ls, kc.n,
+                               kc.rows_pad, (int)kc.w, col0, (float*)M);
+        else
+            hipLaunchKernelGGL(cluster_sums_kernel<CL_NB>, grid, block, 0, kc.sm, (const u32x4*)kc.S->data, kc.pv, ls,
+                               kc.n, kc.rows_pad, (int)kc.w, col0, (float*)M);
+    }
     return hipGetLastError();
 }
 
@@ -621,8 +830,7 @@ hipError_t launch_counts(const KCall& kc, const int32_t* labels, int lo) {
 // kc.counts must hold the member counts of labels.
 template <typename T>
 hipError_t centroid_step(const KCall& kc, const int32_t* labels, void* W, void* M, const void* Cprev, void* C) {
-    hipError_t e = launch_weights_t<T>(kc, labels, W);
-    if (e == hipSuccess) e = s_times(kc, W, M);
+    hipError_t e = s_times_labels<T>(kc, labels, W, M);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(colsq_kernel<T>, dim3((unsigned)kc.tiles, (unsigned)kc.nsl), dim3(KT), 0, kc.sm, (const T*)M,
                        kc.rows_pad, (int)kc.w, kc.ncol, kc.colpart);
@@ -692,7 +900,7 @@ template <typename T>
 symnmf_status kmeans_run(symnmf_ctx* ctx, KCall& kc, Scratch& sc, const std::vector<int64_t>& rows, double tol,
                          int64_t max_iter, int32_t* labels, void* C_out, symnmf_kmeans_stats* st,
                          std::chrono::steady_clock::time_point t0) {
-    void* W = sc.get(kc.factor_bytes());
+    void* W = sc.get(kc.weights_bytes());
     void* M = sc.get(kc.factor_bytes());
     void* C = sc.get(kc.factor_bytes());
     void* Pb = sc.get(kc.factor_bytes());
@@ -1008,7 +1216,7 @@ symnmf_status symnmf_kmeans_centroids(symnmf_ctx* ctx, const symnmf_S* S, const 
     KCall kc;
     symnmf_status r = kcall_setup(ctx, S, K, sc, kc);
     if (r != SYMNMF_OK) return r;
-    void* W = sc.get(kc.factor_bytes());
+    void* W = sc.get(kc.weights_bytes());
     void* M = sc.get(kc.factor_bytes());
     void* Cs = sc.get(kc.factor_bytes());
     if (sc.err != hipSuccess) return fail(ctx, SYMNMF_ENOMEM, "kmeans_centroids: %s", hipGetErrorString(sc.err));
@@ -1077,7 +1285,7 @@ symnmf_status symnmf_silhouette(symnmf_ctx* ctx, const symnmf_S* S, const int32_
     KCall kc;
     symnmf_status r = kcall_setup(ctx, S, K, sc, kc);
     if (r != SYMNMF_OK) return r;
-    void* W = sc.get(kc.factor_bytes());
+    void* W = sc.get(kc.weights_bytes());
     void* M = sc.get(kc.factor_bytes());
     void* Q = sc.get(kc.factor_bytes());
     double* spart = (double*)sc.get(kc.row_blocks() * 8);
@@ -1093,14 +1301,12 @@ symnmf_status symnmf_silhouette(symnmf_ctx* ctx, const symnmf_S* S, const int32_
     if (present < 2) return fail(ctx, SYMNMF_EINVAL, "silhouette: needs at least two non-empty clusters");
     // M = S W (cluster sums of unit rows), Q = S M; s^_i . m_c = Q_ic / ||s_i||
     if (kc.f64) {
-        HIP_OK(ctx, launch_weights_t<double>(kc, labels, W));
-        HIP_OK(ctx, s_times(kc, W, M));
+        HIP_OK(ctx, s_times_labels<double>(kc, labels, W, M));
         HIP_OK(ctx, s_times(kc, M, Q));
         hipLaunchKernelGGL(silhouette_kernel<double>, dim3((unsigned)kc.row_blocks()), dim3(KT), 0, kc.sm,
                            (const double*)Q, kc.norms, labels, kc.counts, kc.n, kc.rows_pad, (int)kc.w, kc.K, spart);
     } else {
-        HIP_OK(ctx, launch_weights_t<float>(kc, labels, W));
-        HIP_OK(ctx, s_times(kc, W, M));
+        HIP_OK(ctx, s_times_labels<float>(kc, labels, W, M));
         HIP_OK(ctx, s_times(kc, M, Q));
         hipLaunchKernelGGL(silhouette_kernel<float>, dim3((unsigned)kc.row_blocks()), dim3(KT), 0, kc.sm,
                            (const float*)Q, kc.norms, labels, kc.counts, kc.n, kc.rows_pad, (int)kc.w, kc.K, spart);

@@ -235,10 +235,10 @@ __global__ __launch_bounds__(256, 2) void stream_f64_mfma(const double* __restri
 template <int KIND, int K>
 constexpr int image_cols_per_wg() { return K == 64 ? 16 : K; }
 
-// H has k <= K columns; the image's other columns are zero.
+// H has k <= K columns, rows ldh apart; the image's other columns are zero.
 template <int KIND, int K>
-__global__ __launch_bounds__(256) void h_image_kernel(const float* __restrict__ H, int k, int64_t chunk0, float wt,
-                                                      u32x4* __restrict__ img) {
+__global__ __launch_bounds__(256) void h_image_kernel(const float* __restrict__ H, int k, int ldh, int64_t chunk0,
+                                                      float wt, u32x4* __restrict__ img) {
     using IS = ImageShape<KIND, K>;
     constexpr int CB = image_cols_per_wg<KIND, K>();
     constexpr int LDH = CB + 1;                           // padded row: column reads spread over banks
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(256) void h_image_kernel(const float* __restrict__ 
     __shared__ float Hs[KC * LDH];
     const int64_t chunk = chunk0 + blockIdx.x;
     const int blk = blockIdx.y;
-    if (k == K) {
+    if (k == K && ldh == K) {
         const float* src = H + chunk * KC * K + CB * blk;
         for (int q = threadIdx.x; q < KC * CB / 4; q += 256) {
             const int r = q / (CB / 4), c = 4 * (q % (CB / 4));
@@ -260,10 +260,10 @@ __global__ __launch_bounds__(256) void h_image_kernel(const float* __restrict__ 
             d[3] = x.w * wt;
         }
     } else {
-        const float* src = H + chunk * KC * k;
+        const float* src = H + chunk * KC * ldh;
         for (int q = threadIdx.x; q < KC * CB; q += 256) {
             const int r = q / CB, c = CB * blk + q % CB;
-            Hs[r * LDH + q % CB] = c < k ? src[r * k + c] * wt : 0.0f;
+            Hs[r * LDH + q % CB] = c < k ? src[r * ldh + c] * wt : 0.0f;
         }
     }
     __syncthreads();
@@ -302,12 +302,14 @@ int64_t h_image_words(int32_t stype, int64_t k, int64_t n_chunks) {
 }
 
 hipError_t launch_h_image(const float* H, int32_t stype, int64_t k, int64_t chunk0, int64_t n_chunks, float wt,
-                          uint32_t* img, hipStream_t stream) {
-    if (k < 1 || k > KMAX || n_chunks < 1) return hipErrorInvalidValue;
+                          uint32_t* img, hipStream_t stream, int64_t ldh) {
+    if (ldh == 0) ldh = k;
+    if (k < 1 || k > KMAX || n_chunks < 1 || ldh < k || ldh > KMAX) return hipErrorInvalidValue;
     const int64_t kw = mfma_width(k);
     dim3 grid(n_chunks, kw == 64 ? 4 : 1), block(256);
 #define IMG(KIND, KK) \
-    hipLaunchKernelGGL((h_image_kernel<KIND, KK>), grid, block, 0, stream, H, (int)k, chunk0, wt, (u32x4*)img)
+    hipLaunchKernelGGL((h_image_kernel<KIND, KK>), grid, block, 0, stream, H, (int)k, (int)ldh, chunk0, wt, \
+                       (u32x4*)img)
     if (stype == SYMNMF_S_FP32) {
         if (kw == 16) IMG(0, 16); else if (kw == 32) IMG(0, 32); else IMG(0, 64);
     } else if (stype == SYMNMF_S_BF16) {
@@ -888,6 +890,67 @@ hipError_t launch_stream(const void* S, int32_t stype, int64_t ld, const void* H
     }
     return hipErrorInvalidValue;
 }
+
+// ---------------------------------------------------------------------------
+// Dense product rows from the partial tiles of a full pass, summed over the
+// work-groups that streamed each tile in increasing order.  32 rows to a
+// work-group and eight elements to a thread, the loads of all of them issued
+// together for every partial: with a 256-row tile to a work-group, its
+// elements one after another, n = 20000 (79 tiles, 64 columns, 39 MB) was 64
+// dependent steps on 79 CUs and took 133 us; 8 us now.
+// ---------------------------------------------------------------------------
+constexpr int DENSE_ROWS = 32, DENSE_NE = 8;
+
+template <typename T>
+__global__ __launch_bounds__(256) void dense_rows_kernel(const T* __restrict__ part, int64_t rows, int k, int kp,
+                                                         PlanView p, const T* __restrict__ X, int64_t ldo,
+                                                         const float* __restrict__ scale,
+                                                         const float* __restrict__ diag, int64_t panel_rows,
+                                                         T* __restrict__ out) {
+    const int32_t tile = blockIdx.x / (TR / DENSE_ROWS);
+    const int r0 = (int)(blockIdx.x % (TR / DENSE_ROWS)) * DENSE_ROWS;
+    int64_t w_lo, w_hi, sb, sm;
+    partial_slots(p, tile, w_lo, w_hi, sb, sm);
+    const int64_t row0 = (int64_t)tile * TR + r0;
+    for (int f0 = threadIdx.x; f0 < DENSE_ROWS * k; f0 += 256 * DENSE_NE) {
+        int r[DENSE_NE], c[DENSE_NE];
+        T s[DENSE_NE];
+#pragma unroll
+        for (int e = 0; e < DENSE_NE; ++e) {
+            const int f = min(f0 + 256 * e, DENSE_ROWS * k - 1);
+            r[e] = f / k;
+            c[e] = f - r[e] * k;
+            s[e] = 0;
+        }
+        for (int64_t q = w_lo; q <= w_hi; ++q) {
+            const T* pq = part + ((sm * q + sb) * TR + r0) * (int64_t)kp;
+#pragma unroll
+            for (int e = 0; e < DENSE_NE; ++e) s[e] += pq[r[e] * kp + c[e]];
+        }
+#pragma unroll
+        for (int e = 0; e < DENSE_NE; ++e) {
+            const int64_t row = row0 + r[e];
+            if (f0 + 256 * e >= DENSE_ROWS * k || row >= rows) continue;
+            T v = s[e];
+            if (scale) v = v / (T)scale[row / panel_rows] + (T)diag[row] * X[row * ldo + c[e]];
+            out[row * ldo + c[e]] = v;
+        }
+    }
+}
+
+template <typename T>
+hipError_t launch_dense_rows(const T* part, int64_t rows, int64_t k, int64_t kp, const PlanView& p, const T* X,
+                             int64_t ldo, const float* scale, const float* diag, int64_t panel_rows, T* out,
+                             hipStream_t stream) {
+    if (!p.full || k < 1 || k > kp || ldo < k || rows > (int64_t)p.n_tiles * TR) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(dense_rows_kernel<T>, dim3((unsigned)p.n_tiles * (TR / DENSE_ROWS)), dim3(256), 0, stream, part,
+                       rows, (int)k, (int)kp, p, X, ldo, scale, diag, panel_rows, out);
+    return hipGetLastError();
+}
+template hipError_t launch_dense_rows<float>(const float*, int64_t, int64_t, int64_t, const PlanView&, const float*,
+                                             int64_t, const float*, const float*, int64_t, float*, hipStream_t);
+template hipError_t launch_dense_rows<double>(const double*, int64_t, int64_t, int64_t, const PlanView&, const double*,
+                                              int64_t, const float*, const float*, int64_t, double*, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Device self-check of the FP8 -> BF16 conversion instruction against the

@@ -27,37 +27,6 @@ hipError_t launch_omega(uint64_t seed, int64_t n, int64_t rows_alloc, int w, flo
     return hipGetLastError();
 }
 
-// Dense S.H rows from the partials of a full pass (FP32 partials), FP8 scale
-// and diagonal applied: out (rows x k).
-__global__ __launch_bounds__(256) void sh_dense_kernel(const float* __restrict__ part, int64_t rows, int k, int kp,
-                                                       int32_t n_tiles, int32_t n_chunks, int32_t P,
-                                                       const float* __restrict__ H, int64_t row0,
-                                                       const float* __restrict__ scale, const float* __restrict__ diag,
-                                                       int64_t panel_rows, float* __restrict__ out) {
-    const int64_t tile = blockIdx.x;
-    const int64_t U = (int64_t)n_tiles * n_chunks;
-    const int64_t Pe = U < P ? U : P;
-    const int64_t w_lo = wg_owner(tile * n_chunks, U, Pe);
-    const int64_t w_hi = wg_owner((tile + 1) * n_chunks - 1, U, Pe);
-    for (int f = threadIdx.x; f < TR * k; f += 256) {
-        const int r = f / k, c = f - r * k;
-        const int64_t prow = tile * TR + r;
-        if (prow >= rows) continue;
-        float s = 0.0f;
-        for (int64_t w = w_lo; w <= w_hi; ++w) s += part[((w + tile) * TR + r) * (int64_t)kp + c];
-        if (scale) s = s / scale[prow / panel_rows] + diag[prow] * H[(row0 + prow) * k + c];
-        out[prow * k + c] = s;
-    }
-}
-
-hipError_t launch_sh_dense(const float* part, int64_t rows, int64_t rows_pad, int64_t k, int64_t kp, int32_t n_chunks, int32_t P,
-                           const float* H, int64_t row0, const float* scale, const float* diag, int64_t panel_rows,
-                           float* out, hipStream_t stream) {
-    hipLaunchKernelGGL(sh_dense_kernel, dim3(rows_pad / TR), dim3(256), 0, stream, part, rows, (int)k, (int)kp,
-                       (int32_t)(rows_pad / TR), n_chunks, P, H, row0, scale, diag, panel_rows, out);
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // Small dense GEMM, FP32 accumulation: C (M x N) = alpha op(A) op(B) + bias,
 // then an epilogue.  A: TA = 0 -> M x K row-major, TA = 1 -> K x M.

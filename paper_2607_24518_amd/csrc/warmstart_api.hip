@@ -355,9 +355,10 @@ symnmf_status symnmf_sketch(symnmf_ctx* ctx, const symnmf_S* S, uint64_t omega_s
         chk(launch_h_image((const float*)Om, S->dtype, width, 0, chunks, 1.0f, (uint32_t*)img, sm));
         PlanView pv = plan_view(nullptr, 1, (int32_t)tiles, (int32_t)chunks, P);
         chk(launch_stream(S->data, S->dtype, S->ld, Om, 0, width, part, 0, pv, sm, img, img));
-        chk(launch_sh_dense((const float*)part, S->rows, S->rows_pad, width, mfma_width(width), (int32_t)chunks, P, (const float*)Om,
-                            S->row0, S->dtype == SYMNMF_S_FP8 ? S->panel_scale : nullptr, S->diag,
-                            S->fp8_panel_rows > 0 ? S->fp8_panel_rows : 1, Y, sm));
+        chk(launch_dense_rows((const float*)part, S->rows, width, mfma_width(width), pv,
+                              (const float*)Om + S->row0 * width, width,
+                              S->dtype == SYMNMF_S_FP8 ? S->panel_scale : nullptr, S->diag,
+                              S->fp8_panel_rows > 0 ? S->fp8_panel_rows : 1, Y, sm));
         chk(hipStreamSynchronize(sm));
     }
     if (e != hipSuccess) return fail(ctx, SYMNMF_EDEVICE, "sketch: %s", hipGetErrorString(e));
