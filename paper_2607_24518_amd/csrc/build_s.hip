@@ -17,7 +17,9 @@
 namespace symnmf {
 
 // ---------------------------------------------------------------------------
-// |corr|: standardised columns
+// |corr|: standardised columns.  Three passes over a column block (the second
+// and third from the caches), 16 loads in flight per thread: 0.16 ms at n =
+// 20000, T = 2500, 0.73 ms with one.
 // ---------------------------------------------------------------------------
 template <typename ZT>
 __global__ __launch_bounds__(256) void standardise_kernel(const float* __restrict__ X, int64_t T, int64_t n,
@@ -29,6 +31,7 @@ __global__ __launch_bounds__(256) void standardise_kernel(const float* __restric
     const bool valid = col < n;
     double s = 0.0;
     if (valid)
+#pragma unroll 16
         for (int64_t t = ph; t < T; t += 4) s += (double)X[t * n + col];
     red[ph][lc] = s;
     __syncthreads();
@@ -36,6 +39,7 @@ __global__ __launch_bounds__(256) void standardise_kernel(const float* __restric
     __syncthreads();
     double ss = 0.0;
     if (valid)
+#pragma unroll 16
         for (int64_t t = ph; t < T; t += 4) {
             const double d = (double)X[t * n + col] - mean;
             ss += d * d;
@@ -52,6 +56,7 @@ __global__ __launch_bounds__(256) void standardise_kernel(const float* __restric
         if (ph == 0) atomicAdd(bad, 1);
         return;
     }
+#pragma unroll 16
     for (int64_t t = ph; t < T; t += 4) Z[t * ldz + col] = (ZT)(((double)X[t * n + col] - mean) / c);
 }
 
@@ -67,6 +72,18 @@ __global__ __launch_bounds__(256) void check_input_kernel(const float* __restric
     }
     if (nonfinite) atomicOr(flag, BAD_NONFINITE);
     if (negative) atomicOr(flag, BAD_NEGATIVE);
+}
+
+__global__ __launch_bounds__(256) void zero_pads_kernel(uint32_t* __restrict__ Z, int64_t K, int64_t first,
+                                                        int64_t end) {
+    const int64_t row = blockIdx.x;
+    for (int64_t c = (row < K ? first : 0) + threadIdx.x; c < end; c += 256) Z[row * end + c] = 0;
+}
+
+hipError_t launch_zero_pads(void* Z, int64_t K, int64_t Kpad, int64_t n, int64_t ldz, int words, hipStream_t stream) {
+    hipLaunchKernelGGL(zero_pads_kernel, dim3((unsigned)Kpad), dim3(256), 0, stream, (uint32_t*)Z, K, n * words,
+                       ldz * words);
+    return hipGetLastError();
 }
 
 hipError_t launch_standardise(const float* X, int64_t T, int64_t n, void* Z, int z_f64, int64_t ldz, int32_t* bad,
@@ -548,14 +565,54 @@ hipError_t launch_tpdm_omega(const float* X, int64_t T, int64_t n, int lower, in
     return hipGetLastError();
 }
 
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// A full square S (no row panel) is symmetric, so the S-building GEMMs
+// compute only the 128 x 128 tiles with ti <= tj; the work-group of an
+// off-diagonal tile also stores its transpose.  The transposed value is
+// bitwise the one the (tj, ti) tile would compute: the products commute and
+// the reduction runs over the same samples in the same order.
+__host__ __device__ inline bool syrk_symmetric(const BuildOut& o) { return o.row0 == 0 && o.rows == o.n; }
+
 // XCD-aware order of the 128 x 128 output tiles of the S-building GEMMs.
-// Work-groups are dispatched round-robin over the 8 XCDs, so the 64 work-groups
-// w = x + 8 (64 g + q), q = 0..63, all land on XCD x; they take the 8 x 8 block
-// of tiles number 8 g + x (in row-major order of 8 x 8 blocks), and per K slab
-// read 8 row blocks and 8 column blocks of Z through that XCD's L2 instead of
-// one row block and 64 column blocks.  False for the padding work-groups.
-__device__ inline bool syrk_tile(int64_t w, int64_t n_ti, int64_t n_tj, int64_t& ti, int64_t& tj) {
+// Work-groups are dispatched round-robin over the 8 XCDs; the 64 that an XCD
+// runs at a time take an 8 x 8 block of tiles and so read, per K slab, 8 row
+// blocks and 8 column blocks of Z through that XCD's L2 instead of one row
+// block and 64 column blocks.
+// Symmetric: the tiles on and above the diagonal, block rows of 8 tile rows,
+// each block by block, are numbered and cut into 8 equal runs, one per XCD.
+// (Dealing whole blocks to the XCDs, the empty ones below the diagonal among
+// them, gave the busiest XCD 1.09 times its share of tiles at n = 20000, 1.9
+// times at n = 4096 and 8000.)  Otherwise block number 8 g + x (row-major) goes
+// to XCD x.  False for the padding work-groups.
+__device__ inline bool syrk_tile(int64_t w, bool sym, int64_t n_ti, int64_t n_tj, int64_t& ti, int64_t& tj) {
     const int64_t x = w & 7, l = w >> 3;
+    if (sym) {
+        const int64_t N = n_ti, A = N * (N + 1) / 2;
+        int64_t a = x * A / 8 + l;
+        if (a >= (x + 1) * A / 8) return false;
+        int64_t i0 = 0, R = min(N, (int64_t)8);           // block row: tile rows i0 .. i0 + R - 1
+        for (;;) {
+            const int64_t in_row = R * (N - i0) - R * (R - 1) / 2;
+            if (a < in_row) break;
+            a -= in_row;
+            i0 += R;
+            R = min(N - i0, (int64_t)8);
+        }
+        const int64_t diag = R * (R + 1) / 2;
+        if (a < diag) {                                    // block on the diagonal, its rows one after another
+            int64_t r = 0;
+            while (a >= R - r) a -= R - r++;
+            ti = i0 + r;
+            tj = i0 + r + a;
+        } else {
+            a -= diag;
+            const int64_t c0 = i0 + R + a / (8 * R) * 8, q = a % (8 * R), W = min(N - c0, (int64_t)8);
+            ti = i0 + q / W;
+            tj = c0 + q % W;
+        }
+        return true;
+    }
     const int64_t blk = (l >> 6) * 8 + x, q = l & 63;
     const int64_t bcols = (n_tj + 7) >> 3;
     const int64_t br = blk / bcols, bc = blk - br * bcols;
@@ -563,20 +620,11 @@ __device__ inline bool syrk_tile(int64_t w, int64_t n_ti, int64_t n_tj, int64_t&
     tj = bc * 8 + (q & 7);
     return ti < n_ti && tj < n_tj;
 }
-inline int64_t syrk_grid(int64_t n_ti, int64_t n_tj) {
+inline int64_t syrk_grid(const BuildOut& o, int64_t n_ti, int64_t n_tj) {
+    if (syrk_symmetric(o)) return (n_ti * (n_ti + 1) / 2 + 7) / 8 * 8;
     const int64_t blocks = ((n_ti + 7) >> 3) * ((n_tj + 7) >> 3);
     return (blocks + 7) / 8 * 8 * 64;
 }
-
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-// A full square S (no row panel) is symmetric, so the S-building GEMMs
-// compute only the 128 x 128 tiles with ti <= tj; the work-group of an
-// off-diagonal tile also stores its transpose.  The transposed value is
-// bitwise the one the (tj, ti) tile would compute: the products commute and
-// the reduction runs over the same samples in the same order.  Work-groups of
-// tiles below the diagonal only clear their sum slot.
-__device__ inline bool syrk_symmetric(const BuildOut& o) { return o.row0 == 0 && o.rows == o.n; }
 
 // Epilogue of the S-building GEMMs: |.|, unit diagonal, storage rounding into
 // the tiled layout, FP64 sums per work-group (MODE 1), or the FP8 panel
@@ -763,23 +811,30 @@ __device__ __attribute__((always_inline)) inline void syrk_epilogue(const floatx
 // output tile per work-group (2 x 2 waves of 64 x 64), K in steps of 16.
 // MODE 0 only finds the largest off-diagonal |S| of every FP8 scale panel;
 // MODE 1 stores and sums.
+// Bound by the FP32 matrix cores: n = 20000, T = 2500 (1.02 TFLOP) takes 7.8 ms,
+// 131 TFLOP/s.  A thread moves 16 bytes at a time, rows of LDS are 144 floats
+// apart so that the four lane groups of an operand read fall on disjoint banks,
+// and 128 registers leave room for four work-groups on a CU; with loads of four
+// bytes, rows of 132 and the uneven order of tiles it took 10.9 ms.
 // ---------------------------------------------------------------------------
+constexpr int SYRK_KS = 16;
+// 16 bytes of four-byte alignment (a row panel may start at any column of Z)
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+
 template <int MODE, int DT>
 __global__ __launch_bounds__(256, 2) void syrk_kernel(const float* __restrict__ Z, int64_t K, int64_t ldz, BuildOut o,
                                                    int64_t n_ti, int64_t n_tj, double* __restrict__ wg_sums,
                                                    uint32_t* __restrict__ panel_max) {
-    __shared__ float As[2][16][128 + 4];
-    __shared__ float Bs[2][16][128 + 4];
+    __shared__ __align__(16) float As[2][SYRK_KS][128 + 16];
+    __shared__ __align__(16) float Bs[2][SYRK_KS][128 + 16];
     __shared__ uint32_t tab[256];
     __shared__ double inv[(MODE == 1 && DT == SYMNMF_S_FP8) ? 256 : 1];
     __shared__ double red[3][4];
     int64_t ti, tj;
-    if (!syrk_tile(blockIdx.x, n_ti, n_tj, ti, tj)) return;
     const bool sym = syrk_symmetric(o);
-    if (sym && ti > tj) {
-        if (MODE == 1 && threadIdx.x < 3) wg_sums[(ti * n_tj + tj) * 3 + threadIdx.x] = 0.0;
-        return;
-    }
+    if (!syrk_tile(blockIdx.x, sym, n_ti, n_tj, ti, tj)) return;
+    // the sum slot of the mirrored tile
+    if (MODE == 1 && sym && ti < tj && threadIdx.x < 3) wg_sums[(tj * n_tj + ti) * 3 + threadIdx.x] = 0.0;
     const int64_t i0 = ti * 128, j0 = tj * 128;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int wr = wv >> 1, wc = wv & 1, lr = lane & 15, lg = lane >> 4;
@@ -792,35 +847,31 @@ __global__ __launch_bounds__(256, 2) void syrk_kernel(const float* __restrict__ 
     const float* Zb = Z + j0;
     // the next K slab is loaded into registers while the current one is
     // multiplied; LDS is double buffered, so one barrier per slab suffices
-    float ra[8], rb[8];
+    constexpr int NV = SYRK_KS / 8;               // 16-byte vectors per thread, side and slab
+    const int kk0 = t >> 5, ii = 4 * (t & 31);
+    float4u ra[NV], rb[NV];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int f = t + 256 * q;
-        const int kk = f >> 7, ii = f & 127;
-        ra[q] = Za[kk * ldz + ii];
-        rb[q] = Zb[kk * ldz + ii];
+    for (int q = 0; q < NV; ++q) {
+        ra[q] = *(const float4u*)(Za + (kk0 + 8 * q) * ldz + ii);
+        rb[q] = *(const float4u*)(Zb + (kk0 + 8 * q) * ldz + ii);
     }
-    for (int64_t k0 = 0; k0 < K; k0 += 16) {
-        const int buf = (int)((k0 >> 4) & 1);
+    for (int64_t k0 = 0; k0 < K; k0 += SYRK_KS) {
+        const int buf = (int)((k0 / SYRK_KS) & 1);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int f = t + 256 * q;
-            const int kk = f >> 7, ii = f & 127;
-            As[buf][kk][ii] = ra[q];
-            Bs[buf][kk][ii] = rb[q];
+        for (int q = 0; q < NV; ++q) {
+            *(floatx4*)&As[buf][kk0 + 8 * q][ii] = ra[q];
+            *(floatx4*)&Bs[buf][kk0 + 8 * q][ii] = rb[q];
         }
         __syncthreads();
-        if (k0 + 16 < K) {
+        // the last slab loads itself again, unused: no branch around the loads
+        const int64_t kn = k0 + SYRK_KS < K ? k0 + SYRK_KS : k0;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int f = t + 256 * q;
-                const int kk = f >> 7, ii = f & 127;
-                ra[q] = Za[(k0 + 16 + kk) * ldz + ii];
-                rb[q] = Zb[(k0 + 16 + kk) * ldz + ii];
-            }
+        for (int q = 0; q < NV; ++q) {
+            ra[q] = *(const float4u*)(Za + (kn + kk0 + 8 * q) * ldz + ii);
+            rb[q] = *(const float4u*)(Zb + (kn + kk0 + 8 * q) * ldz + ii);
         }
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int s = 0; s < SYRK_KS / 4; ++s) {
             const int kk = 4 * s + lg;
             float av[4], bv[4];
 #pragma unroll
@@ -893,12 +944,10 @@ __global__ __launch_bounds__(256, 2) void syrk_split_kernel(const uint16_t* __re
     __shared__ double inv[(MODE == 1 && DT == SYMNMF_S_FP8) ? 256 : 1];
     __shared__ double red[3][4];
     int64_t ti, tj;
-    if (!syrk_tile(blockIdx.x, n_ti, n_tj, ti, tj)) return;
     const bool sym = syrk_symmetric(o);
-    if (sym && ti > tj) {
-        if (MODE == 1 && threadIdx.x < 3) wg_sums[(ti * n_tj + tj) * 3 + threadIdx.x] = 0.0;
-        return;
-    }
+    if (!syrk_tile(blockIdx.x, sym, n_ti, n_tj, ti, tj)) return;
+    // the sum slot of the mirrored tile
+    if (MODE == 1 && sym && ti < tj && threadIdx.x < 3) wg_sums[(tj * n_tj + ti) * 3 + threadIdx.x] = 0.0;
     const int64_t i0 = ti * 128, j0 = tj * 128;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int wr = wv >> 1, wc = wv & 1, lr = lane & 15, lg = lane >> 4;
@@ -1056,7 +1105,7 @@ hipError_t launch_syrk_store(const void* Zv, int z_f64, int64_t K, int64_t ldz, 
     if (o.dtype == SYMNMF_S_FP64) return hipErrorInvalidValue;
     const float* Z = (const float*)Zv;
     const int64_t n_ti = o.rows_pad / 128, n_tj = o.ld / 128;
-    dim3 grid(syrk_grid(n_ti, n_tj)), block(256);
+    dim3 grid(syrk_grid(o, n_ti, n_tj)), block(256);
     const int64_t wgs = n_ti * n_tj;
     double* wg_sums = sums + 4;
     if (o.dtype == SYMNMF_S_FP8) {
@@ -1086,7 +1135,7 @@ hipError_t launch_syrk_split_store(const float* Z, int64_t K, int64_t ldz, const
     uint16_t* P = (uint16_t*)ws;
     hipLaunchKernelGGL(split_planes_kernel, dim3(ldz / 64, Kp / 32), dim3(256), 0, stream, Z, K, ldz, Kp, P);
     const int64_t n_ti = o.rows_pad / 128, n_tj = o.ld / 128;
-    dim3 grid(syrk_grid(n_ti, n_tj)), block(256);
+    dim3 grid(syrk_grid(o, n_ti, n_tj)), block(256);
     const int64_t wgs = n_ti * n_tj;
     double* wg_sums = sums + 4;
     if (o.dtype == SYMNMF_S_FP8) {

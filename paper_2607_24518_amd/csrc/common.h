@@ -414,6 +414,8 @@ struct BuildOut {
 // zero-variance columns.
 constexpr int32_t BAD_NONFINITE = 1 << 30;
 constexpr int32_t BAD_NEGATIVE = 1 << 29;
+// zeros in columns n .. ldz - 1 of rows < K and in rows K .. Kpad - 1 of Z (words 32-bit words per element)
+hipError_t launch_zero_pads(void* Z, int64_t K, int64_t Kpad, int64_t n, int64_t ldz, int words, hipStream_t stream);
 hipError_t launch_standardise(const float* X, int64_t T, int64_t n, void* Z, int z_f64, int64_t ldz, int32_t* bad,
                               hipStream_t stream);
 // TPDM: Omega (n_exc x ldz, FP32 or FP64) = column-normalised angular rows; raises the input
