@@ -534,10 +534,13 @@ hipError_t launch_gram3(const float* A, const float* B, int64_t k, int64_t m, do
 // eigenvalue is not positive and finite, 2 when the sweeps do not converge.
 // A serial chain of about 600 rounds: bound by the latency of a round.  With 32
 // pairs a thread owns the 2 x 2 block of two pairs, so J^T A J is one read and
-// one write per entry and a round has two barriers (rotations; update of A and
-// V), A and V both in LDS.  Updating rows and columns in turn with V in global
-// memory and four barriers a round, the norm and the selection on one thread,
-// took 5.13 ms at w = 64; this takes 1.07 ms.
+// one write per entry and a round has two barriers (rotations; update of A), A
+// and V both in LDS; V, which no rotation depends on, is updated by the other
+// waves while one wave computes the next round's rotations (a chain of three
+// divisions and two square roots).  Updating rows and columns in turn with V
+// in global memory and four barriers a round, the norm and the selection on one
+// thread, took 5.13 ms at w = 64; V in the phase of A 1.07 ms; this takes
+// 0.75 ms.
 // ---------------------------------------------------------------------------
 constexpr int JT = 1024;
 
@@ -549,8 +552,8 @@ __global__ __launch_bounds__(JT) void jacobi_topk_kernel(const double* __restric
     __shared__ int order[KMAX];
     __shared__ int rotated, bad;
     __shared__ double red[JT / 64];
-    __shared__ double cs_s[KMAX / 2], sn_s[KMAX / 2];
-    __shared__ int p_s[KMAX / 2], q_s[KMAX / 2];
+    __shared__ double2 rot[2][KMAX / 2];     // (cos, sin) of every pair, of this round and the one before
+    __shared__ int2 pair[2][KMAX / 2];
     const int t = threadIdx.x;
     const int wp = w + (w & 1);    // even player count; index w (odd w) is a bye: a zero row and column
     const int half = wp / 2;
@@ -574,17 +577,41 @@ __global__ __launch_bounds__(JT) void jacobi_topk_kernel(const double* __restric
     fro = 0.0;
     for (int q = 0; q < JT / 64; ++q) fro += red[q];
     const double floor_abs = 1e-15 * sqrt(fro);
-    int sweep = 0;
+    const int bi = t / half, bj = t - bi * half;           // the thread's block of A
+    int sweep = 0, round = 0;
+    // V <- V J with the rotations of a round, by threads first, first + 1, ...
+    auto rotate_v = [&](int cur, int first) {
+        if (t < first) return;
+        int row = (t - first) % w, pr = (t - first) / w;
+        const int drow = (JT - first) % w, dpr = (JT - first) / w;
+        while (pr < half) {
+            const double2 cs = rot[cur][pr];
+            if (cs.y != 0.0) {
+                const int2 pq = pair[cur][pr];
+                const double vp = V[row][pq.x], vq = V[row][pq.y];
+                V[row][pq.x] = cs.x * vp - cs.y * vq;
+                V[row][pq.y] = cs.y * vp + cs.x * vq;
+            }
+            row += drow;
+            pr += dpr;
+            if (row >= w) {
+                row -= w;
+                ++pr;
+            }
+        }
+    };
     for (; sweep < 60; ++sweep) {
         if (t == 0) rotated = 0;
         __syncthreads();
-        for (int r = 0; r < wp - 1; ++r) {
+        for (int r = 0; r < wp - 1; ++r, ++round) {
             // pair i of round r: (wp-1, r) for i = 0, else ((r+i) mod (wp-1), (r-i) mod (wp-1));
             // every rotation is computed from the block before any row is changed
+            const int cur = round & 1;
             if (t < half) {
-                int p, q;
-                if (t == 0) { p = wp - 1; q = r; }
-                else { p = (r + t) % (wp - 1); q = (r - t + (wp - 1)) % (wp - 1); }
+                int p = r + t, q = r - t;
+                if (p >= wp - 1) p -= wp - 1;
+                if (q < 0) q += wp - 1;
+                if (t == 0) p = wp - 1;
                 if (p > q) { const int tmp = p; p = q; q = tmp; }
                 double c = 1.0, sn = 0.0;
                 const double apq = A[p][q], app = A[p][p], aqq = A[q][q];
@@ -595,31 +622,26 @@ __global__ __launch_bounds__(JT) void jacobi_topk_kernel(const double* __restric
                     c = 1.0 / sqrt(1.0 + tt * tt);
                     sn = tt * c;
                 }
-                cs_s[t] = c; sn_s[t] = sn; p_s[t] = p; q_s[t] = q;
+                rot[cur][t] = double2{c, sn};
+                pair[cur][t] = int2{p, q};
+            } else if (round > 0) {
+                rotate_v(cur ^ 1, 64);                     // of the round before
             }
             __syncthreads();
-            // A <- J^T A J by 2 x 2 blocks, V <- V J
-            for (int f = t; f < half * half; f += JT) {
-                const int bi = f / half, bj = f - bi * half;
-                const double ci = cs_s[bi], si = sn_s[bi], cj = cs_s[bj], sj = sn_s[bj];
-                if (si == 0.0 && sj == 0.0) continue;
-                const int pi = p_s[bi], qi = q_s[bi], pj = p_s[bj], qj = q_s[bj];
-                const double a = A[pi][pj], b = A[pi][qj], c = A[qi][pj], d = A[qi][qj];
-                const double ra = ci * a - si * c, rb = ci * b - si * d;
-                const double rc = si * a + ci * c, rd = si * b + ci * d;
-                A[pi][pj] = cj * ra - sj * rb;
-                A[pi][qj] = sj * ra + cj * rb;
-                A[qi][pj] = cj * rc - sj * rd;
-                A[qi][qj] = sj * rc + cj * rd;
-            }
-            for (int f = t; f < half * w; f += JT) {
-                const int bj = f / w, row = f - bj * w;
-                const double c = cs_s[bj], sn = sn_s[bj];
-                if (sn == 0.0) continue;
-                const int p = p_s[bj], q = q_s[bj];
-                const double vp = V[row][p], vq = V[row][q];
-                V[row][p] = c * vp - sn * vq;
-                V[row][q] = sn * vp + c * vq;
+            // A <- J^T A J by 2 x 2 blocks
+            if (bi < half) {
+                const double2 ri = rot[cur][bi], rj = rot[cur][bj];
+                const double ci = ri.x, si = ri.y, cj = rj.x, sj = rj.y;
+                if (si != 0.0 || sj != 0.0) {
+                    const int2 i = pair[cur][bi], j = pair[cur][bj];
+                    const double a = A[i.x][j.x], b = A[i.x][j.y], c = A[i.y][j.x], d = A[i.y][j.y];
+                    const double ra = ci * a - si * c, rb = ci * b - si * d;
+                    const double rc = si * a + ci * c, rd = si * b + ci * d;
+                    A[i.x][j.x] = cj * ra - sj * rb;
+                    A[i.x][j.y] = sj * ra + cj * rb;
+                    A[i.y][j.x] = cj * rc - sj * rd;
+                    A[i.y][j.y] = sj * rc + cj * rd;
+                }
             }
             __syncthreads();
         }
@@ -627,6 +649,8 @@ __global__ __launch_bounds__(JT) void jacobi_topk_kernel(const double* __restric
         __syncthreads();
         if (!any) break;
     }
+    if (round > 0) rotate_v((round - 1) & 1, 0);
+    __syncthreads();
     // place of every eigenvalue in descending order, lower index first on ties
     if (t < w) {
         const double l = A[t][t];
