@@ -444,20 +444,17 @@ hipError_t launch_objective_tiles(const UpdateArgs& a, int h_f64, const PlanView
 
 // warmstart.hip
 hipError_t launch_omega(uint64_t seed, int64_t n, int64_t rows_alloc, int w, float* out, hipStream_t stream);
-// C = alpha op(A) op(B) + bias with epilogue (0 none, 1 GELU, 2 softplus); Z: pre-epilogue copy
-// or null.  splits > 1 (a value of gemm_splits; no bias, epilogue or Z): C holds that many M x N
-// partials, one per range of K.
+// C = op(A) op(B) + bias with epilogue (0 none, 1 GELU, 2 softplus, 3 max(aux + x, 0), 4 x GELU'(aux)
+// with FP64 column sums over every 64 rows in part, gemm_row_blocks(M) x N); aux: M x N, rows ldaux
+// apart; Z: pre-epilogue copy or null.  splits > 1 (a value of gemm_splits; no bias, epilogue or
+// Z): C holds that many M x N partials, one per range of K.
 hipError_t launch_gemm(int ta, int tb, int b_bf16, int epi, const float* A, const void* B, const float* bias, float* C,
-                       float* Z, int64_t M, int64_t N, int64_t K, float alpha, int64_t splits, hipStream_t stream);
+                       float* Z, int64_t M, int64_t N, int64_t K, int64_t splits, hipStream_t stream,
+                       const float* aux = nullptr, int64_t ldaux = 0, double* part = nullptr);
 int64_t gemm_splits(int64_t M, int64_t N, int64_t K);
 // the most gemm_splits returns for any K
 int64_t gemm_max_splits(int64_t M, int64_t N);
-// dZ = dA * GELU'(Z), part: bias_blocks(m) x ncol FP64 column sums of dZ
-hipError_t launch_gelu_backward(const float* dA, const float* Z, float* dZ, int64_t m, int64_t ncol, double* part,
-                                hipStream_t stream);
-int64_t bias_blocks(int64_t m);
-// residual output A = max(C + z, 0) (A holds z on entry; C = first k columns of X)
-hipError_t launch_residual_relu(const float* X, int64_t ldx, float* A, int64_t rows, int64_t k, hipStream_t stream);
+int64_t gemm_row_blocks(int64_t M);
 // Partials of the parameters' gradient: weights (W1, W2, W3) as split-K partials, biases (b1, b2,
 // b3) as FP64 row-block sums.
 struct GradParts {

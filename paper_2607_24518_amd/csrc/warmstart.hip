@@ -28,30 +28,75 @@ hipError_t launch_omega(uint64_t seed, int64_t n, int64_t rows_alloc, int w, flo
 }
 
 // ---------------------------------------------------------------------------
-// Small dense GEMM, FP32 accumulation: C (M x N) = alpha op(A) op(B) + bias,
-// then an epilogue.  A: TA = 0 -> M x K row-major, TA = 1 -> K x M.
-// B: TB = 0 -> N x K row-major (used transposed), TB = 1 -> K x N.
-// B may hold bf16 values (the network weights at inference).  64 x 64 output
-// tile, K step 16 staged in LDS; each of the four waves computes a 32 x 32
-// quarter as 2 x 2 blocks of v_mfma_f32_16x16x4_f32 (FP32 products and
-// accumulation: the bf16 weights are widened exactly).  blockIdx.z splits K
-// into ranges of kchunk: with more than one range every range writes its own
-// partial C + z M N (no bias, no epilogue), summed in order by the kernel that
-// applies the gradient.
-// EPI: 0 none, 1 GELU x Phi(x) (Phi from erfc), 2 softplus.  Z (optional)
+// Small dense GEMM, FP32 accumulation: C (M x N) = op(A) op(B) + bias, then an
+// epilogue.  A: TA = 0 -> M x K row-major, TA = 1 -> K x M.  B: TB = 0 -> N x K
+// row-major (used transposed), TB = 1 -> K x N.  B may hold bf16 values (the
+// network weights at inference).  64 x 64 output tile, 16 reduction indices at
+// a time; each of the four waves computes a 32 x 32 quarter as 2 x 2 blocks of
+// v_mfma_f32_16x16x4_f32 (FP32 products and accumulation: the bf16 weights are
+// widened exactly).  blockIdx.z splits K into ranges of kchunk: with more than
+// one range every range writes its own partial C + z M N (no bias, no
+// epilogue), summed in order by the kernel that applies the gradient.
+// EPI: 0 none, 1 GELU x Phi(x) (Phi from erfc), 2 softplus, 3 residual output
+// max(aux + x, 0), 4 GELU backward x (Phi(z) + z phi(z)) with z = aux, and the
+// FP64 column sums of the result over the 64 rows in part.  Z (optional)
 // receives the value before the epilogue.
+// The matrices are small and read once: bound by latency, so the next 16
+// indices are in flight in registers, 16 bytes a load, while the current ones
+// are multiplied from one of two LDS buffers; with 21 KB of LDS up to seven
+// work-groups share a CU (two buffers of 32 indices allow four and were 7 % of
+// a training step slower).
+// An operand whose rows hold the reduction index is kept row by row, 20 floats
+// apart, a lane reading four consecutive indices 4 g .. 4 g + 3 at once, MFMA e
+// reducing over the indices 4 g + e; one stored by reduction index is kept that
+// way, 68 floats apart (4 rows are 16 banks): both without bank conflicts.
+// m = 20000 rows, us before (4-byte loads, no overlap, the activation's
+// backward in a launch of its own, weight gradients on 256 work-groups) and
+// now: forward through a 256 x 256 layer 62 -> 43, backward through it 72 -> 46,
+// the three weight gradients 290 -> 70.
 // ---------------------------------------------------------------------------
+constexpr int GK = 16;                            // reduction indices of a slab
+constexpr int GLR = GK + 4, GLK = 64 + 4;         // LDS row strides: rows of reduction indices, of columns
+constexpr int GSIDE = 64 * GLR > GK * GLK ? 64 * GLR : GK * GLK;
+constexpr int GEMM_WGS = 512;                     // split weight gradients up to this many work-groups
+
+// 16 (8) bytes of the alignment of their entries
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t ushort4u __attribute__((ext_vector_type(4), aligned(2)));
+
 __device__ inline float normal_cdf_f(float x) { return 0.5f * erfcf(-x * 0.70710678118654752f); }
+
+// four consecutive entries of p, those at lim or beyond as zeros
+template <typename T>
+__device__ inline floatx4 gemm_load4(const T* p, int64_t lim) {
+    floatx4 v = {0.f, 0.f, 0.f, 0.f};
+    if (lim >= 4) {
+        if constexpr (sizeof(T) == 2) {
+            const ushort4u u = *(const ushort4u*)p;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = bf16_bits_to_f32(u[e]);
+        } else {
+            v = *(const float4u*)p;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (e < lim) {
+                if constexpr (sizeof(T) == 2) v[e] = bf16_bits_to_f32(p[e]);
+                else v[e] = p[e];
+            }
+    }
+    return v;
+}
 
 template <int TA, int TB, typename BT, int EPI>
 __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, const BT* __restrict__ B,
                                                    const float* __restrict__ bias, float* __restrict__ C,
-                                                   float* __restrict__ Z, int64_t M, int64_t N, int64_t K,
-                                                   int64_t kchunk, float alpha) {
-    // row stride 80: the four 16-lane groups of an MFMA operand read (rows kk
-    // .. kk + 3) fall on disjoint banks
-    __shared__ float As[16][80];
-    __shared__ float Bs[16][80];
+                                                   float* __restrict__ Z, const float* __restrict__ aux, int64_t ldaux,
+                                                   double* __restrict__ part, int64_t M, int64_t N, int64_t K,
+                                                   int64_t kchunk) {
+    __shared__ __align__(16) float As[2][GSIDE];
+    __shared__ __align__(16) float Bs[2][GSIDE];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int rb = 32 * (wv >> 1), cb = 32 * (wv & 1);   // this wave's quarter of the tile
     const int li = lane & 15, lk = lane >> 4;
@@ -63,44 +108,65 @@ __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, 
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
         for (int bj = 0; bj < 2; ++bj) acc[bi][bj] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int64_t k0 = kb; k0 < ke; k0 += 16) {
-        __syncthreads();
-        for (int f = t; f < 16 * 64; f += 256) {
-            const int kr = f >> 6, ir = f & 63;   // index fastest: coalesced for K-major operands
-            const int kc = f & 15, ic = f >> 4;   // K fastest: coalesced for row-major operands
-            {
-                const int64_t m = TA ? m0 + ir : m0 + ic, kx = TA ? k0 + kr : k0 + kc;
-                float v = 0.0f;
-                if (m < M && kx < ke) v = TA ? A[kx * M + m] : A[m * K + kx];
-                if (TA) As[kr][ir] = v; else As[kc][ic] = v;
-            }
-            {
-                const int64_t nn = TB ? n0 + ir : n0 + ic, kx = TB ? k0 + kr : k0 + kc;
-                float v = 0.0f;
-                if (nn < N && kx < ke) {
-                    const int64_t off = TB ? kx * N + nn : nn * K + kx;
-                    if constexpr (sizeof(BT) == 2) v = bf16_bits_to_f32(B[off]);
-                    else v = B[off];
-                }
-                if (TB) Bs[kr][ir] = v; else Bs[kc][ic] = v;
-            }
+    // a thread's vectors of a slab: rows t / RV + q RS, indices 4 (t % RV) ..,
+    // or reduction indices t / 16 + 16 q, columns 4 (t % 16) ..
+    constexpr int NQ = GK / 16, RV = GK / 4, RS = 256 / RV;
+    floatx4 ra[NQ], rbv[NQ];
+    auto load = [&](int64_t k0) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int64_t kr = k0 + (t >> 4) + 16 * q, kc = k0 + 4 * (t % RV);
+            const int64_t ar = m0 + t / RV + RS * q, ac = m0 + 4 * (t & 15);
+            const int64_t br = n0 + t / RV + RS * q, bc = n0 + 4 * (t & 15);
+            if (TA) ra[q] = gemm_load4(A + kr * M + ac, kr < ke ? M - ac : 0);
+            else ra[q] = gemm_load4(A + ar * K + kc, ar < M ? ke - kc : 0);
+            if (TB) rbv[q] = gemm_load4(B + kr * N + bc, kr < ke ? N - bc : 0);
+            else rbv[q] = gemm_load4(B + br * K + kc, br < N ? ke - kc : 0);
+        }
+    };
+    load(kb);
+    int buf = 0;
+    for (int64_t k0 = kb; k0 < ke; k0 += GK, buf ^= 1) {
+        const int row = t / RV, idx = 4 * (t % RV), kr = t >> 4, col = 4 * (t & 15);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            *(floatx4*)&As[buf][TA ? (kr + 16 * q) * GLK + col : (row + RS * q) * GLR + idx] = ra[q];
+            *(floatx4*)&Bs[buf][TB ? (kr + 16 * q) * GLK + col : (row + RS * q) * GLR + idx] = rbv[q];
         }
         __syncthreads();
-        // operand A: lane (i, q) holds A[row i][k = 4 s + q]; operand B: lane
-        // (j, q) holds op(B)[k = 4 s + q][column j]
+        if (k0 + GK < ke) load(k0 + GK);
 #pragma unroll
-        for (int st = 0; st < 4; ++st) {
-            const int kk = 4 * st + lk;
-            const float a0 = As[kk][rb + li], a1 = As[kk][rb + 16 + li];
-            const float b0 = Bs[kk][cb + li], b1 = Bs[kk][cb + 16 + li];
-            acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b1, acc[1][1], 0, 0, 0);
+        for (int s = 0; s < GK / 16; ++s) {
+            const int kk = 16 * s + 4 * lk;
+            floatx4 av[2], bv[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int r = rb + 16 * h + li, c = cb + 16 * h + li;
+                if (TA) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) av[h][e] = As[buf][(kk + e) * GLK + r];
+                } else {
+                    av[h] = *(const floatx4*)&As[buf][r * GLR + kk];
+                }
+                if (TB) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) bv[h][e] = Bs[buf][(kk + e) * GLK + c];
+                } else {
+                    bv[h] = *(const floatx4*)&Bs[buf][c * GLR + kk];
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                    for (int bj = 0; bj < 2; ++bj)
+                        acc[bi][bj] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[bi][e], bv[bj][e], acc[bi][bj], 0, 0, 0);
         }
     }
     const bool split = gridDim.z > 1;
     float* Cz = C + (split ? (int64_t)blockIdx.z * M * N : 0);
+    double sum[2] = {0.0, 0.0};
     // output: lane (j, q) holds rows 4 q + v, v < 4, of column j of each block
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
@@ -110,116 +176,85 @@ __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, 
         for (int v = 0; v < 4; ++v) {
             const int64_t m = m0 + rb + 16 * bi + 4 * lk + v, nn = n0 + cb + 16 * bj + li;
             if (m >= M || nn >= N) continue;
-            float v_ = alpha * acc[bi][bj][v];
+            float v_ = acc[bi][bj][v];
             if (split) { Cz[m * N + nn] = v_; continue; }
             if (bias) v_ += bias[nn];
             if (Z) Z[m * N + nn] = v_;
             if (EPI == 1) v_ = v_ * normal_cdf_f(v_);
             else if (EPI == 2) v_ = fmaxf(v_, 0.0f) + log1pf(expf(-fabsf(v_)));
+            else if (EPI == 3) {
+                v_ = aux[m * ldaux + nn] + v_;
+                v_ = v_ > 0.0f ? v_ : 0.0f;
+            } else if (EPI == 4) {
+                const float z = aux[m * ldaux + nn];
+                v_ = v_ * (normal_cdf_f(z) + z * expf(-0.5f * z * z) * 0.3989422804014327f);
+                sum[bj] += (double)v_;
+            }
             Cz[m * N + nn] = v_;
         }
+    if constexpr (EPI == 4) {
+        __shared__ double half[2][64];
+#pragma unroll
+        for (int bj = 0; bj < 2; ++bj) {
+            sum[bj] += __shfl_xor(sum[bj], 16, 64);
+            sum[bj] += __shfl_xor(sum[bj], 32, 64);
+            if (lk == 0) half[wv >> 1][cb + 16 * bj + li] = sum[bj];
+        }
+        __syncthreads();
+        if (t < 64 && n0 + t < N) part[(int64_t)blockIdx.y * N + n0 + t] = half[0][t] + half[1][t];
+    }
 }
 
 // K ranges of a weight gradient (m x n, contraction over K rows): enough to
-// fill the card where the output has few tiles, none shorter than 256 rows
+// give every CU two work-groups where the output has few tiles, none shorter
+// than 256 rows
 int64_t gemm_splits(int64_t M, int64_t N, int64_t K) {
     const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64);
-    if (tiles >= 256 || K < 512) return 1;
-    const int64_t splits = std::max<int64_t>(1, std::min<int64_t>(256 / tiles, K / 256));
+    if (tiles >= GEMM_WGS || K < 512) return 1;
+    const int64_t splits = std::max<int64_t>(1, std::min<int64_t>(GEMM_WGS / tiles, K / 256));
     const int64_t kchunk = ((K + splits - 1) / splits + 15) / 16 * 16;
     return (K + kchunk - 1) / kchunk;
 }
 int64_t gemm_max_splits(int64_t M, int64_t N) {
     const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64);
-    return tiles >= 256 ? 1 : 256 / tiles;
+    return tiles >= GEMM_WGS ? 1 : GEMM_WGS / tiles;
 }
 
+int64_t gemm_row_blocks(int64_t M) { return (M + 63) / 64; }
+
 hipError_t launch_gemm(int ta, int tb, int b_bf16, int epi, const float* A, const void* B, const float* bias, float* C,
-                       float* Z, int64_t M, int64_t N, int64_t K, float alpha, int64_t splits, hipStream_t stream) {
+                       float* Z, int64_t M, int64_t N, int64_t K, int64_t splits, hipStream_t stream, const float* aux,
+                       int64_t ldaux, double* part) {
     if (M < 1 || N < 1 || K < 1 || splits < 1 || (splits > 1 && (epi != 0 || bias || Z))) return hipErrorInvalidValue;
+    if ((epi >= 3) != (aux != nullptr) || (aux && ldaux < N) || (epi == 4) != (part != nullptr)) return hipErrorInvalidValue;
     const int64_t kchunk = ((K + splits - 1) / splits + 15) / 16 * 16;
     if ((K + kchunk - 1) / kchunk != splits) return hipErrorInvalidValue;
     dim3 grid((N + 63) / 64, (M + 63) / 64, splits), block(256);
 #define G(TA, TB, BT, E)                                                                                     \
-    hipLaunchKernelGGL((gemm_kernel<TA, TB, BT, E>), grid, block, 0, stream, A, (const BT*)B, bias, C, Z, M, N, K, \
-                       kchunk, alpha)
-    if (b_bf16) {
-        if (ta == 0 && tb == 0 && epi == 0) G(0, 0, uint16_t, 0);
-        else if (ta == 0 && tb == 0 && epi == 1) G(0, 0, uint16_t, 1);
-        else if (ta == 0 && tb == 0 && epi == 2) G(0, 0, uint16_t, 2);
-        else return hipErrorInvalidValue;
+    hipLaunchKernelGGL((gemm_kernel<TA, TB, BT, E>), grid, block, 0, stream, A, (const BT*)B, bias, C, Z, aux, ldaux, \
+                       part, M, N, K, kchunk)
+    if (ta == 0 && tb == 0) {
+        if (b_bf16) {
+            if (epi == 1) G(0, 0, uint16_t, 1);
+            else if (epi == 2) G(0, 0, uint16_t, 2);
+            else if (epi == 3) G(0, 0, uint16_t, 3);
+            else return hipErrorInvalidValue;
+        } else {
+            if (epi == 1) G(0, 0, float, 1);
+            else if (epi == 2) G(0, 0, float, 2);
+            else if (epi == 3) G(0, 0, float, 3);
+            else return hipErrorInvalidValue;
+        }
+    } else if (b_bf16) {
+        return hipErrorInvalidValue;
+    } else if (ta == 0 && tb == 1 && epi == 4) {
+        G(0, 1, float, 4);
+    } else if (ta == 1 && tb == 1 && epi == 0) {
+        G(1, 1, float, 0);
     } else {
-        if (ta == 0 && tb == 0 && epi == 0) G(0, 0, float, 0);
-        else if (ta == 0 && tb == 0 && epi == 1) G(0, 0, float, 1);
-        else if (ta == 0 && tb == 0 && epi == 2) G(0, 0, float, 2);
-        else if (ta == 0 && tb == 1 && epi == 0) G(0, 1, float, 0);
-        else if (ta == 1 && tb == 1 && epi == 0) G(1, 1, float, 0);
-        else return hipErrorInvalidValue;
+        return hipErrorInvalidValue;
     }
 #undef G
-    return hipGetLastError();
-}
-
-// Backward of an activation and the bias gradient's partial sums in one pass:
-// dZ = dA * GELU'(Z) (Phi(z) + z phi(z)), in place where dZ = dA, and the FP64
-// column sums of dZ over every block of BIAS_ROWS rows.  A work-group takes 64
-// columns of one row block, so m = 20000 rows of 256 columns are 628
-// work-groups: with one work-group per 64 columns summing all rows one after
-// another the three bias sums of a training step took 3.6 of its 4.6 ms
-// (dependent FP64 adds behind load latency, 9 work-groups on 256 CUs); fused
-// here they cost no pass of their own (15.6 us a GELU layer before, without
-// the sums, 17.0 us now, m = 20000, 256 columns).
-constexpr int BIAS_ROWS = 128;
-
-int64_t bias_blocks(int64_t m) { return (m + BIAS_ROWS - 1) / BIAS_ROWS; }
-
-__global__ __launch_bounds__(256) void gelu_backward_kernel(const float* dA, const float* __restrict__ Zpre, float* dZ,
-                                                            int64_t m, int64_t ncol, double* __restrict__ part) {
-    __shared__ double red[4][64];
-    const int lc = threadIdx.x & 63, ph = threadIdx.x >> 6;
-    const int64_t col = blockIdx.x * 64 + lc;
-    const int64_t r0 = (int64_t)blockIdx.y * BIAS_ROWS;
-    const int64_t r1 = r0 + BIAS_ROWS < m ? r0 + BIAS_ROWS : m;
-    double s = 0.0;
-    if (col < ncol) {
-#pragma unroll 4
-        for (int64_t i = r0 + ph; i < r1; i += 4) {
-            const float z = Zpre[i * ncol + col];
-            const float d = normal_cdf_f(z) + z * expf(-0.5f * z * z) * 0.3989422804014327f;
-            const float v = dA[i * ncol + col] * d;
-            dZ[i * ncol + col] = v;
-            s += (double)v;
-        }
-    }
-    red[ph][lc] = s;
-    __syncthreads();
-    if (ph == 0 && col < ncol) part[blockIdx.y * ncol + col] = red[0][lc] + red[1][lc] + red[2][lc] + red[3][lc];
-}
-
-hipError_t launch_gelu_backward(const float* dA, const float* Z, float* dZ, int64_t m, int64_t ncol, double* part,
-                                hipStream_t stream) {
-    if (bias_blocks(m) > 65535) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(gelu_backward_kernel, dim3((ncol + 63) / 64, bias_blocks(m)), dim3(256), 0, stream, dA, Z, dZ, m,
-                       ncol, part);
-    return hipGetLastError();
-}
-
-// Residual output A = max(C + z, 0), C the first k columns of the network input
-// X (leading dimension ldx): A holds z on entry (rows x k).
-__global__ void residual_relu_kernel(const float* __restrict__ X, int64_t ldx, float* __restrict__ A, int64_t rows,
-                                     int k) {
-    const int64_t m = rows * k;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = i / k;
-        const float v = X[r * ldx + (i - r * k)] + A[i];
-        A[i] = v > 0.0f ? v : 0.0f;
-    }
-}
-
-hipError_t launch_residual_relu(const float* X, int64_t ldx, float* A, int64_t rows, int64_t k, hipStream_t stream) {
-    int64_t blocks = (rows * k + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(residual_relu_kernel, dim3(blocks), dim3(256), 0, stream, X, ldx, A, rows, (int)k);
     return hipGetLastError();
 }
 

@@ -51,7 +51,7 @@ symnmf_status ensure_fwd(symnmf_mlp* m, int64_t rows) {
 }
 
 int64_t small_doubles(const symnmf_mlp* m, int64_t rows) {
-    return 4 + 3 * m->k * m->k + 3 * xty_work_doubles(rows, m->k, m->k) + 2 * bias_blocks(rows) * m->h +
+    return 4 + 3 * m->k * m->k + 3 * xty_work_doubles(rows, m->k, m->k) + 2 * gemm_row_blocks(rows) * m->h +
            loss_backward_blocks(rows) * m->k;
 }
 
@@ -87,12 +87,11 @@ symnmf_status forward(symnmf_mlp* m, const float* X, int64_t rows, bool bf16, bo
     const void* W3 = bf16 ? (const void*)(m->Wb + m->off_W3()) : (const void*)(m->P + m->off_W3());
     const int b = bf16 ? 1 : 0;
     HIP_OK(ctx, launch_gemm(0, 0, b, 1, X, W1, m->P + m->off_b1(), m->a1, train ? m->z1 : nullptr, rows, m->h, m->w,
-                            1.0f, 1, sm));
+                            1, sm));
     HIP_OK(ctx, launch_gemm(0, 0, b, 1, m->a1, W2, m->P + m->off_b2(), m->a2, train ? m->z2 : nullptr, rows, m->h,
-                            m->h, 1.0f, 1, sm));
-    HIP_OK(ctx, launch_gemm(0, 0, b, m->residual ? 0 : 2, m->a2, W3, m->P + m->off_b3(), A, train ? m->z3 : nullptr,
-                            rows, m->k, m->h, 1.0f, 1, sm));
-    if (m->residual) HIP_OK(ctx, launch_residual_relu(X, m->w, A, rows, m->k, sm));
+                            m->h, 1, sm));
+    HIP_OK(ctx, launch_gemm(0, 0, b, m->residual ? 3 : 2, m->a2, W3, m->P + m->off_b3(), A, train ? m->z3 : nullptr,
+                            rows, m->k, m->h, 1, sm, m->residual ? X : nullptr, m->w));
     return SYMNMF_OK;
 }
 
@@ -236,8 +235,8 @@ symnmf_status symnmf_mlp_train_step(symnmf_ctx* ctx, symnmf_mlp* m, const float*
     double* gram3 = coef + 4;
     double* work = gram3 + 3 * k * k;
     double* b1p = work + 3 * xty_work_doubles(rows, k, k);
-    double* b2p = b1p + bias_blocks(rows) * h;
-    double* b3p = b2p + bias_blocks(rows) * h;
+    double* b2p = b1p + gemm_row_blocks(rows) * h;
+    double* b3p = b2p + gemm_row_blocks(rows) * h;
     GradParts gp;
     gp.wsize[0] = h * w;
     gp.wsize[1] = h * h;
@@ -256,21 +255,22 @@ symnmf_status symnmf_mlp_train_step(symnmf_ctx* ctx, symnmf_mlp* m, const float*
     gp.bpart[2] = b3p;
     gp.bsize[0] = gp.bsize[1] = h;
     gp.bsize[2] = k;
-    gp.bblocks[0] = gp.bblocks[1] = bias_blocks(rows);
+    gp.bblocks[0] = gp.bblocks[1] = gemm_row_blocks(rows);
     gp.bblocks[2] = loss_backward_blocks(rows);
     HIP_OK(ctx, launch_gram3(m->out, B, k, rows, work, gram3, sm));
     HIP_OK(ctx, launch_loss_coef(gram3, k, loss_kind, coef, sm));
     // backward; the loss is checked on the device (a bad one leaves the
     // parameters, the gradient and the moments as they are) and read at the end
     HIP_OK(ctx, launch_loss_backward(m->out, B, gram3, coef, X, w, m->z3, m->residual, k, rows, m->d3, b3p, sm));
-    HIP_OK(ctx, launch_gemm(1, 1, 0, 0, m->d3, m->a2, nullptr, w3p, nullptr, k, h, rows, 1.0f, gp.splits[2], sm));
-    HIP_OK(ctx, launch_gemm(0, 1, 0, 0, m->d3, m->P + m->off_W3(), nullptr, m->da2, nullptr, rows, h, k, 1.0f, 1, sm));
-    HIP_OK(ctx, launch_gelu_backward(m->da2, m->z2, m->da2, rows, h, b2p, sm));      // d2
-    HIP_OK(ctx, launch_gemm(1, 1, 0, 0, m->da2, m->a1, nullptr, w2p, nullptr, h, h, rows, 1.0f, gp.splits[1], sm));
-    // da1 = d2 W2 into a2 (no longer needed), then d1 in place
-    HIP_OK(ctx, launch_gemm(0, 1, 0, 0, m->da2, m->P + m->off_W2(), nullptr, m->a2, nullptr, rows, h, h, 1.0f, 1, sm));
-    HIP_OK(ctx, launch_gelu_backward(m->a2, m->z1, m->a2, rows, h, b1p, sm));
-    HIP_OK(ctx, launch_gemm(1, 1, 0, 0, m->a2, X, nullptr, w1p, nullptr, h, w, rows, 1.0f, gp.splits[0], sm));
+    HIP_OK(ctx, launch_gemm(1, 1, 0, 0, m->d3, m->a2, nullptr, w3p, nullptr, k, h, rows, gp.splits[2], sm));
+    // d2 = (d3 W3) * GELU'(z2)
+    HIP_OK(ctx, launch_gemm(0, 1, 0, 4, m->d3, m->P + m->off_W3(), nullptr, m->da2, nullptr, rows, h, k, 1, sm, m->z2, h,
+                            b2p));
+    HIP_OK(ctx, launch_gemm(1, 1, 0, 0, m->da2, m->a1, nullptr, w2p, nullptr, h, h, rows, gp.splits[1], sm));
+    // d1 = (d2 W2) * GELU'(z1) into a2 (no longer needed)
+    HIP_OK(ctx, launch_gemm(0, 1, 0, 4, m->da2, m->P + m->off_W2(), nullptr, m->a2, nullptr, rows, h, h, 1, sm, m->z1, h,
+                            b1p));
+    HIP_OK(ctx, launch_gemm(1, 1, 0, 0, m->a2, X, nullptr, w1p, nullptr, h, w, rows, gp.splits[0], sm));
     HIP_OK(ctx, launch_grad_adamw(gp, coef, m->P, m->G, m->Mm, m->V, (float)opt->lr, (float)opt->beta1,
                                   (float)opt->beta2, (float)opt->eps, (float)opt->weight_decay, m->t + 1, sm));
     double hc[4];
