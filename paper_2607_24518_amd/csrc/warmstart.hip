@@ -436,86 +436,88 @@ hipError_t launch_spa(double* R, int64_t m, int64_t k, double* bval, int64_t* bi
 
 // ---------------------------------------------------------------------------
 // FP64 products of two row-major FP32 matrices over m rows, kx, ky <= 64:
-// X^T Y (NP = 1), or X^T X, X^T Y and Y^T Y at once (NP = 3, kx = ky).  A
-// work-group stages XTY_ROWS rows, 64 at a time, in LDS; a thread holds a 4 x 4
-// block of every product in registers (eight 16-byte LDS reads feed 48 FMAs;
-// with one entry per thread and two 4-byte reads per FMA the LDS was the
-// bound), threads left over at small k take rows of their own.  The blocks'
+// X^T Y (NP = 1), or X^T X, X^T Y and Y^T Y at once (NP = 3, kx = ky), on the
+// FP64 matrix cores.  A work-group stages XTY_ROWS rows, 64 at a time, in LDS
+// (rows 80 floats apart: the four rows of an operand read fall on disjoint
+// banks); a wave forms the 16 columns of X (and of Y) that are its own against
+// all columns, four rows to an MFMA, the operands widened exactly.  The blocks'
 // partials are then summed in a fixed order by four phases per entry (one
-// thread per entry walked all of them).  The three products of a training
-// step at m = 20000, k = 64: 99 + 207 us in six launches before, 52 + 6 us in
-// two now.
+// thread per entry walked all of them).  The three products of a training step
+// at m = 20000, k = 64, 0.5 GFLOP: 99 + 207 us in six launches of vector code
+// with two 4-byte LDS reads per FMA, 52 + 6 us in two with a 4 x 4 block in
+// registers, 24 + 6 us now.
 // ---------------------------------------------------------------------------
 constexpr int XTY_ROWS = 128;
-constexpr int XTY_LD = KMAX + 4;
+constexpr int XTY_LD = KMAX + 16;
+typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 template <int NP>
 __global__ __launch_bounds__(256) void xty_slab_kernel(const float* __restrict__ X, int64_t ldx, int kx,
                                                        const float* __restrict__ Y, int64_t ldy, int ky, int64_t m,
                                                        double* __restrict__ part) {
-    __shared__ __align__(16) float lds[2 * 64 * XTY_LD];
-    static_assert(sizeof(lds) >= 256 * 16 * sizeof(double), "the reduction reuses the row buffer");
-    float* xs = lds;
-    float* ys = lds + 64 * XTY_LD;
-    const int t = threadIdx.x;
-    const int ny = (ky + 3) / 4, nt = ((kx + 3) / 4) * ny, groups = 256 / nt;
-    const int grp = t / nt, tile = t - grp * nt;
-    const int ca = 4 * (tile / ny), cb = 4 * (tile % ny);
-    double acc[NP][16];
+    constexpr int NB = KMAX / 16;
+    __shared__ float xs[64 * XTY_LD];
+    __shared__ float ys[64 * XTY_LD];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, li = lane & 15, lk = lane >> 4;
+    doublex4 acc[NP][NB];
 #pragma unroll
     for (int p = 0; p < NP; ++p)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[p][e] = 0.0;
+        for (int n = 0; n < NB; ++n) acc[p][n] = doublex4{0.0, 0.0, 0.0, 0.0};
+    // a thread's 16 entries of each matrix, both halves' asked for ahead
+    float rx[16], ry[16];
+    auto load = [&](int half) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int64_t r = (int64_t)blockIdx.x * XTY_ROWS + 64 * half + 4 * q + wv;
+            rx[q] = r < m && lane < kx ? X[r * ldx + lane] : 0.0f;
+            ry[q] = r < m && lane < ky ? Y[r * ldy + lane] : 0.0f;
+        }
+    };
+    load(0);
+#pragma unroll 1
     for (int half = 0; half < XTY_ROWS / 64; ++half) {
-        const int64_t r0 = (int64_t)blockIdx.x * XTY_ROWS + 64 * half;
         __syncthreads();
-        for (int f = t; f < 64 * KMAX; f += 256) {
-            const int r = f / KMAX, c = f - r * KMAX;
-            const bool in = r0 + r < m;
-            xs[r * XTY_LD + c] = (in && c < kx) ? X[(r0 + r) * ldx + c] : 0.0f;
-            ys[r * XTY_LD + c] = (in && c < ky) ? Y[(r0 + r) * ldy + c] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            xs[(4 * q + wv) * XTY_LD + lane] = rx[q];
+            ys[(4 * q + wv) * XTY_LD + lane] = ry[q];
         }
         __syncthreads();
-        if (grp < groups)
-            for (int r = grp; r < 64; r += groups) {
-                const floatx4 xa = *(const floatx4*)&xs[r * XTY_LD + ca], yb = *(const floatx4*)&ys[r * XTY_LD + cb];
-                floatx4 xb, ya;
-                if (NP == 3) {
-                    xb = *(const floatx4*)&xs[r * XTY_LD + cb];
-                    ya = *(const floatx4*)&ys[r * XTY_LD + ca];
-                }
+        if (half + 1 < XTY_ROWS / 64) load(half + 1);
+        if (16 * wv < kx) {
+#pragma unroll 4
+            for (int s = 0; s < 16; ++s) {
+                const float* x = xs + (4 * s + lk) * XTY_LD + li;
+                const float* y = ys + (4 * s + lk) * XTY_LD + li;
+                const double xa = (double)x[16 * wv], ya = (double)y[16 * wv];
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int e = 4 * i + j;
-                        if (NP == 3) {
-                            acc[0][e] += (double)xa[i] * (double)xb[j];
-                            acc[NP == 3 ? 1 : 0][e] += (double)xa[i] * (double)yb[j];
-                            acc[NP == 3 ? 2 : 0][e] += (double)ya[i] * (double)yb[j];
-                        } else {
-                            acc[0][e] += (double)xa[i] * (double)yb[j];
-                        }
+                for (int n = 0; n < NB; ++n) {
+                    if (16 * n >= ky) break;
+                    const double yb = (double)y[16 * n];
+                    if (NP == 3) {
+                        const double xb = (double)x[16 * n];
+                        acc[0][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa, xb, acc[0][n], 0, 0, 0);
+                        acc[NP == 3 ? 1 : 0][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa, yb, acc[NP == 3 ? 1 : 0][n], 0, 0, 0);
+                        acc[NP == 3 ? 2 : 0][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(ya, yb, acc[NP == 3 ? 2 : 0][n], 0, 0, 0);
+                    } else {
+                        acc[0][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa, yb, acc[0][n], 0, 0, 0);
                     }
+                }
             }
+        }
     }
-    double* red = (double*)lds;
+    // D of the FP64 form: lane (j, q) holds rows 4 v + q of column j
     const int kk = kx * ky;
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        __syncthreads();
+    for (int p = 0; p < NP; ++p)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) red[e * 256 + t] = acc[p][e];
-        __syncthreads();
-        double* dst = part + ((int64_t)blockIdx.x * NP + p) * kk;
-        for (int e = t; e < kk; e += 256) {
-            const int a = e / ky, b = e - a * ky;
-            const int src = (4 * (a & 3) + (b & 3)) * 256 + (a >> 2) * ny + (b >> 2);
-            double sum = 0.0;
-            for (int g = 0; g < groups; ++g) sum += red[src + g * nt];
-            dst[e] = sum;
-        }
-    }
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int a = 16 * wv + 4 * v + lk, c = 16 * n + li;
+                if (a < kx && c < ky) part[((int64_t)blockIdx.x * NP + p) * kk + a * ky + c] = acc[p][n][v];
+            }
 }
 
 // out[e] = sum over the slabs, 64 entries per work-group, four phases each
