@@ -140,10 +140,13 @@ __device__ inline uint32_t sortable_key(float v) {
 // per digit.  A lane finds the lanes of its wave with its digit from eight
 // ballots, its place among them is a popcount, and one lane per digit advances
 // the wave's counter, so there are no atomics and no dependence on the values'
-// distribution.  Bound by the vector ALU (ballots and masks: 32 bits an item)
-// and the LDS.  The bitonic sort of LDS keys that stood here (120 passes over
+// distribution.  Bound by the vector ALU (0.48 of 0.87 ms: a ballot, a bit field
+// and two three-input operations per bit) and, in the phases between, the LDS
+// (0.29 ms, over half of it conflicts of the scatter); 120 KB of keys and
+// numbers leave one work-group to a CU, so the two do not overlap.  The bitonic sort of LDS keys that stood here (120 passes over
 // 32768 keys for T = 20000, then a binary search per sample) took 37.0 ms at
-// n = 4096, T = 20000; this takes 1.03 ms.
+// n = 4096, T = 20000; this takes 0.87 ms (1.02 with six operations a bit and
+// the counters' prefix read twice).
 constexpr int RANK_MAX_T = 32768;
 
 template <int THREADS, int IPT>
@@ -175,13 +178,16 @@ __global__ __launch_bounds__(THREADS) void rank_kernel(const float* __restrict__
         for (int j = 0; j < IPT; ++j) {
             const uint32_t d = (k[j] >> shift) & 255u;
             // lanes of the wave with the same digit: those that vote alike on every bit
-            uint32_t lo = ~0u, hi = ~0u;
+            uint32_t lo = 0, hi = 0;                       // lanes that differ, of the last bit those that do not
 #pragma unroll
             for (int b = 0; b < 8; ++b) {
-                const uint32_t bit = (uint32_t)((int32_t)(d << (31 - b)) >> 31);   // 0 or ~0
+                uint32_t bit = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);   // 0 or ~0
+                asm("" : "+v"(bit));                       // vote on it, not on a shift of the digit of its own
                 const uint64_t votes = __ballot(bit != 0);
-                lo &= ~((uint32_t)votes ^ bit);
-                hi &= ~((uint32_t)(votes >> 32) ^ bit);
+                const uint32_t vl = (uint32_t)votes, vh = (uint32_t)(votes >> 32);
+                // x | (votes ^ bit), and its complement, are one instruction each
+                lo = b < 7 ? __builtin_amdgcn_bitop3_b32(lo, vl, bit, 0xF6) : __builtin_amdgcn_bitop3_b32(lo, vl, bit, 0x09);
+                hi = b < 7 ? __builtin_amdgcn_bitop3_b32(hi, vh, bit, 0xF6) : __builtin_amdgcn_bitop3_b32(hi, vh, bit, 0x09);
             }
             const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
             const uint32_t prev = cnt[wv * 256 + d];
@@ -197,14 +203,14 @@ __global__ __launch_bounds__(THREADS) void rank_kernel(const float* __restrict__
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
         __syncthreads();
-        // exclusive prefix of the counters over (digit, wave)
-        uint32_t tot = 0, incl = 0;
+        // exclusive prefix of the counters over (digit, wave): a thread per
+        // digit, its counters read at once and written back as offsets
+        uint32_t c[WAVES], tot = 0, incl = 0;
         if (t < 256) {
-            for (int q = 0; q < WAVES; ++q) {
-                const uint32_t c = cnt[q * 256 + t];
-                cnt[q * 256 + t] = tot;
-                tot += c;
-            }
+#pragma unroll
+            for (int q = 0; q < WAVES; ++q) c[q] = cnt[q * 256 + t];
+#pragma unroll
+            for (int q = 0; q < WAVES; ++q) tot += c[q];
             incl = tot;
             for (int off = 1; off < 64; off <<= 1) {
                 const uint32_t up = __shfl_up(incl, off, 64);
@@ -216,7 +222,11 @@ __global__ __launch_bounds__(THREADS) void rank_kernel(const float* __restrict__
         if (t < 256) {
             uint32_t base = incl - tot;
             for (int q = 0; q < wv; ++q) base += wsum[q];
-            for (int q = 0; q < WAVES; ++q) cnt[q * 256 + t] += base;
+#pragma unroll
+            for (int q = 0; q < WAVES; ++q) {
+                cnt[q * 256 + t] = base;
+                base += c[q];
+            }
         }
         __syncthreads();
 #pragma unroll
