@@ -255,6 +255,14 @@ __host__ __device__ inline void sample_block_flags(uint64_t seed, int64_t t, int
     for (int i = 0; i < m; ++i) flags[perm[i]] = 1;
 }
 
+// The inverse an ADMM step needs, minv = (2 gram + rho I)^-1 (k x k), formed by the stream's launch
+// where the plan is a quarter-tile one; gram null: none.
+struct AdmmInverse {
+    const double* gram = nullptr;
+    int k = 0;
+    double rho = 0.0;
+    float* minv = nullptr;
+};
 // ---------------------------------------------------------------------------
 // Host launchers
 // ---------------------------------------------------------------------------
@@ -267,7 +275,8 @@ __host__ __device__ inline void sample_block_flags(uint64_t seed, int64_t t, int
 // img1 = images of H, img2 = images of 2H (block steps; may equal img1 otherwise).
 hipError_t launch_stream(const void* S, int32_t stype, int64_t ld, const void* H, int h_f64, int64_t k,
                          void* part, int acc_f64, const PlanView& plan, hipStream_t stream,
-                         const void* img1 = nullptr, const void* img2 = nullptr);
+                         const void* img1 = nullptr, const void* img2 = nullptr,
+                         const AdmmInverse& inv = AdmmInverse());
 // 32-bit words of the H images of all n_chunks chunks for this storage type and rank
 int64_t h_image_words(int32_t stype, int64_t k, int64_t n_chunks);
 // Write the images of chunks [chunk0, chunk0 + n_chunks) of wt * H (FP32, 256 rows x k per chunk,
@@ -297,7 +306,7 @@ int stream_wgs_per_cu(int32_t stype, int64_t k);
 int stream_tall_supported(int32_t stype, int h_f64, int64_t k);
 // work-groups w of a full step that runs the quarter-tile kernel (a plan with quarter = 1), or 0
 // where the step has too many units for it
-int32_t stream_quarter_wgs(int cus, int32_t stype, int64_t n_tiles, int64_t n_chunks, int64_t k);
+int32_t stream_quarter_wgs(int cus, int32_t stype, int64_t n_tiles, int64_t n_chunks, int64_t k, bool inverse);
 
 // plan.hip: build the device plan of a sub-sampled step.
 struct PlanRequest {

@@ -490,7 +490,8 @@ static symnmf_status state_alloc(symnmf_state* st, void** out, int64_t bytes) {
 // in snapshot_s is a full one.
 static int32_t quarter_wgs(const symnmf_state* st) {
     if (!st->mfma || st->p.method == SYMNMF_ROW_SVRG || st->p.method == SYMNMF_BLOCK_SVRG) return 0;
-    return std::min(st->P, stream_quarter_wgs(st->ctx->cus, st->S.dtype, st->tiles, st->chunks, st->k));
+    return std::min(st->P, stream_quarter_wgs(st->ctx->cus, st->S.dtype, st->tiles, st->chunks, st->k,
+                                              st->p.method == SYMNMF_ADMM));
 }
 
 static double tau_g_of(const symnmf_state* st) {
@@ -682,10 +683,18 @@ static symnmf_status do_step(symnmf_ctx* ctx, const symnmf_S* S, symnmf_state* s
                                            (uint32_t*)st->img[i], sm));
         st->img_ready = true;
     }
+    // a quarter-tile stream forms an ADMM step's inverse beside its products
+    AdmmInverse inv;
+    if (p.method == SYMNMF_ADMM && pv.quarter) {
+        inv.gram = st->gram64[st->cur];
+        inv.k = (int)st->k;
+        inv.rho = p.rho;
+        inv.minv = (float*)st->minv;
+    }
     {
         ProfScope ps(ctx, PK_STREAM);
         HIP_OK(ctx, launch_stream(S->data, S->dtype, S->ld, Hc, st->h_f64, st->k, st->part, st->h_f64, pv, sm,
-                                  st->img[0], kind == 2 ? st->img[1] : st->img[0]));
+                                  st->img[0], kind == 2 ? st->img[1] : st->img[0], inv));
     }
     UpdateArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -746,7 +755,7 @@ static symnmf_status do_step(symnmf_ctx* ctx, const symnmf_S* S, symnmf_state* s
         if (p.method == SYMNMF_ADMM) {
             a.rho = p.rho;
             a.minv = st->minv;
-            HIP_OK(ctx, launch_admm(a, st->gram64[st->cur], st->h_f64, pv, sm));
+            HIP_OK(ctx, launch_admm(a, inv.gram ? nullptr : st->gram64[st->cur], st->h_f64, pv, sm));
         } else {
             HIP_OK(ctx, launch_update(a, st->h_f64, pv, sm));
         }

@@ -22,6 +22,7 @@
 // of S are consecutive columns.
 #include <algorithm>
 
+#include "admm_inverse.h"
 #include "image.h"
 
 namespace symnmf {
@@ -618,11 +619,17 @@ __global__ __launch_bounds__(TALL ? 512 : 256, TALL || (ACC64 && NT == 4) ? 1 : 
 // L2) straight into registers, one unit ahead, and the four waves' sums meet in
 // LDS once per tile.  The partial of work-group w for tile a goes to slot
 // w + a as usual, written by the four work-groups 4 w .. 4 w + 3.
+// An ADMM step's inverse, which nothing waits for before the update, is formed
+// by a work-group of its own beside the others: as a launch between the stream
+// and the update it was 5 of 25 us of a step at 512 instruments, k = 16, and
+// more than the stream at k = 64 (42 us).  A step with / without it, us, FP32:
+// n = 512, k = 16 22.8 / 25.8; n = 4100, k = 32 45.7 / 53.9, k = 64 83.8 / 111.6.
 // ---------------------------------------------------------------------------
 template <int KIND, int NT>
 __global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_quarter(const void* __restrict__ Sv,
                                                                       const u32x4* __restrict__ img,
-                                                                      float* __restrict__ part, PlanView p) {
+                                                                      float* __restrict__ part, PlanView p,
+                                                                      AdmmInverse inv) {
     constexpr int K = 16 * NT;
     using IS = ImageShape<KIND, K>;
     constexpr int EB = KIND == 0 ? 4 : (KIND == 1 ? 2 : 1);
@@ -633,8 +640,14 @@ __global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_quarter(const voi
     __shared__ __align__(16) float red[4][64 * K];
     const int64_t U = (int64_t)p.n_tiles * p.n_chunks;
     const int64_t Pe = U < p.P ? U : p.P;
-    const int64_t w = blockIdx.x >> 2;
-    const int sub = blockIdx.x & 3;
+    if (inv.gram && blockIdx.x == 0) {
+        static_assert(sizeof(red) >= 4 * KMAX * sizeof(double), "the inverse works in the sums' LDS");
+        admm_inverse<float, NT>(inv.gram, inv.k, inv.rho, inv.minv, (double*)red);
+        return;
+    }
+    const int block = (int)blockIdx.x - (inv.gram ? 1 : 0);
+    const int64_t w = block >> 2;
+    const int sub = block & 3;
     if (w >= Pe) return;
     const int64_t u0 = wg_start(w, U, Pe), u1 = wg_start(w + 1, U, Pe);
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6, lr = lane & 15, lg = lane >> 4;
@@ -760,8 +773,10 @@ __global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_quarter(const voi
 // 6000 (U = 576: 104 / 77 / 77 against 128 / 87 / 85 us, FP32 / BF16 / FP8) and
 // lose or tie at 8192.  At 512 instruments: k = 16 19.0 against 28.9 us, k = 32
 // 24.8 against 41.0 us, k = 64 50.5 against 78.5 us (FP32).
-int32_t stream_quarter_wgs(int cus, int32_t stype, int64_t n_tiles, int64_t n_chunks, int64_t k) {
-    const int64_t U = n_tiles * n_chunks, P = std::max(cus / 4, 1);
+// The 64-column form's registers fill a CU, so a step with an inverse leaves it
+// one.
+int32_t stream_quarter_wgs(int cus, int32_t stype, int64_t n_tiles, int64_t n_chunks, int64_t k, bool inverse) {
+    const int64_t U = n_tiles * n_chunks, P = std::max((cus - (inverse && mfma_width(k) == 64 ? 1 : 0)) / 4, 1);
     const int64_t most = mfma_width(k) == 64 ? 768 : (stype == SYMNMF_S_FP32 ? 2304 : 1024);
     if (U > most) return 0;
     return (int32_t)std::min(U, P);
@@ -795,14 +810,14 @@ static hipError_t launch_generic(const void* S, int64_t ld, const double* H, int
 // at k = 64 keep one 96 KB image.
 template <int KIND>
 static void launch_mfma_kind(const void* S, const u32x4* img1, const u32x4* img2, void* part, int64_t k,
-                             const PlanView& p, hipStream_t stream) {
+                             const PlanView& p, hipStream_t stream, const AdmmInverse& inv) {
     dim3 grid(p.P);
     k = mfma_width(k);
     if (p.quarter) {
-        const dim3 qg(4 * p.P), qb(256);
-        if (k == 16) hipLaunchKernelGGL((stream_quarter<KIND, 1>), qg, qb, 0, stream, S, img1, (float*)part, p);
-        else if (k == 32) hipLaunchKernelGGL((stream_quarter<KIND, 2>), qg, qb, 0, stream, S, img1, (float*)part, p);
-        else hipLaunchKernelGGL((stream_quarter<KIND, 4>), qg, qb, 0, stream, S, img1, (float*)part, p);
+        const dim3 qg(4 * p.P + (inv.gram ? 1 : 0)), qb(256);
+        if (k == 16) hipLaunchKernelGGL((stream_quarter<KIND, 1>), qg, qb, 0, stream, S, img1, (float*)part, p, inv);
+        else if (k == 32) hipLaunchKernelGGL((stream_quarter<KIND, 2>), qg, qb, 0, stream, S, img1, (float*)part, p, inv);
+        else hipLaunchKernelGGL((stream_quarter<KIND, 4>), qg, qb, 0, stream, S, img1, (float*)part, p, inv);
         return;
     }
     if (p.tall) {
@@ -857,16 +872,16 @@ int stream_wgs_per_cu(int32_t stype, int64_t k) {
 
 hipError_t launch_stream(const void* S, int32_t stype, int64_t ld, const void* H, int h_f64, int64_t k,
                          void* part, int acc_f64, const PlanView& p, hipStream_t stream, const void* img1,
-                         const void* img2) {
-    if (k < 1 || k > KMAX) return hipErrorInvalidValue;
+                         const void* img2, const AdmmInverse& inv) {
+    if (k < 1 || k > KMAX || (inv.gram && !p.quarter)) return hipErrorInvalidValue;
     if (stream_uses_mfma(stype, h_f64, acc_f64, k)) {
         if (!img1) return hipErrorInvalidValue;
         const u32x4* i1 = (const u32x4*)img1;
         const u32x4* i2 = (const u32x4*)(img2 ? img2 : img1);
         float* pf = (float*)part;
-        if (stype == SYMNMF_S_FP32) launch_mfma_kind<0>(S, i1, i2, pf, k, p, stream);
-        else if (stype == SYMNMF_S_BF16) launch_mfma_kind<1>(S, i1, i2, pf, k, p, stream);
-        else if (stype == SYMNMF_S_FP8) launch_mfma_kind<2>(S, i1, i2, pf, k, p, stream);
+        if (stype == SYMNMF_S_FP32) launch_mfma_kind<0>(S, i1, i2, pf, k, p, stream, inv);
+        else if (stype == SYMNMF_S_BF16) launch_mfma_kind<1>(S, i1, i2, pf, k, p, stream, inv);
+        else if (stype == SYMNMF_S_FP8) launch_mfma_kind<2>(S, i1, i2, pf, k, p, stream, inv);
         else return hipErrorInvalidValue;
         return hipGetLastError();
     }

@@ -12,6 +12,7 @@
 //   * writes H_{t+1} and accumulates in FP64 the per-tile partials of
 //     tr(H_t^T S H_t), ||grad_proj||^2 (eq. proj_grad) and Gram(H_{t+1}).
 // The finalize kernel reduces the tile partials in a fixed order.
+#include "admm_inverse.h"
 #include "image.h"
 
 namespace symnmf {
@@ -350,67 +351,11 @@ hipError_t launch_update(const UpdateArgs& a, int h_f64, const PlanView& p, hipS
 //   * W_{t+1} = [H + U]_+ (eq. admm_W), U <- U + H - W_{t+1} (eq. admm_U),
 //   * the FP64 Gram partials of W_{t+1}.
 // ---------------------------------------------------------------------------
-// A chain of k dependent pivots, bound by the latency of one: 16 x 16 threads
-// hold BS x BS blocks of M in registers (padded with the identity), the pivot's
-// row and column go through LDS, in two buffers so that a pivot has one
-// barrier.  The form with [M | I] in LDS, four barriers and two divisions by
-// index per pivot took 441 / 63 / 11.3 us at k = 64 / 32 / 16; this takes
-// 42 / 13.5 / 5.0 us.
 template <typename HT, int BS>
 __global__ __launch_bounds__(256) void admm_minv_kernel(const double* __restrict__ gram, int k, double rho,
                                                         HT* __restrict__ minv) {
-    __shared__ double row[2][KMAX], col[2][KMAX];
-    const int t = threadIdx.x, ti = t >> 4, tj = t & 15;
-    double a[BS][BS];
-#pragma unroll
-    for (int x = 0; x < BS; ++x)
-#pragma unroll
-        for (int y = 0; y < BS; ++y) {
-            const int i = BS * ti + x, j = BS * tj + y;
-            const double m = i < k && j < k ? 2.0 * gram[i * k + j] : 0.0;
-            a[x][y] = i == j ? (i < k ? m + rho : 1.0) : m;
-        }
-#pragma unroll
-    for (int y = 0; y < BS; ++y) {
-        if (ti == 0) row[0][BS * tj + y] = a[0][y];
-        if (tj == 0) col[0][BS * ti + y] = a[y][0];
-    }
-    for (int pb = 0; pb * BS < k; ++pb) {
-#pragma unroll
-        for (int e = 0; e < BS; ++e) {
-            const int p = pb * BS + e;                       // identity past k: nothing changes
-            const int buf = p & 1;
-            __syncthreads();
-            const double d = 1.0 / row[buf][p];
-            double rj[BS], ci[BS];
-#pragma unroll
-            for (int y = 0; y < BS; ++y) {
-                rj[y] = row[buf][BS * tj + y] * d;
-                ci[y] = col[buf][BS * ti + y];
-            }
-#pragma unroll
-            for (int x = 0; x < BS; ++x)
-#pragma unroll
-                for (int y = 0; y < BS; ++y) {
-                    const bool pi = x == e && ti == pb, pj = y == e && tj == pb;
-                    a[x][y] = pi ? (pj ? d : rj[y]) : (pj ? -ci[x] * d : a[x][y] - ci[x] * rj[y]);
-                }
-            // the next pivot's row and column
-            const int nb = e + 1 < BS ? pb : pb + 1, ne = (e + 1) % BS;
-#pragma unroll
-            for (int y = 0; y < BS; ++y) {
-                if (ti == nb) row[buf ^ 1][BS * tj + y] = a[ne][y];
-                if (tj == nb) col[buf ^ 1][BS * ti + y] = a[y][ne];
-            }
-        }
-    }
-#pragma unroll
-    for (int x = 0; x < BS; ++x)
-#pragma unroll
-        for (int y = 0; y < BS; ++y) {
-            const int i = BS * ti + x, j = BS * tj + y;
-            if (i < k && j < k) minv[i * k + j] = (HT)a[x][y];
-        }
+    __shared__ double rc[4 * KMAX];
+    admm_inverse<HT, BS>(gram, k, rho, minv, rc);
 }
 
 template <typename HT>
@@ -603,7 +548,9 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kerne
 
 hipError_t launch_admm(const UpdateArgs& a, const double* gram64, int h_f64, const PlanView& p, hipStream_t stream) {
     if (!p.full || a.k > KMAX || (h_f64 && a.k > 32)) return hipErrorInvalidValue;
-    if (h_f64) launch_minv(gram64, (int)a.k, a.rho, (double*)a.minv, stream);
+    if (!gram64) {
+        // the stream's launch formed the inverse
+    } else if (h_f64) launch_minv(gram64, (int)a.k, a.rho, (double*)a.minv, stream);
     else launch_minv(gram64, (int)a.k, a.rho, (float*)a.minv, stream);
     const int64_t tiles = a.rows_pad / TR;
     dim3 grid(tiles * SUBT), block(UT);
