@@ -48,12 +48,12 @@ struct ImageShape {
 // Images of the 64 rows [g0, g0 + 64) of H, g0 a multiple of 64 (a quarter of a
 // chunk, a run of whole sub-steps): row r < valid from Hn, the others from Ho
 // (both LDS, rows of K floats); img2 (may be null) gets the images of 2 H.
-// Called by all 256 threads of the work-group that has just formed the rows,
+// Called by all threads of the work-group that has just formed the rows,
 // so that H is not read again: a launch of its own for every step took 2.6 us
 // of a step at n = 512, 7 / 13.5 us (FP32 / FP8 S) at n = 10^5, k = 32, and
 // 156 us on the n = 10^6 row share, where it rewrote the images of the 987500
 // rows that no step of the share changes.
-template <int KIND, int K>
+template <int KIND, int K, int THREADS>
 __device__ inline void write_image_slice_kind(const float* Hn, const float* Ho, int valid, int64_t g0, u32x4* img1,
                                               u32x4* img2) {
     using IS = ImageShape<KIND, K>;
@@ -61,7 +61,7 @@ __device__ inline void write_image_slice_kind(const float* Hn, const float* Ho, 
     constexpr int VP = KC * K / EPV;                       // vectors per plane
     const int q = (int)((g0 & (KC - 1)) >> 6);
     const int64_t base = (g0 / KC) * IS::NV;
-    for (int i = threadIdx.x; i < 64 * K / EPV; i += 256) {
+    for (int i = threadIdx.x; i < 64 * K / EPV; i += THREADS) {
         // vector v of the image and the slice row kk of its first entry
         const int c = i & 15, g = (i >> 4) & 3;
         int v, kk, nt;
@@ -113,12 +113,12 @@ __device__ inline void write_image_slice_kind(const float* Hn, const float* Ho, 
 }
 
 // kind: the KIND of the storage type (0 FP32, 1 BF16, 2 FP8)
-template <int K>
+template <int K, int THREADS>
 __device__ inline void write_image_slice(int kind, const float* Hn, const float* Ho, int valid, int64_t g0, void* img1,
                                          void* img2) {
-    if (kind == 0) write_image_slice_kind<0, K>(Hn, Ho, valid, g0, (u32x4*)img1, (u32x4*)img2);
-    else if (kind == 1) write_image_slice_kind<1, K>(Hn, Ho, valid, g0, (u32x4*)img1, (u32x4*)img2);
-    else write_image_slice_kind<2, K>(Hn, Ho, valid, g0, (u32x4*)img1, (u32x4*)img2);
+    if (kind == 0) write_image_slice_kind<0, K, THREADS>(Hn, Ho, valid, g0, (u32x4*)img1, (u32x4*)img2);
+    else if (kind == 1) write_image_slice_kind<1, K, THREADS>(Hn, Ho, valid, g0, (u32x4*)img1, (u32x4*)img2);
+    else write_image_slice_kind<2, K, THREADS>(Hn, Ho, valid, g0, (u32x4*)img1, (u32x4*)img2);
 }
 
 }  // namespace symnmf

@@ -63,14 +63,26 @@ __device__ inline double block_sum(double v, double* sh) {
     return s;   // valid in thread 0
 }
 
-constexpr int UT = 256;   // threads of the update work-group (one row slice of SR rows)
+// Threads of the update work-group (one row slice of SR rows).  A slice is a
+// chain of short phases (loads, H (H^T H), the rule, the Gram), each bound by
+// the latency of LDS reads when a SIMD has one wave of it: with 256 threads the
+// phases of a 64-column slice took 4.9, 8.8, 5.4 and 10 us of 31.  us a step
+// with 256 threads and now, FP32 S: MU k = 64 n = 512 51 / 37, n = 4100 82 / 67;
+// MU k = 32 n = 4100 41 / 39; ADMM k = 64 n = 512 74 / 57, n = 4100 84 / 68, k =
+// 32 n = 512 33 / 28.  The row share of n = 10^6, k = 64: 62 / 37 us in the
+// kernel; n = 10^5, k = 32, where the slices fill the card: 59 / 65 of 1830.
+template <typename HT, int KB>
+constexpr int update_threads() {
+    return sizeof(HT) == 8 ? 256 : (KB == 64 ? 1024 : (KB == 32 ? 512 : 256));
+}
 
 // RULE: the update rule (SYMNMF_ADAM stands for NADAM too), SP: its softplus form.
 // Both are fixed at compile time: with every rule in one kernel a slice of
 // 64 x 32 took 18.5 us at n = 4100 (68 work-groups, so the time of one; 16.1 us
 // now), most of it code and registers of the other rules.
 template <typename HT, int KB, int RULE, bool SP>
-__global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 5 : 1) void update_kernel(UpdateArgs a, PlanView p) {
+__global__ __launch_bounds__((update_threads<HT, KB>()), sizeof(HT) == 8 ? 1 : (KB == 64 ? 4 : 5)) void update_kernel(UpdateArgs a, PlanView p) {
+    constexpr int UT = update_threads<HT, KB>();
     __shared__ __align__(32) HT Hs[SR * KB];
     __shared__ __align__(32) HT Hns[SR * KB];
     __shared__ HT Gs[KB * KB];
@@ -265,14 +277,15 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 5 : 1) void update_kernel(Upd
     __syncthreads();
     if constexpr (sizeof(HT) == 4)
         if (a.img1 && g0 < a.n_chunks * KC)
-            write_image_slice<KB>(a.img_kind, Hns, Hs, (int)min(a.rows - tile * TR - r0, (int64_t)SR), g0, a.img1, a.img2);
+            write_image_slice<KB, UT>(a.img_kind, Hns, Hs, (int)min(a.rows - tile * TR - r0, (int64_t)SR), g0, a.img1, a.img2);
     double* tg = a.tile_gram + slice * (int64_t)k * k;
     if (KB >= 32) {
-        // each thread: entries (ia0 + q, ib), q < NQ (a multiple of 4, ia0 too),
-        // consecutive ia read as aligned 4-wide vectors; the same FP64 sums
-        // over the slice rows
+        // each thread: entries (ia0 + q, ib), q < NQ, consecutive ia read as
+        // aligned vectors; the same FP64 sums over the slice rows
         constexpr int NQ = KB >= 32 ? (KB * KB) / UT : 4;
-        static_assert(NQ % 4 == 0, "4-wide Gram reads need NQ % 4 == 0");
+        constexpr int VQ = NQ < 4 ? NQ : 4;
+        static_assert(NQ % VQ == 0, "vector reads of the Gram rows");
+        typedef HT hvecq __attribute__((ext_vector_type(VQ)));
         const int ib = t % KB, ia0 = (t / KB) * NQ;
         double sq[NQ];
 #pragma unroll
@@ -281,10 +294,10 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 5 : 1) void update_kernel(Upd
         for (int r = 0; r < SR; ++r) {
             const double hb = (double)Hns[r * KB + ib];
 #pragma unroll
-            for (int q = 0; q < NQ; q += 4) {
-                const hvec4 hv = *(const hvec4*)&Hns[r * KB + ia0 + q];
+            for (int q = 0; q < NQ; q += VQ) {
+                const hvecq hv = *(const hvecq*)&Hns[r * KB + ia0 + q];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sq[q + e] += (double)hv[e] * hb;
+                for (int e = 0; e < VQ; ++e) sq[q + e] += (double)hv[e] * hb;
             }
         }
 #pragma unroll
@@ -310,12 +323,15 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 5 : 1) void update_kernel(Upd
 
 template <typename HT, int RULE, bool SP>
 static hipError_t launch_rule(const UpdateArgs& a, const PlanView& p, hipStream_t stream) {
-    const dim3 grid(a.rows_pad / TR * SUBT), block(UT);
+    const dim3 grid(a.rows_pad / TR * SUBT);
     constexpr bool F64 = sizeof(HT) == 8;
-    if (F64 && a.k <= 8) hipLaunchKernelGGL((update_kernel<HT, F64 ? 8 : 16, RULE, SP>), grid, block, 0, stream, a, p);
-    else if (a.k <= 16) hipLaunchKernelGGL((update_kernel<HT, 16, RULE, SP>), grid, block, 0, stream, a, p);
-    else if (a.k <= 32) hipLaunchKernelGGL((update_kernel<HT, 32, RULE, SP>), grid, block, 0, stream, a, p);
-    else if (!F64) hipLaunchKernelGGL((update_kernel<HT, F64 ? 32 : 64, RULE, SP>), grid, block, 0, stream, a, p);
+#define UPDATE(KB) \
+    hipLaunchKernelGGL((update_kernel<HT, KB, RULE, SP>), grid, dim3((update_threads<HT, KB>())), 0, stream, a, p)
+    if (F64 && a.k <= 8) UPDATE(F64 ? 8 : 16);
+    else if (a.k <= 16) UPDATE(16);
+    else if (a.k <= 32) UPDATE(32);
+    else if (!F64) UPDATE(F64 ? 32 : 64);
+#undef UPDATE
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
@@ -366,7 +382,8 @@ static void launch_minv(const double* gram, int k, double rho, HT* minv, hipStre
 }
 
 template <typename HT, int KB>
-__global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kernel(UpdateArgs a, PlanView p) {
+__global__ __launch_bounds__((update_threads<HT, KB>()), sizeof(HT) == 4 ? 4 : 1) void admm_update_kernel(UpdateArgs a, PlanView p) {
+    constexpr int UT = update_threads<HT, KB>();
     __shared__ __align__(32) HT Ws[SR * KB];
     __shared__ __align__(32) HT Wns[SR * KB];
     __shared__ __align__(32) HT As[SR * KB];
@@ -504,13 +521,15 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kerne
     __syncthreads();
     if constexpr (sizeof(HT) == 4)
         if (a.img1 && g0 < a.n_chunks * KC)
-            write_image_slice<KB>(a.img_kind, Wns, Ws, (int)min(a.rows - tile * TR - r0, (int64_t)SR), g0, a.img1, a.img2);
+            write_image_slice<KB, UT>(a.img_kind, Wns, Ws, (int)min(a.rows - tile * TR - r0, (int64_t)SR), g0, a.img1, a.img2);
     double* tg = a.tile_gram + slice * (int64_t)k * k;
     if (KB >= 32) {
         // entries (ia0 + q, ib), q < NQ, as in the update kernel: the same FP64
-        // sums over the slice rows, consecutive ia read as 4-wide vectors
+        // sums over the slice rows, consecutive ia read as vectors
         constexpr int NQ = KB >= 32 ? (KB * KB) / UT : 4;
-        static_assert(NQ % 4 == 0, "4-wide Gram reads need NQ % 4 == 0");
+        constexpr int VQ = NQ < 4 ? NQ : 4;
+        static_assert(NQ % VQ == 0, "vector reads of the Gram rows");
+        typedef HT hvecq __attribute__((ext_vector_type(VQ)));
         const int ib = t % KB, ia0 = (t / KB) * NQ;
         double sq[NQ];
 #pragma unroll
@@ -519,10 +538,10 @@ __global__ __launch_bounds__(UT, sizeof(HT) == 4 ? 4 : 1) void admm_update_kerne
         for (int r = 0; r < SR; ++r) {
             const double hb = (double)Wns[r * KB + ib];
 #pragma unroll
-            for (int q = 0; q < NQ; q += 4) {
-                const hvec4 wv = *(const hvec4*)&Wns[r * KB + ia0 + q];
+            for (int q = 0; q < NQ; q += VQ) {
+                const hvecq wv = *(const hvecq*)&Wns[r * KB + ia0 + q];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sq[q + e] += (double)wv[e] * hb;
+                for (int e = 0; e < VQ; ++e) sq[q + e] += (double)wv[e] * hb;
             }
         }
 #pragma unroll
@@ -553,16 +572,19 @@ hipError_t launch_admm(const UpdateArgs& a, const double* gram64, int h_f64, con
     } else if (h_f64) launch_minv(gram64, (int)a.k, a.rho, (double*)a.minv, stream);
     else launch_minv(gram64, (int)a.k, a.rho, (float*)a.minv, stream);
     const int64_t tiles = a.rows_pad / TR;
-    dim3 grid(tiles * SUBT), block(UT);
+    const dim3 grid(tiles * SUBT);
+#define UPDATE(HT, KB) \
+    hipLaunchKernelGGL((admm_update_kernel<HT, KB>), grid, dim3((update_threads<HT, KB>())), 0, stream, a, p)
     if (h_f64) {
-        if (a.k <= 8) hipLaunchKernelGGL((admm_update_kernel<double, 8>), grid, block, 0, stream, a, p);
-        else if (a.k <= 16) hipLaunchKernelGGL((admm_update_kernel<double, 16>), grid, block, 0, stream, a, p);
-        else hipLaunchKernelGGL((admm_update_kernel<double, 32>), grid, block, 0, stream, a, p);
+        if (a.k <= 8) UPDATE(double, 8);
+        else if (a.k <= 16) UPDATE(double, 16);
+        else UPDATE(double, 32);
     } else {
-        if (a.k <= 16) hipLaunchKernelGGL((admm_update_kernel<float, 16>), grid, block, 0, stream, a, p);
-        else if (a.k <= 32) hipLaunchKernelGGL((admm_update_kernel<float, 32>), grid, block, 0, stream, a, p);
-        else hipLaunchKernelGGL((admm_update_kernel<float, 64>), grid, block, 0, stream, a, p);
+        if (a.k <= 16) UPDATE(float, 16);
+        else if (a.k <= 32) UPDATE(float, 32);
+        else UPDATE(float, 64);
     }
+#undef UPDATE
     return hipGetLastError();
 }
 
