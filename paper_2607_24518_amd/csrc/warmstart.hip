@@ -335,9 +335,11 @@ hipError_t launch_to_bf16(const float* x, uint16_t* y, int64_t m, hipStream_t st
 // before, projects its rows and leaves their block maximum for the next launch
 // (two buffers in turn).  The picked row itself is read by all work-groups of
 // its launch, so its owner clears it one launch later and counts its norm as 0
-// meanwhile.  Four launches per pick over row-major rows (a serial scan of the
-// block maxima among them) took 32.3 us a pick at m = 20000, k = 32; this takes
-// 11.6 us.
+// meanwhile.  At k = 16 and 32, the ranks of most solves, a thread has its whole
+// row in registers, its loads issued together (at 64 the addresses and the row
+// no longer fit).  Four launches per pick over row-major rows (a serial scan of
+// the block maxima among them) took 32.3 us a pick at m = 20000, k = 32, reading
+// the row twice, eight entries at a time, 11.6 us; this takes 8.6 us.
 // ---------------------------------------------------------------------------
 __device__ inline void spa_better(double& v, int64_t& i, double ov, int64_t oi) {
     if (ov > v || (ov == v && oi < i)) {
@@ -360,6 +362,7 @@ __device__ inline void spa_block_argmax(double& v, int64_t& i, double* sv, int64
     for (int q = 1; q < 4; ++q) spa_better(v, i, sv[q], si[q]);
 }
 
+template <int KX>   // k, or 0 for any k
 __global__ __launch_bounds__(256) void spa_step_kernel(double* __restrict__ R, int64_t m, int k, int step,
                                                        const double* __restrict__ bval_in,
                                                        const int64_t* __restrict__ bidx_in, int nb,
@@ -399,6 +402,26 @@ __global__ __launch_bounds__(256) void spa_step_kernel(double* __restrict__ R, i
             // read by every work-group of this launch: left alone
         } else if (i == prev) {
             for (int c = 0; c < k; ++c) R[c * m + i] = 0.0;
+        } else if (KX > 0) {
+            double x[KX > 0 ? KX : 1];
+            double* e = R + i;
+#pragma unroll
+            for (int c = 0; c < KX; ++c, e += m) x[c] = *e;
+            if (step > 0) {
+                double d = 0.0;
+#pragma unroll
+                for (int c = 0; c < KX; ++c) d += x[c] * u[c];
+                e = R + i;
+#pragma unroll
+                for (int c = 0; c < KX; ++c, e += m) {
+                    const double r = x[c] - d * u[c];
+                    *e = r;
+                    s += r * r;
+                }
+            } else {
+#pragma unroll
+                for (int c = 0; c < KX; ++c) s += x[c] * x[c];
+            }
         } else if (step > 0) {
             double d = 0.0;
 #pragma unroll 8
@@ -427,9 +450,14 @@ hipError_t launch_spa(double* R, int64_t m, int64_t k, double* bval, int64_t* bi
                       hipStream_t stream) {
     for (int s = 0; s <= k; ++s) {
         const int in = (s + 1) & 1, out = s & 1;
-        hipLaunchKernelGGL(spa_step_kernel, dim3(s == k ? 1 : nb), dim3(256), 0, stream, R, m, (int)k, s,
-                           (const double*)bval + in * nb, (const int64_t*)bidx + in * nb, nb, bval + out * nb,
-                           bidx + out * nb, pick);
+        const dim3 grid(s == k ? 1 : nb), block(256);
+#define SPA(KX)                                                                                                   \
+    hipLaunchKernelGGL(spa_step_kernel<KX>, grid, block, 0, stream, R, m, (int)k, s, (const double*)bval + in * nb, \
+                       (const int64_t*)bidx + in * nb, nb, bval + out * nb, bidx + out * nb, pick)
+        if (k == 16) SPA(16);
+        else if (k == 32) SPA(32);
+        else SPA(0);
+#undef SPA
     }
     return hipGetLastError();
 }
