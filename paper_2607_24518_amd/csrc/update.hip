@@ -883,7 +883,8 @@ __global__ void piecewise_kernel(HT* __restrict__ G, const HT* __restrict__ g, i
 // block of it per thread from rows in LDS (threads left over at small k take
 // rows of their own; their sums are added in a fixed order).  One work-group per
 // 256 rows with an entry of the Gram per thread, read from memory, took 711 us
-// at n = 20000, k = 64; this takes 44 us.
+// at n = 20000, k = 64; with the partials of an element one after another 44 us;
+// this takes 30 us.
 template <typename HT>
 __global__ __launch_bounds__(256) void objective_tiles_kernel(UpdateArgs a, PlanView p) {
     constexpr int LD = KMAX + 2;
@@ -910,16 +911,32 @@ __global__ __launch_bounds__(256) void objective_tiles_kernel(UpdateArgs a, Plan
     const int64_t w_lo = wg_owner(tile * p.n_chunks, U, Pe);
     const int64_t w_hi = wg_owner((tile + 1) * p.n_chunks - 1, U, Pe);
     double tr = 0.0;
-#pragma unroll 4
-    for (int f = t; f < SR * k; f += 256) {
-        const int r = f / k, c = f - r * k;
-        const int64_t prow = tile * TR + r0 + r;
-        if (prow >= a.rows) continue;
-        double sh = 0.0;
-        for (int64_t w = w_lo; w <= w_hi; ++w) sh += part[((w + tile) * TR + r0 + r) * a.kp + c];
-        const double h = Hs[r * LD + c];
-        if (a.fp8) sh = sh / (double)a.panel_scale[(uint32_t)prow / (uint32_t)a.panel_rows] + (double)a.diag[prow] * h;
-        tr += h * sh;
+    constexpr int NE = 8;                                  // elements of a thread whose loads are in flight together
+    for (int f0 = t; f0 < SR * k; f0 += 256 * NE) {
+        int r[NE], c[NE];
+        double sh[NE];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const int f = min(f0 + 256 * e, SR * k - 1);
+            r[e] = f / k;
+            c[e] = f - r[e] * k;
+            sh[e] = 0.0;
+        }
+#pragma unroll 2
+        for (int64_t w = w_lo; w <= w_hi; ++w) {
+            const double* pw = part + ((w + tile) * TR + r0) * a.kp;
+#pragma unroll
+            for (int e = 0; e < NE; ++e) sh[e] += pw[r[e] * a.kp + c[e]];
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const int64_t prow = tile * TR + r0 + r[e];
+            if (f0 + 256 * e >= SR * k || prow >= a.rows) continue;
+            const double h = Hs[r[e] * LD + c[e]];
+            double v = sh[e];
+            if (a.fp8) v = v / (double)a.panel_scale[(uint32_t)prow / (uint32_t)a.panel_rows] + (double)a.diag[prow] * h;
+            tr += h * v;
+        }
     }
     const int nk = kr / 4, nt = nk * nk, groups = 256 / nt;
     const int grp = t / nt, blk = t - grp * nt;
