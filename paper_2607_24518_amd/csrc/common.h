@@ -283,6 +283,12 @@ int64_t h_image_words(int32_t stype, int64_t k, int64_t n_chunks);
 // rows ldh apart, 0 = k; img: those of all chunks), zero past column k.
 hipError_t launch_h_image(const float* H, int32_t stype, int64_t k, int64_t chunk0, int64_t n_chunks, float wt,
                           uint32_t* img, hipStream_t stream, int64_t ldh = 0);
+// product of FP32 S with 80 columns at once, 64 of X and 16 of X2 (rows 64 apart), on a tall full
+// plan; partial rows of 80 entries; img: wide_image_words
+constexpr int WIDE_COLS = 80;
+int64_t wide_image_words(int64_t n_chunks);
+hipError_t launch_stream_wide(const void* S, const float* X, const float* X2, uint32_t* img, float* part,
+                              const PlanView& plan, hipStream_t stream);
 // out (rows x k, row stride ldo) = the dense product from the partials of a full pass (float or
 // double, rows of kp); FP8: / scale + diag X, X the streamed factor's rows of this panel (stride ldo)
 template <typename T>

@@ -648,6 +648,7 @@ struct KCall {
     bool f64, mfma;
     int64_t esz;
     bool by_label;           // cluster sums by cluster_sums_kernel
+    bool wide;               // the last two slices in one pass
     PlanView pv;
     void* part = nullptr;    // stream partials
     void* img = nullptr;     // chunk images of one slice
@@ -670,7 +671,8 @@ struct KCall {
 
 int64_t slice_width(int64_t K) { return K <= 16 ? 16 : (K <= 32 ? 32 : 64); }
 
-symnmf_status kcall_setup(symnmf_ctx* ctx, const symnmf_S* S, int64_t K, Scratch& sc, KCall& kc) {
+// labels: the call forms cluster sums
+symnmf_status kcall_setup(symnmf_ctx* ctx, const symnmf_S* S, int64_t K, Scratch& sc, KCall& kc, bool labels) {
     if (!S || !S->data) return fail(ctx, SYMNMF_EINVAL, "kmeans: S is NULL");
     if (S->rows != S->n || S->row0 != 0)
         return fail(ctx, SYMNMF_EUNSUPPORTED, "kmeans: needs the full matrix (rows == n), not a row panel");
@@ -708,8 +710,26 @@ symnmf_status kcall_setup(symnmf_ctx* ctx, const symnmf_S* S, int64_t K, Scratch
     // BF16 and FP8 products reduce 32 columns in one MFMA, in an order that the
     // lists could not keep.
     kc.by_label = S->dtype == SYMNMF_S_FP32 && kc.pv.tall && kc.w == 64;
-    kc.part = sc.get(part_tiles * TR * kc.w * kc.esz);
-    if (kc.mfma) kc.img = sc.get(h_image_words(S->dtype, kc.w, kc.chunks) * 4);
+    // The last two slices in one pass where the last holds at most 16 columns
+    // and the scratch is no larger for it than with passes of 64 columns (and
+    // the label factor in full, where the call forms cluster sums): partials
+    // only of the work-groups that have units.
+    int64_t part_bytes = part_tiles * TR * kc.w * kc.esz;
+    int64_t img_bytes = kc.mfma ? h_image_words(S->dtype, kc.w, kc.chunks) * 4 : 0;
+    kc.wide = false;
+    if (kc.by_label && kc.nsl >= 2 && K - (kc.nsl - 1) * kc.w <= WIDE_COLS - kc.w) {
+        const int64_t pairs = tall_pairs(kc.tiles);
+        const int64_t pb = 2 * (std::min<int64_t>(kc.pv.P, pairs * kc.chunks) + pairs) * TR * WIDE_COLS * 4;
+        const int64_t ib = wide_image_words(kc.chunks) * 4;
+        const int64_t saved = labels ? kc.factor_bytes() - kc.weights_bytes() : 0;
+        if (pb + ib <= part_bytes + img_bytes + saved) {
+            kc.wide = true;
+            part_bytes = pb;
+            img_bytes = ib;
+        }
+    }
+    kc.part = sc.get(part_bytes);
+    if (kc.mfma) kc.img = sc.get(img_bytes);
     kc.norms = (double*)sc.get(kc.rows_pad * 8);
     kc.counts = (int32_t*)sc.get(kc.ncol * 4);
     kc.bad = (int32_t*)sc.get(16);
@@ -761,7 +781,8 @@ symnmf_status compute_norms(symnmf_ctx* ctx, KCall& kc, Scratch& sc) {
 }
 
 // Y = S X for slice-major factors (every slice one stream pass, the last one of
-// as few columns as the MFMA kernels have for what is left of K)
+// as few columns as the MFMA kernels have for what is left of K, or the last
+// two at once)
 hipError_t s_times(const KCall& kc, const void* X, void* Y) {
     const symnmf_S* S = kc.S;
     const bool fp8 = S->dtype == SYMNMF_S_FP8;
@@ -771,6 +792,19 @@ hipError_t s_times(const KCall& kc, const void* X, void* Y) {
     for (int64_t s = 0; s < kc.nsl; ++s) {
         const char* Xs = (const char*)X + s * kc.rows_pad * kc.w * kc.esz;
         char* Ys = (char*)Y + s * kc.rows_pad * kc.w * kc.esz;
+        if (kc.wide && s == kc.nsl - 2) {
+            const int64_t step = kc.rows_pad * kc.w;
+            const float* X0 = (const float*)Xs;
+            float* Y0 = (float*)Ys;
+            hipError_t e = launch_stream_wide(S->data, X0, X0 + step, (uint32_t*)kc.img, (float*)kc.part, kc.pv, kc.sm);
+            if (e == hipSuccess)
+                e = launch_dense_rows((const float*)kc.part, kc.n, kc.w, WIDE_COLS, kc.pv, X0, kc.w, scale, diag, pr, Y0,
+                                      kc.sm);
+            if (e == hipSuccess)
+                e = launch_dense_rows((const float*)kc.part + kc.w, kc.n, WIDE_COLS - kc.w, WIDE_COLS, kc.pv, X0 + step,
+                                      kc.w, scale, diag, pr, Y0 + step, kc.sm);
+            return e;
+        }
         const int64_t cols = kc.mfma ? mfma_width(std::min(kc.w, kc.K - s * kc.w)) : kc.w;
         hipError_t e = hipSuccess;
         if (kc.mfma)
@@ -1158,7 +1192,7 @@ symnmf_status symnmf_kmeans_seed_pp(symnmf_ctx* ctx, const symnmf_S* S, int64_t 
     Scratch sc(ctx);
     KCall kc;
     // one-column passes: K = 1 sets up a 16-wide slice; the seed count is K
-    symnmf_status r = kcall_setup(ctx, S, 1, sc, kc);
+    symnmf_status r = kcall_setup(ctx, S, 1, sc, kc, false);
     if (r != SYMNMF_OK) return r;
     if (K < 1 || K > kc.n) return fail(ctx, SYMNMF_EINVAL, "kmeans_seed_pp: need 1 <= K <= n");
     kc.K = K;
@@ -1174,7 +1208,7 @@ symnmf_status symnmf_row_norms(symnmf_ctx* ctx, const symnmf_S* S, double* norms
     if (!norms) return fail(ctx, SYMNMF_EINVAL, "row_norms: norms is NULL");
     Scratch sc(ctx);
     KCall kc;
-    symnmf_status r = kcall_setup(ctx, S, 1, sc, kc);
+    symnmf_status r = kcall_setup(ctx, S, 1, sc, kc, false);
     if (r == SYMNMF_OK) r = compute_norms(ctx, kc, sc);
     if (r != SYMNMF_OK) return r;
     HIP_OK(ctx, hipMemcpyAsync(norms, kc.norms, kc.n * 8, hipMemcpyDeviceToDevice, kc.sm));
@@ -1188,7 +1222,7 @@ symnmf_status symnmf_kmeans_assign(symnmf_ctx* ctx, const symnmf_S* S, const voi
     if (!C || !labels) return fail(ctx, SYMNMF_EINVAL, "kmeans_assign: NULL argument");
     Scratch sc(ctx);
     KCall kc;
-    symnmf_status r = kcall_setup(ctx, S, K, sc, kc);
+    symnmf_status r = kcall_setup(ctx, S, K, sc, kc, false);
     if (r != SYMNMF_OK) return r;
     void* Cs = sc.get(kc.factor_bytes());
     void* Pb = sc.get(kc.factor_bytes());
@@ -1214,7 +1248,7 @@ symnmf_status symnmf_kmeans_centroids(symnmf_ctx* ctx, const symnmf_S* S, const 
     if (!labels || !C) return fail(ctx, SYMNMF_EINVAL, "kmeans_centroids: NULL argument");
     Scratch sc(ctx);
     KCall kc;
-    symnmf_status r = kcall_setup(ctx, S, K, sc, kc);
+    symnmf_status r = kcall_setup(ctx, S, K, sc, kc, true);
     if (r != SYMNMF_OK) return r;
     void* W = sc.get(kc.weights_bytes());
     void* M = sc.get(kc.factor_bytes());
@@ -1245,7 +1279,7 @@ symnmf_status symnmf_kmeans(symnmf_ctx* ctx, const symnmf_S* S, int64_t K, uint6
         return fail(ctx, SYMNMF_EINVAL, "kmeans: need tol >= 0 and max_iter >= 0");
     Scratch sc(ctx);
     KCall kc;
-    symnmf_status r = kcall_setup(ctx, S, K, sc, kc);
+    symnmf_status r = kcall_setup(ctx, S, K, sc, kc, true);
     if (r != SYMNMF_OK) return r;
     std::vector<int64_t> rows;
     if (init_rows) {
@@ -1270,7 +1304,7 @@ symnmf_status symnmf_spectral(symnmf_ctx* ctx, const symnmf_S* S, int64_t max_it
     if (max_iter < 1 || !(tol >= 0.0)) return fail(ctx, SYMNMF_EINVAL, "spectral: need max_iter >= 1, tol >= 0");
     Scratch sc(ctx);
     KCall kc;
-    symnmf_status r = kcall_setup(ctx, S, 1, sc, kc);
+    symnmf_status r = kcall_setup(ctx, S, 1, sc, kc, false);
     if (r != SYMNMF_OK) return r;
     if (kc.f64)
         return spectral_run<double>(ctx, kc, sc, max_iter, tol, lambda1, trace, r_eff, collapse, collapse_rows, iters,
@@ -1283,7 +1317,7 @@ symnmf_status symnmf_silhouette(symnmf_ctx* ctx, const symnmf_S* S, const int32_
     if (!labels || !sil) return fail(ctx, SYMNMF_EINVAL, "silhouette: NULL argument");
     Scratch sc(ctx);
     KCall kc;
-    symnmf_status r = kcall_setup(ctx, S, K, sc, kc);
+    symnmf_status r = kcall_setup(ctx, S, K, sc, kc, true);
     if (r != SYMNMF_OK) return r;
     void* W = sc.get(kc.weights_bytes());
     void* M = sc.get(kc.factor_bytes());

@@ -234,12 +234,13 @@ __global__ __launch_bounds__(256, 2) void stream_f64_mfma(const double* __restri
 // state, of a factor handed in, and the chunks of a row panel whose first row
 // is no multiple of 64.
 template <int KIND, int K>
-constexpr int image_cols_per_wg() { return K == 64 ? 16 : K; }
+constexpr int image_cols_per_wg() { return K >= 64 ? 16 : K; }
 
 // H has k <= K columns, rows ldh apart; the image's other columns are zero.
 template <int KIND, int K>
 __global__ __launch_bounds__(256) void h_image_kernel(const float* __restrict__ H, int k, int ldh, int64_t chunk0,
-                                                      float wt, u32x4* __restrict__ img) {
+                                                      float wt, u32x4* __restrict__ img,
+                                                      const float* __restrict__ H2 = nullptr) {
     using IS = ImageShape<KIND, K>;
     constexpr int CB = image_cols_per_wg<KIND, K>();
     constexpr int LDH = CB + 1;                           // padded row: column reads spread over banks
@@ -261,7 +262,8 @@ __global__ __launch_bounds__(256) void h_image_kernel(const float* __restrict__ 
             d[3] = x.w * wt;
         }
     } else {
-        const float* src = H + chunk * KC * ldh;
+        // columns 64 and up of a wide pass are the first ones of H2
+        const float* src = (K > 64 && CB * blk >= 64 ? H2 - 64 : H) + chunk * KC * ldh;
         for (int q = threadIdx.x; q < KC * CB; q += 256) {
             const int r = q / CB, c = CB * blk + q % CB;
             Hs[r * LDH + q % CB] = c < k ? src[r * ldh + c] * wt : 0.0f;
@@ -370,7 +372,7 @@ __global__ __launch_bounds__(TALL ? 512 : 256, TALL || (ACC64 && NT == 4) ? 1 : 
     constexpr int CPT = NV / NTHR;                         // image vectors per thread
     static_assert(NV % NTHR == 0, "image vectors must split evenly over the threads");
     constexpr bool SPLIT = !DB;                            // single buffer, refilled in parts
-    constexpr int QP = 4;                                  // parts per image
+    constexpr int QP = CPT % 4 == 0 ? 4 : 2;               // parts per image
     constexpr int NSV = NV / ((KIND == 0 ? 1 : 3) * NT);   // vectors per (plane, 16-column) block
     constexpr int HSV = NSV / QP;                          // ... in one part of its sub-steps
     constexpr int CPH = CPT / QP;                          // image vectors per thread and part
@@ -831,6 +833,25 @@ static void launch_mfma_kind(const void* S, const u32x4* img1, const u32x4* img2
     if (k == 16) hipLaunchKernelGGL((stream_mfma<KIND, 1, true, true, false, false>), grid, block, 0, stream, S, img1, img2, part, p);
     else if (k == 32) hipLaunchKernelGGL((stream_mfma<KIND, 2, KIND == 0, true, false, false>), grid, block, 0, stream, S, img1, img2, part, p);
     else hipLaunchKernelGGL((stream_mfma<KIND, 4, false, false, false, false>), grid, block, 0, stream, S, img1, img2, part, p);
+}
+
+// Wide pass: FP32 S, tall full plans, 80 columns, the first 64 of them those of X
+// and the others the first of X2 (rows 64 apart).  For a factor of more than 64
+// columns with at most 16 left, e.g. 141 = 64 + 64 + 13: a pass of 16 columns
+// takes as long as S takes to read, 0.27 ms at n = 20000, and its products a
+// quarter of the 0.46 ms of 64 columns: 0.58 ms for both.  (96
+// columns do not fit the registers beside the S in flight.)
+int64_t wide_image_words(int64_t n_chunks) { return KC * WIDE_COLS * n_chunks; }
+
+hipError_t launch_stream_wide(const void* S, const float* X, const float* X2, uint32_t* img, float* part,
+                              const PlanView& p, hipStream_t stream) {
+    if (!p.full || !p.tall) return hipErrorInvalidValue;
+    u32x4* im = (u32x4*)img;
+    hipLaunchKernelGGL((h_image_kernel<0, WIDE_COLS>), dim3((unsigned)p.n_chunks, WIDE_COLS / 16), dim3(256), 0, stream,
+                       X, WIDE_COLS, 64, (int64_t)0, 1.0f, im, X2);
+    hipLaunchKernelGGL((stream_mfma<0, WIDE_COLS / 16, false, false, false, true>), dim3(p.P), dim3(512), 0, stream, S,
+                       im, im, (void*)part, p);
+    return hipGetLastError();
 }
 
 int stream_tall_supported(int32_t stype, int h_f64, int64_t k) {

@@ -1,6 +1,7 @@
 """K-means at the edges of its kernels: the cluster sums of FP32 storage (lists
 of a chunk's columns, passes of 192 clusters, runs of units of a tile pair), the
-last, narrower slice of a product, and the assignment's four lanes to a row.
+last, narrower slice of a product (together with the one before it where it has
+at most 16 columns), and the assignment's four lanes to a row.
 
 Oracle: FP64 on the stored S.  A centroid entry is a sum of at most n FP32 terms
 of one sign times one factor: its error is a random walk, at most
@@ -61,7 +62,8 @@ def test_centroids(n, K, kind):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16", "fp8"])
-@pytest.mark.parametrize("n,K", [(70, 65), (300, 81), (513, 100), (1100, 190), (1300, 3), (700, 1)])
+@pytest.mark.parametrize("n,K", [(70, 65), (300, 80), (300, 81), (513, 100), (600, 129), (1100, 141), (1100, 190),
+                                 (2900, 200), (1300, 3), (700, 1)])
 def test_assignment(dtype, n, K):
     S, M, norms = _store(n, dtype)
     g = torch.Generator("cuda").manual_seed(K)
