@@ -116,30 +116,38 @@ __global__ __launch_bounds__(KT) void rownorm_finish_kernel(const double* __rest
 // Cluster sums of FP32 storage.  A row of the label matrix W has one non-zero,
 // so M = S W is n^2 multiply-adds and not n^2 K, if the columns of S are
 // brought into the order of their clusters.  Every 256-column chunk gets a list
-// of its columns, grouped by 16-cluster block (one MFMA accumulator tile) and
+// of its columns, grouped by block of at most 16 clusters (one MFMA accumulator tile) and
 // in the order in which the stream's MFMAs reduce them; strips of 16 rows x 256
 // columns are staged in LDS and the listed columns taken from there, four to
 // an MFMA whose other operand holds 1 / ||s_j|| at the column's cluster and
 // zero elsewhere.  Adding a zero product changes no sum, so every sum has the same
 // terms in the same order, and the same value, as the dense product, whose
 // runs of units (one FP32 partial each, added in increasing order) are kept.
-// n = 20000, 141 clusters: 0.346 ms (4.7 TB/s of S; 0.26 ms, 6.3 TB/s, without
+// n = 20000, 141 clusters: 0.347 ms (4.7 TB/s of S; 0.26 ms, 6.3 TB/s, without
 // the MFMAs), where the dense product took three passes, 1.34 ms.
 // --------------------------------------------------------------------------
+// Accumulator tiles of a pass over Kp clusters, and the clusters of one: dealt
+// evenly, up to 16 to a tile, so that the four waves of a strip have the same
+// work.  With 16 to a tile 33 clusters took 0.375 ms and 64 0.378, now 0.310
+// and 0.295; 141 (nine tiles on four waves) 0.354, now 0.347.
+__host__ __device__ inline int cl_tiles(int64_t Kp) { return Kp <= 64 ? 4 : (Kp <= 128 ? 8 : 12); }
+__host__ __device__ inline int cl_per_tile(int64_t Kp) { return (int)((Kp + cl_tiles(Kp) - 1) / cl_tiles(Kp)); }
+
 constexpr int CL_PAD = 8;                         // entries of one loop step (two MFMAs)
-constexpr int CL_NB = 12;                         // 16-cluster blocks of a pass over S
+constexpr int CL_NB = 12;                         // most accumulator tiles (blocks) of a pass over S
+constexpr int CL_PASS = 16 * CL_NB;               // clusters of a pass
 constexpr int CL_PARTS = 4;                       // waves that share a strip, each a quarter of the blocks
 constexpr int CL_ENT = KC + CL_NB * (CL_PAD - 1) + 2 * CL_PAD;   // entries of a list and what is read past its end
 constexpr int CL_WORDS = 2 * CL_ENT + 16;         // entries (position | cluster << 16, weight), block starts / CL_PAD
 static_assert(CL_ENT % 4 == 0, "lists are moved in 16-byte vectors");
 
 // One work-group per (chunk, pass): the list of the chunk's columns with
-// clusters [16 CL_NB pass, 16 CL_NB (pass + 1)).  Thread t takes the column
+// clusters [CL_PASS pass, CL_PASS (pass + 1)) below K.  Thread t takes the column
 // that the dense product reduces as number t of the chunk.  Blocks are listed
 // in the order part 0 (blocks 0, 4, 8), part 1, ..., so that a wave's entries
 // are contiguous.
 __global__ __launch_bounds__(KT) void cluster_lists_kernel(const int32_t* __restrict__ labels,
-                                                           const double* __restrict__ norms, int64_t n,
+                                                           const double* __restrict__ norms, int64_t n, int64_t K,
                                                            uint32_t* __restrict__ lists) {
     __shared__ uint32_t out[CL_WORDS];
     __shared__ int cnt[KT / 64][CL_NB];
@@ -147,8 +155,10 @@ __global__ __launch_bounds__(KT) void cluster_lists_kernel(const int32_t* __rest
     const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
     const int s = t >> 4, m = (t >> 2) & 3, g = t & 3;
     const int64_t j = (int64_t)blockIdx.x * KC + 16 * s + 4 * g + m;
-    const int64_t lab = j < n ? (int64_t)labels[j] - (int64_t)blockIdx.y * 16 * CL_NB : -1;
-    const int b = lab >= 0 && lab < 16 * CL_NB ? (int)lab >> 4 : -1;
+    const int64_t first = (int64_t)blockIdx.y * CL_PASS;
+    const int Kp = (int)min(K - first, (int64_t)CL_PASS), per = cl_per_tile(Kp);
+    const int64_t lab = j < n ? (int64_t)labels[j] - first : -1;
+    const int b = lab >= 0 && lab < Kp ? (int)lab / per : -1;
     for (int i = t; i < CL_WORDS; i += KT) out[i] = 0;
     const int place = b < 0 ? -1 : b % CL_PARTS * (CL_NB / CL_PARTS) + b / CL_PARTS;
     int rank = 0;
@@ -177,7 +187,7 @@ __global__ __launch_bounds__(KT) void cluster_lists_kernel(const int32_t* __rest
     if (b >= 0) {
         const int e = cnt[wv][place] + rank;
         // byte position of the column in a 16-row strip of the tile, row 0
-        out[2 * e] = (uint32_t)(s * 1024 + g * 256 + m * 4) | (uint32_t)(lab & 15) << 16;
+        out[2 * e] = (uint32_t)(s * 1024 + g * 256 + m * 4) | (uint32_t)(lab - b * per) << 16;
         out[2 * e + 1] = __builtin_bit_cast(uint32_t, (float)(1.0 / norms[j]));
     }
     if (t <= CL_NB) out[2 * CL_ENT + t] = (uint32_t)(start[t] / CL_PAD);
@@ -194,7 +204,7 @@ __global__ __launch_bounds__(KT) void cluster_lists_kernel(const int32_t* __rest
 template <int NB>
 __global__ __launch_bounds__(512, 6) void cluster_sums_kernel(const u32x4* __restrict__ S, PlanView p,
                                                               const uint32_t* __restrict__ lists, int64_t n,
-                                                              int64_t rows_pad, int w, int col0,
+                                                              int64_t rows_pad, int w, int col0, int Kp,
                                                               float* __restrict__ M) {
     constexpr int NP = NB / CL_PARTS;             // blocks of a wave
     constexpr int LV = CL_WORDS / 4;              // 16-byte vectors of a list
@@ -264,11 +274,13 @@ __global__ __launch_bounds__(512, 6) void cluster_sums_kernel(const u32x4* __res
         __syncthreads();
     }
     const int64_t r0 = (int64_t)tile * TR + 16 * sixteen + 4 * lg;
+    const int per = cl_per_tile(Kp);
 #pragma unroll
     for (int b = 0; b < NP; ++b) {
-        const int col = col0 + 16 * (CL_PARTS * b + part);
-        const int64_t slice = col / w;
-        float* out = M + slice * rows_pad * w + (col - (int)slice * w) + lr;
+        const int c = (CL_PARTS * b + part) * per + lr;    // cluster of the pass
+        if (lr >= per || c >= Kp) continue;
+        const int64_t slice = (col0 + c) / w;
+        float* out = M + slice * rows_pad * w + (col0 + c - (int)slice * w);
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             if (r0 + v < n) out[(r0 + v) * w] = tot[b][v];
@@ -663,7 +675,7 @@ struct KCall {
 
     int64_t factor_elems() const { return nsl * rows_pad * w; }
     int64_t factor_bytes() const { return factor_elems() * esz; }
-    int64_t passes() const { return (K + 16 * CL_NB - 1) / (16 * CL_NB); }
+    int64_t passes() const { return (K + CL_PASS - 1) / CL_PASS; }
     // of the label factor W, or of the lists that take its place
     int64_t weights_bytes() const { return by_label ? passes() * chunks * CL_WORDS * 4 : factor_bytes(); }
     int64_t row_blocks() const { return (n + KT - 1) / KT; }
@@ -705,7 +717,7 @@ symnmf_status kcall_setup(symnmf_ctx* ctx, const symnmf_S* S, int64_t K, Scratch
                                                   : (kc.f64 ? 2 : stream_wgs_per_cu(S->dtype, kc.w)));
         part_tiles = (int64_t)kc.pv.P + kc.tiles;
     }
-    // FP32 storage and K > 32: 0.35 ms for up to 192 clusters at n = 20000
+    // FP32 storage and K > 32: 0.30 .. 0.35 ms for up to 192 clusters at n = 20000
     // against 0.42 .. 0.47 per 64 dense columns; 32 dense columns take 0.29.
     // BF16 and FP8 products reduce 32 columns in one MFMA, in an order that the
     // lists could not keep.
@@ -835,19 +847,17 @@ hipError_t s_times_labels(const KCall& kc, const int32_t* labels, void* W, void*
     uint32_t* lists = (uint32_t*)W;
     const dim3 grid((unsigned)(8 * kc.tiles)), block(512);
     hipLaunchKernelGGL(cluster_lists_kernel, dim3((unsigned)kc.chunks, (unsigned)kc.passes()), dim3(KT), 0, kc.sm,
-                       labels, kc.norms, kc.n, lists);
+                       labels, kc.norms, kc.n, kc.K, lists);
     for (int64_t q = 0; q < kc.passes(); ++q) {
-        const int col0 = (int)(16 * CL_NB * q), left = (int)kc.ncol - col0;
+        const int col0 = (int)(CL_PASS * q), Kp = (int)std::min<int64_t>(kc.K - col0, CL_PASS);
         const uint32_t* ls = lists + q * kc.chunks * CL_WORDS;
-        if (left <= 64)
-            hipLaunchKernelGGL(cluster_sums_kernel<4>, grid, block, 0, kc.sm, (const u32x4*)kc.S->data, kc.pv, ls, kc.n,
-                               kc.rows_pad, (int)kc.w, col0, (float*)M);
-        else if (left <= 128)
-            hipLaunchKernelGGL(cluster_sums_kernel<8>, grid, block, 0, kc.sm, (const u32x4*)kc.S->data, kc.pv, ls, kc.n,
-                               kc.rows_pad, (int)kc.w, col0, (float*)M);
-        else
-            hipLaunchKernelGGL(cluster_sums_kernel<CL_NB>, grid, block, 0, kc.sm, (const u32x4*)kc.S->data, kc.pv, ls,
-                               kc.n, kc.rows_pad, (int)kc.w, col0, (float*)M);
+#define CLUSTER_SUMS(NB)                                                                                            \
+    hipLaunchKernelGGL(cluster_sums_kernel<NB>, grid, block, 0, kc.sm, (const u32x4*)kc.S->data, kc.pv, ls, kc.n, \
+                       kc.rows_pad, (int)kc.w, col0, Kp, (float*)M)
+        if (cl_tiles(Kp) == 4) CLUSTER_SUMS(4);
+        else if (cl_tiles(Kp) == 8) CLUSTER_SUMS(8);
+        else CLUSTER_SUMS(CL_NB);
+#undef CLUSTER_SUMS
     }
     return hipGetLastError();
 }
