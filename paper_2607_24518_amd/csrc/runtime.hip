@@ -486,10 +486,13 @@ static symnmf_status state_alloc(symnmf_state* st, void** out, int64_t bytes) {
 }
 
 // Work-groups of the quarter-tile stream kernel for the full steps of a state,
-// or 0.  The sampled methods keep the kernels above for them: only one step
-// in snapshot_s is a full one.
+// or 0.  ADMM and MU only: the adaptive rules divide a gradient by its own size,
+// so that an entry near zero moves by eta in the direction its last bits give,
+// and the kernels above keep the order of summation of their trajectories (2000
+// AdaGrad steps at n = 4096 end 1.3e-5 from the FP64 run in the other order,
+// past the 1e-5 that this library holds itself to).
 static int32_t quarter_wgs(const symnmf_state* st) {
-    if (!st->mfma || st->p.method == SYMNMF_ROW_SVRG || st->p.method == SYMNMF_BLOCK_SVRG) return 0;
+    if (!st->mfma || (st->p.method != SYMNMF_ADMM && st->p.method != SYMNMF_MU)) return 0;
     return std::min(st->P, stream_quarter_wgs(st->ctx->cus, st->S.dtype, st->tiles, st->chunks, st->k,
                                               st->p.method == SYMNMF_ADMM));
 }
