@@ -103,6 +103,7 @@ __global__ __launch_bounds__(KT) void rownorm_finish_kernel(const double* __rest
     const int64_t i = (int64_t)blockIdx.x * KT + threadIdx.x;
     if (i >= rows) return;
     double s = 0.0;
+#pragma unroll 16
     for (int64_t c = 0; c < n_chunks; ++c) s += part[c * rows_pad + i];
     if (scale) {
         const double sc = (double)scale[i / panel_rows], d = (double)diag[i];
@@ -643,13 +644,13 @@ inline unsigned blocks_for(int64_t m) { return (unsigned)std::max<int64_t>(1, st
 // --------------------------------------------------------------------------
 // Host side
 // --------------------------------------------------------------------------
-// Device allocations of one call, zero-filled, freed on scope exit.
-// Scratch of one K-means call, from the context pool (zeroed buffers).
+// Scratch of one K-means call, from the context pool, zero-filled unless asked
+// otherwise.
 struct Scratch {
     CallScratch cs;
     hipError_t& err;
     explicit Scratch(symnmf_ctx* c) : cs(c), err(cs.err) {}
-    void* get(int64_t bytes) { return cs.get(bytes, true); }
+    void* get(int64_t bytes, bool zero = true) { return cs.get(bytes, zero); }
 };
 
 // Everything one K-means call needs to multiply S by n x K factors.
@@ -740,8 +741,9 @@ symnmf_status kcall_setup(symnmf_ctx* ctx, const symnmf_S* S, int64_t K, Scratch
             img_bytes = ib;
         }
     }
-    kc.part = sc.get(part_bytes);
-    if (kc.mfma) kc.img = sc.get(img_bytes);
+    // written in full before they are read
+    kc.part = sc.get(part_bytes, false);
+    if (kc.mfma) kc.img = sc.get(img_bytes, false);
     kc.norms = (double*)sc.get(kc.rows_pad * 8);
     kc.counts = (int32_t*)sc.get(kc.ncol * 4);
     kc.bad = (int32_t*)sc.get(16);

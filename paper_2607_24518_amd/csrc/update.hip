@@ -69,11 +69,11 @@ __device__ inline double block_sum(double v, double* sh) {
 // phases of a 64-column slice took 4.9, 8.8, 5.4 and 10 us of 31.  us a step
 // with 256 threads and now, FP32 S: MU k = 64 n = 512 51 / 37, n = 4100 82 / 67;
 // MU k = 32 n = 4100 41 / 39; ADMM k = 64 n = 512 74 / 57, n = 4100 84 / 68, k =
-// 32 n = 512 33 / 28.  The row share of n = 10^6, k = 64: 62 / 37 us in the
+// 32 n = 512 33 / 28, k = 16 n = 512 22.0 / 20.5.  The row share of n = 10^6, k = 64: 62 / 37 us in the
 // kernel; n = 10^5, k = 32, where the slices fill the card: 59 / 65 of 1830.
 template <typename HT, int KB>
 constexpr int update_threads() {
-    return sizeof(HT) == 8 ? 256 : (KB == 64 ? 1024 : (KB == 32 ? 512 : 256));
+    return sizeof(HT) == 8 ? 256 : (KB == 64 ? 1024 : 512);
 }
 
 // RULE: the update rule (SYMNMF_ADAM stands for NADAM too), SP: its softplus form.
