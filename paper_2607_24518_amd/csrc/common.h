@@ -467,8 +467,8 @@ hipError_t launch_gemm(int ta, int tb, int b_bf16, int epi, const float* A, cons
                        float* Z, int64_t M, int64_t N, int64_t K, int64_t splits, hipStream_t stream,
                        const float* aux = nullptr, int64_t ldaux = 0, double* part = nullptr);
 int64_t gemm_splits(int64_t M, int64_t N, int64_t K);
-// the most gemm_splits returns for any K
-int64_t gemm_max_splits(int64_t M, int64_t N);
+// the most gemm_splits returns for any reduction length up to K
+int64_t gemm_max_splits(int64_t M, int64_t N, int64_t K);
 int64_t gemm_row_blocks(int64_t M);
 // Partials of the parameters' gradient: weights (W1, W2, W3) as split-K partials, biases (b1, b2,
 // b3) as FP64 row-block sums.

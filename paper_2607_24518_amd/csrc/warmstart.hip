@@ -208,18 +208,16 @@ __global__ __launch_bounds__(256) void gemm_kernel(const float* __restrict__ A, 
 // K ranges of a weight gradient (m x n, contraction over K rows): enough to
 // give every CU two work-groups where the output has few tiles, none shorter
 // than 256 rows
-int64_t gemm_splits(int64_t M, int64_t N, int64_t K) {
+int64_t gemm_max_splits(int64_t M, int64_t N, int64_t K) {
     const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64);
     if (tiles >= GEMM_WGS || K < 512) return 1;
-    const int64_t splits = std::max<int64_t>(1, std::min<int64_t>(GEMM_WGS / tiles, K / 256));
+    return std::max<int64_t>(1, std::min<int64_t>(GEMM_WGS / tiles, K / 256));
+}
+int64_t gemm_splits(int64_t M, int64_t N, int64_t K) {
+    const int64_t splits = gemm_max_splits(M, N, K);
     const int64_t kchunk = ((K + splits - 1) / splits + 15) / 16 * 16;
     return (K + kchunk - 1) / kchunk;
 }
-int64_t gemm_max_splits(int64_t M, int64_t N) {
-    const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64);
-    return tiles >= GEMM_WGS ? 1 : GEMM_WGS / tiles;
-}
-
 int64_t gemm_row_blocks(int64_t M) { return (M + 63) / 64; }
 
 hipError_t launch_gemm(int ta, int tb, int b_bf16, int epi, const float* A, const void* B, const float* bias, float* C,

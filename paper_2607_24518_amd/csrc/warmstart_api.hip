@@ -57,9 +57,12 @@ int64_t small_doubles(const symnmf_mlp* m, int64_t rows) {
 
 symnmf_status ensure_train(symnmf_mlp* m, int64_t rows) {
     if (m->cap_train >= rows) return SYMNMF_OK;
-    free_all({m->z1, m->z2, m->z3, m->out, m->d3, m->da2, m->small});
-    m->z1 = m->z2 = m->z3 = m->out = m->d3 = m->da2 = nullptr;
+    free_all({m->z1, m->z2, m->z3, m->out, m->d3, m->da2, m->small, m->split_ws});
+    m->z1 = m->z2 = m->z3 = m->out = m->d3 = m->da2 = m->split_ws = nullptr;
     m->small = nullptr;
+    const int64_t split_floats = gemm_max_splits(m->h, m->w, rows) * m->h * m->w +
+                                 gemm_max_splits(m->h, m->h, rows) * m->h * m->h +
+                                 gemm_max_splits(m->k, m->h, rows) * m->k * m->h;
     m->cap_train = 0;
     HIP_OK(m->ctx, hipMalloc((void**)&m->z1, rows * m->h * 4));
     HIP_OK(m->ctx, hipMalloc((void**)&m->z2, rows * m->h * 4));
@@ -68,6 +71,7 @@ symnmf_status ensure_train(symnmf_mlp* m, int64_t rows) {
     HIP_OK(m->ctx, hipMalloc((void**)&m->out, rows * m->k * 4));
     HIP_OK(m->ctx, hipMalloc((void**)&m->d3, rows * m->k * 4));
     HIP_OK(m->ctx, hipMalloc((void**)&m->small, small_doubles(m, rows) * 8));
+    HIP_OK(m->ctx, hipMalloc((void**)&m->split_ws, split_floats * 4));
     m->cap_train = rows;
     return SYMNMF_OK;
 }
@@ -137,9 +141,6 @@ symnmf_status symnmf_mlp_create(symnmf_ctx* ctx, int64_t width, int64_t hidden, 
     m->k = k;
     m->np = np;
     m->nw = hidden * width + hidden * hidden + k * hidden;
-    const int64_t split_floats = gemm_max_splits(hidden, width) * hidden * width +
-                                 gemm_max_splits(hidden, hidden) * hidden * hidden +
-                                 gemm_max_splits(k, hidden) * k * hidden;
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
     chk(hipMalloc((void**)&m->P, np * 4));
@@ -147,7 +148,6 @@ symnmf_status symnmf_mlp_create(symnmf_ctx* ctx, int64_t width, int64_t hidden, 
     chk(hipMalloc((void**)&m->Mm, np * 4));
     chk(hipMalloc((void**)&m->V, np * 4));
     chk(hipMalloc((void**)&m->Wb, m->nw * 2));
-    chk(hipMalloc((void**)&m->split_ws, split_floats * 4));
     if (e == hipSuccess) chk(hipMemcpyAsync(m->P, params, np * 4, hipMemcpyDeviceToDevice, ctx->stream));
     if (e == hipSuccess) chk(launch_zero(m->G, np * 4, ctx->stream));
     if (e == hipSuccess) chk(launch_zero(m->Mm, np * 4, ctx->stream));
