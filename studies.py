@@ -718,7 +718,12 @@ def kmeans_bench(args):
             t0 = time.perf_counter()
             sil = sym.symnmf_silhouette(ctx, S, labels, K)
             sil_s = time.perf_counter() - t0
-            passes = 2 * slices * (st["iters"] + 1)            # stream passes of the Lloyd iterations
+            # passes over S of the Lloyd iterations: the products with the centroids (the last slice joins
+            # the one before it where it has at most 16 columns) and the cluster sums, by column lists of
+            # 192 clusters each for FP32 storage and K > 32
+            lists = dname == "fp32" and K > 32
+            products = slices - (1 if lists and slices > 1 and (K - 1) % 64 < 16 else 0)
+            passes = (products + (-(-K // 192) if lists else slices)) * (st["iters"] + 1)
             rec = {"S_storage": dname, "K": K, "slice_width": w, "slices": slices, "seconds": round(wall, 4),
                    "seeding": args.kmeans_seeding, "seeding_s": round(seed_s, 4),
                    "iters": st["iters"], "converged": bool(st["converged"]), "J0": st["J0"], "J": st["J"],
