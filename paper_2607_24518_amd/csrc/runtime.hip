@@ -485,14 +485,28 @@ static symnmf_status state_alloc(symnmf_state* st, void** out, int64_t bytes) {
     return SYMNMF_OK;
 }
 
+// ADMM and the adaptive rules amplify the last bits of S.H: ADMM's dual keeps
+// them (ten steps in another order of summation end 9e-6 apart in the gradient
+// at n = 1000, 1.7e-5 at 2500 and 2e-5 to 5e-5 at 4000 to 5900), the adaptive
+// rules divide a gradient by its own size, so that an entry near zero moves by
+// eta in the direction its last bits give (2000 AdaGrad steps at n = 4096 end
+// 1.3e-5 from the FP64 run).  Their steps therefore keep one order each: that
+// of the tall kernel at k = 16, 32 and 64, the order of the columns at other
+// ranks; only ADMM steps of at most 1536 instruments leave it.  MU
+// (5e-6 after ten steps at n = 5900) takes the fastest kernel.
+constexpr int64_t ADMM_FREE_N = 1536;
+
+static bool admm_free(const symnmf_state* st) {
+    return st->p.method == SYMNMF_ADMM && st->n <= ADMM_FREE_N;
+}
+static bool ordered_steps(const symnmf_state* st) {
+    return st->mfma && st->k != mfma_width(st->k) && st->p.method != SYMNMF_MU && !admm_free(st);
+}
+
 // Work-groups of the quarter-tile stream kernel for the full steps of a state,
-// or 0.  ADMM and MU only: the adaptive rules divide a gradient by its own size,
-// so that an entry near zero moves by eta in the direction its last bits give,
-// and the kernels above keep the order of summation of their trajectories (2000
-// AdaGrad steps at n = 4096 end 1.3e-5 from the FP64 run in the other order,
-// past the 1e-5 that this library holds itself to).
+// or 0.
 static int32_t quarter_wgs(const symnmf_state* st) {
-    if (!st->mfma || (st->p.method != SYMNMF_ADMM && st->p.method != SYMNMF_MU)) return 0;
+    if (!st->mfma || (st->p.method != SYMNMF_MU && !admm_free(st))) return 0;
     return std::min(st->P, stream_quarter_wgs(st->ctx->cus, st->S.dtype, st->tiles, st->chunks, st->k,
                                               st->p.method == SYMNMF_ADMM));
 }
@@ -645,7 +659,10 @@ static symnmf_status do_step(symnmf_ctx* ctx, const symnmf_S* S, symnmf_state* s
     if (p.method == SYMNMF_ROW_SVRG) kind = (t % p.snapshot_s == 0) ? 0 : 1;
     if (p.method == SYMNMF_BLOCK_SVRG) kind = (st->phi >= 1.0 || t % p.snapshot_s == 0) ? 0 : 2;
     PlanView pv = plan_view(st->plan, kind == 0, (int32_t)st->tiles, (int32_t)st->chunks, st->P);
-    if (kind == 0 && st->P_quarter > 0) {
+    const bool ordered = ordered_steps(st);
+    if (ordered) {
+        pv.ordered = 1;
+    } else if (kind == 0 && st->P_quarter > 0) {
         pv.quarter = 1;
         pv.P = st->P_quarter;
     } else if (kind == 0 && st->tall) {
@@ -676,13 +693,14 @@ static symnmf_status do_step(symnmf_ctx* ctx, const symnmf_S* S, symnmf_state* s
     // time; a panel that starts off a multiple of 64 has its chunks' images
     // written here instead.  The images of the rows outside a panel stay.
     const bool img_fused = st->mfma && st->row0 % SR == 0;
+    const int32_t img_type = ordered ? (int32_t)SYMNMF_S_FP32 : S->dtype;
     if (st->mfma && !(st->img_ready && img_fused)) {
         ProfScope pi(ctx, PK_IMAGE);
         const int64_t c0 = st->img_ready ? st->row0 / KC : 0;
         const int64_t c1 = st->img_ready ? (st->row0 + st->rows + KC - 1) / KC : st->chunks;
         for (int i = 0; i < 2; ++i)
             if (st->img[i])
-                HIP_OK(ctx, launch_h_image((const float*)Hc, S->dtype, st->k, c0, c1 - c0, i ? 2.0f : 1.0f,
+                HIP_OK(ctx, launch_h_image((const float*)Hc, img_type, st->k, c0, c1 - c0, i ? 2.0f : 1.0f,
                                            (uint32_t*)st->img[i], sm));
         st->img_ready = true;
     }
@@ -750,7 +768,7 @@ static symnmf_status do_step(symnmf_ctx* ctx, const symnmf_S* S, symnmf_state* s
     if (img_fused) {
         a.img1 = st->img[0];
         a.img2 = st->img[1];
-        a.img_kind = S->dtype == SYMNMF_S_FP32 ? 0 : (S->dtype == SYMNMF_S_BF16 ? 1 : 2);
+        a.img_kind = img_type == SYMNMF_S_FP32 ? 0 : (img_type == SYMNMF_S_BF16 ? 1 : 2);
         a.n_chunks = st->chunks;
     }
     {

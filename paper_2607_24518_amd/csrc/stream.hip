@@ -788,6 +788,163 @@ __global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_quarter(const voi
     }
 }
 
+// ---------------------------------------------------------------------------
+// Products summed by increasing column, one FP32 multiply-add after another, as
+// a thread per row forms them (v_mfma_f32_16x16x4_f32 adds its four products in
+// the order of the lane groups): the steps of ADMM and of the adaptive rules at
+// ranks that are no width of the kernels above, whose trajectories amplify the
+// last bits (ten ADMM steps at n = 5900 in another order end 2e-5 to 5e-5 from
+// each other in the gradient).  A lane's consecutive columns of S become the
+// lane groups' columns by a 4 x 4 transpose over the groups, two register swaps
+// for two registers; codes are widened to floats first.  H comes from an FP32
+// image in LDS, read so that lane group g gets the g-th of four rows.
+// Four waves of 64 rows, a unit at a time, P work-groups in even runs of units.
+// Bound by the FP32 matrix cores, up to 16 columns by memory.  Ten ADMM steps,
+// against a thread per row in FP32 multiply-adds, in ms: n = 5900, k = 12, FP32
+// 4.02 / 0.63; k = 25, BF16 6.58 / 0.77; k = 50, BF16 15.1 / 1.43; k = 22, FP8
+// 6.05 / 0.77; n = 1800, k = 36, BF16 6.12 / 0.70, the same bits each time.
+// ---------------------------------------------------------------------------
+// t[G] of lane group g <- t[g] of lane group G
+__device__ inline void group_transpose(float (&t)[4]) {
+    auto swap32 = [](float& x, float& y) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y),
+                                                        false, false);
+        x = __builtin_bit_cast(float, (uint32_t)r[0]);
+        y = __builtin_bit_cast(float, (uint32_t)r[1]);
+    };
+    auto swap16 = [](float& x, float& y) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y),
+                                                        false, false);
+        x = __builtin_bit_cast(float, (uint32_t)r[0]);
+        y = __builtin_bit_cast(float, (uint32_t)r[1]);
+    };
+    swap32(t[0], t[2]);
+    swap32(t[1], t[3]);
+    swap16(t[0], t[1]);
+    swap16(t[2], t[3]);
+}
+
+template <int KIND, int NT>
+__global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_ordered(const void* __restrict__ Sv,
+                                                                      const u32x4* __restrict__ img1,
+                                                                      const u32x4* __restrict__ img2,
+                                                                      float* __restrict__ part, PlanView p) {
+    constexpr int K = 16 * NT, NV = KC * K / 4;
+    constexpr int EB = KIND == 0 ? 4 : (KIND == 1 ? 2 : 1);
+    constexpr int NS = KIND == 0 ? 16 : (KIND == 1 ? 8 : 4);
+    constexpr int NH = 16 / NS;                            // floats of a lane's vector / 4
+    constexpr int RING = 4, D = RING - 1;
+    __shared__ u32x4 lds[NV];
+    const float* hs = (const float*)lds;
+    int64_t U;
+    int32_t na;
+    plan_bounds(p, U, na);
+    if (U == 0) return;
+    const int64_t Pe = U < p.P ? U : p.P;
+    const int64_t w = blockIdx.x;
+    if (w >= Pe) return;
+    const int64_t u0 = wg_start(w, U, Pe), u1 = wg_start(w + 1, U, Pe);
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, lr = lane & 15, lg = lane >> 4;
+    auto s_run = [&](int32_t aa, int32_t ch) -> const u32x4* {
+        return (const u32x4*)((const uint8_t*)Sv + ((int64_t)tile_of(p, aa) * p.n_chunks + ch) * TILE_ELEMS * EB +
+                              (int64_t)wv * (TILE_ELEMS * EB / 4)) + lane;
+    };
+    int32_t a = find_active(p, u0, na), chunk;
+    float wt;
+    unit_decode(p, u0, a, chunk, wt);
+    const u32x4* sp = s_run(a, chunk);
+    u32x4 ring[RING][4];
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) ring[d][rg] = __builtin_nontemporal_load(sp + (d * 4 + rg) * 64);
+    floatx4 acc[4][NT];
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[rg][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    int32_t a_next = a;
+    for (int64_t u = u0; u < u1; ++u) {
+        const bool more = u + 1 < u1;
+        const u32x4* src = (wt > 1.5f ? img2 : img1) + (int64_t)chunk * NV;
+        u32x4 h[NV / 256];
+#pragma unroll
+        for (int i = 0; i < NV / 256; ++i) h[i] = src[t + 256 * i];
+        int32_t chunk_n = chunk;
+        float wt_n = wt;
+        const u32x4* sp_n = sp;                            // the last unit reads its own S again, unused
+        if (more) {
+            unit_decode(p, u + 1, a_next, chunk_n, wt_n);
+            sp_n = s_run(a_next, chunk_n);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NV / 256; ++i) lds[t + 256 * i] = h[i];
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int sd = s + D;
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg)
+                ring[sd % RING][rg] = __builtin_nontemporal_load((sd < NS ? sp + (sd * 4 + rg) * 64
+                                                                          : sp_n + ((sd - NS) * 4 + rg) * 64));
+            __builtin_amdgcn_sched_barrier(0);
+            // x[rg][q][G]: columns of float 4 q + (lane group), of lane group G
+            float x[4][NH][4];
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                const u32x4 r = ring[s % RING][rg];
+#pragma unroll
+                for (int q = 0; q < NH; ++q) {
+                    float(&y)[4] = x[rg][q];               // floats 4 q .. 4 q + 3 of the vector
+                    if (KIND == 0) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) y[e] = __uint_as_float(r[e]);
+                    } else if (KIND == 1) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            y[e] = bf16_bits_to_f32((uint16_t)(r[(2 * q + (e >> 1)) & 3] >> (16 * (e & 1))));
+                    } else {
+                        const int code = (int)r[q];
+                        y[0] = __builtin_amdgcn_cvt_f32_fp8(code, 0);
+                        y[1] = __builtin_amdgcn_cvt_f32_fp8(code, 1);
+                        y[2] = __builtin_amdgcn_cvt_f32_fp8(code, 2);
+                        y[3] = __builtin_amdgcn_cvt_f32_fp8(code, 3);
+                    }
+                    group_transpose(x[rg][q]);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 4 * NH; ++j) {             // columns 4 j .. 4 j + 3 of the sub-step
+                const int g16 = NH * s + (j >> 2);         // 16-row group of the chunk
+                float b[NT];
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) b[nt] = hs[(((nt * 16 + g16) * 4 + (j & 3)) * 16 + lr) * 4 + lg];
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        acc[rg][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[rg][j % NH][j / NH], b[nt], acc[rg][nt], 0, 0, 0);
+            }
+        }
+        if (!more || a_next != a) {
+            float* dst = part + (w + a) * (int64_t)TR * K;
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) dst[(64 * wv + 16 * rg + 4 * lg + v) * K + 16 * nt + lr] = acc[rg][nt][v];
+                    acc[rg][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
+        a = a_next;
+        chunk = chunk_n;
+        wt = wt_n;
+        sp = sp_n;
+    }
+}
+
 // One work-group per CU (64 w of four): with two or four per CU a tile has more
 // partials to write and to sum (n = 4100, k = 32, FP32: 40.6, 48.4 and 58.1 us a
 // step).  The line lies where the measured steps cross: FP32 S up to 32 columns
@@ -837,6 +994,12 @@ static void launch_mfma_kind(const void* S, const u32x4* img1, const u32x4* img2
                              const PlanView& p, hipStream_t stream, const AdmmInverse& inv) {
     dim3 grid(p.P);
     k = mfma_width(k);
+    if (p.ordered) {
+        if (k == 16) hipLaunchKernelGGL((stream_ordered<KIND, 1>), grid, dim3(256), 0, stream, S, img1, img2, (float*)part, p);
+        else if (k == 32) hipLaunchKernelGGL((stream_ordered<KIND, 2>), grid, dim3(256), 0, stream, S, img1, img2, (float*)part, p);
+        else hipLaunchKernelGGL((stream_ordered<KIND, 4>), grid, dim3(256), 0, stream, S, img1, img2, (float*)part, p);
+        return;
+    }
     if (p.quarter) {
         const dim3 qg(4 * p.P + (inv.gram ? 1 : 0)), qb(256);
         if (k == 16) hipLaunchKernelGGL((stream_quarter<KIND, 1>), qg, qb, 0, stream, S, img1, (float*)part, p, inv);
@@ -909,7 +1072,7 @@ hipError_t launch_stream_acc64(const void* S, int32_t stype, int64_t k, const vo
 }
 
 int stream_wgs_per_cu(int32_t stype, int64_t k) {
-    if ((stype == SYMNMF_S_BF16 || stype == SYMNMF_S_FP8) && mfma_width(k) == 64) return 1;
+    if ((stype == SYMNMF_S_BF16 || stype == SYMNMF_S_FP8) && k == 64) return 1;
     return 2;
 }
 

@@ -481,7 +481,7 @@ __global__ __launch_bounds__((update_threads<HT, KB>()), sizeof(HT) == 4 ? 4 : 1
             kkt += (double)pg * (double)pg;
             if (!(g == g) || g - g != (HT)0) ++bad;
             if (Go) Go[idx] = g;
-            av = (HT)2 * sw + rho * (w - uv[j]);
+            av = __builtin_elementwise_fma((HT)2, sw, rho * (w - uv[j]));   // one rounding order: ADMM's dual keeps it
         }
         As[r * KB + cc] = av;
     }
