@@ -624,8 +624,8 @@ __global__ __launch_bounds__(TALL ? 512 : 256, TALL || (ACC64 && NT == 4) ? 1 : 
 // An ADMM step's inverse, which nothing waits for before the update, is formed
 // by a work-group of its own beside the others: as a launch between the stream
 // and the update it was 5 of 25 us of a step at 512 instruments, k = 16, and
-// more than the stream at k = 64 (42 us).  A step with / without it, us, FP32:
-// n = 512, k = 16 22.8 / 25.8; n = 4100, k = 32 45.7 / 53.9, k = 64 83.8 / 111.6.
+// more than the stream at k = 64 (42 us).  A step with / without it at n = 512,
+// k = 16, FP32: 22.8 / 25.8 us.
 // ---------------------------------------------------------------------------
 template <int KIND, int NT>
 __global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_quarter(const void* __restrict__ Sv,
@@ -799,7 +799,10 @@ __global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_quarter(const voi
 // for two registers; codes are widened to floats first.  H comes from an FP32
 // image in LDS, read so that lane group g gets the g-th of four rows.
 // Four waves of 64 rows, a unit at a time, P work-groups in even runs of units.
-// Bound by the FP32 matrix cores, up to 16 columns by memory.  Ten ADMM steps,
+// A launch at n = 5900 (576 units for 512 work-groups, so some have two; the
+// even runs are part of the order) takes 38.2 us at k = 12, FP32 (a plain read of
+// those 139 MB takes 20) and 83.8 us at k = 50, BF16 (its FP32 matrix
+// instructions alone take 31).  Ten ADMM steps,
 // against a thread per row in FP32 multiply-adds, in ms: n = 5900, k = 12, FP32
 // 4.02 / 0.63; k = 25, BF16 6.58 / 0.77; k = 50, BF16 15.1 / 1.43; k = 22, FP8
 // 6.05 / 0.77; n = 1800, k = 36, BF16 6.12 / 0.70, the same bits each time.
