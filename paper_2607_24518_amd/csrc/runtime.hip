@@ -487,14 +487,14 @@ static symnmf_status state_alloc(symnmf_state* st, void** out, int64_t bytes) {
 
 // ADMM and the adaptive rules amplify the last bits of S.H: ADMM's dual keeps
 // them (ten steps in another order of summation end 9e-6 apart in the gradient
-// at n = 1000, 1.7e-5 at 2500 and 2e-5 to 5e-5 at 4000 to 5900), the adaptive
+// at n = 1000, 1.6e-5 at 1530 and 2e-5 to 5e-5 at 4000 to 5900), the adaptive
 // rules divide a gradient by its own size, so that an entry near zero moves by
 // eta in the direction its last bits give (2000 AdaGrad steps at n = 4096 end
 // 1.3e-5 from the FP64 run).  Their steps therefore keep one order each: that
 // of the tall kernel at k = 16, 32 and 64, the order of the columns at other
-// ranks; only ADMM steps of at most 1536 instruments leave it.  MU
+// ranks; only ADMM steps of at most 1024 instruments leave it.  MU
 // (5e-6 after ten steps at n = 5900) takes the fastest kernel.
-constexpr int64_t ADMM_FREE_N = 1536;
+constexpr int64_t ADMM_FREE_N = 1024;
 
 static bool admm_free(const symnmf_state* st) {
     return st->p.method == SYMNMF_ADMM && st->n <= ADMM_FREE_N;

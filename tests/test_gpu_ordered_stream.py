@@ -48,7 +48,7 @@ def test_order_of_the_products(dtype, n, k):
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16", "fp8"])
 @pytest.mark.parametrize("n,row0,rows,k,method", [(1, 0, 1, 1, sym.ADAGRAD), (255, 0, 255, 17, sym.ADAGRAD),
-                                                  (1537, 0, 1537, 15, sym.ADMM), (1536, 0, 1536, 15, sym.ADMM),
+                                                  (1025, 0, 1025, 15, sym.ADMM), (1024, 0, 1024, 15, sym.ADMM),
                                                   (2100, 0, 2100, 20, sym.ADMM), (6100, 0, 6100, 33, sym.ADMM),
                                                   (8200, 0, 8200, 63, sym.ADAGRAD), (9000, 1300, 300, 31, sym.ADAGRAD)])
 def test_gradient_against_64_bits(dtype, n, row0, rows, k, method):
