@@ -304,9 +304,12 @@ hipError_t launch_read_probe(const void* src, int64_t bytes, uint32_t* sink, int
 // Objective pass on the MFMA path: FP32 sums within each 256-column chunk,
 // FP64 across chunks; FP64 partials.  img: chunk images of FP32 H.
 int stream_acc64_supported(int32_t stype, int64_t k);
-int stream_acc64_wgs_per_cu(int64_t k);
 hipError_t launch_stream_acc64(const void* S, int32_t stype, int64_t k, const void* img, double* part,
                                const PlanView& p, hipStream_t stream);
+// Objective pass at any rank: FP64 products and sums of tiled S with FP32 H (rows of k, padded to
+// whole chunks); FP64 partials of a full plan, rows of k.
+hipError_t launch_stream_f64_tiled(const void* S, int32_t stype, const float* H, int64_t k, double* part,
+                                   const PlanView& p, hipStream_t stream);
 int stream_uses_mfma(int32_t stype, int h_f64, int acc_f64, int64_t k);
 // resident work-groups per CU of the stream kernel for this storage and rank
 int stream_wgs_per_cu(int32_t stype, int64_t k);

@@ -875,24 +875,24 @@ symnmf_status symnmf_state_read(symnmf_ctx* ctx, symnmf_state* st, int32_t which
 
 }  // extern "C"
 
-// Scratch of objective_terms: H padded to whole tiles (as it came on the MFMA
-// path, with its chunk images; else FP64), the S.H partials, the per-slice FP64
-// partials, the Gram, three effective Grams, the statistics.
+// Scratch of objective_terms: H padded to whole tiles (FP32 H of tiled S as it
+// came, else FP64), at ranks 16 and 32 its chunk images, the S.H partials, the
+// per-slice FP64 partials, the Gram, three effective Grams, the statistics.
 struct ObjWs {
     int64_t h, part, tg, ttr, tk, tb, g, gi, sc, img;
-    int64_t kp;
     int32_t P;
-    bool mfma;
+    bool h32;     // FP32 H of tiled S
+    bool mfma;    // FP32 sums within a chunk (FP32 H, ranks 16 and 32)
 };
 static ObjWs objective_ws(const symnmf_ctx* ctx, const symnmf_S* S, int64_t k, int32_t h_is_f64) {
     ObjWs w;
     const int64_t tiles = S->rows_pad / TR, chunks = S->ld / KC;
-    w.mfma = !h_is_f64 && stream_acc64_supported(S->dtype, k);
-    w.P = ctx->cus * (ctx->wgs_per_cu > 0 ? ctx->wgs_per_cu : (w.mfma ? stream_acc64_wgs_per_cu(k) : 2));
-    w.kp = w.mfma ? mfma_width(k) : k;
+    w.h32 = !h_is_f64 && S->dtype != SYMNMF_S_FP64;
+    w.mfma = w.h32 && stream_acc64_supported(S->dtype, k);
+    w.P = ctx->cus * (ctx->wgs_per_cu > 0 ? ctx->wgs_per_cu : 2);
     const int64_t hrows = std::max(round_up(S->n, PAD), S->row0 + S->rows_pad);
-    w.h = hrows * k * (w.mfma ? 4 : 8);
-    w.part = ((int64_t)w.P + tiles) * TR * w.kp * 8;
+    w.h = hrows * k * (w.h32 ? 4 : 8);
+    w.part = ((int64_t)w.P + tiles) * TR * k * 8;
     w.tg = tiles * SUBT * k * k * 8;
     w.ttr = tiles * SUBT * 8;
     w.tk = tiles * SUBT * 8;
@@ -927,11 +927,13 @@ symnmf_status objective_terms(symnmf_ctx* ctx, const symnmf_S* S, const void* H,
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
     PlanView pv = plan_view(nullptr, 1, (int32_t)tiles, (int32_t)chunks, w.P);
-    chk(launch_copy_h(H, h_is_f64, Hp, w.mfma ? 0 : 1, S->n * k, sm));
+    chk(launch_copy_h(H, h_is_f64, Hp, w.h32 ? 0 : 1, S->n * k, sm));
     if (w.mfma) {
         // MFMA products, FP32 within each 256-column chunk, FP64 across chunks
         chk(launch_h_image((const float*)Hp, S->dtype, k, 0, chunks, 1.0f, (uint32_t*)img, sm));
         chk(launch_stream_acc64(S->data, S->dtype, k, img, (double*)part, pv, sm));
+    } else if (w.h32) {
+        chk(launch_stream_f64_tiled(S->data, S->dtype, (const float*)Hp, k, (double*)part, pv, sm));
     } else {
         chk(launch_stream(S->data, S->dtype, S->ld, Hp, 1, k, part, 1, pv, sm));
     }
@@ -944,7 +946,7 @@ symnmf_status objective_terms(symnmf_ctx* ctx, const symnmf_S* S, const void* H,
     a.row0 = S->row0;
     a.H = Hp;
     a.part = part;
-    a.kp = w.kp;
+    a.kp = k;
     a.fp8 = S->dtype == SYMNMF_S_FP8;
     a.panel_scale = S->panel_scale;
     a.diag = S->diag;
@@ -953,7 +955,7 @@ symnmf_status objective_terms(symnmf_ctx* ctx, const symnmf_S* S, const void* H,
     a.tile_tr = (double*)ttr;
     a.tile_kkt = (double*)tk;
     a.tile_bad = (int32_t*)tb;
-    chk(launch_objective_tiles(a, w.mfma ? 0 : 1, pv, sm));
+    chk(launch_objective_tiles(a, w.h32 ? 0 : 1, pv, sm));
     chk(launch_finalize(tiles * SUBT, k, (double*)tg, (double*)ttr, (double*)tk, (int32_t*)tb, nullptr, nullptr,
                         (double*)g, gi, 1, (double*)sc, sm));
     std::vector<double> gram(k * k);

@@ -223,6 +223,133 @@ __global__ __launch_bounds__(256, 2) void stream_f64_mfma(const double* __restri
     }
 }
 
+// ---------------------------------------------------------------------------
+// The objective of an FP32 H at ranks other than 16 and 32: FP64 products and
+// FP64 sums on the FP64 matrix cores, from tiled FP32 / BF16 / FP8 S (full
+// plans).  Both operands are widened exactly and a product of two FP32 numbers
+// is exact in FP64, so the result differs from the thread-per-row form's in the
+// order of its FP64 sums only.  (FP32 sums within a chunk were no substitute:
+// they put f 1e-9 to 2e-8 of ||S||^2 off at n = 700 to 10000, these 1e-14, and
+// f cancels as E gets small.)
+// Bound by the FP64 matrix cores: n = 20000, k = 64, FP32 S takes 1.0 ms for the
+// whole call (0.7 at the rate of a large FP64 product), 10.5 with a thread per
+// row; k = 17 0.55, k = 1 0.33.  A lane's 16 bytes of S are E consecutive
+// columns of its row; MFMA e of a sub-step reduces over the columns E g + e of
+// the four lane groups g.  H stays FP32 in LDS, rows E apart on disjoint banks
+// (LD), so two work-groups share a CU; k is padded to a multiple of 16 there,
+// and the partial rows have k entries.
+// ---------------------------------------------------------------------------
+template <int KIND, int NT>
+__global__ __launch_bounds__(256, 2) void stream_f64_tiled(const void* __restrict__ Sv, const float* __restrict__ H,
+                                                           int k, double* __restrict__ part, PlanView p) {
+    constexpr int K = 16 * NT, E = KIND == 0 ? 4 : (KIND == 1 ? 8 : 16), EB = 16 / E;
+    constexpr int NS = KC / (4 * E), LD = K + 16 / E;
+    __shared__ float Hs[KC * LD];
+    const int64_t U = (int64_t)p.n_tiles * p.n_chunks, Pe = U < p.P ? U : p.P;
+    const int64_t w = blockIdx.x;
+    if (w >= Pe) return;
+    int64_t u = wg_start(w, U, Pe);
+    const int64_t u1 = wg_start(w + 1, U, Pe);
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6, lr = lane & 15, lg = lane >> 4;
+    while (u < u1) {
+        const int64_t tile = u / p.n_chunks, run_end = min(u1, (tile + 1) * p.n_chunks);
+        doublex4 acc[4][NT];
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[rg][nt] = doublex4{0.0, 0.0, 0.0, 0.0};
+        for (; u < run_end; ++u) {
+            const int64_t chunk = u - tile * p.n_chunks;
+            const u32x4* sp = (const u32x4*)((const uint8_t*)Sv + u * TILE_ELEMS * EB + (int64_t)wv * (TILE_ELEMS * EB / 4)) + lane;
+            u32x4 cur[4], nxt[4];
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) cur[rg] = __builtin_nontemporal_load(sp + rg * 64);
+            __syncthreads();
+#pragma unroll 16
+            for (int f = t; f < KC * K; f += 256) {
+                const int r = f / K, c = f % K;
+                Hs[r * LD + c] = c < k ? H[(chunk * KC + r) * k + c] : 0.0f;
+            }
+            __syncthreads();
+#pragma unroll 1
+            for (int s = 0; s < NS; ++s) {
+                // the last sub-step loads itself again, unused
+                const int sn = s + 1 < NS ? s + 1 : s;
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg) nxt[rg] = __builtin_nontemporal_load(sp + (sn * 4 + rg) * 64);
+#pragma unroll
+                for (int q = 0; q < E / 4; ++q) {          // elements 4 q .. 4 q + 3 of the vectors
+                    float x[4][4];
+#pragma unroll
+                    for (int rg = 0; rg < 4; ++rg) {
+                        const u32x4 r = cur[rg];
+                        if (KIND == 0) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) x[rg][e] = __uint_as_float(r[e]);
+                        } else if (KIND == 1) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                x[rg][e] = bf16_bits_to_f32((uint16_t)(r[(2 * q + (e >> 1)) & 3] >> (16 * (e & 1))));
+                        } else {
+                            const int code = (int)r[q & 3];
+                            x[rg][0] = __builtin_amdgcn_cvt_f32_fp8(code, 0);
+                            x[rg][1] = __builtin_amdgcn_cvt_f32_fp8(code, 1);
+                            x[rg][2] = __builtin_amdgcn_cvt_f32_fp8(code, 2);
+                            x[rg][3] = __builtin_amdgcn_cvt_f32_fp8(code, 3);
+                        }
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float* hrow = Hs + (4 * E * s + E * lg + 4 * q + e) * LD + lr;
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) {
+                            const double b = (double)hrow[16 * nt];
+#pragma unroll
+                            for (int rg = 0; rg < 4; ++rg)
+                                acc[rg][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[rg][e], b, acc[rg][nt], 0, 0, 0);
+                        }
+                        // LDS reads and conversions of later elements stay behind (hoisted: 3 % slower)
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg) cur[rg] = nxt[rg];
+            }
+        }
+        double* dst = part + (w + tile) * TR * (int64_t)k + (64 * wv + lg) * k + lr;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            if (16 * nt + lr < k) {
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) dst[(16 * rg + 4 * v) * k + 16 * nt] = acc[rg][nt][v];
+            }
+    }
+}
+
+template <int KIND>
+static void launch_f64_tiled_kind(const void* S, const float* H, int64_t k, double* part, const PlanView& p,
+                                  hipStream_t stream) {
+    const dim3 grid(p.P), block(256);
+#define F64_TILED(NT) hipLaunchKernelGGL((stream_f64_tiled<KIND, NT>), grid, block, 0, stream, S, H, (int)k, part, p)
+    if (k <= 16) F64_TILED(1);
+    else if (k <= 32) F64_TILED(2);
+    else if (k <= 48) F64_TILED(3);
+    else F64_TILED(4);
+#undef F64_TILED
+}
+
+hipError_t launch_stream_f64_tiled(const void* S, int32_t stype, const float* H, int64_t k, double* part,
+                                   const PlanView& p, hipStream_t stream) {
+    if (k < 1 || k > KMAX || !p.full || p.tall) return hipErrorInvalidValue;
+    if (stype == SYMNMF_S_FP32) launch_f64_tiled_kind<0>(S, H, k, part, p, stream);
+    else if (stype == SYMNMF_S_BF16) launch_f64_tiled_kind<1>(S, H, k, part, p, stream);
+    else if (stype == SYMNMF_S_FP8) launch_f64_tiled_kind<2>(S, H, k, part, p, stream);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
 // One work-group per (chunk, block of CB columns of H): the block's 256 x CB
 // values (scaled by wt) are staged in LDS with 16-byte loads, then every
 // thread assembles whole 16-byte image vectors (all three bf16 planes at once
@@ -357,7 +484,7 @@ constexpr int RING_F32 = 8;
 // (tile pair, chunk) unit against one chunk image, halving image traffic per
 // byte of S.
 template <int KIND, int NT, bool DB, bool PF, bool ACC64, bool TALL>
-__global__ __launch_bounds__(TALL ? 512 : 256, TALL || (ACC64 && NT == 4) ? 1 : 2) void stream_mfma(const void* __restrict__ Sv,
+__global__ __launch_bounds__(TALL ? 512 : 256, TALL ? 1 : 2) void stream_mfma(const void* __restrict__ Sv,
                                                                              const u32x4* __restrict__ img1,
                                                                              const u32x4* __restrict__ img2,
                                                                              void* __restrict__ part, PlanView plan) {
@@ -1046,23 +1173,17 @@ int stream_tall_supported(int32_t stype, int h_f64, int64_t k) {
     return stream_uses_mfma(stype, h_f64, 0, k);
 }
 
-// The 64-column form holds 128 registers of FP64 sums beside 64 of FP32 ones and
-// runs one work-group per CU.
 template <int KIND>
 static void launch_mfma_kind_acc64(const void* S, const u32x4* img, void* part, int64_t k, const PlanView& p,
                                    hipStream_t stream) {
     dim3 grid(p.P), block(256);
-    k = mfma_width(k);
     if (k == 16) hipLaunchKernelGGL((stream_mfma<KIND, 1, true, false, true, false>), grid, block, 0, stream, S, img, img, part, p);
-    else if (k == 32) hipLaunchKernelGGL((stream_mfma<KIND, 2, KIND == 0, false, true, false>), grid, block, 0, stream, S, img, img, part, p);
-    else hipLaunchKernelGGL((stream_mfma<KIND, 4, false, false, true, false>), grid, block, 0, stream, S, img, img, part, p);
+    else hipLaunchKernelGGL((stream_mfma<KIND, 2, KIND == 0, false, true, false>), grid, block, 0, stream, S, img, img, part, p);
 }
 
 int stream_acc64_supported(int32_t stype, int64_t k) {
-    return (stype == SYMNMF_S_FP32 || stype == SYMNMF_S_BF16 || stype == SYMNMF_S_FP8) && k >= 1 && k <= KMAX;
+    return (stype == SYMNMF_S_FP32 || stype == SYMNMF_S_BF16 || stype == SYMNMF_S_FP8) && (k == 16 || k == 32);
 }
-
-int stream_acc64_wgs_per_cu(int64_t k) { return mfma_width(k) == 64 ? 1 : 2; }
 
 hipError_t launch_stream_acc64(const void* S, int32_t stype, int64_t k, const void* img, double* part,
                                const PlanView& p, hipStream_t stream) {
