@@ -806,13 +806,22 @@ __global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_quarter(const voi
     for (int rg = 0; rg < 4; ++rg)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[rg][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    // At 16 columns there is room to sum every unit by itself and the units'
-    // sums apart: shorter chains of roundings (ADMM, k = 2, n = 12000, two steps:
-    // 3.8e-7 from the FP64 result against 1.4e-6 in one chain), 1 to 6 % slower.
+    // The units of a tile are not summed in one chain of roundings: at 16 columns,
+    // where there is room, every unit by itself and the units' sums apart (ADMM,
+    // k = 2, n = 12000, two steps: 3.8e-7 from the FP64 result against 1.4e-6 in
+    // one chain; 1 to 6 % slower), at more columns RUN units by themselves, their
+    // sums in LDS, where the tile's sums meet anyway.  Error of a gradient, FP32 S,
+    // k = 20, n = 6000 / 8200 / 12200: 2.7 / 4.2 / 5.2e-7 in one chain, 1.9 / 2.2 /
+    // 1.7e-7 so; a thread per row, whose runs are half as long, had 2.7 / 3.3 /
+    // 3.5e-7.  0 to 2.5 % slower.
     constexpr bool SUMS = NT == 1;
+    constexpr int RUN = 4;                                 // 256 columns a wave: a unit's of the tall kernel
     floatx4 sum[SUMS ? 4 : 1];
 #pragma unroll
     for (int rg = 0; rg < (SUMS ? 4 : 1); ++rg) sum[rg] = floatx4{0.f, 0.f, 0.f, 0.f};
+    floatx4* held = (floatx4*)red[wv] + lane;              // this lane's sums of the tile's earlier runs
+    int in_run = 0;
+    bool any_held = false;
     u32x4 s[QS][4], b[NB], sn[QS][4], bn[NB];
     int64_t tile = u0 / p.n_chunks, ch = u0 - tile * p.n_chunks;
     load(tile, ch, s, b);
@@ -855,8 +864,12 @@ __global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_quarter(const voi
                             av[rg] = __builtin_bit_cast(bf16x8, r);
                         }
                     }
+                    // the lowest plane of H first: its products and the middle one's are small beside
+                    // the highest one's, and a tile of few columns rounds at full size once, not three
+                    // times (BF16, n = 20, k = 2: error of the gradient 7.6e-8 the other way round,
+                    // 4.2e-8 so, 6.7e-8 with a thread per row; n = 256: 6.7e-8, 5.2e-8, 2.0e-7)
 #pragma unroll
-                    for (int pl = 0; pl < NP; ++pl)
+                    for (int pl = NP - 1; pl >= 0; --pl)
 #pragma unroll
                         for (int rg = 0; rg < 4; ++rg)
 #pragma unroll
@@ -875,14 +888,36 @@ __global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_quarter(const voi
                 acc[rg][0] = floatx4{0.f, 0.f, 0.f, 0.f};
             }
         }
-        if (u + 1 == u1 || tile_n != tile) {
+        const bool last = u + 1 == u1 || tile_n != tile;
+        if (!SUMS && !last && ++in_run == RUN) {
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    floatx4* h = held + (rg * NT + nt) * 64;
+                    *h = any_held ? *h + acc[rg][nt] : acc[rg][nt];
+                    acc[rg][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+                }
+            in_run = 0;
+            any_held = true;
+        }
+        if (last) {
             if (SUMS) {
 #pragma unroll
                 for (int rg = 0; rg < 4; ++rg) {
                     acc[rg][0] = sum[SUMS ? rg : 0];
                     sum[SUMS ? rg : 0] = floatx4{0.f, 0.f, 0.f, 0.f};
                 }
+            } else if (any_held) {
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) acc[rg][nt] = held[(rg * NT + nt) * 64] + acc[rg][nt];
+                // the wave's lanes have read theirs before any writes its rows over them
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             }
+            in_run = 0;
+            any_held = false;
 #pragma unroll
             for (int rg = 0; rg < 4; ++rg)
 #pragma unroll
