@@ -137,6 +137,7 @@ struct PlanView {
     int32_t tall;             // full plans only: units are (pair of row tiles, chunk), see below
     int32_t quarter;          // full plans only: four work-groups per w, one per 64 rows of its tiles
     int32_t ordered;          // products summed by increasing column (stream_ordered)
+    int32_t by_unit;          // tall plans of FP32 S: units summed by themselves
     int32_t n_tiles;          // row tiles of the stored panel
     int32_t n_chunks;         // column chunks (ld / KC)
     int32_t P;                // launched persistent work-groups
@@ -156,7 +157,7 @@ inline int64_t plan_words(int64_t n_tiles, int64_t n_chunks) {
 }
 inline PlanView plan_view(int32_t* base, int32_t full, int32_t n_tiles, int32_t n_chunks, int32_t P) {
     PlanView v;
-    v.full = full; v.tall = 0; v.quarter = 0; v.ordered = 0; v.n_tiles = n_tiles; v.n_chunks = n_chunks; v.P = P;
+    v.full = full; v.tall = 0; v.quarter = 0; v.ordered = 0; v.by_unit = 0; v.n_tiles = n_tiles; v.n_chunks = n_chunks; v.P = P;
     v.hdr = base;
     v.active_tile = base + 8;
     v.active_class = v.active_tile + n_tiles;

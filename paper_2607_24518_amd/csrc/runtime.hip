@@ -668,6 +668,8 @@ static symnmf_status do_step(symnmf_ctx* ctx, const symnmf_S* S, symnmf_state* s
     } else if (kind == 0 && st->tall) {
         pv.tall = 1;
         pv.P = st->P_tall;
+        // ranks 16, 32 and 64 keep their order of summation
+        pv.by_unit = S->dtype == SYMNMF_S_FP32 && st->k != mfma_width(st->k);
     }
     if (kind != 0) {
         PlanRequest r;

@@ -21,6 +21,7 @@
 // long as A and B agree; each kernel uses the one in which a lane's 16 bytes
 // of S are consecutive columns.
 #include <algorithm>
+#include <type_traits>
 
 #include "admm_inverse.h"
 #include "image.h"
@@ -475,15 +476,20 @@ hipError_t launch_h_image(const float* H, int32_t stype, int64_t k, int64_t chun
 // part r (a barrier) the next image's part r is written over it (the last part
 // at the unit's end); each part is fetched into registers one part ahead.
 // ---------------------------------------------------------------------------
-// ACC64: FP32 MFMA sums within each 256-column chunk, added into FP64
-// accumulators at every chunk boundary; the partials are written as doubles
-// (the objective pass).
+// SUM: where a unit's FP32 MFMA sums go at its end.  SUM_RUN: they go on, one
+// chain for the tile's run of units.  SUM_F64: into FP64 sums, the partials are
+// written as doubles (the objective pass).  SUM_UNIT: into FP32 sums of units
+// (MU steps of FP32 S at ranks other than 16, 32 and 64: one chain was 1 to 5 %
+// further from 64 bits at n = 13000 to 20000 than a thread per row with its
+// slightly shorter runs.  Error of a gradient, k = 20, n = 18000: 6.8e-7 in one
+// chain, 6.6e-7 with a thread per row, 2.2e-7 so; 248.9 us a step either way).
+constexpr int SUM_RUN = 0, SUM_F64 = 1, SUM_UNIT = 2;
 constexpr int RING_F32 = 8;
 
 // TALL (full plans): 8 waves, the two halves stream row tiles 2q and 2q+1 of a
 // (tile pair, chunk) unit against one chunk image, halving image traffic per
 // byte of S.
-template <int KIND, int NT, bool DB, bool PF, bool ACC64, bool TALL>
+template <int KIND, int NT, bool DB, bool PF, int SUM, bool TALL>
 __global__ __launch_bounds__(TALL ? 512 : 256, TALL ? 1 : 2) void stream_mfma(const void* __restrict__ Sv,
                                                                              const u32x4* __restrict__ img1,
                                                                              const u32x4* __restrict__ img2,
@@ -508,7 +514,7 @@ __global__ __launch_bounds__(TALL ? 512 : 256, TALL ? 1 : 2) void stream_mfma(co
     constexpr int EB = KIND == 0 ? 4 : (KIND == 1 ? 2 : 1);
     // S prefetch ring and distance (sub-steps): deeper for FP32 S, whose sub-steps
     // are the slowest, to keep more bytes in flight per wave
-    constexpr int RING = (KIND <= 1 && NT <= 2 && !ACC64) ? RING_F32 : 4, D = RING - 1;
+    constexpr int RING = (KIND <= 1 && NT <= 2 && SUM != SUM_F64) ? RING_F32 : 4, D = RING - 1;
     static_assert(NS % RING == 0, "ring must divide the sub-steps of a unit");
     static_assert(!SPLIT || NS % QP == 0, "image parts must hold whole sub-steps");
     __shared__ u32x4 lds[(DB ? 2 : 1) * NV];
@@ -558,14 +564,16 @@ __global__ __launch_bounds__(TALL ? 512 : 256, TALL ? 1 : 2) void stream_mfma(co
     for (int rg = 0; rg < 4; ++rg)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[rg][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    double acc64[ACC64 ? 4 : 1][ACC64 ? NT : 1][ACC64 ? 4 : 1];
-    if (ACC64) {
+    typedef std::conditional_t<SUM == SUM_F64, double, float> sum_t;
+    constexpr bool SUMS = SUM != SUM_RUN;
+    sum_t sums[SUMS ? 4 : 1][SUMS ? NT : 1][SUMS ? 4 : 1];
+    if (SUMS) {
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc64[ACC64 ? rg : 0][ACC64 ? nt : 0][ACC64 ? v : 0] = 0.0;
+                for (int v = 0; v < 4; ++v) sums[SUMS ? rg : 0][SUMS ? nt : 0][SUMS ? v : 0] = 0;
     }
 
     // vector index of the j-th vector of this thread's share of image part r
@@ -679,13 +687,13 @@ __global__ __launch_bounds__(TALL ? 512 : 256, TALL ? 1 : 2) void stream_mfma(co
                 }
             }
         }
-        if (ACC64) {
+        if (SUMS) {
 #pragma unroll
             for (int rg = 0; rg < 4; ++rg)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) acc64[ACC64 ? rg : 0][ACC64 ? nt : 0][ACC64 ? v : 0] += (double)acc[rg][nt][v];
+                    for (int v = 0; v < 4; ++v) sums[SUMS ? rg : 0][SUMS ? nt : 0][SUMS ? v : 0] += (sum_t)acc[rg][nt][v];
                     acc[rg][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
                 }
         }
@@ -701,9 +709,9 @@ __global__ __launch_bounds__(TALL ? 512 : 256, TALL ? 1 : 2) void stream_mfma(co
                     for (int v = 0; v < 4; ++v) {
                         if (!store) continue;
                         const int64_t o = slot * (int64_t)TR * K + (64 * wv + 16 * rg + 4 * lg + v) * K + 16 * nt + lr;
-                        if (ACC64) {
-                            ((double*)part)[o] = acc64[ACC64 ? rg : 0][ACC64 ? nt : 0][ACC64 ? v : 0];
-                            acc64[ACC64 ? rg : 0][ACC64 ? nt : 0][ACC64 ? v : 0] = 0.0;
+                        if (SUMS) {
+                            ((sum_t*)part)[o] = sums[SUMS ? rg : 0][SUMS ? nt : 0][SUMS ? v : 0];
+                            sums[SUMS ? rg : 0][SUMS ? nt : 0][SUMS ? v : 0] = 0;
                         } else {
                             ((float*)part)[o] = acc[rg][nt][v];
                         }
@@ -1174,15 +1182,22 @@ static void launch_mfma_kind(const void* S, const u32x4* img1, const u32x4* img2
     }
     if (p.tall) {
         dim3 block(512);
-        if (k == 16) hipLaunchKernelGGL((stream_mfma<KIND, 1, true, true, false, true>), grid, block, 0, stream, S, img1, img2, part, p);
-        else if (k == 32) hipLaunchKernelGGL((stream_mfma<KIND, 2, true, true, false, true>), grid, block, 0, stream, S, img1, img2, part, p);
-        else hipLaunchKernelGGL((stream_mfma<KIND, 4, KIND == 0, false, false, true>), grid, block, 0, stream, S, img1, img2, part, p);
+        if constexpr (KIND == 0)
+            if (p.by_unit) {
+                if (k == 16) hipLaunchKernelGGL((stream_mfma<0, 1, true, true, SUM_UNIT, true>), grid, block, 0, stream, S, img1, img2, part, p);
+                else if (k == 32) hipLaunchKernelGGL((stream_mfma<0, 2, true, true, SUM_UNIT, true>), grid, block, 0, stream, S, img1, img2, part, p);
+                else hipLaunchKernelGGL((stream_mfma<0, 4, true, false, SUM_UNIT, true>), grid, block, 0, stream, S, img1, img2, part, p);
+                return;
+            }
+        if (k == 16) hipLaunchKernelGGL((stream_mfma<KIND, 1, true, true, SUM_RUN, true>), grid, block, 0, stream, S, img1, img2, part, p);
+        else if (k == 32) hipLaunchKernelGGL((stream_mfma<KIND, 2, true, true, SUM_RUN, true>), grid, block, 0, stream, S, img1, img2, part, p);
+        else hipLaunchKernelGGL((stream_mfma<KIND, 4, KIND == 0, false, SUM_RUN, true>), grid, block, 0, stream, S, img1, img2, part, p);
         return;
     }
     dim3 block(256);
-    if (k == 16) hipLaunchKernelGGL((stream_mfma<KIND, 1, true, true, false, false>), grid, block, 0, stream, S, img1, img2, part, p);
-    else if (k == 32) hipLaunchKernelGGL((stream_mfma<KIND, 2, KIND == 0, true, false, false>), grid, block, 0, stream, S, img1, img2, part, p);
-    else hipLaunchKernelGGL((stream_mfma<KIND, 4, false, false, false, false>), grid, block, 0, stream, S, img1, img2, part, p);
+    if (k == 16) hipLaunchKernelGGL((stream_mfma<KIND, 1, true, true, SUM_RUN, false>), grid, block, 0, stream, S, img1, img2, part, p);
+    else if (k == 32) hipLaunchKernelGGL((stream_mfma<KIND, 2, KIND == 0, true, SUM_RUN, false>), grid, block, 0, stream, S, img1, img2, part, p);
+    else hipLaunchKernelGGL((stream_mfma<KIND, 4, false, false, SUM_RUN, false>), grid, block, 0, stream, S, img1, img2, part, p);
 }
 
 // Wide pass: FP32 S, tall full plans, 80 columns, the first 64 of them those of X
@@ -1199,7 +1214,7 @@ hipError_t launch_stream_wide(const void* S, const float* X, const float* X2, ui
     u32x4* im = (u32x4*)img;
     hipLaunchKernelGGL((h_image_kernel<0, WIDE_COLS>), dim3((unsigned)p.n_chunks, WIDE_COLS / 16), dim3(256), 0, stream,
                        X, WIDE_COLS, 64, (int64_t)0, 1.0f, im, X2);
-    hipLaunchKernelGGL((stream_mfma<0, WIDE_COLS / 16, false, false, false, true>), dim3(p.P), dim3(512), 0, stream, S,
+    hipLaunchKernelGGL((stream_mfma<0, WIDE_COLS / 16, false, false, SUM_RUN, true>), dim3(p.P), dim3(512), 0, stream, S,
                        im, im, (void*)part, p);
     return hipGetLastError();
 }
@@ -1212,8 +1227,8 @@ template <int KIND>
 static void launch_mfma_kind_acc64(const void* S, const u32x4* img, void* part, int64_t k, const PlanView& p,
                                    hipStream_t stream) {
     dim3 grid(p.P), block(256);
-    if (k == 16) hipLaunchKernelGGL((stream_mfma<KIND, 1, true, false, true, false>), grid, block, 0, stream, S, img, img, part, p);
-    else hipLaunchKernelGGL((stream_mfma<KIND, 2, KIND == 0, false, true, false>), grid, block, 0, stream, S, img, img, part, p);
+    if (k == 16) hipLaunchKernelGGL((stream_mfma<KIND, 1, true, false, SUM_F64, false>), grid, block, 0, stream, S, img, img, part, p);
+    else hipLaunchKernelGGL((stream_mfma<KIND, 2, KIND == 0, false, SUM_F64, false>), grid, block, 0, stream, S, img, img, part, p);
 }
 
 int stream_acc64_supported(int32_t stype, int64_t k) {
