@@ -74,14 +74,16 @@ __global__ __launch_bounds__(256) void check_input_kernel(const float* __restric
     if (negative) atomicOr(flag, BAD_NEGATIVE);
 }
 
-__global__ __launch_bounds__(256) void zero_pads_kernel(uint32_t* __restrict__ Z, int64_t K, int64_t first,
-                                                        int64_t end) {
-    const int64_t row = blockIdx.x;
-    for (int64_t c = (row < K ? first : 0) + threadIdx.x; c < end; c += 256) Z[row * end + c] = 0;
+__global__ __launch_bounds__(256) void zero_pads_kernel(uint32_t* __restrict__ Z, int64_t K, int64_t Kpad,
+                                                        int64_t first, int64_t end) {
+    for (int64_t row = blockIdx.x; row < Kpad; row += gridDim.x)
+        for (int64_t c = (row < K ? first : 0) + threadIdx.x; c < end; c += 256) Z[row * end + c] = 0;
 }
 
 hipError_t launch_zero_pads(void* Z, int64_t K, int64_t Kpad, int64_t n, int64_t ldz, int words, hipStream_t stream) {
-    hipLaunchKernelGGL(zero_pads_kernel, dim3((unsigned)Kpad), dim3(256), 0, stream, (uint32_t*)Z, K, n * words,
+    // a grid holds less than 2^32 threads: rows beyond 2^20 in turn
+    const unsigned blocks = (unsigned)std::min<int64_t>(Kpad, 1 << 20);
+    hipLaunchKernelGGL(zero_pads_kernel, dim3(blocks), dim3(256), 0, stream, (uint32_t*)Z, K, Kpad, n * words,
                        ldz * words);
     return hipGetLastError();
 }
