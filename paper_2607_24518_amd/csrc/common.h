@@ -318,7 +318,7 @@ int stream_wgs_per_cu(int32_t stype, int64_t k);
 int stream_tall_supported(int32_t stype, int h_f64, int64_t k);
 // work-groups w of a full step that runs the quarter-tile kernel (a plan with quarter = 1), or 0
 // where the step has too many units for it
-int32_t stream_quarter_wgs(int cus, int32_t stype, int64_t n_tiles, int64_t n_chunks, int64_t k, bool inverse);
+int32_t stream_quarter_wgs(int cus, int32_t stype, int64_t n_tiles, int64_t n_chunks, int64_t k);
 
 // plan.hip: build the device plan of a sub-sampled step.
 struct PlanRequest {

@@ -507,8 +507,7 @@ static bool ordered_steps(const symnmf_state* st) {
 // or 0.
 static int32_t quarter_wgs(const symnmf_state* st) {
     if (!st->mfma || (st->p.method != SYMNMF_MU && !admm_free(st))) return 0;
-    return std::min(st->P, stream_quarter_wgs(st->ctx->cus, st->S.dtype, st->tiles, st->chunks, st->k,
-                                              st->p.method == SYMNMF_ADMM));
+    return std::min(st->P, stream_quarter_wgs(st->ctx->cus, st->S.dtype, st->tiles, st->chunks, st->k));
 }
 
 static double tau_g_of(const symnmf_state* st) {

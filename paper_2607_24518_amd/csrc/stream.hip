@@ -756,11 +756,11 @@ __global__ __launch_bounds__(TALL ? 512 : 256, TALL ? 1 : 2) void stream_mfma(co
 // L2) straight into registers, one unit ahead, and the four waves' sums meet in
 // LDS once per tile.  The partial of work-group w for tile a goes to slot
 // w + a as usual, written by the four work-groups 4 w .. 4 w + 3.
-// An ADMM step's inverse, which nothing waits for before the update, is formed
-// by a work-group of its own beside the others: as a launch between the stream
-// and the update it was 5 of 25 us of a step at 512 instruments, k = 16, and
-// more than the stream at k = 64 (42 us).  A step with / without it at n = 512,
-// k = 16, FP32: 22.8 / 25.8 us.
+// The inverse of an ADMM step (which runs here up to 1024 instruments), that
+// nothing waits for before the update, is formed by a work-group of its own
+// beside the others.  A step so / with a launch for it between the stream and
+// the update, n = 512, FP32: k = 16 18.1 / 22.7 us, k = 32 24.6 / 29.9, k = 64
+// 54.4 / 62.8.
 // ---------------------------------------------------------------------------
 template <int KIND, int NT>
 __global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_quarter(const void* __restrict__ Sv,
@@ -1120,17 +1120,14 @@ __global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_ordered(const voi
 
 // One work-group per CU (64 w of four): with two or four per CU a tile has more
 // partials to write and to sum (n = 4100, k = 32, FP32: 40.6, 48.4 and 58.1 us a
-// step).  The line lies where the measured steps cross: FP32 S up to 32 columns
-// gains to 12000 instruments (U = 2209: 118 us against 138 of the tall kernel)
-// and about breaks even at 16000; BF16 / FP8 S gains to 8192 (U = 1024: 50.3 /
-// 45.2 against 63.8 / 52.8 us) and loses at 12000 or 16000; 64 columns gain to
-// 6000 (U = 576: 104 / 77 / 77 against 128 / 87 / 85 us, FP32 / BF16 / FP8) and
-// lose or tie at 8192.  At 512 instruments: k = 16 19.0 against 28.9 us, k = 32
-// 24.8 against 41.0 us, k = 64 50.5 against 78.5 us (FP32).
-// The 64-column form's registers fill a CU, so a step with an inverse leaves it
-// one.
-int32_t stream_quarter_wgs(int cus, int32_t stype, int64_t n_tiles, int64_t n_chunks, int64_t k, bool inverse) {
-    const int64_t U = n_tiles * n_chunks, P = std::max((cus - (inverse && mfma_width(k) == 64 ? 1 : 0)) / 4, 1);
+// step).  The line lies where MU steps of this kernel and of the tall one cross,
+// us here / there, FP32, BF16, FP8 S.  Up to 32 columns (k = 32): n = 512 21 / 37,
+// 21 / 25, 21 / 25; 8192 (U = 1024) 63 / 77, 46 / 59, 40 / 47; 12000 (U = 2209)
+// 114 / 133 on FP32, which is level at 16000, where BF16 and FP8 lose.  64
+// columns: n = 512 34 / 61, 32 / 39, 33 / 40; 6000 (U = 576) 88 / 109, 60 / 67,
+// 58 / 62; 6900 (U = 729) 106 / 107, 69 / 66, 65 / 62; all lose or tie at 8192.
+int32_t stream_quarter_wgs(int cus, int32_t stype, int64_t n_tiles, int64_t n_chunks, int64_t k) {
+    const int64_t U = n_tiles * n_chunks, P = std::max(cus / 4, 1);
     const int64_t most = mfma_width(k) == 64 ? 768 : (stype == SYMNMF_S_FP32 ? 2304 : 1024);
     if (U > most) return 0;
     return (int32_t)std::min(U, P);

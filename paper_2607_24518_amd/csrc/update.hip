@@ -67,10 +67,11 @@ __device__ inline double block_sum(double v, double* sh) {
 // chain of short phases (loads, H (H^T H), the rule, the Gram), each bound by
 // the latency of LDS reads when a SIMD has one wave of it: with 256 threads the
 // phases of a 64-column slice took 4.9, 8.8, 5.4 and 10 us of 31.  us a step
-// with 256 threads and now, FP32 S: MU k = 64 n = 512 51 / 37, n = 4100 82 / 67;
-// MU k = 32 n = 4100 41 / 39; ADMM k = 64 n = 512 74 / 57, n = 4100 84 / 68, k =
-// 32 n = 512 33 / 28, k = 16 n = 512 22.0 / 20.5.  The row share of n = 10^6, k = 64: 62 / 37 us in the
-// kernel; n = 10^5, k = 32, where the slices fill the card: 59 / 65 of 1830.
+// with 256 threads and now, FP32 S: MU k = 64 n = 512 48.5 / 33.8, n = 4100 80 / 65;
+// MU k = 32 n = 4100 38.5 / 36.5; ADMM k = 64 n = 512 70 / 54, n = 4100 121 / 104,
+// k = 32 n = 512 29.2 / 24.9, k = 16 n = 512 18.7 / 17.9.  The row share of n = 10^6,
+// k = 64: 62 / 37 us in the kernel; n = 10^5, k = 32, FP8 S, AdaGrad, where the
+// slices fill the card: 49.5 / 57.4 of 1615.
 template <typename HT, int KB>
 constexpr int update_threads() {
     return sizeof(HT) == 8 ? 256 : (KB == 64 ? 1024 : 512);
