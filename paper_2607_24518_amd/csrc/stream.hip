@@ -1128,7 +1128,8 @@ __global__ __launch_bounds__(256, NT == 4 ? 1 : 2) void stream_ordered(const voi
 // 58 / 62; 6900 (U = 729) 106 / 107, 69 / 66, 65 / 62; all lose or tie at 8192.
 int32_t stream_quarter_wgs(int cus, int32_t stype, int64_t n_tiles, int64_t n_chunks, int64_t k) {
     const int64_t U = n_tiles * n_chunks, P = std::max(cus / 4, 1);
-    const int64_t most = mfma_width(k) == 64 ? 768 : (stype == SYMNMF_S_FP32 ? 2304 : 1024);
+    const bool fp32 = stype == SYMNMF_S_FP32;
+    const int64_t most = mfma_width(k) == 64 ? (fp32 ? 768 : 640) : (fp32 ? 2304 : 1024);
     if (U > most) return 0;
     return (int32_t)std::min(U, P);
 }
