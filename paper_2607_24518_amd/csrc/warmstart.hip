@@ -614,16 +614,22 @@ __global__ __launch_bounds__(JT) void jacobi_topk_kernel(const double* __restric
     __shared__ double V[KMAX][KMAX + 1];
     __shared__ int order[KMAX];
     __shared__ int rotated, bad;
+    __shared__ uint8_t dead[KMAX + 1];       // columns of a sketch with a NaN in them
     __shared__ double red[JT / 64];
     __shared__ double2 rot[2][KMAX / 2];     // (cos, sin) of every pair, of this round and the one before
     __shared__ int2 pair[2][KMAX / 2];
     const int t = threadIdx.x;
     const int wp = w + (w & 1);    // even player count; index w (odd w) is a bye: a zero row and column
     const int half = wp / 2;
+    // A NaN in column p of the sketch makes row and column p of G NaN: they take
+    // no part in any rotation, as if they were zero, and the column's eigenvector
+    // is its own; the others are those of the rest of G.
+    if (t <= w) dead[t] = t < w && !(G[t * w + t] == G[t * w + t]);
+    __syncthreads();
     double fro = 0.0;
     for (int e = t; e < wp * wp; e += JT) {
         const int i = e / wp, j = e - i * wp;
-        const double a = i < w && j < w ? 0.5 * (G[i * w + j] + G[j * w + i]) : 0.0;
+        const double a = i < w && j < w && !dead[i] && !dead[j] ? 0.5 * (G[i * w + j] + G[j * w + i]) : 0.0;
         A[i][j] = a;
         V[i][j] = i == j ? 1.0 : 0.0;
         fro += a * a;
@@ -714,13 +720,22 @@ __global__ __launch_bounds__(JT) void jacobi_topk_kernel(const double* __restric
     }
     if (round > 0) rotate_v((round - 1) & 1, 0);
     __syncthreads();
-    // place of every eigenvalue in descending order, lower index first on ties
-    if (t < w) {
-        const double l = A[t][t];
+    // place of every eigenvalue in descending order, lower index first on ties;
+    // a dead column comes once all columns before it have been taken
+    auto place = [&](int i) {
         int rank = 0;
-        for (int j = 0; j < w; ++j) rank += A[j][j] > l || (A[j][j] == l && j < t) ? 1 : 0;
+        for (int j = 0; j < w; ++j) rank += !dead[j] && (A[j][j] > A[i][i] || (A[j][j] == A[i][i] && j < i)) ? 1 : 0;
+        return rank;
+    };
+    if (t < w && !dead[t]) {
+        const double l = A[t][t];
+        const int rank = place(t);
         if (rank < k) order[rank] = t;
         if (!(l == l) || (rank < k && (!(l > 0.0) || !isfinite(l)))) bad = 1;
+    } else if (t < w) {
+        int at = 0;
+        for (int j = 0; j < t && !dead[j]; ++j) at = max(at, place(j) + 1);
+        if (at < k) bad = 1;
     }
     __syncthreads();
     if (t < k) lam_out[t] = A[order[t]][order[t]];
