@@ -23,6 +23,8 @@ def built(X, **kw):
         return torch.from_numpy(stored_numpy(sym.symnmf_build_S(c, X, dtype=sym.S_FP64, **kw)))
     finally:
         sym.symnmf_destroy(c)
+        del work
+        torch.cuda.empty_cache()         # tens of GB, back to the card
 
 
 def test_correlation_of_more_than_2_24_samples():
